@@ -26,13 +26,13 @@ constexpr int kLRowB = kLKS * 2;            // bytes per tile row and stage
 constexpr int kLTileB = kLTile * kLRowB;    // one operand tile of one stage
 constexpr int kLStageB = 2 * kLTileB;       // W tile, then h tile
 constexpr int kLLds = 2 * kLStageB;         // two stages
-constexpr int kLGroupM = 8, kLGroupN = 4;   // workgroups of one XCD that run together: 8 token x 4 vocab tiles
+constexpr int kLGroupM = 8;                 // token tiles of the workgroups that run together on an XCD, at most
 
 struct LogprobParams {
     const uint16_t *h;
     const uint16_t *w;
     float *pmax, *psum;  // [n_blocks][T]
-    int T, H, V, n_blocks, m_tiles, n_mgroups;
+    int T, H, V, n_blocks, m_tiles, n_mgroups, group_m, per_xcd;
     float inv_temp;
 };
 
@@ -44,14 +44,19 @@ __global__ __launch_bounds__(kLThreads, 2) void lmhead_lse_kernel(LogprobParams 
     const int wm = wave >> 2, wt = wave & 3;   // 128 vocabulary rows x 64 tokens per wavefront
     const int c = lane & 31, h = lane >> 5;
 
-    // Consecutive workgroup ids go round-robin over the 8 XCDs.  The workgroups that run together on one
-    // XCD (32 CUs, one workgroup each) form an 8-token-tile x 4-vocabulary-tile block, so that its L2
-    // fetches 12 operand tiles for 32 output tiles.
-    const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
-    const int super = (idx / (kLGroupM * kLGroupN)) * 8 + xcd, within = idx % (kLGroupM * kLGroupN);
-    const int mt = (super % p.n_mgroups) * kLGroupM + within % kLGroupM;
-    const int nb = (super / p.n_mgroups) * kLGroupN + within / kLGroupM;
-    if (mt >= p.m_tiles || nb >= p.n_blocks) return;
+    // Consecutive workgroup ids go round-robin over the 8 XCDs; every XCD takes a contiguous eighth of the tiles, in
+    // the order (group of token tiles, vocabulary tile, token tile of the group).  The 32 workgroups that run together on
+    // one XCD (one per CU) so cover a block of group_m token tiles x 32 / group_m vocabulary tiles (8 x 4 where there
+    // are that many token tiles), and its L2 fetches 12 operand tiles for 32 output tiles.  No workgroup is without
+    // a tile (but for the last few): ids go round-robin over the shader engines of an XCD too, whether they have work
+    // or not, and a regular pattern of empty ones leaves engines idle (256 tokens on places for 2048, 151936 x 2048:
+    // 500 us; so: 210; 2300 tokens, nine tiles on places for sixteen, 1760 us; in groups of five and four: 1160).
+    const int tile = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+    if (tile >= p.m_tiles * p.n_blocks) return;
+    const int mg = min(tile / (p.group_m * p.n_blocks), p.n_mgroups - 1);
+    const int in_group = tile - mg * p.group_m * p.n_blocks;
+    const int gm = min(p.group_m, p.m_tiles - mg * p.group_m);   // the last group may be smaller
+    const int mt = mg * p.group_m + in_group % gm, nb = in_group / gm;
 
     const int T = p.T, H = p.H, V = p.V;
     const int v0 = nb * kLTile, t0 = mt * kLTile;
@@ -68,6 +73,7 @@ __global__ __launch_bounds__(kLThreads, 2) void lmhead_lse_kernel(LogprobParams 
     }
     const unsigned char *wbase = (const unsigned char *)p.w + (int64_t)v0 * H * 2;
     const unsigned char *hbase = (const unsigned char *)p.h + (int64_t)t0 * H * 2;
+    const int stages = H / kLKS;
     // copy i of the wavefront's eight per stage (four W row groups, then four h row groups)
     auto copy_one = [&](int ks, int buf, int i) {
         unsigned char *dst = smem + buf * kLStageB + wave * 32 * kLRowB;
@@ -130,7 +136,6 @@ __global__ __launch_bounds__(kLThreads, 2) void lmhead_lse_kernel(LogprobParams 
     // Rotated loop: the MFMAs of a stage's last slice run in the next trip, behind the stage barrier and
     // under the first operand reads of the next stage, so no operand read is outstanding at the back edge
     // and every wait inside the trip counts exactly the reads it needs.
-    const int stages = H / kLKS;
     Frags last, f0, f1, f2, f3;
 #pragma unroll
     for (int i = 0; i < 4; ++i) last.a[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -199,6 +204,22 @@ __global__ __launch_bounds__(kLThreads, 2) void lmhead_lse_kernel(LogprobParams 
     }
 }
 
+// <a, b> over K bf16 elements in fp32 by one wavefront (K % 8 == 0).
+__device__ __forceinline__ float row_dot(const uint16_t *a, const uint16_t *b, int K, int lane)
+{
+    const u32x4 *ar = (const u32x4 *)a, *br = (const u32x4 *)b;
+    float s = 0.f;
+    for (int q = lane; q < K / 8; q += 64) {
+        const u32x4 va = ar[q], vb = br[q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s = fmaf(__uint_as_float(va[i] << 16), __uint_as_float(vb[i] << 16), s);
+            s = fmaf(__uint_as_float(va[i] & 0xffff0000u), __uint_as_float(vb[i] & 0xffff0000u), s);
+        }
+    }
+    return wave_sum(s);
+}
+
 // Target logit of each token: inv_T * <h_t, w_{y_t}> in fp32, one wavefront per token.  A target outside
 // [0, V) yields NaN.
 __global__ __launch_bounds__(256) void target_logit_kernel(const uint16_t *__restrict__ hmat,
@@ -213,17 +234,7 @@ __global__ __launch_bounds__(256) void target_logit_kernel(const uint16_t *__res
         if (lane == 0) tgt[t] = __uint_as_float(0x7fc00000u);
         return;
     }
-    const u32x4 *hr = (const u32x4 *)(hmat + (int64_t)t * H), *wr = (const u32x4 *)(w + (int64_t)y * H);
-    float s = 0.f;
-    for (int q = lane; q < H / 8; q += 64) {
-        const u32x4 a = hr[q], b = wr[q];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s = fmaf(__uint_as_float(a[i] << 16), __uint_as_float(b[i] << 16), s);
-            s = fmaf(__uint_as_float(a[i] & 0xffff0000u), __uint_as_float(b[i] & 0xffff0000u), s);
-        }
-    }
-    s = wave_sum(s);
+    const float s = row_dot(hmat + (int64_t)t * H, w + (int64_t)y * H, H, lane);
     if (lane == 0) tgt[t] = s * inv_temp;
 }
 
@@ -267,6 +278,292 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float *__restri
     }
 }
 
+// ---- few tokens (a decode step; at most kSMaxTok): the vocabulary matrix is read once, and that is all the time
+// there is.  A workgroup owns a contiguous range of vocabulary rows and walks it in tiles of `rows` <= 256 rows x kTok
+// tokens; W rows and h rows reach LDS by the same asynchronous copies and swizzle as above, in a ring of kSBufs 64-k
+// stages that runs on across the tiles: two or three stages (50-75 KB of W per CU) are in flight at any time, with
+// one barrier per stage and a counted wait for the oldest.  The h rows are re-read from L2 once per tile
+// (kTok / rows of the W bytes).  Copies of rows past T are not issued: what the LDS holds there only reaches columns
+// that no one reads.  The running (max, sum) of the workgroup's rows stays in LDS over its tiles: one partial per
+// token and workgroup, so the merge is one wavefront per token, which computes the target logit as well.
+// 151936 x 2048, whole call: 1 token 456 -> 103 us (6.0 TB/s), 61 tokens 484 -> 104-123 us, 128 tokens 497 -> 140 us
+// (bound by the compute phase between two barriers, no longer by the stream; beyond that the 256 x 256 tiles, which
+// take 210 us for 129 to 256 tokens, are as good: two 128-token tiles here took 220-230).
+constexpr int kSWaves = 8, kSMaxTok = 128;
+
+struct LogprobStreamParams {
+    const uint16_t *h;
+    const uint16_t *w;
+    float *pmax, *psum;  // [T][n_ranges]
+    int T, H, V;
+    int n_ranges;        // ranges of vocabulary rows
+    int rows8;           // 8-row units per tile, at most 32
+    int passes;          // tiles per range
+    float inv_temp;
+};
+
+// s_waitcnt vmcnt(n) for a wave-uniform n the compiler does not know (0 for n beyond the table: waits for more)
+__device__ __forceinline__ void wait_vmcnt_uniform(int n)
+{
+    switch (n) {
+    case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+    case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+    case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+    case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+    case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+    case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+    case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
+    case 12: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    }
+}
+
+template <int kTok, int kSBufs>
+__global__ __launch_bounds__(64 * kSWaves, 2) void lmhead_stream_kernel(LogprobStreamParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int WT = kTok > 64 ? 2 : 1;            // wavefronts along the tokens
+    constexpr int WM = kSWaves / WT;                 // and along the rows
+    constexpr int MS = WT, NT = kTok / 32 / WT;      // 32-row and 32-token MFMA tiles of a wavefront
+    constexpr int kHCopies = kTok > 64 ? kTok / 64 : 1;   // h copies per wavefront and stage (at most)
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WT, wt = wave % WT;
+    const int c = lane & 31, h = lane >> 5;
+    const int H = p.H, V = p.V, rows = p.rows8 * 8;
+    const int stage_b = (rows + kTok) * kLRowB;
+    // (max, sum) of each wavefront row group in the current tile, then the workgroup's running pair
+    float *s_m = (float *)smem, *s_s = s_m + WM * kTok, *s_run = s_s + WM * kTok;
+    unsigned char *ring = smem + (2 * WM + 2) * kTok * 4;
+
+    const int range = blockIdx.x, T = p.T;
+    const int64_t first = (int64_t)range * p.passes * rows;
+    if (tid < kTok) {
+        s_run[tid] = -INFINITY;
+        s_run[kTok + tid] = 0.f;
+    }
+    // tiles of this workgroup that hold rows of the vocabulary
+    const int my_rows = (int)max((int64_t)0, min((int64_t)V - first, (int64_t)p.passes * rows));
+    const int my_tiles = (my_rows + rows - 1) / rows;
+    const int stages = H / kLKS, total = my_tiles * stages;
+
+    // this wavefront's copies of a stage: 8-row units wave, wave + 8, ... of the W tile, then of the h tile
+    const int nw = (p.rows8 - wave + kSWaves - 1) / kSWaves;                   // wave-uniform, 0..4
+    const int nh = max(0, ((T + 7) / 8 - wave + kSWaves - 1) / kSWaves);       // 0..kHCopies
+    const int n_copies = nw + nh;
+    uint32_t hoff[kHCopies];
+#pragma unroll
+    for (int i = 0; i < kHCopies; ++i) {
+        const int r = (wave + i * kSWaves) * 8 + (lane >> 3);
+        hoff[i] = (uint32_t)min(r, T - 1) * (uint32_t)(H * 2) + (((lane & 7) ^ ((r >> 1) & 7)) * 16);
+    }
+    const unsigned char *hbase = (const unsigned char *)p.h;
+    uint32_t woff[4];
+    const unsigned char *wbase = nullptr;
+    auto set_tile = [&](int tile) {
+        const int64_t v0 = first + (int64_t)tile * rows;
+        wbase = (const unsigned char *)p.w + v0 * H * 2;
+        const int last = (int)min((int64_t)V - 1 - v0, (int64_t)(rows - 1));   // rows past V read the last one: never used
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = (wave + i * kSWaves) * 8 + (lane >> 3);
+            woff[i] = (uint32_t)min(r, last) * (uint32_t)(H * 2) + (((lane & 7) ^ ((r >> 1) & 7)) * 16);
+        }
+    };
+    // The next stage to request.  The tiles start their k range at different places: rows lie H * 2 bytes apart, and
+    // workgroups that all read the same k of their rows at the same time meet on a fraction of the memory channels
+    // (151936 x 2048, 61 tokens: 135 us with one starting point, 104 us with these).
+    int c_tile = 0, c_ks = 0, k_at = (range / 8) % stages;
+    auto copy_one = [&](int buf, int i) {   // i < 4: W, else h
+        unsigned char *dst = ring + buf * stage_b;
+        if (i < 4) {
+            if (i < nw)   // nontemporal: read once (temporal: 117 us)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wbase + k_at * kLRowB + woff[i]),
+                                                 (__attribute__((address_space(3))) void *)(dst + (wave + i * kSWaves) * 8 * kLRowB),
+                                                 16, 0, 2);
+        } else if (i - 4 < nh) {
+            copy16_to_lds(hbase + k_at * kLRowB + hoff[i - 4], dst + rows * kLRowB + (wave + (i - 4) * kSWaves) * 8 * kLRowB);
+        }
+    };
+    auto advance = [&]() {
+        k_at = k_at + 1 == stages ? 0 : k_at + 1;
+        if (++c_ks == stages) {
+            c_ks = 0;
+            ++c_tile;
+        }
+    };
+    auto copy_stage = [&](int buf) {
+        if (c_ks == 0) set_tile(c_tile);
+#pragma unroll
+        for (int i = 0; i < 4 + kHCopies; ++i) copy_one(buf, i);
+        advance();
+    };
+
+    const bool busy = wm * MS * 32 < rows;
+    int aoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) aoff[j] = c * kLRowB + (((2 * j + h) ^ ((c >> 1) & 7)) * 16);
+    f32x16 acc[MS][NT];
+    auto clear = [&]() {
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[ms][nt][i] = 0.f;
+    };
+    clear();
+    const float k2 = p.inv_temp * 1.44269504088896340736f;
+#pragma unroll
+    for (int b = 0; b < kSBufs - 1; ++b)
+        if (b < total) copy_stage(b);
+    int ks = 0, tile = 0, buf = 0;
+    for (int s = 0; s < total; ++s) {
+        // stage s has landed: at most the copies of the kSBufs - 2 stages behind it are still on their way
+        wait_vmcnt_uniform(s + kSBufs - 1 <= total ? n_copies * (kSBufs - 2) : 0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // everybody's; and stage s - 1 is no longer read
+        const bool more = s + kSBufs - 1 < total;
+        const int nbuf = buf == 0 ? kSBufs - 1 : buf - 1;
+        if (more && c_ks == 0) set_tile(c_tile);
+        const unsigned char *abase = ring + buf * stage_b + wm * MS * 32 * kLRowB;
+        const unsigned char *bbase = ring + buf * stage_b + (rows + wt * NT * 32) * kLRowB;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (more) {   // the copies go out between the matrix instructions (128 tokens: 2-3 % faster than all in front)
+#pragma unroll
+                for (int i = 2 * j; i < 2 * j + 2; ++i)
+                    if (i < 4 + kHCopies) copy_one(nbuf, i);
+            }
+            if (busy) {
+                bf16x8 a[MS];
+#pragma unroll
+                for (int ms = 0; ms < MS; ++ms) a[ms] = *(const bf16x8 *)(abase + ms * 32 * kLRowB + aoff[j]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const bf16x8 b = *(const bf16x8 *)(bbase + nt * 32 * kLRowB + aoff[j]);
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms)
+                        acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ms], b, acc[ms][nt], 0, 0, 0);
+                }
+            }
+        }
+        if (more) advance();
+        buf = buf + 1 == kSBufs ? 0 : buf + 1;
+        if (++ks == stages) {
+            // end of a tile: lane (c, h), register i of acc[ms][nt] -> row 32 (MS wm + ms) + 8 (i / 4) + 4 h + i % 4,
+            // token 32 (NT wt + nt) + c
+            const int valid = (int)min((int64_t)rows, (int64_t)V - (first + (int64_t)tile * rows));
+            const int row_lane = wm * MS * 32 + 4 * h;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float m = -INFINITY;
+#pragma unroll
+                for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        if (row_lane + ms * 32 + 8 * (i >> 2) + (i & 3) >= valid) acc[ms][nt][i] = -INFINITY;
+                        m = fmaxf(m, acc[ms][nt][i]);
+                    }
+                m = fmaxf(m, __shfl_xor(m, 32, 64));
+                float sum = 0.f;
+                if (m > -INFINITY) {
+                    const float mk = m * k2;
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(acc[ms][nt][i], k2, -mk));
+                }
+                sum += __shfl_xor(sum, 32, 64);
+                if (h == 0) {
+                    s_m[wm * kTok + (wt * NT + nt) * 32 + c] = m;
+                    s_s[wm * kTok + (wt * NT + nt) * 32 + c] = sum;
+                }
+            }
+            clear();
+            lds_barrier();
+            // the next write of s_m / s_s lies behind at least one further stage barrier
+            if (tid < kTok) {
+                float m = s_run[tid];
+                const float m_old = m;
+#pragma unroll
+                for (int w = 0; w < WM; ++w) m = fmaxf(m, s_m[w * kTok + tid]);
+                float sum = m_old > -INFINITY ? s_run[kTok + tid] * __builtin_amdgcn_exp2f((m_old - m) * k2) : 0.f;
+#pragma unroll
+                for (int w = 0; w < WM; ++w) {
+                    const float mw = s_m[w * kTok + tid];
+                    if (mw > -INFINITY) sum += s_s[w * kTok + tid] * __builtin_amdgcn_exp2f((mw - m) * k2);
+                }
+                s_run[tid] = m;
+                s_run[kTok + tid] = sum;
+            }
+            ks = 0;
+            ++tile;
+        }
+    }
+    if (tid < T) {   // own thread's entry
+        p.pmax[(int64_t)tid * p.n_ranges + range] = s_run[tid] * p.inv_temp;
+        p.psum[(int64_t)tid * p.n_ranges + range] = s_run[kTok + tid];
+    }
+}
+
+// One wavefront per token: the target logit as in target_logit_kernel, then the workgroups' partials, folded by a
+// wavefront reduction in a fixed order.
+__global__ __launch_bounds__(64) void lse_stream_finalize_kernel(LogprobStreamParams p, const int32_t *__restrict__ target,
+                                                                 float *__restrict__ logprob)
+{
+    const int t = blockIdx.x, lane = threadIdx.x;
+    float m = -INFINITY, s = 0.f;
+    for (int b = lane; b < p.n_ranges; b += 64) {
+        const float mb = p.pmax[(int64_t)t * p.n_ranges + b], sb = p.psum[(int64_t)t * p.n_ranges + b];
+        if (mb > m) {
+            s = s * expf(m - mb) + sb;
+            m = mb;
+        } else if (mb > -INFINITY) {
+            s += sb * expf(mb - m);
+        }
+    }
+    const float mm = wave_max(m);
+    double ss = m > -INFINITY ? (double)s * (double)expf(m - mm) : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    const int y = target[t];
+    float z = __uint_as_float(0x7fc00000u);
+    if (y >= 0 && y < p.V) z = row_dot(p.h + (int64_t)t * p.H, p.w + (int64_t)y * p.H, p.H, lane) * p.inv_temp;
+    if (lane == 0) logprob[t] = z - (mm + (float)log(ss));
+}
+
+template <int kTok, int kSBufs>
+int launch_lmhead_stream(const LogprobStreamParams &p, hipStream_t s)
+{
+    auto kern = lmhead_stream_kernel<kTok, kSBufs>;
+    static LdsLimitOnce once;
+    if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(lmhead stream)")) return rc;
+    const size_t lds = (size_t)(2 * (kTok > 64 ? 4 : 8) + 2) * kTok * 4 + (size_t)kSBufs * (p.rows8 * 8 + kTok) * kLRowB;
+    kern<<<dim3((unsigned)p.n_ranges), dim3(64 * kSWaves), lds, s>>>(p);
+    return check_hip(hipGetLastError(), "lmhead_stream_kernel");
+}
+
+int launch_logprob_stream(LogprobStreamParams p, const int32_t *target, float *logprob, void *ws, hipStream_t s)
+{
+    // one workgroup per CU, but no more partials per token than the workspace of the tiled kernel holds
+    const int64_t units = ((int64_t)p.V + 7) / 8;
+    const int64_t max_units = 32;
+        const int tok = p.T <= 32 ? 32 : p.T <= 64 ? 64 : 128;
+    p.n_ranges = (int)min((int64_t)256, ((int64_t)p.V + kLTile - 1) / kLTile);
+    p.passes = (int)((units + (int64_t)p.n_ranges * max_units - 1) / ((int64_t)p.n_ranges * max_units));
+    p.rows8 = (int)((units + (int64_t)p.n_ranges * p.passes - 1) / ((int64_t)p.n_ranges * p.passes));
+    p.pmax = (float *)ws;
+    p.psum = p.pmax + (size_t)p.n_ranges * p.T;
+    int rc;
+    if (tok == 32) rc = launch_lmhead_stream<32, 4>(p, s);
+    else if (tok == 64 && p.rows8 <= 30) rc = launch_lmhead_stream<64, 4>(p, s);
+    else if (tok == 64) rc = launch_lmhead_stream<64, 3>(p, s);
+    else rc = launch_lmhead_stream<128, 3>(p, s);
+    if (rc) return rc;
+    lse_stream_finalize_kernel<<<dim3((unsigned)p.T), dim3(64), 0, s>>>(p, target, logprob);
+    return check_hip(hipGetLastError(), "lse_stream_finalize_kernel");
+}
+
 size_t logprob_ws_bytes(int T, int H, int V)
 {
     (void)H;
@@ -286,6 +583,7 @@ int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T,
     p.n_blocks = (V + kLTile - 1) / kLTile;
     p.m_tiles = (T + kLTile - 1) / kLTile;
     p.n_mgroups = (p.m_tiles + kLGroupM - 1) / kLGroupM;
+    p.group_m = (p.m_tiles + p.n_mgroups - 1) / p.n_mgroups;
     p.pmax = (float *)ws;
     p.psum = p.pmax + (size_t)p.n_blocks * T;
     float *tgt = p.psum + (size_t)p.n_blocks * T;
@@ -294,19 +592,28 @@ int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T,
         set_error("logprob: H too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    const int64_t n_ngroups = (p.n_blocks + kLGroupN - 1) / kLGroupN;
-    const int64_t supers = (((int64_t)p.n_mgroups * n_ngroups + 7) / 8) * 8;
-    const int64_t grid = supers * kLGroupM * kLGroupN;
-    if (grid > 0x7fffffffLL) {
+    if (T <= kSMaxTok) {
+        LogprobStreamParams q;
+        q.h = p.h;
+        q.w = p.w;
+        q.T = T;
+        q.H = H;
+        q.V = V;
+        q.inv_temp = inv_temp;
+        return launch_logprob_stream(q, target, logprob, ws, s);
+    }
+    const int64_t tiles = (int64_t)p.m_tiles * p.n_blocks;
+    if (tiles > 0x7ffffff0LL) {
         set_error("logprob: grid too large");
         return QARL_ERR_UNSUPPORTED;
     }
+    p.per_xcd = (int)((tiles + 7) / 8);
     static LdsLimitOnce once;
     if (int rc0 = raise_lds_limit((const void *)lmhead_lse_kernel, once, "hipFuncSetAttribute(lmhead)")) return rc0;
     target_logit_kernel<<<dim3((T + 3) / 4), dim3(256), 0, s>>>(p.h, p.w, target, T, H, V, inv_temp, tgt);
     int rc = check_hip(hipGetLastError(), "target_logit_kernel");
     if (rc) return rc;
-    lmhead_lse_kernel<<<dim3((unsigned)grid), dim3(kLThreads), kLLds, s>>>(p);
+    lmhead_lse_kernel<<<dim3((unsigned)p.per_xcd * 8), dim3(kLThreads), kLLds, s>>>(p);
     rc = check_hip(hipGetLastError(), "lmhead_lse_kernel");
     if (rc) return rc;
     lse_finalize_kernel<<<dim3((T + kFinTokens - 1) / kFinTokens), dim3(kFinTokens * kFinSlices), 0, s>>>(p.pmax, p.psum, tgt, T, p.n_blocks,

@@ -90,3 +90,20 @@ def test_target_outside_vocabulary_gives_nan_for_that_token_only(q, oracle):
     ok = np.ones(T, dtype=bool)
     ok[[3, 40, 69]] = False
     assert np.abs(got[ok].astype(np.float64) - ref[ok]).max() <= TOL_LP
+
+
+@pytest.mark.parametrize("T,H,V", [
+    (1, 64, 40), (1, 2048, 3001), (31, 128, 257), (32, 192, 256), (33, 64, 2049), (61, 320, 70001), (64, 128, 66000),
+    (65, 64, 8), (127, 128, 9000), (128, 256, 131073), (129, 128, 9000), (257, 64, 4097), (2305, 64, 520)])
+def test_logprob_edges_of_the_token_and_vocabulary_tiles(q, oracle, T, H, V):
+    """Both kernels on either side of their boundary (128 tokens), token tiles of 32 / 64 / 128 / 256 with remainders, one
+    to several vocabulary tiles per workgroup, the last one ragged or empty, nine token tiles (two uneven groups)."""
+    h = synth.normal_bf16((T, H), 1.0, seed=T + H)
+    w = synth.normal_bf16((V, H), 2.0 / math.sqrt(H), seed=V)
+    tg = synth.targets(T, V, seed=9)
+    tg[0], tg[-1] = V - 1, 0
+    got = q.qarl_token_logprob(h.cuda(), w.cuda(), tg.cuda(), 1.5)["logprob"]
+    assert torch.equal(got, q.qarl_token_logprob(h.cuda(), w.cuda(), tg.cuda(), 1.5)["logprob"])
+    rows = np.arange(T) if T <= 130 and V * H < 10 ** 7 else np.unique(np.linspace(0, T - 1, 24).astype(np.int64))
+    ref = oracle.token_logprob(np_bits(h)[rows], np_bits(w), tg.numpy()[rows], 1.5)
+    assert np.abs(got.cpu().numpy()[rows].astype(np.float64) - ref).max() <= TOL_LP
