@@ -413,11 +413,13 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
         return QARL_ERR_WORKSPACE;
     }
     hipStream_t st = (hipStream_t)stream;
+    if (epilogue == QARL_EPI_COMBINE && !combine_w) {
+        set_error("qarl_qgemm_routed: COMBINE needs combine_w");
+        return QARL_ERR_INVALID_ARG;
+    }
+    if (int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
+        return launch_qgemm_small_w4(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
     if (epilogue == QARL_EPI_COMBINE) {
-        if (!combine_w) {
-            set_error("qarl_qgemm_routed: COMBINE needs combine_w");
-            return QARL_ERR_INVALID_ARG;
-        }
         a.epilogue = QARL_EPI_NONE;
         a.out = ws;
         a.out_f32 = 1;

@@ -117,6 +117,20 @@ __device__ __forceinline__ u32x2 e4m3_quantize_bf16x8(const RowScale &rs, u32x4 
     return o;
 }
 
+// Eight e4m3 bytes -> the bf16 values they stand for (exact: four significant bits).
+__device__ __forceinline__ u32x4 e4m3_as_bf16x8(u32x2 q8)
+{
+    u32x4 o;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)q8[i], false);
+        const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)q8[i], true);
+        o[2 * i] = (__float_as_uint(lo[0]) >> 16) | (__float_as_uint(lo[1]) & 0xffff0000u);
+        o[2 * i + 1] = (__float_as_uint(hi[0]) >> 16) | (__float_as_uint(hi[1]) & 0xffff0000u);
+    }
+    return o;
+}
+
 // A constant the optimiser cannot see through, held in a scalar (vector) register.  (a & mask) | c with such operands
 // is selected as one v_and_or_b32; with literal operands the compiler emits v_and + v_or (a VOP3 encoding takes no
 // literal on this target).  The operation itself must stay an instruction the compiler knows: a matrix instruction
@@ -231,6 +245,9 @@ bool qgemm_stream_routed_supported(int fmt, int N, int K, int T, int topk);
 int launch_qgemm_stream_w4(const GemmArgs &a, hipStream_t s);
 bool qgemm_stream_w4_supported(int N, int K);
 bool qgemm_stream_w4_routed_supported(int N, int K, int T, int topk);
+// Routed W4A16 / W4A8 calls of a few pairs; combine_w: the COMBINE epilogue, a.out then is its [T][N] output
+bool qgemm_small_w4_supported(int N, int K, int T, int topk, int epilogue);
+int launch_qgemm_small_w4(const GemmArgs &a, const float *combine_w, hipStream_t s);
 int launch_qgemm_tile(const GemmArgs &a, hipStream_t s);
 int launch_qgemm_tile_fp8(const GemmArgs &a, hipStream_t s);
 // Straight-through backward of the W4A16 grouped GEMM: a.x = dY bf16 [M][N], a.out = dX [M][K]

@@ -352,15 +352,7 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
                         const int ch = lane + 64 * u;
                         if (ch < n16) {
                             const u32x2 q8 = e4m3_quantize_bf16x8(rs, v[rr][u]);
-                            u32x4 o;   // e4m3 -> fp32 is exact, and so is its upper half as bf16 (four significant bits)
-#pragma unroll
-                            for (int i = 0; i < 2; ++i) {
-                                const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)q8[i], false);
-                                const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)q8[i], true);
-                                o[2 * i] = (__float_as_uint(lo[0]) >> 16) | (__float_as_uint(lo[1]) & 0xffff0000u);
-                                o[2 * i + 1] = (__float_as_uint(hi[0]) >> 16) | (__float_as_uint(hi[1]) & 0xffff0000u);
-                            }
-                            *(u32x4 *)(xs + r * stride + ch * 16) = o;
+                            *(u32x4 *)(xs + r * stride + ch * 16) = e4m3_as_bf16x8(q8);
                         }
                     }
                     if (lane == 0) s_rsc[r] = sxr;

@@ -473,6 +473,41 @@ def test_routed_mode_quantizes_its_rows_like_the_row_quantizer(q, oracle, fmt_na
     assert np.array_equal(np_bits(out_rt), np_bits(out_grp))
 
 
+# Few pairs (T * topk <= 64) take kernels of their own: one pair, one token with eight slots, several column blocks with a
+# remainder, the most pairs, 16 slots (the most the fused combine takes) and 32 (two launches), one pair too many.
+_FEW_PAIRS = [(64, 32, 256, 1, 1), (64, 96, 2048, 1, 8), (64, 1056, 1024, 3, 8), (64, 544, 768, 8, 8), (64, 64, 1280, 4, 16),
+              (64, 64, 512, 2, 32), (64, 160, 512, 13, 5)]
+
+
+@pytest.mark.parametrize("fmt_name,E,N,K,T,topk", [(f,) + sh for f in ("w4a16", "w4a8") for sh in _FEW_PAIRS])
+def test_routed_mode_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, T, topk):
+    """Bit for bit the grouped decode path (itself held against the oracle) on the grouping of the same ids: plain
+    epilogue fp32 and bf16, SiLU*mul, the combine in fp32 and bf16 with rows per pair and per token."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    w = synth.normal_bf16((E, N, K), 0.02, seed=K + T).cuda()
+    x = synth.normal_bf16((T, K), 1.0, seed=K + T + 1).cuda()
+    qw = q.qarl_quantize_weights(w, fmt)
+    r = q.qarl_moe_route(synth.router_logits(T, E, K + T + 2).cuda(), topk)
+    M, inv = T * topk, r.pairs.long()
+
+    def grouped(rows, **kw):
+        if fmt != q.QARL_W4A16_G128:
+            rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(rows)
+        return q.qarl_qgemm_grouped(qw, rows, r.offsets, M, path=q.QARL_PATH_DECODE, **kw)
+
+    for dt in (q.QARL_OUT_F32, q.QARL_OUT_BF16):
+        got = q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, out_dtype=dt)
+        assert torch.equal(got[inv], grouped(x, row_map=r.tokens, out_dtype=dt))
+    got = q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, epilogue=q.QARL_EPI_SILU_MUL)
+    assert torch.equal(got[inv], grouped(x, row_map=r.tokens, epilogue=q.QARL_EPI_SILU_MUL))
+    xp = synth.normal_bf16((M, K), 1.0, seed=K + T + 3).cuda()           # one row per pair, pair order
+    kw = dict(epilogue=q.QARL_EPI_COMBINE, combine_w=r.w)
+    for dt in (q.QARL_OUT_F32, q.QARL_OUT_BF16):
+        for per_token, rows, ordered in ((False, xp, xp[inv]), (True, x, x[r.tokens.long()])):
+            got = q.qarl_qgemm_routed(qw, rows, r.ids, T, topk, per_token, out_dtype=dt, **kw)
+            assert torch.equal(got, grouped(ordered.contiguous(), sorted_pairs=r.pairs, T=T, topk=topk, out_dtype=dt, **kw))
+
+
 @pytest.mark.parametrize("fmt_name", ["fp8", "w4a8"])
 def test_routed_mode_rows_outside_the_fast_division_range(q, oracle, fmt_name):
     """Rows whose scale leaves the range of the corrected-reciprocal division (absmax near 2^-100 and near 2^100),
