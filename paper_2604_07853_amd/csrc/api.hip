@@ -419,6 +419,8 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
     }
     if (int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
         return launch_qgemm_small_w4(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
+    if (!int4_weights(W->fmt) && qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))
+        return launch_qgemm_small_fp8(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
     if (epilogue == QARL_EPI_COMBINE) {
         a.epilogue = QARL_EPI_NONE;
         a.out = ws;

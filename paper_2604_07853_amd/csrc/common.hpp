@@ -169,6 +169,21 @@ __device__ __forceinline__ bf16x8 unpack_int4_word(uint32_t w)
     return __builtin_bit_cast(bf16x8, d);
 }
 
+// e2m1 magnitude code (3 bits) -> e4m3 byte of the same value: 0, 0.5, 1, 1.5 | 2, 3, 4, 6.  Every e2m1 value is
+// an e4m3 value, so FP4 weights are widened in registers (one byte permute per four codes) and meet the e4m3
+// token rows in the same matrix instruction as FP8 weights do.
+constexpr uint32_t kE2m1LutLo = 0x3c383000u, kE2m1LutHi = 0x4c484440u;
+
+// A word of eight packed e2m1 codes (byte b: element b in the low nibble, element 4 + b in the high nibble)
+// -> the eight e4m3 bytes in element order.
+__device__ __forceinline__ u32x2 widen_e2m1_word(uint32_t w)
+{
+    u32x2 o;
+    o[0] = __builtin_amdgcn_perm(kE2m1LutHi, kE2m1LutLo, w & 0x07070707u) | ((w & 0x08080808u) << 4);
+    o[1] = __builtin_amdgcn_perm(kE2m1LutHi, kE2m1LutLo, (w >> 4) & 0x07070707u) | (w & 0x80808080u);
+    return o;
+}
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also drains every outstanding
 // global load of the wavefront (the workgroup-scope fence waits on vmcnt), which would stall the
 // weight prefetch rings; kernels whose cross-wavefront traffic goes through LDS alone use this.
@@ -248,6 +263,9 @@ bool qgemm_stream_w4_routed_supported(int N, int K, int T, int topk);
 // Routed W4A16 / W4A8 calls of a few pairs; combine_w: the COMBINE epilogue, a.out then is its [T][N] output
 bool qgemm_small_w4_supported(int N, int K, int T, int topk, int epilogue);
 int launch_qgemm_small_w4(const GemmArgs &a, const float *combine_w, hipStream_t s);
+// The same for FP8 / FP4
+bool qgemm_small_fp8_supported(int N, int K, int T, int topk, int epilogue);
+int launch_qgemm_small_fp8(const GemmArgs &a, const float *combine_w, hipStream_t s);
 int launch_qgemm_tile(const GemmArgs &a, hipStream_t s);
 int launch_qgemm_tile_fp8(const GemmArgs &a, hipStream_t s);
 // Straight-through backward of the W4A16 grouped GEMM: a.x = dY bf16 [M][N], a.out = dX [M][K]

@@ -69,21 +69,6 @@ size_t stream_lds_bytes(int K, int MT, bool routed = false)
     return rows * 12 + 16 + rows * x_stride(K) + (routed ? 8 * (size_t)kIdsRows + 4 * kSWaves : 0);
 }
 
-// e2m1 magnitude code (3 bits) -> e4m3 byte of the same value: 0, 0.5, 1, 1.5 | 2, 3, 4, 6.  Every e2m1 value is
-// an e4m3 value, so FP4 weights are widened in registers (one byte permute per four codes) and meet the e4m3
-// token rows in the same matrix instruction as FP8 weights do.
-constexpr uint32_t kE2m1LutLo = 0x3c383000u, kE2m1LutHi = 0x4c484440u;
-
-// A word of eight packed e2m1 codes (byte b: element b in the low nibble, element 4 + b in the high nibble)
-// -> the eight e4m3 bytes in element order.
-__device__ __forceinline__ u32x2 widen_e2m1_word(uint32_t w)
-{
-    u32x2 o;
-    o[0] = __builtin_amdgcn_perm(kE2m1LutHi, kE2m1LutLo, w & 0x07070707u) | ((w & 0x08080808u) << 4);
-    o[1] = __builtin_amdgcn_perm(kE2m1LutHi, kE2m1LutLo, (w >> 4) & 0x07070707u) | (w & 0x80808080u);
-    return o;
-}
-
 // EPI: NONE or SILU_MUL; MT: 16-row token tiles per block; R: ring depth in 128-k steps (must divide K/128);
 // W4: the weights are packed e2m1 codes (half a byte per weight) instead of e4m3 bytes; QX: routed mode.
 template <int EPI, int MT, int R, bool W4, bool QX>

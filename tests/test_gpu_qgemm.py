@@ -479,7 +479,7 @@ _FEW_PAIRS = [(64, 32, 256, 1, 1), (64, 96, 2048, 1, 8), (64, 1056, 1024, 3, 8),
               (64, 64, 512, 2, 32), (64, 160, 512, 13, 5)]
 
 
-@pytest.mark.parametrize("fmt_name,E,N,K,T,topk", [(f,) + sh for f in ("w4a16", "w4a8") for sh in _FEW_PAIRS])
+@pytest.mark.parametrize("fmt_name,E,N,K,T,topk", [(f,) + sh for f in ("w4a16", "w4a8", "fp8", "fp4") for sh in _FEW_PAIRS])
 def test_routed_mode_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, T, topk):
     """Bit for bit the grouped decode path (itself held against the oracle) on the grouping of the same ids: plain
     epilogue fp32 and bf16, SiLU*mul, the combine in fp32 and bf16 with rows per pair and per token."""
