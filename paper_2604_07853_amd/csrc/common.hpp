@@ -208,6 +208,55 @@ __device__ __forceinline__ void copy_barrier()
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Tiles of a grouped launch: `rows` (expert_offsets) are cut into tiles of kTile rows that never span two experts, and
+// every tile has n_blocks work items.  The host only knows an upper bound of the tiles (every expert may end in a
+// partial one), so the grid is that bound, rounded up, and the true number comes from the scan every wavefront makes
+// here (four experts per lane, E <= 256, no barrier).  Workgroup ids go round-robin over the 8 XCDs; an XCD gets a
+// contiguous eighth of the TRUE items (the blocks of one tile share its L2), the surplus workgroups of all XCDs leave.
+// (Eighths of the bound left the surplus on the last XCDs: 7 of 8 worked on 3001 tokens and 128 experts.  W4A8 layer of
+// 3001 tokens 415 -> 389 us, FP8 of 8192 723 -> 695, W4A16 of 16384 1697 -> 1682.)
+struct GroupedTile {
+    int e, mtile, block;   // expert, tile within the expert, work item of the tile
+};
+template <int kTile>
+__device__ __forceinline__ bool find_grouped_tile(const int32_t *offsets, int E, int n_blocks, GroupedTile &t)
+{
+    const int lane = threadIdx.x & 63;
+    int cnt[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int ex = lane * 4 + q;
+        cnt[q] = ex < E ? (offsets[ex + 1] - offsets[ex] + kTile - 1) / kTile : 0;
+        sum += cnt[q];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    const unsigned items = (unsigned)__builtin_amdgcn_readlane(incl, 63) * (unsigned)n_blocks;   // at most the grid: below 2^31
+    const unsigned per_xcd = (items + 7) / 8, idx = blockIdx.x / 8, v = (blockIdx.x % 8) * per_xcd + idx;
+    if (idx >= per_xcd || v >= items) return false;
+    const int slot = (int)(v / (unsigned)n_blocks);
+    t.block = (int)(v - (unsigned)slot * (unsigned)n_blocks);
+    int base = incl - sum, found = -1, mt = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (slot >= base && slot < base + cnt[q]) {
+            found = lane * 4 + q;
+            mt = slot - base;
+        }
+        base += cnt[q];
+    }
+    const unsigned long long hit = __ballot(found >= 0);
+    if (hit == 0) return false;   // does not happen: slot < number of tiles
+    const int src = __ffsll((long long)hit) - 1;
+    t.e = __builtin_amdgcn_readfirstlane(__shfl(found, src, 64));
+    t.mtile = __builtin_amdgcn_readfirstlane(__shfl(mt, src, 64));
+    return true;
+}
+
 // Host-side error plumbing (api.hip).
 void set_error(const char *fmt, ...);
 int check_hip(hipError_t e, const char *what);

@@ -38,7 +38,6 @@ struct DxParams {
     const int32_t *out_row_map;
     void *out;                // [M][K]
     int E, N, K, out_f32;
-    int m_slots, total;
 };
 
 // 16-byte chunk swizzles of 256-byte LDS rows.  As: rows are gradient rows, read by 32 consecutive rows at once.
@@ -101,43 +100,10 @@ __global__ __launch_bounds__(kBwThreads, 4) void qgemm_dx_kernel(DxParams p)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int N = p.N, K = p.K, G = K / kGroup;
 
-    const int per_xcd = p.total / 8;
-    const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int g = v % G;   // output column block = scale group
-    const int slot = v / G;
-    if (slot >= p.m_slots) return;
-    // slot -> (expert, row tile): wavefront-level scan of the per-expert tile counts (four experts per lane)
-    int e, mtile;
-    {
-        int cnt[4], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int ex = lane * 4 + q;
-            cnt[q] = ex < p.E ? (p.offsets[ex + 1] - p.offsets[ex] + kTM - 1) / kTM : 0;
-            sum += cnt[q];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int base = incl - sum, found = -1, mt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (slot >= base && slot < base + cnt[q]) {
-                found = lane * 4 + q;
-                mt = slot - base;
-            }
-            base += cnt[q];
-        }
-        const unsigned long long hit = __ballot(found >= 0);
-        if (hit == 0) return;
-        const int src = __ffsll((long long)hit) - 1;
-        e = __builtin_amdgcn_readfirstlane(__shfl(found, src, 64));
-        mtile = __builtin_amdgcn_readfirstlane(__shfl(mt, src, 64));
-    }
-    const int row0 = p.offsets[e] + mtile * kTM;
+    GroupedTile tile;
+    if (!find_grouped_tile<kTM>(p.offsets, p.E, G, tile)) return;
+    const int e = tile.e, g = tile.block;   // output column block = scale group
+    const int row0 = p.offsets[e] + tile.mtile * kTM;
     const int mrem = min(kTM, p.offsets[e + 1] - row0);
     if (tid < kTM) s_orow[tid] = tid < mrem ? (p.out_row_map ? p.out_row_map[row0 + tid] : row0 + tid) : -1;
     for (int n = tid; n < N; n += kBwThreads) sc[n] = bf16_bits_to_f32(p.scales[((int64_t)e * N + n) * G + g]);
@@ -572,8 +538,6 @@ int launch_qgemm_dx(const GemmArgs &a, hipStream_t s)
         set_error("qgemm dx: grid too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    p.m_slots = (int)slots;
-    p.total = (int)total;
     const size_t lds = (size_t)(kTM + kTK) * kStageN * 2 + (size_t)a.N * 4;
     static LdsLimitOnce once;
     if (int rc = raise_lds_limit((const void *)qgemm_dx_kernel, once, "hipFuncSetAttribute(qgemm dx)")) return rc;

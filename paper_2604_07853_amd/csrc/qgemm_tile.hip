@@ -42,8 +42,6 @@ struct TileParams {
     void *out;
     int E, N, K, out_f32;
     int n_blocks;   // column blocks per expert
-    int m_slots;    // upper bound of token tiles over all experts
-    int total;      // n_blocks * m_slots rounded up to a multiple of 8
 };
 
 // MS: 32-row token tiles per wavefront (workgroup tile = 32 MS tokens x 256 columns).
@@ -63,47 +61,10 @@ __global__ __launch_bounds__(kTileThreads, MS == 2 ? 4 : 2) void qgemm_tile_kern
     const int tid = threadIdx.x, lane = tid & 63, wn = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
 
-    // workgroup id -> (m slot, column block): consecutive ids go round-robin over the 8 XCDs, so
-    // give every XCD a contiguous range of tiles: column blocks of one token tile share its L2.
-    const int per_xcd = p.total / 8;
-    const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int nb = v % p.n_blocks;
-    const int slot = v / p.n_blocks;
-    if (slot >= p.m_slots) return;
-
-    // slot -> (expert, tile within expert): every wavefront scans the per-expert tile counts itself
-    // (four experts per lane, prefix sum across lanes), so no barrier is needed to agree on it.
-    int e, mtile;
-    {
-        int cnt[4], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int ex = lane * 4 + q;
-            cnt[q] = ex < p.E ? (p.offsets[ex + 1] - p.offsets[ex] + kBM - 1) / kBM : 0;
-            sum += cnt[q];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int base = incl - sum, found = -1, mt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (slot >= base && slot < base + cnt[q]) {
-                found = lane * 4 + q;
-                mt = slot - base;
-            }
-            base += cnt[q];
-        }
-        const unsigned long long hit = __ballot(found >= 0);
-        if (hit == 0) return;
-        const int src = __ffsll((long long)hit) - 1;
-        e = __builtin_amdgcn_readfirstlane(__shfl(found, src, 64));
-        mtile = __builtin_amdgcn_readfirstlane(__shfl(mt, src, 64));
-    }
-    const int row0 = p.offsets[e] + mtile * kBM;
+    GroupedTile tile;
+    if (!find_grouped_tile<kBM>(p.offsets, p.E, p.n_blocks, tile)) return;
+    const int e = tile.e, nb = tile.block;
+    const int row0 = p.offsets[e] + tile.mtile * kBM;
     const int mrem = min(kBM, p.offsets[e + 1] - row0);
     if (tid < kBM) {
         // rows past the expert's end read the tile's first row (valid data, results never stored)
@@ -356,8 +317,6 @@ static int launch_cfg(const GemmArgs &a, hipStream_t s)
         set_error("qgemm (prefill path): grid too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    p.m_slots = (int)slots;
-    p.total = (int)total;
     const size_t lds = 2 * ((size_t)kBM * kARowB + kBM * 4);
     static LdsLimitOnce once;
     auto kern = qgemm_tile_kernel<EPI, MS>;

@@ -47,7 +47,6 @@ struct Tile8Params {
     int n_blocks;   // column blocks per expert
     int bpw;        // consecutive column blocks one workgroup computes
     int n_bgroups;  // ceil(n_blocks / bpw)
-    int m_slots, total;
 };
 
 template <int EPI, bool W4>
@@ -67,45 +66,10 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
     const int wm = wave >> 2, wn = wave & 3;
     const int c = lane & 31, h = lane >> 5;
 
-    // workgroup id -> (m slot, column block); XCD-contiguous ranges, column blocks of a token tile adjacent
-    const int per_xcd = p.total / 8;
-    const int v = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int nb0 = (v % p.n_bgroups) * p.bpw;
-    const int slot = v / p.n_bgroups;
-    if (slot >= p.m_slots) return;
-
-    // slot -> (expert, tile within expert): wavefront-level scan of the per-expert tile counts
-    int e, mtile;
-    {
-        int cnt[4], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int ex = lane * 4 + q;
-            cnt[q] = ex < p.E ? (p.offsets[ex + 1] - p.offsets[ex] + kFTM - 1) / kFTM : 0;
-            sum += cnt[q];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int base = incl - sum, found = -1, mt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (slot >= base && slot < base + cnt[q]) {
-                found = lane * 4 + q;
-                mt = slot - base;
-            }
-            base += cnt[q];
-        }
-        const unsigned long long hit = __ballot(found >= 0);
-        if (hit == 0) return;
-        const int src = __ffsll((long long)hit) - 1;
-        e = __builtin_amdgcn_readfirstlane(__shfl(found, src, 64));
-        mtile = __builtin_amdgcn_readfirstlane(__shfl(mt, src, 64));
-    }
-    const int row0 = p.offsets[e] + mtile * kFTM;
+    GroupedTile tile;
+    if (!find_grouped_tile<kFTM>(p.offsets, p.E, p.n_bgroups, tile)) return;
+    const int e = tile.e, nb0 = tile.block * p.bpw;
+    const int row0 = p.offsets[e] + tile.mtile * kFTM;
     const int mrem = min(kFTM, p.offsets[e + 1] - row0);
     if (tid < kFTM) {
         // rows past the expert's end read the tile's first row (valid data, results never stored)
@@ -458,8 +422,6 @@ static int launch_fp8_cfg(const GemmArgs &a, hipStream_t s)
         set_error("qgemm (prefill path): grid too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    p.m_slots = (int)slots;
-    p.total = (int)total;
     static LdsLimitOnce once;
     auto kern = qgemm_tile_fp8_kernel<EPI, W4>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(tile fp8)")) return rc;
