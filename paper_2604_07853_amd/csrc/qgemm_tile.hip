@@ -3,70 +3,82 @@
 // scales and with the same exact dequantized weight s*q, for experts that see hundreds to
 // thousands of token rows, where the path is a dense contraction.  (FP8: qgemm_tile_fp8.hip.)
 //
-// A workgroup owns a (32*MS)-token x 256-column tile of one expert.  Its eight wavefronts split
-// the columns: each owns 32 of them as MS v_mfma_f32_32x32x16 tiles, so no packed weight is read
-// or expanded twice in a workgroup.  Token rows are gathered once per workgroup into a
-// double-buffered LDS tile (one 128-k scale group per step) by asynchronous global -> LDS copies,
-// 16-byte chunks XOR-swizzled with the row so that copies and operand reads are free of bank
-// conflicts; packed weights go global ->
-// registers and are expanded there, so the LDS only carries the activation operand.  Small
-// wavefront tiles keep the register count at 128, four wavefronts per SIMD from two workgroups
-// that run out of step: global-load latency and the VALU work of the expansion are hidden by the
-// other wavefronts' MFMAs rather than by a deep software pipeline.  The kernel is bound by VALU
-// issue next to the MFMAs, so everything outside the k loop is kept short: the expert lookup is a
-// wavefront-level scan, output rows wait in LDS, SiLU uses the hardware
-// exp2 / rcp, and gate and up meet through one 16-lane row swap.
+// A workgroup owns 64 token rows x 256 columns of one expert, its four wavefronts 64 x 64 each (2 x 2 tiles of
+// v_mfma_f32_32x32x16_bf16): every operand read, every start value and every expanded word feeds two matrix
+// instructions, and no packed weight is read or expanded twice in a workgroup.  Everything a stage (one scale group)
+// needs reaches LDS by asynchronous copies one stage ahead: 16 KiB of gathered token rows (16-byte chunks XOR-swizzled
+// with the row, so that copies and operand reads are free of bank conflicts) and, for each wavefront alone, its four
+// 1 KiB blocks of codes, the group sums and the scales of its columns.  Two stages are 68 KiB, a wavefront takes at most 256
+// registers: two workgroups per CU that run out of step, one's lookup, first stage and stores under the other's loop.
+// In a slice of 8 k per lane the operand reads and the expansion of the next slice are spread between the four matrix
+// instructions of this one.  (Eight wavefronts of 64 x 32 with the codes in registers, operand reads twice as many per
+// matrix instruction, ran 2 % slower.)  A workgroup computes up to four neighbouring column blocks one after the other: the
+// expert lookup and the row gather are paid once, and the next block's first stage travels during the epilogue.  A
+// W4A16 layer of 16384 tokens with popular experts takes 1570 us with four blocks, 1585 with two, 1640 with one,
+// 1690 with all six / eight (fewer workgroups share a token tile in L2) and took 1670 with the wavefronts of 64 x 32.
 //
-// The group handling is the one described in qgemm_stream_w4.hip: codes become the exact bf16
-// values (q+24)/16, every scale group accumulates in its own fp32 accumulator that starts at
-// -1.5 * sum_k x (the sums come from a small pre-pass over the activations, once per call), and
-// is folded in with one FMA by 16*s.
+// What bounds it: 0.825 TFLOP of gate_up in 0.82-0.93 ms, about 0.95 PFLOP/s, where nothing but the matrix instructions of
+// this shape runs at 1.35; next to them a stage issues 6 VALU operations per matrix instruction (expansion 3.5, fold 2).
+//
+// The group handling is the one described in qgemm_stream_w4.hip: codes become the exact bf16 values (q+24)/16, every
+// scale group accumulates in its own fp32 accumulator that starts at -1.5 * sum_k x (the sums come from a small pre-pass
+// over the activations, once per call), and is folded in with one FMA by 16*s.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace qarl {
 
-constexpr int kBN = 256;
-constexpr int kTileWaves = kBN / 32;          // each wavefront owns 32 columns
-constexpr int kTileThreads = 64 * kTileWaves;
-constexpr int kARowB = kGroup * 2;            // bytes per LDS row: 128 bf16, no padding (chunks are swizzled)
+constexpr int kRows = 64, kCols = 256;        // tile of a workgroup
+constexpr int kWaves = 4, kThreads = 64 * kWaves;
+constexpr int kRowBytes = kGroup * 2;         // bytes of a token row per stage (bf16, no padding: chunks are swizzled)
+constexpr int kXBytes = kRows * kRowBytes;    // token rows of a stage
+constexpr int kWaveBytes = 4 * 1024 + 256 + 256;   // a wavefront's codes, group sums, scales
+constexpr int kStageBytes = kXBytes + kWaves * kWaveBytes;
+constexpr int kCopies = 10;                   // copies of a wavefront per stage
 
 struct TileParams {
-    const uint32_t *codes;
-    const void *scales;
-    const void *x;
-    const float *x_group_sums;
-    const float *x_scales;   // W4A8: scale of each activation row (x then holds e4m3 values as bf16), else null
+    const unsigned char *codes;   // 1 KiB blocks [E * N / 16][K / 128]
+    const unsigned char *scales;  // bf16 [E][N][K / 128]
+    const unsigned char *x;       // bf16 [x_rows][K]
+    const float *x_group_sums;    // [x_rows][K / 128]: -1.5 * sum of the group
+    const float *x_scales;        // W4A8: scale of each activation row (x then holds e4m3 values as bf16), else null
     const int32_t *row_map;
     const int32_t *out_row_map;
     const int32_t *offsets;
     void *out;
     int E, N, K, out_f32;
     int n_blocks;   // column blocks per expert
+    int bpw;        // consecutive column blocks one workgroup computes
+    int n_bgroups;  // ceil(n_blocks / bpw)
 };
 
-// MS: 32-row token tiles per wavefront (workgroup tile = 32 MS tokens x 256 columns).
-template <int EPI, int MS>
-__global__ __launch_bounds__(kTileThreads, MS == 2 ? 4 : 2) void qgemm_tile_kernel(TileParams p)
+__device__ __forceinline__ void copy4_to_lds(const void *gsrc, void *lds_dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gsrc,
+                                     (__attribute__((address_space(3))) void *)lds_dst, 4, 0, 0);
+}
+
+template <int EPI>
+__global__ __launch_bounds__(kThreads, 2) void qgemm_tile_kernel(TileParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr bool kSilu = (EPI == QARL_EPI_SILU_MUL);
-    constexpr int kBM = 32 * MS;
-    constexpr int kThreads = kTileThreads;
-    constexpr int kStride = kARowB;
-    constexpr int kBufBytes = kBM * kStride + kBM * 4;  // tile + per-row group sums
-    __shared__ __attribute__((aligned(16))) int s_rows[kBM];   // activation row of each tile row (clamped to a valid one)
-    __shared__ __attribute__((aligned(16))) int s_orow[kBM];   // output row, -1 past the expert's last row
-    __shared__ __attribute__((aligned(16))) float s_xsc[kBM];  // W4A8: row scale s_x (1 otherwise)
+    __shared__ __attribute__((aligned(16))) int s_rows[kRows];   // activation row of each tile row (clamped to a valid one)
+    __shared__ __attribute__((aligned(16))) int s_orow[kRows];   // output row, -1 past the expert's last row
+    __shared__ __attribute__((aligned(16))) float s_xsc[kRows];  // row scale s_x
 
-    const int tid = threadIdx.x, lane = tid & 63, wn = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
 
     GroupedTile tile;
-    if (!find_grouped_tile<kBM>(p.offsets, p.E, p.n_blocks, tile)) return;
-    const int e = tile.e, nb = tile.block;
-    const int row0 = p.offsets[e] + tile.mtile * kBM;
-    const int mrem = min(kBM, p.offsets[e + 1] - row0);
-    if (tid < kBM) {
+    if (!find_grouped_tile<kRows>(p.offsets, p.E, p.n_bgroups, tile)) return;
+    const int e = tile.e, nb_end = min(p.n_blocks, (tile.block + 1) * p.bpw);
+    int nb = tile.block * p.bpw;   // column block
+    const int row0 = p.offsets[e] + tile.mtile * kRows;
+    const int mrem = min(kRows, p.offsets[e + 1] - row0);
+    if (tid < kRows) {
         // rows past the expert's end read the tile's first row (valid data, results never stored)
         const int i = row0 + (tid < mrem ? tid : 0);
         const int xrow = p.row_map ? p.row_map[i] : i;
@@ -77,192 +89,203 @@ __global__ __launch_bounds__(kTileThreads, MS == 2 ? 4 : 2) void qgemm_tile_kern
     lds_barrier();
 
     const int N = p.N, K = p.K, G = K / kGroup;
-    // Weight row of this lane (any row may feed any lane of the B operand).  SILU_MUL: lanes c < 16
-    // take 16 gate rows, lanes c >= 16 the matching 16 up rows, so gate j and up j sit 16 lanes apart.
-    int nrow, ocol;
-    bool tile_ok;
-    if (kSilu) {
-        ocol = nb * (kBN / 2) + wn * 16 + (c & 15);
-        nrow = (c < 16 ? 0 : N / 2) + ocol;
-        tile_ok = ocol - (c & 15) + 16 <= N / 2;
-    } else {
-        ocol = nrow = nb * kBN + wn * 32 + c;
-        tile_ok = nrow - c + 32 <= N;
+    // Column tile t (0..7, 32 columns; this wavefront's are 2 wave and 2 wave + 1) -> first weight rows of its two 16-row
+    // blocks.  SILU_MUL: 16 gate rows and the matching 16 up rows, so gate j and up j sit 16 lanes apart in the result.
+    // Tiles past N read the expert's first rows (valid data, results never stored).
+    auto tile_ok = [&](int t) { return kSilu ? nb * (kCols / 2) + t * 16 + 16 <= N / 2 : nb * kCols + t * 32 + 32 <= N; };
+    auto block_row = [&](int t, int half) {
+        const int n = kSilu ? nb * (kCols / 2) + t * 16 + half * (N / 2) : nb * kCols + t * 32 + half * 16;
+        return tile_ok(t) ? n : half * 16;   // N >= 32
+    };
+
+    // ---- copies.  Token rows: an instruction moves 4 rows x 256 bytes, chunk q of row r to position q ^ (r & 15).
+    const unsigned char *xsrc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = wave * 16 + i * 4 + (lane >> 4);
+        xsrc[i] = p.x + (int64_t)s_rows[r] * K * 2 + (((lane & 15) ^ (r & 15)) << 4);
     }
-    // columns past N read row 0 of the expert (valid data, results never stored)
-    const int64_t wr = (int64_t)e * N + (tile_ok ? nrow : 0);
-    // Byte offsets from the (uniform) array bases; the launcher checks that every array is below 4 GiB.
-    //   codes: block (16-row tile, group g) is 1 KiB; this lane's row is wr % 16 of tile wr / 16 and it
-    //   takes the 16-byte pieces q = 2h + u (k in [32 q, +32)).
-    const uint32_t woff = (uint32_t)((wr / 16) * G * 1024 + (wr % 16) * 16 + h * 512);
-    const uint32_t soff = (uint32_t)(wr * G * 2);   // the row's bf16 scales
-
-    // ---- activation tile: kBM rows x 128 k by asynchronous copies.  A wavefront instruction moves 4 rows x 256
-    // bytes (lane L: row L / 16, LDS chunk L % 16); chunk q of row r sits at r * 256 + (q ^ (r & 15)) * 16, so
-    // the lane fetches the chunk that belongs there.
-    constexpr int kARegs = (kBM * 16) / kThreads;
-    const unsigned char *arow[kARegs];
+    const float *sum_src = p.x_group_sums + (int64_t)s_rows[lane] * G;
+    // Codes: whole blocks.  Scales: the aligned dword that holds the column's bf16 scale (lane = column of the wavefront).
+    // Byte offsets from the array bases; the launcher checks that the codes stay below 4 GiB.
+    uint32_t boff[4], sidx, sidx_c[2];
+    auto set_block = [&]() {
 #pragma unroll
-    for (int u = 0; u < kARegs; ++u) {
-        const int r = u * (kThreads / 16) + (tid >> 4);
-        const int q = (lane & 15) ^ (r & 15);
-        arow[u] = (const unsigned char *)p.x + (int64_t)s_rows[r] * K * 2 + q * 16;
-    }
-    const float *gsrow = p.x_group_sums + (int64_t)s_rows[tid % kBM] * G;
-    auto copy_a = [&](int g, int buf) {
-        unsigned char *xs = smem + buf * kBufBytes;
+        for (int i = 0; i < 4; ++i) boff[i] = (uint32_t)((e * (int64_t)N + block_row(2 * wave + (i >> 1), i & 1)) / 16 * G) * 1024u + lane * 16;
+        sidx = (uint32_t)((e * (int64_t)N + block_row(2 * wave + (lane >> 5), (lane >> 4) & 1) + (lane & 15)) * G);
+        sidx_c[0] = (uint32_t)__shfl((int)sidx, c, 64);
+        sidx_c[1] = (uint32_t)__shfl((int)sidx, 32 + c, 64);
+    };
+    set_block();
+    auto copy_one = [&](int g, int buf, int j) {
+        unsigned char *xs = smem + buf * kStageBytes, *ws = xs + kXBytes + wave * kWaveBytes;
+        if (j < 4) copy16_to_lds(xsrc[j] + g * kRowBytes, xs + (wave * 16 + j * 4) * kRowBytes);
+        else if (j < 8) copy16_to_lds(p.codes + (boff[j - 4] + (uint32_t)g * 1024u), ws + (j - 4) * 1024);
+        else if (j == 8) copy4_to_lds(sum_src + g, ws + 4096);
+        else copy4_to_lds(p.scales + (((sidx + (uint32_t)g) * 2u) & ~3u), ws + 4096 + 256);
+    };
+    auto copy_stage = [&](int g, int buf) {
 #pragma unroll
-        for (int u = 0; u < kARegs; ++u)
-            copy16_to_lds(arow[u] + g * kGroup * 2, xs + (u * (kThreads / 16) + wn * 4) * kStride);
-        if (tid < kBM)   // whole wavefronts: kBM is a multiple of 64
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gsrow + g),
-                                             (__attribute__((address_space(3))) void *)(xs + kBM * kStride + (tid & ~63) * 4), 4, 0, 0);
+        for (int j = 0; j < kCopies; ++j) copy_one(g, buf, j);
     };
 
-    // ---- packed weights of one group
-    constexpr int kWRegs = 2;  // 16-byte loads per lane
-    struct BRegs {
-        u32x4 w[kWRegs];
-        uint32_t s;
-    };
-    auto load_b = [&](BRegs &dst, int g) {
-        const unsigned char *wb = (const unsigned char *)p.codes;
-        const uint32_t o = woff + (uint32_t)g * 1024u;
+    // ---- operand reads.  Lane (row or column c of the tile, half h) takes k [64 h + 8 j, + 8) of the stage in slice j: chunk
+    // 8 h + j of its token row, word j % 4 of piece 2 h + j / 4 of its weight row.
+    int xoff[8];
 #pragma unroll
-        for (int u = 0; u < kWRegs; ++u) dst.w[u] = *(const u32x4 *)(wb + (o + u * 256u));
-        dst.s = *(const uint16_t *)((const unsigned char *)p.scales + (soff + (uint32_t)g * 2u));
-    };
+    for (int j = 0; j < 8; ++j) xoff[j] = c * kRowBytes + (((8 * h + j) ^ (c & 15)) << 4);
+    const int woff = kXBytes + wave * kWaveBytes + (c >> 4) * 1024 + h * 512 + (c & 15) * 16;
+    const int soff = kXBytes + wave * kWaveBytes + 4096;
 
-    f32x16 acc[MS];
+    f32x16 acc[2][2];   // [row tile][column tile]
+    auto stage = [&](int g, auto buf_c) {
+        constexpr int buf = decltype(buf_c)::value;
+        const unsigned char *st = smem + buf * kStageBytes;
+        u32x4 w[2][2];
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
+        for (int ns = 0; ns < 2; ++ns)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[ms][i] = 0.f;
-
-    // One 128-k step on the LDS buffer `buf` with the weights in `b`.
-    const int afrag = c * kStride;   // this lane's operand read: row c (+32 ms); chunk 8 h + j, swizzled
-    auto step = [&](const BRegs &b, int buf) {
-        const unsigned char *xs = smem + buf * kBufBytes + afrag;
-        const float *sx = (const float *)(smem + buf * kBufBytes + kBM * kStride);
-        f32x16 ag[MS];
+            for (int u = 0; u < 2; ++u) w[ns][u] = *(const u32x4 *)(st + woff + ns * 2048 + u * 256);
+        f32x16 init[2];
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
+        for (int ms = 0; ms < 2; ++ms)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
-                const f32x4 init = *(const f32x4 *)(sx + ms * 32 + 8 * i4 + 4 * h);
+                const f32x4 v = *(const f32x4 *)(st + soff + (ms * 32 + 8 * i4 + 4 * h) * 4);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) ag[ms][i4 * 4 + i] = init[i];
+                for (int i = 0; i < 4; ++i) init[ms][i4 * 4 + i] = v[i];
             }
+        float s16[2];
+#pragma unroll
+        for (int ns = 0; ns < 2; ++ns) {
+            const uint32_t d = *(const uint32_t *)(st + soff + 256 + (ns * 32 + c) * 4);
+            s16[ns] = 16.f * __uint_as_float(((sidx_c[ns] + (uint32_t)g) & 1) ? d & 0xffff0000u : d << 16);
+        }
+        f32x16 ag[2][2];
+        // Slice j: its four MFMAs with the expansion and the operand reads of slice j + 1 spread between them.
+        bf16x8 a[2][2], b[2][2];   // [slice parity]
+        auto operands = [&](int j) {
+#pragma unroll
+            for (int ms = 0; ms < 2; ++ms) a[j & 1][ms] = *(const bf16x8 *)(st + xoff[j] + ms * 32 * kRowBytes);
+#pragma unroll
+            for (int ns = 0; ns < 2; ++ns) b[j & 1][ns] = unpack_int4_word(w[ns][j >> 2][j & 3]);
+        };
+        operands(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const bf16x8 bw = unpack_int4_word(b.w[j >> 2][j & 3]);
+            if (j < 7) operands(j + 1);
 #pragma unroll
-            for (int ms = 0; ms < MS; ++ms) {
-                const bf16x8 a = *(const bf16x8 *)(xs + ms * 32 * kStride + (((8 * h + j) ^ (c & 15)) << 4));
-                ag[ms] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bw, ag[ms], 0, 0, 0);
+            for (int ns = 0; ns < 2; ++ns)
+#pragma unroll
+                for (int ms = 0; ms < 2; ++ms)
+                    ag[ms][ns] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j & 1][ms], b[j & 1][ns], j == 0 ? init[ms] : ag[ms][ns], 0, 0, 0);
+            if (j < 7) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read (two in all)
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // VALU
+                }
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const float s16 = 16.f * bf16_bits_to_f32(b.s);
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
+        for (int ns = 0; ns < 2; ++ns)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ms][i] = fmaf(s16, ag[ms][i], acc[ms][i]);
+            for (int ms = 0; ms < 2; ++ms)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[ms][ns][i] = fmaf(s16[ns], ag[ms][ns][i], acc[ms][ns][i]);
     };
 
-    // Two steps per trip so that the two weight register sets swap roles without copies.  The weight registers
-    // of a step are touched before the next copies and loads go out: the compiler waits for every outstanding
-    // vector load at the first use of a loaded register while asynchronous copies are in flight, and at that
-    // point nothing is.
-    BRegs b0, b1;
-    b0.s = 0;
-    b1.s = 0;
-    copy_a(0, 0);
-    load_b(b0, 0);
-    copy_barrier();
+    // The copies of a stage travel during the stage before it.
+    copy_stage(0, 0);
+  for (;;) {   // column blocks (body not indented)
+#pragma unroll
+    for (int ms = 0; ms < 2; ++ms)
+#pragma unroll
+        for (int ns = 0; ns < 2; ++ns)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[ms][ns][i] = 0.f;
+    copy_barrier();   // also: the last block's epilogue has left the second buffer
     for (int g = 0; g < G; g += 2) {
-        asm volatile("" : "+v"(b0.w[0]), "+v"(b0.w[1]), "+v"(b0.s));
-        if (g + 1 < G) {
-            copy_a(g + 1, 1);
-            load_b(b1, g + 1);
-        }
-        step(b0, 0);
+        if (g + 1 < G) copy_stage(g + 1, 1);
+        stage(g, std::integral_constant<int, 0>());
         copy_barrier();
         if (g + 1 >= G) break;
-        asm volatile("" : "+v"(b1.w[0]), "+v"(b1.w[1]), "+v"(b1.s));
-        if (g + 2 < G) {
-            copy_a(g + 2, 0);
-            load_b(b0, g + 2);
-        }
-        step(b1, 1);
+        if (g + 2 < G) copy_stage(g + 2, 0);
+        stage(g + 1, std::integral_constant<int, 1>());
         copy_barrier();
     }
 
-    // ---- epilogue: lane (c,h), register i -> token row 8*(i/4) + 4h + i%4, column c of the tile.
-    // A lane holds one column of 16 rows, so a direct store would move 4 (or 2) bytes per lane.  The results
-    // take a turn through the activation buffers, which are free after the loop's last barrier, and leave as
-    // 16-byte pieces of whole 128-byte row segments.
-    static_assert(2 * kBufBytes >= kBM * (kBN / 2) * 2 && 2 * kBufBytes >= (kThreads / 64) * 32 * 32 * 4, "epilogue tile does not fit");
+    const int nb_done = nb;
+    if (++nb < nb_end) {   // the next block's first stage travels during the epilogue, which keeps to the second buffer
+        set_block();
+        copy_stage(0, 0);
+    }
+
+    // ---- epilogue: lane (c, h), register i -> token row 8 (i / 4) + 4 h + i % 4, column c of the tile.  A direct store would
+    // move 2 or 4 bytes per lane: the results take a turn through the stage buffers and leave as 16-byte pieces.
     if (kSilu) {
-        // workgroup tile [kBM rows][128 columns] bf16 in LDS
-        uint16_t *ot = (uint16_t *)smem;
+        uint16_t *ot = (uint16_t *)(smem + kStageBytes);   // [64 rows][128 columns] bf16
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms) {
+        for (int ns = 0; ns < 2; ++ns)
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                f32x4 vv;
+            for (int ms = 0; ms < 2; ++ms)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) vv[i] = acc[ms][i4 * 4 + i];
-                // Registers i and i+1 trade 16-lane rows: afterwards every lane holds a gate value
-                // and the up value of the same column; lanes c < 16 for row i, lanes c >= 16 for row i+1.
+                for (int i4 = 0; i4 < 4; ++i4)
 #pragma unroll
-                for (int ip = 0; ip < 2; ++ip) {
-                    const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(vv[2 * ip]),
-                                                                      __float_as_uint(vv[2 * ip + 1]), false, false);
-                    const int row = ms * 32 + 8 * i4 + 4 * h + 2 * ip + (c >> 4);
-                    const float rs = s_xsc[row];
-                    const float a = silu_mul_f32(__uint_as_float(sw[0]) * rs, __uint_as_float(sw[1]) * rs);
-                    ot[row * (kBN / 2) + wn * 16 + (c & 15)] = f32_to_bf16_hw(a);
-                }
-            }
-        }
+                    for (int ip = 0; ip < 2; ++ip) {
+                        // Registers i and i+1 trade 16-lane rows: afterwards every lane holds a gate value and the up
+                        // value of the same column; lanes c < 16 for row i, lanes c >= 16 for row i+1.
+                        const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[ms][ns][i4 * 4 + 2 * ip]),
+                                                                          __float_as_uint(acc[ms][ns][i4 * 4 + 2 * ip + 1]), false, false);
+                        const int row = ms * 32 + 8 * i4 + 4 * h + 2 * ip + (c >> 4);
+                        const float rs = s_xsc[row];
+                        const float a = silu_mul_f32(__uint_as_float(sw[0]) * rs, __uint_as_float(sw[1]) * rs);
+                        ot[row * (kCols / 2) + (2 * wave + ns) * 16 + (c & 15)] = f32_to_bf16_hw(a);
+                    }
         lds_barrier();
-        constexpr int kPieces = kBM * (kBN / 2) * 2 / 16;   // 16 pieces per row
-        const uint32_t rstride = (uint32_t)(N / 2) * 2u;    // bytes per output row (< 2^31: checked by the launcher)
+        constexpr int kPieces = kRows * (kCols / 2) * 2 / 16;   // 16 pieces per row
+        const uint32_t rstride = (uint32_t)(N / 2) * 2u;        // bytes per output row (< 2^31: checked by the launcher)
 #pragma unroll
         for (int q0 = 0; q0 < kPieces; q0 += kThreads) {
             const int q = q0 + tid, row = q >> 4, piece = q & 15;
             const int orow = s_orow[row];
-            const int oc = nb * (kBN / 2) + piece * 8;
-            const u32x4 v4 = *(const u32x4 *)(ot + row * (kBN / 2) + piece * 8);
+            const int oc = nb_done * (kCols / 2) + piece * 8;
+            const u32x4 v4 = *(const u32x4 *)(ot + row * (kCols / 2) + piece * 8);
             if (orow >= 0 && oc + 8 <= N / 2)
                 *(u32x4 *)((unsigned char *)p.out + ((uint64_t)(uint32_t)orow * rstride + (uint32_t)oc * 2u)) = v4;
         }
     } else {
-        // per wavefront [32 rows][32 columns] fp32 in LDS, one 32-row tile after the other; only the wavefront
-        // itself touches its region, and the LDS operations of a wavefront execute in order
-        float *ot = (float *)smem + wn * (32 * 32);
+        // per wavefront [32 rows][64 columns] fp32 in LDS, 16-byte chunks XOR-swizzled with the row; only the wavefront itself
+        // touches its region, and the LDS operations of a wavefront execute in order
+        float *ot = (float *)(smem + kStageBytes) + wave * (32 * 64);
         const int esz = p.out_f32 ? 4 : 2;
         const uint32_t rstride = (uint32_t)N * (uint32_t)esz;   // bytes per output row (< 2^31: checked by the launcher)
-        const int oc = nb * kBN + wn * 32 + (lane & 7) * 4;      // first of this lane's four columns
+        const int oc = nb_done * kCols + wave * 64 + (lane & 15) * 4;   // first of this lane's four columns
+        const bool ok = oc - (lane & 7) * 4 + 32 <= N;
         unsigned char *obase = (unsigned char *)p.out + (int64_t)oc * esz;
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms) {
+        for (int ms = 0; ms < 2; ++ms) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
-                f32x4 vv;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) vv[i] = acc[ms][i4 * 4 + i];
                 const f32x4 rs4 = *(const f32x4 *)(s_xsc + ms * 32 + 8 * i4 + 4 * h);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) ot[(8 * i4 + 4 * h + i) * 32 + c] = vv[i] * rs4[i];
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 8 * i4 + 4 * h + i;
+#pragma unroll
+                    for (int ns = 0; ns < 2; ++ns)
+                        ot[row * 64 + ((ns * 32 + c) ^ ((row & 4) << 3))] = acc[ms][ns][i4 * 4 + i] * rs4[i];
+                }
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-            for (int pass = 0; pass < 4; ++pass) {
-                const int row = pass * 8 + (lane >> 3);
-                const f32x4 v4 = *(const f32x4 *)(ot + row * 32 + (lane & 7) * 4);
+            for (int pass = 0; pass < 8; ++pass) {
+                const int row = pass * 4 + (lane >> 4);
+                const f32x4 v4 = *(const f32x4 *)(ot + row * 64 + (((lane & 15) * 4) ^ ((row & 4) << 3)));
                 const int orow = s_orow[ms * 32 + row];
-                if (orow >= 0 && tile_ok) {
+                if (orow >= 0 && ok) {
                     unsigned char *dst = obase + (uint64_t)(uint32_t)orow * rstride;
                     if (p.out_f32) {
                         __builtin_nontemporal_store(v4, (f32x4 *)dst);
@@ -277,12 +300,15 @@ __global__ __launch_bounds__(kTileThreads, MS == 2 ? 4 : 2) void qgemm_tile_kern
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     }
+    if (nb >= nb_end) break;
+  }
 }
 
-template <int EPI, int MS>
+constexpr int kItems = 2048, kMaxBlocks = 4;   // see the launcher
+
+template <int EPI>
 static int launch_cfg(const GemmArgs &a, hipStream_t s)
 {
-    constexpr int kBM = 32 * MS;
     if (a.E > 256) {
         set_error("qgemm (prefill path): at most 256 experts (got %d)", a.E);
         return QARL_ERR_UNSUPPORTED;
@@ -297,9 +323,9 @@ static int launch_cfg(const GemmArgs &a, hipStream_t s)
         return QARL_ERR_UNSUPPORTED;
     }
     TileParams p;
-    p.codes = (const uint32_t *)a.codes;
-    p.scales = a.scales;
-    p.x = a.x;
+    p.codes = (const unsigned char *)a.codes;
+    p.scales = (const unsigned char *)a.scales;
+    p.x = (const unsigned char *)a.x;
     p.x_group_sums = a.x_group_sums;
     p.x_scales = a.fmt == QARL_W4A8_G128 ? a.x_scales : nullptr;
     p.row_map = a.row_map;
@@ -310,25 +336,24 @@ static int launch_cfg(const GemmArgs &a, hipStream_t s)
     p.N = a.N;
     p.K = a.K;
     p.out_f32 = a.out_f32;
-    p.n_blocks = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2 + kBN / 2 - 1) / (kBN / 2) : (a.N + kBN - 1) / kBN;
-    const int64_t slots = (a.M + kBM - 1) / kBM + a.E;
-    const int64_t total = ((slots * p.n_blocks + 7) / 8) * 8;
+    p.n_blocks = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2 + kCols / 2 - 1) / (kCols / 2) : (a.N + kCols - 1) / kCols;
+    const int64_t slots = (a.M + kRows - 1) / kRows + a.E;
+    // up to kMaxBlocks column blocks per workgroup, as long as kItems workgroups remain (four rounds of the two a CU
+    // holds; with half as many a layer of 3001 tokens takes 398 us instead of 389), in groups of about equal size
+    int bpw = (int)std::min<int64_t>(std::max<int64_t>(slots * p.n_blocks / kItems, 1), std::min(kMaxBlocks, p.n_blocks));
+    p.n_bgroups = (p.n_blocks + bpw - 1) / bpw;
+    p.bpw = (p.n_blocks + p.n_bgroups - 1) / p.n_bgroups;
+    p.n_bgroups = (p.n_blocks + p.bpw - 1) / p.bpw;
+    const int64_t total = ((slots * p.n_bgroups + 7) / 8) * 8;
     if (total > 0x7fffffffLL) {
         set_error("qgemm (prefill path): grid too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    const size_t lds = 2 * ((size_t)kBM * kARowB + kBM * 4);
     static LdsLimitOnce once;
-    auto kern = qgemm_tile_kernel<EPI, MS>;
+    auto kern = qgemm_tile_kernel<EPI>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(tile)")) return rc;
-    kern<<<dim3((unsigned)total), dim3(kTileThreads), lds, s>>>(p);
+    kern<<<dim3((unsigned)total), dim3(kThreads), 2 * kStageBytes, s>>>(p);
     return check_hip(hipGetLastError(), "qgemm_tile_kernel");
-}
-
-template <int EPI>
-static int launch_one(const GemmArgs &a, hipStream_t s)
-{
-    return launch_cfg<EPI, 2>(a, s);
 }
 
 // sums[row][g] = -1.5 * sum over the 128 k of group g of x[row][k]: the start value of a group's
@@ -363,7 +388,7 @@ int launch_group_sums(const void *x_bf16, int64_t rows, int K, float *sums, hipS
 int launch_qgemm_tile(const GemmArgs &a, hipStream_t s)
 {
     if (a.fmt == QARL_W4A16_G128 || a.fmt == QARL_W4A8_G128)
-        return a.epilogue == QARL_EPI_SILU_MUL ? launch_one<QARL_EPI_SILU_MUL>(a, s) : launch_one<QARL_EPI_NONE>(a, s);
+        return a.epilogue == QARL_EPI_SILU_MUL ? launch_cfg<QARL_EPI_SILU_MUL>(a, s) : launch_cfg<QARL_EPI_NONE>(a, s);
     return launch_qgemm_tile_fp8(a, s);
 }
 

@@ -163,6 +163,74 @@ def test_one_hot_probe_bit_exact(q, oracle, fmt):
         assert np.array_equal(y.cpu().numpy().astype(np.float64), want.astype(np.float32).astype(np.float64)), (fmt, path)
 
 
+@pytest.mark.parametrize("E,N,K,rows", _TALL_SHAPES + [(3, 160, 640, (65, 0, 63))])
+def test_w4a8_tiled_path_against_the_oracle(q, oracle, E, N, K, rows):
+    """W4A8 on the tiled path: one to eight scale groups (odd counts: scales at odd halves of a dword), partial
+    row and column tiles, empty experts, the three kinds of output."""
+    seed = 2700 + N + K
+    w = synth.normal_bf16((E, N, K), 0.02, seed=seed)
+    M = int(sum(rows))
+    x = synth.normal_bf16((M, K), 1.0, seed=seed + 1)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    rm = np.random.default_rng(seed).permutation(M).astype(np.int32)
+    xq_ref, sx_ref = oracle.quantize_fp8_rows(np_bits(x))
+    xq, sx = q.qarl_quantize_rows_fp8(x.cuda())
+    c4, s4 = oracle.quantize_int4(np_bits(w))
+    ref = oracle.qgemm_w4a8(xq_ref, sx_ref, c4, s4, off, rm)
+    qw = q.qarl_quantize_weights(w.cuda(), q.QARL_W4A8_G128)
+    run = lambda **kw: q.qarl_qgemm_grouped(qw, xq, _i32(off), M, row_map=_i32(rm), x_scales=sx, path=q.QARL_PATH_PREFILL, **kw)
+    y = run(out_dtype=q.QARL_OUT_F32)
+    assert norm_err(y.cpu().numpy(), ref) <= TOL_F32
+    assert np.array_equal(np_bits(run()), np_bits(y.to(torch.bfloat16)))
+    a_bits, a_ref = oracle.silu_mul(ref)
+    a = run(epilogue=q.QARL_EPI_SILU_MUL)
+    assert norm_err_bf16(a.float().cpu().numpy(), a_ref) <= TOL_BF16
+    assert flip_fraction(np_bits(a), a_bits) <= MAX_FLIPS
+
+
+def test_int4_tiled_path_several_column_blocks_per_workgroup(q):
+    """256 experts and 18 column blocks (the last one holds a single 32-column tile): workgroups take two blocks each.  An
+    expert on its own takes one block per workgroup and has to give the same bits (three scale groups, ragged rows)."""
+    E, N, K = 256, 4384, 384
+    w = synth.normal_bf16((E, N, K), 0.02, seed=91, device="cuda")
+    rows = np.random.default_rng(92).integers(0, 9, E)
+    rows[[0, 255]] = (70, 64)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    M = int(off[-1])
+    x = synth.normal_bf16((M, K), 1.0, seed=93, device="cuda")
+    xq, sx = q.qarl_quantize_rows_fp8(x)
+    for fmt, xs, kw in ((q.QARL_W4A16_G128, x, {}), (q.QARL_W4A8_G128, xq, dict(x_scales=sx))):
+        qw = q.qarl_quantize_weights(w, fmt)
+        for out in (dict(out_dtype=q.QARL_OUT_F32), dict(epilogue=q.QARL_EPI_SILU_MUL)):
+            y = q.qarl_qgemm_grouped(qw, xs, _i32(off), M, path=q.QARL_PATH_PREFILL, **kw, **out)
+            for e in (0, int(np.argmax(rows[1:255])) + 1, 255):
+                lo, hi = int(off[e]), int(off[e + 1])
+                one = q.qarl_qgemm_grouped(q.qarl_quantize_weights(w[e:e + 1].contiguous(), fmt), xs[lo:hi].contiguous(), _i32([0, hi - lo]), hi - lo,
+                                           path=q.QARL_PATH_PREFILL, **{k: v[lo:hi].contiguous() for k, v in kw.items()}, **out)
+                assert torch.equal(y[lo:hi], one), (fmt, out, e)
+
+
+def test_w4a8_every_code_under_every_e4m3_value(q, oracle):
+    """One-hot rows that carry every finite e4m3 byte (subnormals and both zeros included) over weights that take every
+    code: one product per output, so the tiled path returns it exactly."""
+    K, N = 128, 64
+    w = synth.normal_bf16((1, N, K), 0.02, seed=67)
+    c4, s4 = oracle.quantize_int4(np_bits(w))
+    deq = oracle.dequant_int4(c4, s4)[0].astype(np.float64)
+    finite = [b for b in range(256) if b & 0x7f != 0x7f]
+    for k0 in range(0, K, 16):    # 16 k per launch, every byte at each of them
+        rows = [(b, k) for b in finite for k in range(k0, k0 + 16)]
+        xq = np.zeros((len(rows), K), dtype=np.uint8)
+        for i, (b, k) in enumerate(rows):
+            xq[i, k] = b
+        val = oracle.e4m3_decode(xq[np.arange(len(rows)), [k for _, k in rows]]).astype(np.float64)
+        want = (val[:, None] * deq[:, [k for _, k in rows]].T).astype(np.float32)
+        qw = q.qarl_quantize_weights(w.cuda(), q.QARL_W4A8_G128)
+        y = q.qarl_qgemm_grouped(qw, torch.from_numpy(xq).cuda(), _i32([0, len(rows)]), len(rows),
+                                 x_scales=torch.ones(len(rows), device="cuda"), out_dtype=q.QARL_OUT_F32, path=q.QARL_PATH_PREFILL)
+        assert np.array_equal(y.cpu().numpy(), want), k0
+
+
 @pytest.mark.parametrize("path", [1, 2])
 @pytest.mark.parametrize("fmt", ["fp4", "w4a8"])
 def test_moe_layer_stage_wise(q, oracle, fmt, path):
