@@ -499,7 +499,7 @@ int qarl_grouped_dw(const void *dy_bf16, const void *x_bf16, const int32_t *row_
         set_error("qarl_grouped_dw: dy, x and dw must be 16-byte aligned");
         return QARL_ERR_ALIGNMENT;
     }
-    return launch_grouped_dw(dy_bf16, x_bf16, row_map, expert_offsets, E, N, K, dw, out_dtype == QARL_OUT_F32,
+    return launch_grouped_dw(dy_bf16, x_bf16, row_map, expert_offsets, M, E, N, K, dw, out_dtype == QARL_OUT_F32,
                              (hipStream_t)stream);
 }
 

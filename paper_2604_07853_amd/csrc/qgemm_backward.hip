@@ -16,6 +16,7 @@
 // regime stay exact).  The codes go through the same exponent trick as in the forward, (q+24)/16 as an exact
 // bf16, written row by row ([n][k]) into LDS; the offset is removed at the end with the row sums of A' (fp32,
 // accumulated while A' is staged): dX = 16 * acc - 24 * rowsum.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -213,6 +214,8 @@ struct DwParams {
     const int32_t *offsets;
     void *out;            // [E][N][K]
     int E, N, K, out_f32;
+    int chain;            // wide kernel: neighbouring tiles of an expert one workgroup computes
+    int heavy_rows;       // wide kernel: an expert with more rows may be heavy; 0: the experts are not looked at
 };
 
 __global__ __launch_bounds__(kBwThreads, 4) void grouped_dw_kernel(DwParams p)
@@ -308,6 +311,8 @@ constexpr int kDwWTile = 256;                       // n rows and k columns per 
 constexpr int kDwWRowB = kDwWTile * 2;              // bytes of an LDS row
 constexpr int kDwWTileB = kStageM * kDwWRowB;       // one operand tile of a stage: 32 KiB
 constexpr int kDwWStageB = 2 * kDwWTileB;           // Ys, then Xs
+constexpr int kDwRankE = 256;                       // experts that are put in order
+__host__ __device__ inline bool dw_wide_by_xcd(int N, int K) { return (N / kDwWTile) % 2 == 0 && (K / kDwWTile) % 4 == 0; }
 __device__ __attribute__((aligned(256))) const unsigned char kDwZeroRow[kDwWRowB] = {0};
 
 __device__ __forceinline__ TrBase tr_base_512(int col0, int lane)
@@ -321,31 +326,25 @@ __device__ __forceinline__ TrBase tr_base_512(int col0, int lane)
     return b;
 }
 
-__global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams p, const int32_t *__restrict__ row_map)
+__global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams p, const int32_t *__restrict__ row_map,
+                                                                        const int32_t *__restrict__ offsets)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave >> 2, wk = wave & 3;   // 128 n x 64 k per wavefront
     const int m32 = lane & 31, h = lane >> 5;
     const int N = p.N, K = p.K;
-    const int nbn = N / kDwWTile, nbk = K / kDwWTile, tiles = nbn * nbk;
-    // Every expert's tiles are spread over all eight XCDs (consecutive workgroup ids go round-robin over them), so a
-    // skewed router loads the XCDs alike; where the tile grid allows it an XCD takes half of the n blocks and a
-    // quarter of the k blocks of every expert, i.e. its L2 fetches a fifth of the expert's operand bytes, not all.
-    int e, nb, kb;
-    if (nbn % 2 == 0 && nbk % 4 == 0) {
-        const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8, per = tiles / 8, hn = nbn / 2;
-        e = idx / per;
-        nb = (xcd & 1) * hn + (idx % per) % hn;
-        kb = (xcd >> 1) * (nbk / 4) + (idx % per) / hn;
-    } else {
-        e = blockIdx.x / tiles;
-        nb = (blockIdx.x % tiles) / nbk;
-        kb = (blockIdx.x % tiles) % nbk;
-    }
-    if (e >= p.E) return;
-    const int row0 = p.offsets[e], Me = p.offsets[e + 1] - row0;
-    const int stages = (Me + kStageM - 1) / kStageM;
+    const int nbn = N / kDwWTile, nbk = K / kDwWTile;
+    // Lists of tiles.  Consecutive workgroup ids go round-robin over the eight XCDs; where the tile grid allows it an XCD
+    // has its own list with half of the n blocks and a quarter of the k blocks of every expert, so that a skewed router
+    // loads the XCDs alike and an XCD's L2 fetches a fifth of the expert's operand bytes, not all.
+    const bool by_xcd = dw_wide_by_xcd(N, K);
+    const int xcd = by_xcd ? blockIdx.x % 8 : 0, first = by_xcd ? blockIdx.x / 8 : blockIdx.x;
+    const int hn = by_xcd ? nbn / 2 : nbn, per = by_xcd ? nbn * nbk / 8 : nbn * nbk;   // n blocks, tiles per expert of the list
+    // Items of the list: one tile of a heavy expert (below), p.chain neighbouring tiles of another.  The workgroups of the
+    // list take item `first`, then (heavy experts make more items than workgroups) go back and forth over the rest.
+    const int wpe = (per + p.chain - 1) / p.chain;
+    const int wgs = by_xcd ? gridDim.x / 8 : gridDim.x;   // E wpe
 
     // ---- copies: instruction i (0..3) of this wavefront moves rows 8 w + 2 i and 8 w + 2 i + 1 of a tile; lane L
     // fills position L % 32 of row 8 w + 2 i + L / 32 with the chunk that belongs there
@@ -356,9 +355,9 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
         rrow[i] = wave * 8 + 2 * i + h;
         chunkb[i] = (uint32_t)(((lane & 31) ^ ((rrow[i] & 3) << 2)) << 4);
     }
-    const unsigned char *ybase = (const unsigned char *)p.dy + ((int64_t)row0 * N + nb * kDwWTile) * 2;
-    const unsigned char *xbase = (const unsigned char *)p.x + (int64_t)kb * kDwWTile * 2;
-    const int32_t *mbase = row_map ? row_map + row0 : nullptr;
+    int row0 = 0, Me = 0, stages = 0;   // of the item's expert
+    const unsigned char *ybase = nullptr, *xbase = nullptr;
+    const int32_t *mbase = nullptr;
     int32_t ids[8];                       // x rows of the wavefront's eight token rows of the stage addressed next
     const unsigned char *ysrc[4], *xsrc[4];
     auto load_ids = [&](int s) {
@@ -417,12 +416,6 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]));
     };
     f32x16 acc[4][2];
-#pragma unroll
-    for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ms][nt][i] = 0.f;
     // Slice j (16 token rows) of stage ks: the eight MFMAs on `cur`, behind each of the first six one operand of
     // `nxt` (two transposing reads), in slices 0 and 1 behind every second MFMA one copy of the next stage.
     auto slice = [&](Frags &cur, Frags &nxt, int ks, auto j_c, auto more_t) {
@@ -447,70 +440,162 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
 
-    if (stages > 0) {
-        Frags last, f0, f1, f2, f3;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) last.a[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < 2; ++i) last.b[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    // Tile t of the expert: blocks and operand bases, and the copies of its first stage into buffer 0
+    int nb = 0, kb = 0;
+    auto begin_tile = [&](int t) {
+        nb = (xcd & 1) * hn + t % hn;
+        kb = (xcd >> 1) * (nbk / 4) + t / hn;
+        if (stages == 0) return;
+        ybase = (const unsigned char *)p.dy + ((int64_t)row0 * N + nb * kDwWTile) * 2;
+        xbase = (const unsigned char *)p.x + (int64_t)kb * kDwWTile * 2;
         load_ids(0);
         form_addresses(0);
 #pragma unroll
         for (int i = 0; i < 8; ++i) copy_one(0, i);
         load_ids(1);
-        stage_barrier();
-        auto stage = [&](int ks, auto more_t) {
-            if (decltype(more_t)::value) {
-                form_addresses(ks + 1);   // from the ids loaded during the stage before
-                load_ids(ks + 2);
-            }
-            slice(last, f0, ks, std::integral_constant<int, 0>{}, more_t);
-            slice(f0, f1, ks, std::integral_constant<int, 1>{}, more_t);
-            slice(f1, f2, ks, std::integral_constant<int, 2>{}, more_t);
-            slice(f2, f3, ks, std::integral_constant<int, 3>{}, more_t);
-            stage_barrier();
-            last = f3;
-        };
-        for (int ks = 0; ks + 1 < stages; ++ks) stage(ks, std::true_type{});
-        stage(stages - 1, std::false_type{});
-        wait_frags(last);
+    };
+    int e, t0, t1;
+    auto begin_item = [&](int expert, int item, int chain) {   // item: of the expert
+        e = expert;
+        t0 = item * chain;
+        t1 = min(t0 + chain, per);
+        row0 = offsets[e];
+        Me = offsets[e + 1] - row0;
+        stages = (Me + kStageM - 1) / kStageM;
+        mbase = row_map ? row_map + row0 : nullptr;
+        begin_tile(t0);
+    };
+    // Heavy experts: more than twice the mean of rows, and more than heavy_rows.  If there are any, the experts are taken in
+    // descending order of their rows (ties by id), so that what starts last is short; in the order of their ids a
+    // popular expert's tiles (0.5 ms each under a Zipf router of 16384 tokens) may start when the others are done: 1.25 ->
+    // 1.02 ms for gate_up.  Without heavy experts the order of the ids stays, and the first item's copies, which are
+    // issued before the counts are looked at, are the right ones.
+    int cnt[kDwRankE / 64];
 #pragma unroll
-        for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-                acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(last.a[ms], last.b[nt], acc[ms][nt], 0, 0, 0);
+    for (int q = 0; q < kDwRankE / 64; ++q) {
+        const int ex = q * 64 + lane;
+        cnt[q] = p.heavy_rows > 0 && ex < p.E ? p.offsets[ex + 1] - p.offsets[ex] : 0;
     }
-
-    // ---- epilogue: lane (k column m32 of tile nt, half h), register i -> weight row 32 ms + 8 (i / 4) + 4 h + i % 4.
-    // Every 32 x 32 tile turns through this wavefront's own piece of the first stage buffer (rows of 36 floats) and
-    // leaves as 16-byte (fp32) or 8-byte (bf16) pieces of whole 128-byte / 64-byte row segments.
-    constexpr int kORow = 36 * 4;
-    unsigned char *ot = smem + wave * (32 * kORow);
-    const int64_t obase = ((int64_t)e * N + nb * kDwWTile + wn * 128) * K + kb * kDwWTile + wk * 64;
+    __builtin_amdgcn_sched_barrier(0);
+    begin_item(first / wpe, first % wpe, p.chain);
+    bool begun = true;
+    int n_heavy = 0;
+    if (p.heavy_rows > 0) {
+        const int64_t twice = 2 * (int64_t)(offsets[p.E] - offsets[0]);
 #pragma unroll
-    for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                *(float *)(ot + (8 * (i >> 2) + 4 * h + (i & 3)) * kORow + m32 * 4) = acc[ms][nt][i];
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int pass = 0; pass < 4; ++pass) {
-                const int row = pass * 8 + (lane >> 3);
-                const f32x4 v4 = *(const f32x4 *)(ot + row * kORow + (lane & 7) * 16);
-                const int64_t o = obase + (int64_t)(ms * 32 + row) * K + nt * 32 + (lane & 7) * 4;
-                if (p.out_f32) {
-                    *(f32x4 *)((float *)p.out + o) = v4;
-                } else {
-                    u32x2 ob;
-                    ob[0] = (uint32_t)f32_to_bf16_hw(v4[0]) | ((uint32_t)f32_to_bf16_hw(v4[1]) << 16);
-                    ob[1] = (uint32_t)f32_to_bf16_hw(v4[2]) | ((uint32_t)f32_to_bf16_hw(v4[3]) << 16);
-                    *(u32x2 *)((uint16_t *)p.out + o) = ob;
-                }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        for (int q = 0; q < kDwRankE / 64; ++q) n_heavy += __popcll(__ballot(cnt[q] > p.heavy_rows && (int64_t)cnt[q] * p.E > twice));
+    }
+    __shared__ __attribute__((aligned(16))) int s_key[kDwRankE];
+    __shared__ int s_rank[kDwRankE], s_order[kDwRankE];
+    if (n_heavy > 0) {   // a thread counts the larger keys among a part of the experts for one of them
+        const int ep = p.E <= 128 ? 128 : 256, i = tid & (ep - 1), len = ep * ep / kBwThreads, j0 = (tid / ep) * len;
+        if (tid < ep) {
+            const int rows = tid < p.E ? min(offsets[tid + 1] - offsets[tid], 0x7ffffe) : -1;
+            s_key[tid] = rows * 256 + 255 - tid;   // padding: below every expert's key
+            s_rank[tid] = 0;
         }
+        lds_barrier();
+        const int key = s_key[i];
+        int larger = 0;
+        for (int j = 0; j < len; j += 4) {
+            const i32x4 k4 = *(const i32x4 *)(s_key + j0 + j);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) larger += k4[q] > key;
+        }
+        atomicAdd(&s_rank[i], larger);
+        lds_barrier();
+        if (tid < p.E) s_order[s_rank[tid]] = tid;
+        stage_barrier();   // also: the copies of the item that is given up have landed
+        begun = false;
+    }
+    const int n_items = n_heavy * per + (p.E - n_heavy) * wpe;
+    for (int round = 0; round * wgs < n_items; ++round) {
+        if (!begun) {
+            const int idx = round * wgs + ((round & 1) ? wgs - 1 - first : first);
+            if (idx >= n_items) continue;
+            const bool light = idx >= n_heavy * per;
+            const int li = light ? idx - n_heavy * per : idx, w = light ? wpe : per;
+            const int r = (light ? n_heavy : 0) + li / w;
+            if (round > 0) lds_barrier();   // the last item's epilogue has left the buffers
+            begin_item(n_heavy > 0 ? __builtin_amdgcn_readfirstlane(s_order[r]) : r, li % w, light ? p.chain : 1);
+        }
+        begun = false;
+        for (int t = t0; t < t1; ++t) {
+            const int64_t obase = ((int64_t)e * N + nb * kDwWTile + wn * 128) * K + kb * kDwWTile + wk * 64;
+#pragma unroll
+            for (int ms = 0; ms < 4; ++ms)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[ms][nt][i] = 0.f;
+            if (stages > 0) {
+                Frags last, f0, f1, f2, f3;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) last.a[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int i = 0; i < 2; ++i) last.b[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                stage_barrier();   // the first stage has landed; the last tile's epilogue has left the second buffer
+                auto stage = [&](int ks, auto more_t) {
+                    if (decltype(more_t)::value) {
+                        form_addresses(ks + 1);   // from the ids loaded during the stage before
+                        load_ids(ks + 2);
+                    }
+                    slice(last, f0, ks, std::integral_constant<int, 0>{}, more_t);
+                    slice(f0, f1, ks, std::integral_constant<int, 1>{}, more_t);
+                    slice(f1, f2, ks, std::integral_constant<int, 2>{}, more_t);
+                    slice(f2, f3, ks, std::integral_constant<int, 3>{}, more_t);
+                    stage_barrier();
+                    last = f3;
+                };
+                for (int ks = 0; ks + 1 < stages; ++ks) stage(ks, std::true_type{});
+                stage(stages - 1, std::false_type{});
+                wait_frags(last);
+#pragma unroll
+                for (int ms = 0; ms < 4; ++ms)
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt)
+                        acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(last.a[ms], last.b[nt], acc[ms][nt], 0, 0, 0);
+            }
+            if (t + 1 < t1) begin_tile(t + 1);   // travels during the epilogue, which keeps to the second buffer
+
+            // ---- epilogue: lane (k column m32 of tile nt, half h), register i -> weight row 32 ms + 8 (i / 4) + 4 h + i % 4.
+            // 32 rows x 64 columns turn through this wavefront's own piece of the second stage buffer (rows that differ by 4
+            // trade their halves: no bank conflicts) and leave as whole 256-byte (fp32) or 128-byte (bf16) row segments.
+            int el = lane;   // opaque: addresses worked out here, not kept in registers across the k loop
+            asm volatile("" : "+v"(el));
+            const int ec = el & 31, eh = el >> 5;
+            const int esz = p.out_f32 ? 4 : 2;
+            unsigned char *dst = (unsigned char *)p.out + (obase + (int64_t)(el >> 4) * K + (el & 15) * 4) * esz;   // row el / 16
+            const int64_t step = (int64_t)4 * K * esz;
+            float *ot = (float *)(smem + kDwWStageB) + wave * (32 * 64);
+#pragma unroll
+            for (int ms = 0; ms < 4; ++ms) {
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int row = 8 * (i >> 2) + 4 * eh + (i & 3);
+                        ot[row * 64 + ((nt * 32 + ec) ^ ((row & 4) << 3))] = acc[ms][nt][i];
+                    }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int pass = 0; pass < 8; ++pass) {
+                    const int row = pass * 4 + (el >> 4);
+                    const f32x4 v4 = *(const f32x4 *)(ot + row * 64 + (((el & 15) * 4) ^ ((row & 4) << 3)));
+                    if (p.out_f32) {
+                        *(f32x4 *)dst = v4;
+                    } else {
+                        u32x2 ob;
+                        ob[0] = (uint32_t)f32_to_bf16_hw(v4[0]) | ((uint32_t)f32_to_bf16_hw(v4[1]) << 16);
+                        ob[1] = (uint32_t)f32_to_bf16_hw(v4[2]) | ((uint32_t)f32_to_bf16_hw(v4[3]) << 16);
+                        *(u32x2 *)dst = ob;
+                    }
+                    dst += step;
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+        }
+    }
 }
 
 }  // namespace
@@ -545,8 +630,8 @@ int launch_qgemm_dx(const GemmArgs &a, hipStream_t s)
     return check_hip(hipGetLastError(), "qgemm_dx_kernel");
 }
 
-int launch_grouped_dw(const void *dy, const void *x, const int32_t *row_map, const int32_t *offsets, int E, int N, int K,
-                      void *out, int out_f32, hipStream_t s)
+int launch_grouped_dw(const void *dy, const void *x, const int32_t *row_map, const int32_t *offsets, int64_t M, int E, int N,
+                      int K, void *out, int out_f32, hipStream_t s)
 {
     if (N % kTM != 0 || K % kTK != 0) {
         set_error("grouped dw: needs N %% 128 == 0 and K %% 128 == 0 (got N=%d K=%d)", N, K);
@@ -567,11 +652,27 @@ int launch_grouped_dw(const void *dy, const void *x, const int32_t *row_map, con
     p.N = N;
     p.K = K;
     p.out_f32 = out_f32;
-    if (N % kDwWTile == 0 && K % kDwWTile == 0 && (int64_t)N * 2 < (1LL << 31) && (int64_t)K * 2 < (1LL << 31)) {
-        const int64_t total = (int64_t)E * (N / kDwWTile) * (K / kDwWTile);
+    p.chain = 1;
+    p.heavy_rows = 0;
+    // 256 x 256 tiles, but not for up to four rounds of workgroups with few rows each: there a tile is mostly start-up and
+    // result, of which the two smaller workgroups of a CU hide each other's (64 experts, 512 x 1024 weights: 51 instead of
+    // 58 us at 62 rows per expert, popular experts; 57 instead of 56 at 125, even experts; from 1500 tiles on 124 instead of
+    // 110 us at 62)
+    const int64_t wide_tiles = (int64_t)E * (N / kDwWTile) * (K / kDwWTile);
+    const bool few = wide_tiles <= 4 * 256 && M < (int64_t)96 * E;
+    if (!few && N % kDwWTile == 0 && K % kDwWTile == 0 && (int64_t)N * 2 < (1LL << 31) && (int64_t)K * 2 < (1LL << 31)) {
+        // Tiles of a workgroup: up to three, as long as six rounds of workgroups remain.  Looking for heavy experts costs a
+        // workgroup 0.5 us and ranking them 1 us: worth it where the order of the work matters: chained tiles (from 4 stages
+        // on), or from four rounds of workgroups and 128 rows per expert on (from 16 stages on; 1024 tiles, 187 rows per
+        // expert: popular experts 157 -> 142 us, 121 -> 122 without).
+        const int lists = dw_wide_by_xcd(N, K) ? 8 : 1;
+        const int64_t per = wide_tiles / E / lists;
+        p.chain = E > kDwRankE ? 1 : (int)std::min<int64_t>(std::min<int64_t>(3, per), std::max<int64_t>(1, wide_tiles / (6 * 256)));
+        p.heavy_rows = E > kDwRankE ? 0 : p.chain > 1 ? 3 * kStageM : M >= (int64_t)128 * E && wide_tiles >= 4 * 256 ? 15 * kStageM : 0;
+        const int64_t total = lists * E * ((per + p.chain - 1) / p.chain);
         static LdsLimitOnce once;
         if (int rc = raise_lds_limit((const void *)grouped_dw_wide_kernel, once, "hipFuncSetAttribute(grouped dw)")) return rc;
-        grouped_dw_wide_kernel<<<dim3((unsigned)total), dim3(kBwThreads), 2 * kDwWStageB, s>>>(p, row_map);
+        grouped_dw_wide_kernel<<<dim3((unsigned)total), dim3(kBwThreads), 2 * kDwWStageB, s>>>(p, row_map, offsets);
         return check_hip(hipGetLastError(), "grouped_dw_wide_kernel");
     }
     grouped_dw_kernel<<<dim3((unsigned)grid), dim3(kBwThreads), 0, s>>>(p);

@@ -139,6 +139,30 @@ def test_backward_full_size_gate_up_sampled(q, oracle):
         assert norm_err(dw[e].cpu().numpy(), ref[0]) <= TOL_F32, e
 
 
+@pytest.mark.parametrize("E,N,K,heavy,rest", [(256, 512, 1536, (700, 300), 9),      # ranked in 256 places, tiles chained, one list
+                                              (130, 1536, 2048, (3, 0, 900), 12),   # ... three lists' worth of tiles per expert, one list per XCD
+                                              (128, 512, 1024, (1500,), 250),       # ranked, one tile per workgroup
+                                              (300, 512, 512, (400,), 200),         # too many experts to rank
+                                              (65, 512, 1024, (64, 0), 30)])        # few rows: the 128 x 128 tiles
+def test_dw_in_every_order_of_the_experts(q, E, N, K, heavy, rest):
+    """Popular experts first, tiles of the others in chains: every expert's gradient against 64-bit sums."""
+    rng = np.random.default_rng(E + N)
+    rows = rng.integers(0, rest, E)
+    rows[rng.permutation(E)[:len(heavy)]] = heavy
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    M = int(off[-1])
+    dy = synth.normal_bf16((M, N), 1.0, seed=8501, device="cuda")
+    x = synth.normal_bf16((M + 5, K), 1.0, seed=8502, device="cuda")
+    rm = torch.from_numpy(rng.permutation(M + 5)[:M].astype(np.int64)).cuda()
+    dw = torch.full((E, N, K), float("nan"), dtype=torch.float32, device="cuda")
+    q.qarl_grouped_dw(dy, x, _i32(off), E, row_map=rm.to(torch.int32), out_dtype=q.QARL_OUT_F32, out=dw)
+    for e in range(E):
+        lo, hi = int(off[e]), int(off[e + 1])
+        want = dy[lo:hi].double().t() @ x[rm[lo:hi]].double()
+        err = (dw[e].double() - want).abs() / (want.abs() + max(1.0, float(hi - lo)) ** 0.5)
+        assert float(err.max()) <= TOL_F32, (e, hi - lo)
+
+
 def test_backward_errors(q):
     w = synth.normal_bf16((1, 64, 128), 0.02, seed=85).cuda()
     qw = q.qarl_quantize_weights(w)                                  # N = 64: not a multiple of 128
