@@ -317,9 +317,11 @@ int qarl_qgemm_grouped(const qarl_qweight *W, const void *x, const float *x_scal
     }
     if (xwide) {   // W4A8: e4m3 rows -> the same values as bf16 rows; the kernels scale by s_x in their epilogue
         void *x16 = (char *)ws + stage + sums;
-        rc = launch_e4m3_to_bf16(x, x_rows * (int64_t)W->K, x16, st);
+        float *gs = sums ? (float *)((char *)ws + stage) : nullptr;
+        rc = launch_e4m3_to_bf16(x, x_rows * (int64_t)W->K, x16, gs, st);
         if (rc) return rc;
         a.x = x16;
+        a.x_group_sums = gs;
     }
     if (epilogue == QARL_EPI_COMBINE) {
         if (!combine_w || !sorted_pairs) {
@@ -331,7 +333,7 @@ int qarl_qgemm_grouped(const qarl_qweight *W, const void *x, const float *x_scal
         a.out_f32 = 1;
         a.out_row_map = sorted_pairs;  // Y lands in pair order: row t*topk + slot
     }
-    if (sums) {
+    if (sums && !xwide) {
         float *gs = (float *)((char *)ws + stage);
         rc = launch_group_sums(a.x, x_rows, W->K, gs, st);
         if (rc) return rc;

@@ -82,6 +82,15 @@ struct RowScale {
     }
 };
 
+// Sum of eight bf16 values, in the order of the group sums (pairs, then ascending).
+__device__ __forceinline__ float group_chunk_sum(u32x4 v)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s += __uint_as_float(v[i] << 16) + __uint_as_float(v[i] & 0xffff0000u);
+    return s;
+}
+
 // absmax of eight bf16 values held in four dwords, folded into am
 __device__ __forceinline__ float absmax_bf16x8(u32x4 v, float am)
 {
@@ -275,7 +284,7 @@ int launch_quantize_int4(const void *w, int64_t rows, int K, void *codes, void *
 int launch_quantize_fp8_rows(const void *x, int64_t rows, int K, void *codes, float *scales, hipStream_t s);
 int launch_quantize_fp4_rows(const void *x, int64_t rows, int K, void *codes, float *scales, hipStream_t s);
 int launch_canonical_codes(int fmt, const void *codes, int64_t rows, int K, void *out, hipStream_t s);
-int launch_e4m3_to_bf16(const void *x8, int64_t n, void *x16, hipStream_t s);               // e4m3 bytes -> bf16 (exact)
+int launch_e4m3_to_bf16(const void *x8, int64_t n, void *x16, float *sums, hipStream_t s);  // e4m3 bytes -> bf16 (exact); sums: as launch_group_sums, or null
 int launch_route_only(const void *logits, int T, int E, int topk, int renorm, int32_t *ids, float *w, hipStream_t s);
 int launch_route(const void *logits, int T, int E, int topk, int renorm, int32_t *ids, float *w,
                  int32_t *counts, int32_t *offsets, int32_t *pairs, int32_t *tokens, hipStream_t s);

@@ -364,9 +364,7 @@ __global__ __launch_bounds__(256) void group_sums_kernel(const u32x4 *__restrict
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;  // 16-byte chunk = 8 elements
     u32x4 v = {0, 0, 0, 0};
     if (c < n_chunks) v = x[c];
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s += __uint_as_float(v[i] << 16) + __uint_as_float(v[i] & 0xffff0000u);
+    float s = group_chunk_sum(v);
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
     if (c < n_chunks && (c & 15) == 0) sums[c >> 4] = -1.5f * s;

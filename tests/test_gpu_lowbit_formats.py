@@ -296,3 +296,23 @@ def test_codes_to_canonical_equals_the_oracles_packing(q, oracle):
     assert np.array_equal(q.qarl_codes_to_canonical(q8).cpu().numpy(), f8)
     assert q.lib().qarl_codes_bytes(q.QARL_FP8_E4M3_CH, E, N, K) == E * N * K
     assert q.lib().qarl_codes_bytes(99, E, N, K) == 0
+
+
+@pytest.mark.parametrize("K,T,E", [(128, 1, 1), (384, 17, 3), (768, 130, 5), (2048, 33, 2)])
+def test_w4a8_tiled_path_is_the_w4a16_path_on_widened_rows(q, K, T, E):
+    """The tiled W4A8 GEMM widens the e4m3 rows and forms their group sums in one pass: with unit row scales it gives the
+    bits of the tiled W4A16 GEMM on the same values in bf16, whose sums come from a pass of their own (groups at the
+    first and last chunk of a workgroup, a last workgroup that is not full, every e4m3 value)."""
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, 64, K), 0.02, 5).cuda(), q.QARL_W4A16_G128)
+    q8 = q.QWeight.empty(q.QARL_W4A8_G128, E, 64, K)
+    q8.codes.copy_(qw.codes)
+    q8.scales.copy_(qw.scales)
+    g = torch.Generator().manual_seed(K + T)
+    x8 = torch.randint(0, 256, (T, K), generator=g, dtype=torch.uint8)
+    x8[(x8 & 0x7f) == 0x7f] = 0        # the two NaN patterns
+    x16 = x8.view(torch.float8_e4m3fn).float().bfloat16()
+    off = torch.tensor([T * e // E for e in range(E + 1)], dtype=torch.int32).cuda()
+    kw = dict(out_dtype=q.QARL_OUT_F32, path=q.QARL_PATH_PREFILL)
+    want = q.qarl_qgemm_grouped(qw, x16.cuda(), off, T, **kw)
+    got = q.qarl_qgemm_grouped(q8, x8.cuda(), off, T, x_scales=torch.ones(T, device="cuda"), **kw)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
