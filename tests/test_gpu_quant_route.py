@@ -163,3 +163,19 @@ def test_route_empty_and_errors(q):
     assert ei.value.status == q.QARL_ERR_UNSUPPORTED
     with pytest.raises(q.QarlError):
         q.qarl_quantize_weights(torch.zeros((1, 32, 100), dtype=torch.bfloat16, device="cuda"))
+
+
+@pytest.mark.parametrize("T,E,topk", [(513, 64, 1), (520, 64, 32), (16384, 128, 8), (20011, 64, 7)])
+def test_grouping_ranges(q, oracle, T, E, topk):
+    """The large-batch grouping at the ends of its range: less than a batch of loads per wavefront, exactly as many pairs as
+    the hit bits in registers cover (131072), and more (the rest is read again); one and 32 slots per token."""
+    lg = synth.router_logits(T, E, seed=T + topk, zipf_s=1.1)
+    ids, w = oracle.route(np_bits(lg), topk)
+    counts, offsets, pairs = oracle.group(ids, E)
+    r = q.qarl_moe_route(lg.cuda(), topk)
+    torch.cuda.synchronize()
+    assert np.array_equal(r.ids.cpu().numpy(), ids)
+    assert np.array_equal(r.counts.cpu().numpy(), counts)
+    assert np.array_equal(r.offsets.cpu().numpy(), offsets)
+    assert np.array_equal(r.pairs.cpu().numpy(), pairs)
+    assert np.array_equal(r.tokens.cpu().numpy(), pairs // topk)
