@@ -179,3 +179,24 @@ def test_grouping_ranges(q, oracle, T, E, topk):
     assert np.array_equal(r.offsets.cpu().numpy(), offsets)
     assert np.array_equal(r.pairs.cpu().numpy(), pairs)
     assert np.array_equal(r.tokens.cpu().numpy(), pairs // topk)
+
+
+@pytest.mark.parametrize("E,topk", [(64, 32), (128, 1), (192, 5), (256, 32)])
+def test_route_probabilities(q, oracle, E, topk):
+    """Every kernel of the router (one, two and four logits per lane; 192 experts leave the fourth empty), without
+    renormalisation too, negative and positive winners, ties, masked (-inf) experts."""
+    T = 301
+    lb = np_bits(synth.router_logits(T, E, seed=7 * E + topk)).copy()
+    lb[::3] |= 0x8000                                  # all logits negative: the keys are inverted patterns
+    lb[1::7, : E - topk] = 0xff80                      # -inf: the last topk experts win
+    lb[2::7] = lb[2::7, :1]                            # all tie
+    ids, _ = oracle.route(lb, topk)
+    x = (lb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    p = np.exp(x - x.max(axis=1, keepdims=True))
+    p = np.take_along_axis(p / p.sum(axis=1, keepdims=True), ids.astype(np.int64), axis=1)
+    # 3e-6: l - m is rounded to 24 bits (|l - m| < 16: 1e-6 in the exponential), expf, eight additions in a chain, a division
+    for renorm, ref in ((False, p), (True, p / p.sum(axis=1, keepdims=True))):
+        r = q.qarl_moe_route(synth.from_bits(lb).cuda(), topk, renorm, group=False)
+        torch.cuda.synchronize()
+        assert np.array_equal(r.ids.cpu().numpy(), ids)
+        assert np.allclose(r.w.cpu().numpy().astype(np.float64), ref, rtol=3e-6, atol=0)
