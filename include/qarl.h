@@ -190,7 +190,8 @@ int qarl_grouped_dw(const void *dy_bf16, const void *x_bf16, const int32_t *row_
  * pr, which is the (expert, token, slot) order of qarl_moe_route's grouping.
  *   epilogue   NONE: out [T*topk][N];  SILU_MUL: out bf16 [T*topk][N/2];
  *              COMBINE: Y staged in ws as fp32 [T*topk][N] (qarl_qgemm_workspace_bytes with M = T*topk),
- *              out [T][N] = sum over slots of combine_w[t][slot] * Y[t*topk + slot], in slot order
+ *              out [T][N] = sum over slots of combine_w[t][slot] * Y[t*topk + slot], in slot order.  out may lie
+ *              on top of x or topk_ids
  * x is 16-bit for every format.  For the e4m3-activation formats FP8, FP4 and W4A8 the kernel applies the activation
  * quantizer of eq. (2) to the rows it gathers (s_x = absmax / 448 per row, e4m3 codes of x / s_x: the arithmetic
  * of qarl_quantize_rows_fp8), so a decode step has no separate quantizer launch for x or for the intermediate.

@@ -419,9 +419,14 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
         set_error("qarl_qgemm_routed: COMBINE needs combine_w");
         return QARL_ERR_INVALID_ARG;
     }
-    if (int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
+    // The kernels for few pairs write the combined rows while other workgroups still read x and the ids; the staged path
+    // writes them in a launch of its own, so a caller may put out on top of either.
+    const bool in_place = epilogue == QARL_EPI_COMBINE &&
+                          (ranges_overlap(out, (size_t)T * W->N * (a.out_f32 ? 4 : 2), x, (size_t)a.x_rows * W->K * 2) ||
+                           ranges_overlap(out, (size_t)T * W->N * (a.out_f32 ? 4 : 2), topk_ids, (size_t)M * 4));
+    if (!in_place && int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
         return launch_qgemm_small_w4(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
-    if (!int4_weights(W->fmt) && qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))
+    if (!in_place && !int4_weights(W->fmt) && qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))
         return launch_qgemm_small_fp8(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
     if (epilogue == QARL_EPI_COMBINE) {
         a.epilogue = QARL_EPI_NONE;

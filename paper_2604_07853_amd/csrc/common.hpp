@@ -266,6 +266,12 @@ __device__ __forceinline__ bool find_grouped_tile(const int32_t *offsets, int E,
     return true;
 }
 
+// Whether two byte ranges share memory.
+inline bool ranges_overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // Host-side error plumbing (api.hip).
 void set_error(const char *fmt, ...);
 int check_hip(hipError_t e, const char *what);

@@ -605,3 +605,24 @@ def test_routed_mode_ids_outside_the_expert_range_leave_their_rows_alone(q, orac
     keep[skipped] = False
     assert bool((y[skipped] == -777.0).all())
     assert torch.equal(y[torch.tensor(keep)], y2[torch.tensor(keep)])
+
+
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
+def test_routed_combine_written_over_its_own_input(q, fmt_name):
+    """The combined rows may land on top of x or of the ids: they are written when every workgroup has read both."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    E, N, K, T, topk = 64, 512, 512, 8, 8
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=61).cuda(), fmt)
+    x = synth.normal_bf16((T, K), 1.0, seed=62).cuda()
+    r = q.qarl_moe_route(synth.router_logits(T, E, 63).cuda(), topk)
+    kw = dict(epilogue=q.QARL_EPI_COMBINE, combine_w=r.w)
+    want = q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, **kw)
+    over_x = x.clone()
+    q.qarl_qgemm_routed(qw, over_x, r.ids, T, topk, True, out=over_x, **kw)
+    assert torch.equal(over_x, want)
+    buf = torch.zeros((T * N * 2,), dtype=torch.uint8, device="cuda")
+    ids = buf.view(torch.int32)[:T * topk]
+    ids.copy_(r.ids.reshape(-1))
+    over_ids = buf.view(torch.bfloat16).reshape(T, N)
+    q.qarl_qgemm_routed(qw, x, ids, T, topk, True, out=over_ids, **kw)
+    assert torch.equal(over_ids, want)
