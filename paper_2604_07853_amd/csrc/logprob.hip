@@ -592,7 +592,12 @@ int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T,
         set_error("logprob: H too large");
         return QARL_ERR_UNSUPPORTED;
     }
-    if (T <= kSMaxTok) {
+    // The streaming path's last kernel writes results while it still reads h, the vocabulary rows and the targets; the tiled
+    // one has finished with them by then, so a caller may put logprob on top of any of them.
+    const bool in_place = ranges_overlap(logprob, (size_t)T * 4, h, (size_t)T * H * 2) ||
+                          ranges_overlap(logprob, (size_t)T * 4, wlm, (size_t)V * H * 2) ||
+                          ranges_overlap(logprob, (size_t)T * 4, target, (size_t)T * 4);
+    if (T <= kSMaxTok && !in_place) {
         LogprobStreamParams q;
         q.h = p.h;
         q.w = p.w;

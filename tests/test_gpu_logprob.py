@@ -107,3 +107,19 @@ def test_logprob_edges_of_the_token_and_vocabulary_tiles(q, oracle, T, H, V):
     rows = np.arange(T) if T <= 130 and V * H < 10 ** 7 else np.unique(np.linspace(0, T - 1, 24).astype(np.int64))
     ref = oracle.token_logprob(np_bits(h)[rows], np_bits(w), tg.numpy()[rows], 1.5)
     assert np.abs(got.cpu().numpy()[rows].astype(np.float64) - ref).max() <= TOL_LP
+
+
+def test_logprob_written_over_its_own_inputs(q):
+    """logprob may land on top of h or of the targets (here one element off), also for the few tokens of a decode step."""
+    T, H, V = 61, 256, 9000
+    h = synth.normal_bf16((T, H), 1.0, seed=41).cuda()
+    w = synth.normal_bf16((V, H), 0.2, seed=42).cuda()
+    tg = synth.targets(T, V, seed=43).cuda()
+    want = q.qarl_token_logprob(h, w, tg)["logprob"]
+    over_h = h.clone()
+    got = q.qarl_token_logprob_static(over_h, w, tg, over_h.view(-1).view(torch.float32)[:T])
+    assert (got - want).abs().max().item() <= TOL_LP
+    buf = torch.empty((T + 1,), dtype=torch.int32, device="cuda")
+    buf[1:] = tg
+    got = q.qarl_token_logprob_static(h, w, buf[1:], buf.view(torch.float32)[:T])
+    assert (got - want).abs().max().item() <= TOL_LP
