@@ -200,7 +200,7 @@ int qarl_grouped_dw(const void *dy_bf16, const void *x_bf16, const int32_t *row_
  * Supported: W4A16_G128 and W4A8_G128 (N % 32 == 0, K % 256 == 0, K <= 2048), FP8_E4M3_CH and FP4_E2M1_CH (N % 32 == 0,
  * K % 128 == 0, K <= 4096); T <= 512, T*topk <= 4096, a token listing an expert at most once (as the router's
  * output does; rows past 512 of one expert would be dropped); ids outside [0, E) select no expert and leave their
- * output rows unwritten.  topk_ids 16-byte aligned.  Errors as for qarl_qgemm_grouped.  T == 0 is a no-op. */
+ * output rows unwritten (COMBINE: their Y counts as zeros).  topk_ids 16-byte aligned.  Errors as for qarl_qgemm_grouped.  T == 0 is a no-op. */
 int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, const int32_t *topk_ids,
                       int T, int topk, int epilogue, const float *combine_w, void *out, int out_dtype,
                       void *ws, size_t ws_bytes, void *stream);

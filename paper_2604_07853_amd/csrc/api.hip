@@ -342,7 +342,7 @@ int qarl_qgemm_grouped(const qarl_qweight *W, const void *x, const float *x_scal
     rc = (use == QARL_PATH_DECODE) ? launch_qgemm_stream(a, st) : launch_qgemm_tile(a, st);
     if (rc) return rc;
     if (epilogue == QARL_EPI_COMBINE)
-        return launch_combine((const float *)ws, combine_w, T, topk, W->N, out, out_dtype == QARL_OUT_F32, st);
+        return launch_combine((const float *)ws, combine_w, nullptr, 0, T, topk, W->N, out, out_dtype == QARL_OUT_F32, st);
     return QARL_OK;
 }
 
@@ -421,9 +421,9 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
     }
     // The kernels for few pairs write the combined rows while other workgroups still read x and the ids; the staged path
     // writes them in a launch of its own, so a caller may put out on top of either.
-    const bool in_place = epilogue == QARL_EPI_COMBINE &&
-                          (ranges_overlap(out, (size_t)T * W->N * (a.out_f32 ? 4 : 2), x, (size_t)a.x_rows * W->K * 2) ||
-                           ranges_overlap(out, (size_t)T * W->N * (a.out_f32 ? 4 : 2), topk_ids, (size_t)M * 4));
+    const size_t comb_bytes = epilogue == QARL_EPI_COMBINE ? (size_t)T * W->N * (a.out_f32 ? 4 : 2) : 0;
+    const bool over_ids = comb_bytes && ranges_overlap(out, comb_bytes, topk_ids, (size_t)M * 4);
+    const bool in_place = over_ids || (comb_bytes && ranges_overlap(out, comb_bytes, x, (size_t)a.x_rows * W->K * 2));
     if (!in_place && int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
         return launch_qgemm_small_w4(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
     if (!in_place && !int4_weights(W->fmt) && qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))
@@ -432,11 +432,16 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
         a.epilogue = QARL_EPI_NONE;
         a.out = ws;
         a.out_f32 = 1;
+        if (over_ids) {   // the combine cannot look at them any more: rows no expert writes are zeros beforehand
+            rc = launch_fill_f32((float *)ws, M * W->N, 0.f, st);
+            if (rc) return rc;
+        }
     }
     rc = launch_qgemm_stream(a, st);
     if (rc) return rc;
     if (epilogue == QARL_EPI_COMBINE)
-        return launch_combine((const float *)ws, combine_w, T, topk, W->N, out, out_dtype == QARL_OUT_F32, st);
+        return launch_combine((const float *)ws, combine_w, over_ids ? nullptr : topk_ids, W->E, T, topk, W->N, out,
+                              out_dtype == QARL_OUT_F32, st);
     return QARL_OK;
 }
 

@@ -5,9 +5,12 @@
 namespace qarl {
 
 // out[t][n] = sum_{slot} w[t][slot] * Y[t*topk + slot][n], slots in ascending order, fp32,
-// rounded once.  Y is in pair order (the grouped GEMM scatters its rows there).
+// rounded once.  Y is in pair order (the grouped GEMM scatters its rows there).  IDS: pair p's row was written only if
+// ids[p] lies in [0, E); another one counts as zeros.
+template <bool IDS>
 __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ y, const float *__restrict__ w,
-                                                      int T, int topk, int N, void *__restrict__ out, int out_f32)
+                                                      const int32_t *__restrict__ ids, int E, int T, int topk, int N,
+                                                      void *__restrict__ out, int out_f32)
 {
     const int n4 = N / 4;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -17,20 +20,23 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
     // eight slots' loads go out together (the rows are read once: nontemporal), the sum stays in slot order
     const float *yt = y + (int64_t)t * topk * N + c4 * 4;
     const float *wt = w + (int64_t)t * topk;
+    const int32_t *it = IDS ? ids + (int64_t)t * topk : nullptr;
     for (int j0 = 0; j0 < topk; j0 += 8) {
         f32x4 v[8];
         float wj[8];
+        int ij[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int jj = min(j0 + j, topk - 1);
             v[j] = __builtin_nontemporal_load((const f32x4 *)(yt + (int64_t)jj * N));
             wj[j] = wt[jj];
+            ij[j] = IDS ? it[jj] : 0;
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
             if (j0 + j < topk) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wj[j], v[j][i], acc[i]);
+                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wj[j], IDS && (uint32_t)ij[j] >= (uint32_t)E ? 0.f : v[j][i], acc[i]);
             }
     }
     if (out_f32) {
@@ -43,11 +49,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
     }
 }
 
-int launch_combine(const float *y, const float *w, int T, int topk, int N, void *out, int out_f32, hipStream_t s)
+int launch_combine(const float *y, const float *w, const int32_t *ids, int E, int T, int topk, int N, void *out, int out_f32,
+                   hipStream_t s)
 {
     if (T == 0) return QARL_OK;
     const int64_t n = (int64_t)T * (N / 4);
-    combine_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(y, w, T, topk, N, out, out_f32);
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (ids) combine_kernel<true><<<grid, block, 0, s>>>(y, w, ids, E, T, topk, N, out, out_f32);
+    else combine_kernel<false><<<grid, block, 0, s>>>(y, w, nullptr, 0, T, topk, N, out, out_f32);
     return check_hip(hipGetLastError(), "combine_kernel");
 }
 

@@ -337,15 +337,16 @@ int launch_qgemm_dx(const GemmArgs &a, hipStream_t s);
 int launch_grouped_dw(const void *dy, const void *x, const int32_t *row_map, const int32_t *offsets, int64_t M, int E, int N,
                       int K, void *out, int out_f32, hipStream_t s);
 int launch_group_sums(const void *x_bf16, int64_t rows, int K, float *sums, hipStream_t s);
-int launch_combine(const float *y_pair_order, const float *w, int T, int topk, int N, void *out, int out_f32,
-                   hipStream_t s);
+// ids: of the pairs, or null (every row of Y was written)
+int launch_combine(const float *y_pair_order, const float *w, const int32_t *ids, int E, int T, int topk, int N, void *out,
+                   int out_f32, hipStream_t s);
 int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T, int H, int V,
                    float inv_temp, float *logprob, void *ws, hipStream_t s);
 size_t logprob_ws_bytes(int T, int H, int V);
 // Device address, on the current device, of the library's own file-scope scratch array (kLogprobScratchBytes).
 constexpr size_t kLogprobScratchBytes = (size_t)4 << 20;
 int logprob_static_scratch(void **ptr);
-int launch_fill_f32(float *p, int n, float v, hipStream_t s);
+int launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 int launch_tbpo(const float *lp_cur, const float *lp_old, const float *lp_smp, const int32_t *seq_offsets, int S,
                 const float *adv, float eps_low, float eps_high, float delta_low, float delta_high, float c,
                 float *r_seq, float *w_clip, float *r_clip, int32_t *in_band, float *obj_seq, float *objective,

@@ -111,16 +111,16 @@ __global__ __launch_bounds__(kTbpoThreads) void tbpo_grad_kernel(TbpoParams p)
     for (int t = lo + (int)threadIdx.x; t < hi; t += kTbpoThreads) p.grad[t] = g;
 }
 
-__global__ void fill_f32_kernel(float *p, int n, float v)
+__global__ void fill_f32_kernel(float *p, int64_t n, float v)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) p[i] = v;
 }
 
-int launch_fill_f32(float *p, int n, float v, hipStream_t s)
+int launch_fill_f32(float *p, int64_t n, float v, hipStream_t s)
 {
     if (n <= 0) return QARL_OK;
-    fill_f32_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(p, n, v);
+    fill_f32_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(p, n, v);
     return check_hip(hipGetLastError(), "fill_f32_kernel");
 }
 

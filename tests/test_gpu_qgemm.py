@@ -626,3 +626,31 @@ def test_routed_combine_written_over_its_own_input(q, fmt_name):
     over_ids = buf.view(torch.bfloat16).reshape(T, N)
     q.qarl_qgemm_routed(qw, x, ids, T, topk, True, out=over_ids, **kw)
     assert torch.equal(over_ids, want)
+
+
+@pytest.mark.parametrize("fmt_name,T", [(f, T) for f in ("w4a16", "w4a8", "fp8", "fp4") for T in (8, 200)])
+def test_routed_combine_counts_ids_outside_the_expert_range_as_zeros(q, fmt_name, T):
+    """Few and many pairs, whatever the workspace and the weights of such slots hold, also with out on top of the ids: the
+    same as with a weight of zero on a row that exists."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    E, N, K, topk = 64, 160, 512, 4
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=71).cuda(), fmt)
+    x = synth.normal_bf16((T * topk, K), 1.0, seed=72).cuda()
+    r = q.qarl_moe_route(synth.router_logits(T, E, 73).cuda(), topk)
+    ids, w = r.ids.clone(), r.w.clone()
+    for t, slot, bad in ((0, 0, -1), (2, 3, E), (3, 1, 2 ** 31 - 1), (T - 1, 2, -2 ** 31)):
+        ids[t, slot] = bad
+        w[t, slot] = 0.0
+    ids[5] = -1
+    w[5] = 0.0
+    kw = dict(epilogue=q.QARL_EPI_COMBINE, out_dtype=q.QARL_OUT_F32)
+    want = q.qarl_qgemm_routed(qw, x, r.ids, T, topk, False, combine_w=w, **kw)
+    ws = torch.full((T * topk * (N + K // 128 + K),), float("nan"), dtype=torch.float32, device="cuda")
+    got = q.qarl_qgemm_routed(qw, x, ids, T, topk, False, combine_w=r.w, ws=ws, **kw)
+    assert torch.equal(got, want) and bool((got[5] == 0).all())
+    ws.fill_(float("nan"))
+    buf = torch.zeros((T, N), dtype=torch.float32, device="cuda")
+    over = buf.view(torch.int32).view(-1)[:T * topk]
+    over.copy_(ids.reshape(-1))
+    q.qarl_qgemm_routed(qw, x, over, T, topk, False, combine_w=r.w, ws=ws, out=buf, **kw)
+    assert torch.equal(buf, want)
