@@ -1,5 +1,7 @@
 // Weighted combine of the expert outputs and the log-prob mismatch comparison:
 // small bandwidth-bound kernels with fixed summation order.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace qarl {
@@ -17,28 +19,42 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
     if (idx >= (int64_t)T * n4) return;
     const int t = (int)(idx / n4), c4 = (int)(idx % n4);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    // eight slots' loads go out together (the rows are read once: nontemporal), the sum stays in slot order
+    // The loads of eight (or four) slots go out together (the rows are read once: nontemporal), the rows first; the sum stays in
+    // slot order.  Without a test per slot where all exist: the look at the ids then costs nothing (routed call of 16 tokens,
+    // top-4, 1024 x 512: 12.3 us without the ids, 12.6 with them and a test per slot, 12.1 so).
     const float *yt = y + (int64_t)t * topk * N + c4 * 4;
     const float *wt = w + (int64_t)t * topk;
     const int32_t *it = IDS ? ids + (int64_t)t * topk : nullptr;
-    for (int j0 = 0; j0 < topk; j0 += 8) {
-        f32x4 v[8];
-        float wj[8];
-        int ij[8];
+    auto add = [&](int j0, auto n_t, auto all_t) {   // slots j0 .. j0 + n_t - 1; all_t: all of them exist
+        constexpr int n = decltype(n_t)::value;
+        constexpr bool kAll = decltype(all_t)::value;
+        f32x4 v[n];
+        float wj[n];
+        int ij[n];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int jj = min(j0 + j, topk - 1);
-            v[j] = __builtin_nontemporal_load((const f32x4 *)(yt + (int64_t)jj * N));
+        for (int j = 0; j < n; ++j)
+            v[j] = __builtin_nontemporal_load((const f32x4 *)(yt + (int64_t)(kAll ? j0 + j : min(j0 + j, topk - 1)) * N));
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const int jj = kAll ? j0 + j : min(j0 + j, topk - 1);
             wj[j] = wt[jj];
             ij[j] = IDS ? it[jj] : 0;
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j0 + j < topk) {
+        for (int j = 0; j < n; ++j)
+            if (kAll || j0 + j < topk) {
+                if (IDS && (uint32_t)ij[j] >= (uint32_t)E) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wj[j], IDS && (uint32_t)ij[j] >= (uint32_t)E ? 0.f : v[j][i], acc[i]);
+                for (int i = 0; i < 4; ++i) acc[i] = fmaf(wj[j], v[j][i], acc[i]);
             }
-    }
+    };
+    constexpr std::integral_constant<int, 8> eight;
+    constexpr std::integral_constant<int, 4> four;
+    int j0 = 0;
+    for (; j0 + 8 <= topk; j0 += 8) add(j0, eight, std::true_type{});
+    if (j0 + 4 == topk) add(j0, four, std::true_type{});
+    else if (j0 + 4 < topk) add(j0, eight, std::false_type{});
+    else if (j0 < topk) add(j0, four, std::false_type{});
     if (out_f32) {
         *(f32x4 *)((float *)out + (int64_t)t * N + c4 * 4) = acc;
     } else {
