@@ -424,10 +424,18 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
     const size_t comb_bytes = epilogue == QARL_EPI_COMBINE ? (size_t)T * W->N * (a.out_f32 ? 4 : 2) : 0;
     const bool over_ids = comb_bytes && ranges_overlap(out, comb_bytes, topk_ids, (size_t)M * 4);
     const bool in_place = over_ids || (comb_bytes && ranges_overlap(out, comb_bytes, x, (size_t)a.x_rows * W->K * 2));
-    if (!in_place && int4_weights(W->fmt) && qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue))
-        return launch_qgemm_small_w4(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
-    if (!in_place && !int4_weights(W->fmt) && qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))
-        return launch_qgemm_small_fp8(a, epilogue == QARL_EPI_COMBINE ? combine_w : nullptr, st);
+    // They read the weights of every pair by themselves: with few experts, or many columns, the streaming kernels are faster
+    // from a handful of pairs on.
+    const bool int4 = int4_weights(W->fmt);
+    if (!in_place && (int4 ? qgemm_small_w4_supported(W->N, W->K, T, topk, epilogue)
+                           : qgemm_small_fp8_supported(W->N, W->K, T, topk, epilogue))) {
+        const double small_us = int4 ? qgemm_small_w4_us(W->fmt, W->N, W->K, T, topk, epilogue)
+                                     : qgemm_small_fp8_us(W->fmt, W->N, W->K, T, topk, epilogue);
+        if (small_us <= qgemm_stream_routed_us(W->fmt, W->N, W->K, W->E, T, topk, epilogue)) {
+            const float *cw = epilogue == QARL_EPI_COMBINE ? combine_w : nullptr;
+            return int4 ? launch_qgemm_small_w4(a, cw, st) : launch_qgemm_small_fp8(a, cw, st);
+        }
+    }
     if (epilogue == QARL_EPI_COMBINE) {
         a.epilogue = QARL_EPI_NONE;
         a.out = ws;

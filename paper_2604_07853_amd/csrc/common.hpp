@@ -321,14 +321,20 @@ struct GemmArgs {
 int launch_qgemm_stream(const GemmArgs &a, hipStream_t s);
 bool qgemm_stream_supported(int fmt, int N, int K);
 bool qgemm_stream_routed_supported(int fmt, int N, int K, int T, int topk);
+// Estimated times (us) of a routed call under an even router, epilogue included, on the streaming kernels and on the kernels
+// for few pairs: the rule between the two (qgemm_small_w4.hip says how they were measured).
+double qgemm_stream_routed_us(int fmt, int N, int K, int E, int T, int topk, int epilogue);
+int qgemm_stream_w4_units_per_wave(int N, int K, int E, int64_t M);
 int launch_qgemm_stream_w4(const GemmArgs &a, hipStream_t s);
 bool qgemm_stream_w4_supported(int N, int K);
 bool qgemm_stream_w4_routed_supported(int N, int K, int T, int topk);
 // Routed W4A16 / W4A8 calls of a few pairs; combine_w: the COMBINE epilogue, a.out then is its [T][N] output
 bool qgemm_small_w4_supported(int N, int K, int T, int topk, int epilogue);
+double qgemm_small_w4_us(int fmt, int N, int K, int T, int topk, int epilogue);
 int launch_qgemm_small_w4(const GemmArgs &a, const float *combine_w, hipStream_t s);
 // The same for FP8 / FP4
 bool qgemm_small_fp8_supported(int N, int K, int T, int topk, int epilogue);
+double qgemm_small_fp8_us(int fmt, int N, int K, int T, int topk, int epilogue);
 int launch_qgemm_small_fp8(const GemmArgs &a, const float *combine_w, hipStream_t s);
 int launch_qgemm_tile(const GemmArgs &a, hipStream_t s);
 int launch_qgemm_tile_fp8(const GemmArgs &a, hipStream_t s);

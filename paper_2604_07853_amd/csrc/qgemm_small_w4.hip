@@ -263,13 +263,48 @@ __global__ __launch_bounds__(kThreads, 4) void qgemm_small_w4_kernel(SmallParams
     }
 }
 
-// Where the line lies (128 experts, hidden 2048, intermediate 768, top-8; layer of router, gate_up, down + combine): 8
+// Where the line lies.  128 experts, hidden 2048, intermediate 768, top-8; layer of router, gate_up, down + combine: 8
 // tokens = 64 pairs 41 us here against 58 on the streaming kernel; 12 tokens 61 against 58: by then a third of the pairs
 // share their expert with another one, and every pair reads its weights by itself.  1 token: 26 against 56 us (the host
 // issues three calls in 25 us; gate_up 9.5 against 30 us between events, down + combine 9.7 against 22.5).
+// With few experts all pairs share them (six experts of 4096 x 2048, combine: 6 pairs 15 us here against 20 streaming, 30
+// pairs 38 against 22), so up to 64 pairs the estimated times decide.
 constexpr int kSmallPairs = 64;
 
+// The workgroups of a call: pairs of 16-row weight tiles each computes (about two workgroups per CU; a thread folds one
+// column of one slot), and their number along the columns.
+struct SmallGrid {
+    int units, n_slices;
+    int64_t items;
+};
+SmallGrid small_grid(int N, int64_t M, int slots)
+{
+    SmallGrid g;
+    const int n_units = N / 32;   // SILU_MUL: (N / 2) / 16
+    g.items = M / slots;
+    const int64_t units = (g.items * n_units + 511) / 512;
+    const int max_units = kThreads / (32 * slots);
+    g.units = (int)(units < 1 ? 1 : units > max_units ? max_units : units);
+    g.n_slices = (n_units + g.units - 1) / g.units;
+    return g;
+}
+
 }  // namespace
+
+// Time of a call in us: start-up, a wavefront's tasks one after the other, and a share per workgroup beyond the chip's first
+// 512.  This and the estimates beside it are least squares over 2000 calls per format (1 to 256 experts, N 32 to 4096, every
+// K, top-1 to top-16, up to 64 pairs, all epilogues; both kernels timed, launches back to back): off by 8 % here (rms), 6 to
+// 10 % for FP8 and FP4, 8 to 15 % for the streaming kernels.  A rule of pairs alone took the kernel that was slower by more
+// than 5 % in an eighth of the calls, at worst 14 times slower; the estimates do in 2 %, at worst 1.3 times.
+double qgemm_small_w4_us(int fmt, int N, int K, int T, int topk, int epilogue)
+{
+    const bool comb = epilogue == QARL_EPI_COMBINE, qx = fmt == QARL_W4A8_G128;
+    const int slots = comb ? topk : 1, G = K / kGroup;
+    const SmallGrid g = small_grid(N, (int64_t)T * topk, slots);
+    const double wgs = (double)(g.items * g.n_slices) / 512, per_wave = (double)(slots * g.units * G) / kWaves;
+    return qx ? 4.4 + 0.89 * per_wave + wgs * (1.6 + 0.4 * per_wave + 0.055 * slots * G) + (comb ? 0.35 : 0.)
+              : 3.3 + 0.79 * per_wave + wgs * (1.55 + 0.49 * per_wave + 0.034 * slots * G) + (comb ? 0.3 : 0.);
+}
 
 bool qgemm_small_w4_supported(int N, int K, int T, int topk, int epilogue)
 {
@@ -294,17 +329,14 @@ int launch_qgemm_small_w4(const GemmArgs &a, const float *combine_w, hipStream_t
     p.topk = a.topk;
     p.x_per_token = a.x_per_token;
     p.qx = a.fmt == QARL_W4A8_G128;
-    p.n_units = epi == QARL_EPI_SILU_MUL ? (a.N / 2) / 16 : a.N / 32;
+    p.n_units = a.N / 32;
     const int G = a.K / kGroup, slots = epi == QARL_EPI_COMBINE ? a.topk : 1;
-    const int64_t items = a.M / slots;
-    // about two workgroups per CU; a thread folds one column of one slot
-    int64_t units = (items * p.n_units + 511) / 512;
-    const int max_units = kThreads / (32 * slots);
-    p.units = (int)(units < 1 ? 1 : units > max_units ? max_units : units);
-    p.n_slices = (p.n_units + p.units - 1) / p.units;
+    const SmallGrid sg = small_grid(a.N, a.M, slots);
+    p.units = sg.units;
+    p.n_slices = sg.n_slices;
     p.g_magic = (65536u + G - 1) / G;   // exact for task indices below 65536 / (G - 1); there are at most 16 * 16 * 16
     const size_t lds = small_lds_bytes(a.K, slots, p.units);
-    const dim3 grid((unsigned)(items * p.n_slices)), block(kThreads);
+    const dim3 grid((unsigned)(sg.items * p.n_slices)), block(kThreads);
     static LdsLimitOnce once[3];
     auto go = [&](auto kern, int i) -> int {
         if (lds > 64 * 1024)

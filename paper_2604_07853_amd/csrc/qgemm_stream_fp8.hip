@@ -27,6 +27,8 @@
 
 #include <type_traits>
 
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace qarl {
@@ -400,6 +402,30 @@ int launch_ring(const StreamParams &p, hipStream_t s)
     return launch_cfg<EPI, MT, 1>(p, s);
 }
 
+// Rows (in 16-row tiles, row blocks) and slices of the weight tiles that a launch gives every expert; MT 0: K too large.
+struct StreamGrid {
+    int MT, m_split, n_slices;
+};
+StreamGrid stream_grid(int N, int K, int E, int64_t M, bool routed)
+{
+    StreamGrid g;
+    // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
+    const double mean = (double)M / (double)E;
+    const double need = mean + 4.0 * sqrt(mean);
+    // token tiles per workgroup: limited by the LDS tile, which holds the whole K of every row
+    const int mt_fit = stream_lds_bytes(K, 2, routed) <= 160 * 1024 ? 2 : (stream_lds_bytes(K, 1, routed) <= 160 * 1024 ? 1 : 0);
+    g.MT = need <= 16.0 ? 1 : 2;  // more rows per expert go to further row blocks (m_split)
+    if (g.MT > mt_fit) g.MT = mt_fit < 1 ? 0 : 1;
+    const int ms = g.MT ? (int)ceil(need / (16.0 * g.MT)) : 1;
+    g.m_split = ms < 1 ? 1 : (ms > 8 ? 8 : ms);
+    // slices per expert: aim at one workgroup per CU, at least one pair of tiles per wavefront
+    g.n_slices = (256 + E * g.m_split - 1) / (E * g.m_split);
+    const int max_slices = (N / 32 + kSWaves - 1) / kSWaves;
+    if (g.n_slices > max_slices) g.n_slices = max_slices;
+    if (g.n_slices < 1) g.n_slices = 1;
+    return g;
+}
+
 template <int EPI>
 int launch_one(const GemmArgs &a, hipStream_t s)
 {
@@ -427,26 +453,14 @@ int launch_one(const GemmArgs &a, hipStream_t s)
         return QARL_ERR_UNSUPPORTED;
     }
     p.n_units = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2) / 16 : a.N / 32;
-    // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
-    const double mean = (double)a.M / (double)a.E;
-    const double need = mean + 4.0 * sqrt(mean);
-    // token tiles per workgroup: limited by the LDS tile, which holds the whole K of every row
-    const int mt_fit = stream_lds_bytes(a.K, 2, routed) <= 160 * 1024 ? 2 : (stream_lds_bytes(a.K, 1, routed) <= 160 * 1024 ? 1 : 0);
-    if (mt_fit < 1) {
+    const StreamGrid g = stream_grid(a.N, a.K, a.E, a.M, routed);
+    if (g.MT < 1) {
         set_error("qgemm (decode path): K=%d does not fit the LDS tile", a.K);
         return QARL_ERR_UNSUPPORTED;
     }
-    int MT = need <= 16.0 ? 1 : 2;  // more rows per expert go to further row blocks (m_split)
-    if (MT > mt_fit) MT = 1;
-    const int ms = (int)ceil(need / (16.0 * MT));
-    p.m_split = ms < 1 ? 1 : (ms > 8 ? 8 : ms);
-    // slices per expert: aim at one workgroup per CU, at least one pair of tiles per wavefront
-    int slices = (256 + a.E * p.m_split - 1) / (a.E * p.m_split);
-    const int max_slices = (p.n_units + kSWaves - 1) / kSWaves;
-    if (slices > max_slices) slices = max_slices;
-    if (slices < 1) slices = 1;
-    p.n_slices = slices;
-    if (MT == 1) return launch_ring<EPI, 1>(p, s);
+    p.m_split = g.m_split;
+    p.n_slices = g.n_slices;
+    if (g.MT == 1) return launch_ring<EPI, 1>(p, s);
     return launch_ring<EPI, 2>(p, s);
 }
 
@@ -459,6 +473,25 @@ bool qgemm_stream_routed_supported(int fmt, int N, int K, int T, int topk)
     if (!qgemm_stream_supported(fmt, N, K) || T <= 0 || topk <= 0) return false;
     if (T > kIdsRows || (int64_t)T * topk > kIdsMax) return false;
     return stream_lds_bytes(K, 1, true) <= 160 * 1024;
+}
+
+// See qgemm_small_w4_us: start-up, a wavefront's pairs of tiles one after the other, the weights of the experts that have
+// rows, the results, the combine's launch, and the rows such an expert has.
+double qgemm_stream_routed_us(int fmt, int N, int K, int E, int T, int topk, int epilogue)
+{
+    const int64_t M = (int64_t)T * topk;
+    const double G = K / kGroup, comb = epilogue == QARL_EPI_COMBINE;
+    const double used = E * (1. - pow(1. - std::min(1., (double)topk / E), T)), rows = M / used;
+    const double w = used * N * K * 1e-6, y = (double)M * N * 1e-6;
+    if (fmt == QARL_W4A16_G128 || fmt == QARL_W4A8_G128) {
+        const double c = qgemm_stream_w4_units_per_wave(N, K, E, M);
+        return fmt == QARL_W4A16_G128 ? 5.9 + c * (0.61 + 0.436 * G) + 0.035 * w + 13 * y + 2.25 * comb + 0.05 * rows
+                                      : 6.5 + c * (0.39 + 0.476 * G) + 0.033 * w + 12 * y + 2.1 * comb + rows * (0.17 + 0.0015 * G);
+    }
+    const StreamGrid g = stream_grid(N, K, E, M, true);
+    const double c = (N / 32 + g.n_slices * kSWaves - 1) / (g.n_slices * kSWaves);
+    return fmt == QARL_FP8_E4M3_CH ? 4.1 + c * (1.13 + 0.574 * G) + 0.132 * w + 16 * y + 2.1 * comb + rows * (0.095 + 0.012 * G)
+                                   : 4.1 + c * (0.59 + 0.42 * G) + 0.046 * w + 17 * y + 2.1 * comb + rows * (0.09 + 0.01 * G);
 }
 
 bool qgemm_stream_supported(int fmt, int N, int K)

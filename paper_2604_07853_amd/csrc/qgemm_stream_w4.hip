@@ -858,6 +858,31 @@ int launch_ring(const W4Params &p, hipStream_t s)
     return launch_cfg<EPI, MT, 2>(p, s);
 }
 
+// Row blocks and slices of the weight tiles that a launch gives every expert (the wide kernel chooses its own).
+struct W4Grid {
+    double need;      // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
+    int MT, half_tile, msplit_sh, slice_sh, max_slices;
+};
+W4Grid w4_grid(int N, int K, int E, int64_t M)
+{
+    W4Grid g;
+    const double mean = (double)M / (double)E;
+    g.need = mean + 4.0 * sqrt(mean);
+    // 64-row blocks where the whole K of 64 rows fits the LDS tile, 32-row blocks otherwise, 16-row blocks for K
+    // beyond 2048
+    g.MT = (g.need > 32.0 && lds_bytes(K, 2) <= 160 * 1024) ? 2 : 1;
+    g.half_tile = lds_bytes(K, 1) > 160 * 1024;
+    // row blocks per (expert, slice) and slices per expert are powers of two (the kernel splits ids by shifts)
+    const int ms = (int)ceil(g.need / (g.half_tile ? 16.0 : 32.0 * g.MT));
+    g.msplit_sh = 0;
+    while ((1 << g.msplit_sh) < ms && g.msplit_sh < 3) ++g.msplit_sh;
+    // slices per expert: aim at one workgroup per CU, at least one pair of tiles per wavefront
+    g.max_slices = (N / 32 + kWaves - 1) / kWaves;
+    g.slice_sh = 0;
+    while (((int64_t)E << g.msplit_sh << (g.slice_sh + 1)) <= 256 && (2 << g.slice_sh) <= g.max_slices) ++g.slice_sh;
+    return g;
+}
+
 template <int EPI>
 int launch_one(const GemmArgs &a, hipStream_t s)
 {
@@ -881,22 +906,11 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     p.x_per_token = a.x_per_token;
     p.qx = (a.ids && a.fmt == QARL_W4A8_G128) ? 1 : 0;
     p.n_units = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2) / 16 : a.N / 32;
-    // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
-    const double mean = (double)a.M / (double)a.E;
-    const double need = mean + 4.0 * sqrt(mean);
-    // 64-row blocks where the whole K of 64 rows fits the LDS tile, 32-row blocks otherwise, 16-row blocks for K
-    // beyond 2048
-    const int MT = (need > 32.0 && lds_bytes(a.K, 2) <= 160 * 1024) ? 2 : 1;
-    p.half_tile = lds_bytes(a.K, 1) > 160 * 1024;
-    // row blocks per (expert, slice) and slices per expert are powers of two (the kernel splits ids by shifts)
-    const int ms = (int)ceil(need / (p.half_tile ? 16.0 : 32.0 * MT));
-    int msh = 0;
-    while ((1 << msh) < ms && msh < 3) ++msh;
-    p.msplit_sh = msh;
-    // slices per expert: aim at one workgroup per CU, at least one pair of tiles per wavefront
-    const int max_slices = (p.n_units + kWaves - 1) / kWaves;
-    int ssh = 0;
-    while (((int64_t)a.E << msh << (ssh + 1)) <= 256 && (2 << ssh) <= max_slices) ++ssh;
+    const W4Grid g = w4_grid(a.N, a.K, a.E, a.M);
+    const double need = g.need;
+    const int MT = g.MT, max_slices = g.max_slices, ssh = g.slice_sh;
+    p.half_tile = g.half_tile;
+    p.msplit_sh = g.msplit_sh;
     p.slice_sh = ssh;
     p.per_slice = (p.n_units + (1 << ssh) - 1) >> ssh;
     // 64-row blocks over a K-chunked tile: K = 2048 (two chunks of eight scale groups), more than 32 rows per expert
@@ -963,6 +977,12 @@ int launch_one(const GemmArgs &a, hipStream_t s)
 }
 
 }  // namespace
+
+int qgemm_stream_w4_units_per_wave(int N, int K, int E, int64_t M)
+{
+    const int n = kWaves << w4_grid(N, K, E, M).slice_sh;
+    return (N / 32 + n - 1) / n;
+}
 
 bool qgemm_stream_w4_supported(int N, int K)
 {

@@ -654,3 +654,32 @@ def test_routed_combine_counts_ids_outside_the_expert_range_as_zeros(q, fmt_name
     over.copy_(ids.reshape(-1))
     q.qarl_qgemm_routed(qw, x, over, T, topk, False, combine_w=r.w, ws=ws, out=buf, **kw)
     assert torch.equal(buf, want)
+
+
+@pytest.mark.parametrize("fmt_name,E,N,K,T,topk,staged", [
+    ("w4a16", 6, 4096, 2048, 10, 6, True), ("w4a8", 6, 4096, 2048, 10, 6, True), ("fp8", 6, 4096, 2048, 4, 6, True),
+    ("fp4", 6, 4096, 2048, 10, 6, True), ("fp8", 1, 1024, 512, 64, 1, True), ("fp4", 128, 2048, 768, 64, 1, True),
+    ("w4a16", 128, 2048, 768, 8, 8, False), ("w4a8", 1, 512, 256, 1, 1, False), ("fp8", 128, 2048, 768, 2, 8, False),
+    ("fp4", 6, 1024, 512, 1, 6, False)])
+def test_routed_combine_of_few_pairs_reads_shared_weights_once(q, fmt_name, E, N, K, T, topk, staged):
+    """Pairs that share their experts' weights go through the kernel that reads a matrix once for all of its rows, which stages
+    its rows in the workspace; few pairs of many experts don't touch it.  The same bits as grouped decode either way."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=81).cuda(), fmt)
+    M = T * topk
+    x = synth.normal_bf16((M, K), 1.0, seed=82).cuda()
+    rng = np.random.default_rng(83)
+    ids = torch.tensor(np.stack([rng.permutation(E)[:topk] for _ in range(T)]).astype(np.int32), device="cuda")
+    w = torch.tensor(rng.random((T, topk)).astype(np.float32), device="cuda")
+    ws = torch.full((M * (N + K),), -777.0, dtype=torch.float32, device="cuda")
+    kw = dict(epilogue=q.QARL_EPI_COMBINE, combine_w=w, out_dtype=q.QARL_OUT_F32)
+    got = q.qarl_qgemm_routed(qw, x, ids, T, topk, False, ws=ws, **kw)
+    assert bool((ws[:M * N] != -777.0).all()) == staged and (staged or bool((ws == -777.0).all()))
+    pairs = torch.argsort(ids.view(-1), stable=True)
+    off = torch.zeros((E + 1,), dtype=torch.int32, device="cuda")
+    off[1:] = torch.cumsum(torch.bincount(ids.view(-1).long(), minlength=E), 0)
+    rows = x[pairs].contiguous()
+    if fmt != q.QARL_W4A16_G128:
+        rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(rows)
+    want = q.qarl_qgemm_grouped(qw, rows, off, M, sorted_pairs=pairs.int(), T=T, topk=topk, path=q.QARL_PATH_DECODE, **kw)
+    assert torch.equal(got, want)
