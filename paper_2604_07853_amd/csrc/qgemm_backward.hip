@@ -326,13 +326,15 @@ __device__ __forceinline__ TrBase tr_base_512(int col0, int lane)
     return b;
 }
 
+// kOrdered: more than one tile per workgroup or an order of the experts (p.chain > 1 or p.heavy_rows > 0); else tile = workgroup.
+template <bool kOrdered>
 __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams p, const int32_t *__restrict__ row_map,
                                                                         const int32_t *__restrict__ offsets)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave >> 2, wk = wave & 3;   // 128 n x 64 k per wavefront
-    const int m32 = lane & 31, h = lane >> 5;
+    const int h = lane >> 5;
     const int N = p.N, K = p.K;
     const int nbn = N / kDwWTile, nbk = K / kDwWTile;
     // Lists of tiles.  Consecutive workgroup ids go round-robin over the eight XCDs; where the tile grid allows it an XCD
@@ -343,7 +345,8 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
     const int hn = by_xcd ? nbn / 2 : nbn, per = by_xcd ? nbn * nbk / 8 : nbn * nbk;   // n blocks, tiles per expert of the list
     // Items of the list: one tile of a heavy expert (below), p.chain neighbouring tiles of another.  The workgroups of the
     // list take item `first`, then (heavy experts make more items than workgroups) go back and forth over the rest.
-    const int wpe = (per + p.chain - 1) / p.chain;
+    const int chain0 = kOrdered ? p.chain : 1;
+    const int wpe = kOrdered ? (per + chain0 - 1) / chain0 : per;
     const int wgs = by_xcd ? gridDim.x / 8 : gridDim.x;   // E wpe
 
     // ---- copies: instruction i (0..3) of this wavefront moves rows 8 w + 2 i and 8 w + 2 i + 1 of a tile; lane L
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
     auto begin_item = [&](int expert, int item, int chain) {   // item: of the expert
         e = expert;
         t0 = item * chain;
-        t1 = min(t0 + chain, per);
+        t1 = kOrdered ? min(t0 + chain, per) : t0 + 1;
         row0 = offsets[e];
         Me = offsets[e + 1] - row0;
         stages = (Me + kStageM - 1) / kStageM;
@@ -474,20 +477,20 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
 #pragma unroll
     for (int q = 0; q < kDwRankE / 64; ++q) {
         const int ex = q * 64 + lane;
-        cnt[q] = p.heavy_rows > 0 && ex < p.E ? p.offsets[ex + 1] - p.offsets[ex] : 0;
+        cnt[q] = kOrdered && p.heavy_rows > 0 && ex < p.E ? p.offsets[ex + 1] - p.offsets[ex] : 0;
     }
     __builtin_amdgcn_sched_barrier(0);
-    begin_item(first / wpe, first % wpe, p.chain);
+    begin_item(first / wpe, first % wpe, chain0);
     bool begun = true;
     int n_heavy = 0;
-    if (p.heavy_rows > 0) {
+    if (kOrdered && p.heavy_rows > 0) {
         const int64_t twice = 2 * (int64_t)(offsets[p.E] - offsets[0]);
 #pragma unroll
         for (int q = 0; q < kDwRankE / 64; ++q) n_heavy += __popcll(__ballot(cnt[q] > p.heavy_rows && (int64_t)cnt[q] * p.E > twice));
     }
     __shared__ __attribute__((aligned(16))) int s_key[kDwRankE];
     __shared__ int s_rank[kDwRankE], s_order[kDwRankE];
-    if (n_heavy > 0) {   // a thread counts the larger keys among a part of the experts for one of them
+    if (kOrdered && n_heavy > 0) {   // a thread counts the larger keys among a part of the experts for one of them
         const int ep = p.E <= 128 ? 128 : 256, i = tid & (ep - 1), len = ep * ep / kBwThreads, j0 = (tid / ep) * len;
         if (tid < ep) {
             const int rows = tid < p.E ? min(offsets[tid + 1] - offsets[tid], 0x7ffffe) : -1;
@@ -509,18 +512,18 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
         begun = false;
     }
     const int n_items = n_heavy * per + (p.E - n_heavy) * wpe;
-    for (int round = 0; round * wgs < n_items; ++round) {
-        if (!begun) {
+    for (int round = 0; kOrdered ? round * wgs < n_items : round < 1; ++round) {
+        if (kOrdered && !begun) {
             const int idx = round * wgs + ((round & 1) ? wgs - 1 - first : first);
             if (idx >= n_items) continue;
             const bool light = idx >= n_heavy * per;
             const int li = light ? idx - n_heavy * per : idx, w = light ? wpe : per;
             const int r = (light ? n_heavy : 0) + li / w;
             if (round > 0) lds_barrier();   // the last item's epilogue has left the buffers
-            begin_item(n_heavy > 0 ? __builtin_amdgcn_readfirstlane(s_order[r]) : r, li % w, light ? p.chain : 1);
+            begin_item(n_heavy > 0 ? __builtin_amdgcn_readfirstlane(s_order[r]) : r, li % w, light ? chain0 : 1);
         }
         begun = false;
-        for (int t = t0; t < t1; ++t) {
+        for (int t = t0; kOrdered ? t < t1 : t == t0; ++t) {
             const int64_t obase = ((int64_t)e * N + nb * kDwWTile + wn * 128) * K + kb * kDwWTile + wk * 64;
 #pragma unroll
             for (int ms = 0; ms < 4; ++ms)
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
                     for (int nt = 0; nt < 2; ++nt)
                         acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(last.a[ms], last.b[nt], acc[ms][nt], 0, 0, 0);
             }
-            if (t + 1 < t1) begin_tile(t + 1);   // travels during the epilogue, which keeps to the second buffer
+            if (kOrdered && t + 1 < t1) begin_tile(t + 1);   // travels during the epilogue, which keeps to the second buffer
 
             // ---- epilogue: lane (k column m32 of tile nt, half h), register i -> weight row 32 ms + 8 (i / 4) + 4 h + i % 4.
             // 32 rows x 64 columns turn through this wavefront's own piece of the second stage buffer (rows that differ by 4
@@ -661,18 +664,25 @@ int launch_grouped_dw(const void *dy, const void *x, const int32_t *row_map, con
     const int64_t wide_tiles = (int64_t)E * (N / kDwWTile) * (K / kDwWTile);
     const bool few = wide_tiles <= 4 * 256 && M < (int64_t)96 * E;
     if (!few && N % kDwWTile == 0 && K % kDwWTile == 0 && (int64_t)N * 2 < (1LL << 31) && (int64_t)K * 2 < (1LL << 31)) {
-        // Tiles of a workgroup: up to three, as long as six rounds of workgroups remain.  Looking for heavy experts costs a
-        // workgroup 0.5 us and ranking them 1 us: worth it where the order of the work matters: chained tiles (from 4 stages
-        // on), or from four rounds of workgroups and 128 rows per expert on (from 16 stages on; 1024 tiles, 187 rows per
-        // expert: popular experts 157 -> 142 us, 121 -> 122 without).
+        // Tiles of a workgroup: up to three, as long as six rounds of workgroups remain.  Chains and an order of the experts
+        // cost a tile 1 us (scalar registers spill, the loops start cold), looking for heavy experts another 0.5 and ranking
+        // them 1: worth it where the order of the work matters.  Chained tiles: heavy experts from 4 stages on, if there are
+        // rows enough for one (512 tokens, top-4, popular experts, 128 of 1536 x 2048: 201 us in the order of their ids, 226
+        // ranked; 1024 tokens: 258, 244).  Single tiles: from four rounds and 128 rows per expert on, heavy from 16 stages on;
+        // 1024 tiles, 187 rows per expert: popular experts 157 -> 142 us, 121 -> 122 without.  There not for few experts, whose
+        // workgroups all meet the heavy one (8 of 4096 x 4096, 187 rows: 98 us unordered, 107 ordered), and not for more than
+        // 128, whose heavy ones have few tiles each (256 of 512 x 1024, 187 rows, even 123 and 140, popular 336 either way).
         const int lists = dw_wide_by_xcd(N, K) ? 8 : 1;
         const int64_t per = wide_tiles / E / lists;
         p.chain = E > kDwRankE ? 1 : (int)std::min<int64_t>(std::min<int64_t>(3, per), std::max<int64_t>(1, wide_tiles / (6 * 256)));
-        p.heavy_rows = E > kDwRankE ? 0 : p.chain > 1 ? 3 * kStageM : M >= (int64_t)128 * E && wide_tiles >= 4 * 256 ? 15 * kStageM : 0;
+        const bool single = E >= 16 && E <= 128 && M >= (int64_t)128 * E && wide_tiles >= 4 * 256;
+        p.heavy_rows = E > kDwRankE ? 0 : p.chain > 1 ? (M >= 3072 ? 3 * kStageM : 0) : single ? 15 * kStageM : 0;
         const int64_t total = lists * E * ((per + p.chain - 1) / p.chain);
-        static LdsLimitOnce once;
-        if (int rc = raise_lds_limit((const void *)grouped_dw_wide_kernel, once, "hipFuncSetAttribute(grouped dw)")) return rc;
-        grouped_dw_wide_kernel<<<dim3((unsigned)total), dim3(kBwThreads), 2 * kDwWStageB, s>>>(p, row_map, offsets);
+        static LdsLimitOnce once[2];
+        const bool ordered = p.chain > 1 || p.heavy_rows > 0;
+        auto kern = ordered ? grouped_dw_wide_kernel<true> : grouped_dw_wide_kernel<false>;
+        if (int rc = raise_lds_limit((const void *)kern, once[ordered], "hipFuncSetAttribute(grouped dw)")) return rc;
+        kern<<<dim3((unsigned)total), dim3(kBwThreads), 2 * kDwWStageB, s>>>(p, row_map, offsets);
         return check_hip(hipGetLastError(), "grouped_dw_wide_kernel");
     }
     grouped_dw_kernel<<<dim3((unsigned)grid), dim3(kBwThreads), 0, s>>>(p);

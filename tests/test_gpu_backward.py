@@ -139,8 +139,11 @@ def test_backward_full_size_gate_up_sampled(q, oracle):
         assert norm_err(dw[e].cpu().numpy(), ref[0]) <= TOL_F32, e
 
 
-@pytest.mark.parametrize("E,N,K,heavy,rest", [(256, 512, 1536, (700, 300), 9),      # ranked in 256 places, tiles chained, one list
+@pytest.mark.parametrize("E,N,K,heavy,rest", [(256, 512, 1536, (700, 300), 9),      # tiles chained, one list, experts not looked at
                                               (130, 1536, 2048, (3, 0, 900), 12),   # ... three lists' worth of tiles per expert, one list per XCD
+                                              (256, 512, 1536, (700, 300), 30),     # the same, ranked in 256 places
+                                              (130, 1536, 2048, (3, 0, 900), 40),
+                                              (5, 512, 1024, (1300, 0), 400),       # one tile per workgroup, no order
                                               (128, 512, 1024, (1500,), 250),       # ranked, one tile per workgroup
                                               (300, 512, 512, (400,), 200),         # too many experts to rank
                                               (65, 512, 1024, (64, 0), 30)])        # few rows: the 128 x 128 tiles
