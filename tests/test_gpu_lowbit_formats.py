@@ -188,12 +188,14 @@ def test_w4a8_tiled_path_against_the_oracle(q, oracle, E, N, K, rows):
     assert flip_fraction(np_bits(a), a_bits) <= MAX_FLIPS
 
 
-def test_int4_tiled_path_several_column_blocks_per_workgroup(q):
-    """256 experts and 18 column blocks (the last one holds a single 32-column tile): workgroups take two blocks each.  An
-    expert on its own takes one block per workgroup and has to give the same bits (three scale groups, ragged rows)."""
-    E, N, K = 256, 4384, 384
+@pytest.mark.parametrize("N,K,rest", [(4384, 384, 9), (1280, 256, 500)])
+def test_int4_tiled_path_several_column_blocks_per_workgroup(q, N, K, rest):
+    """256 experts and 18 column blocks (the last one holds a single 32-column tile): workgroups take two blocks each; five
+    blocks of many rows: three blocks, then two.  An expert on its own takes one block per workgroup and has to give the same
+    bits (three scale groups, ragged rows)."""
+    E = 256
     w = synth.normal_bf16((E, N, K), 0.02, seed=91, device="cuda")
-    rows = np.random.default_rng(92).integers(0, 9, E)
+    rows = np.random.default_rng(92).integers(0, rest, E)
     rows[[0, 255]] = (70, 64)
     off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
     M = int(off[-1])

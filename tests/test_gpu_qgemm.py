@@ -473,7 +473,7 @@ def test_routed_mode_quantizes_its_rows_like_the_row_quantizer(q, oracle, fmt_na
     assert np.array_equal(np_bits(out_rt), np_bits(out_grp))
 
 
-# Few pairs (T * topk <= 64) take kernels of their own: one pair, one token with eight slots, several column blocks with a
+# Few pairs (T * topk <= 64) can take kernels of their own: one pair, one token with eight slots, several column blocks with a
 # remainder, the most pairs, 16 slots (the most the fused combine takes) and 32 (two launches), one pair too many.
 _FEW_PAIRS = [(64, 32, 256, 1, 1), (64, 96, 2048, 1, 8), (64, 1056, 1024, 3, 8), (64, 544, 768, 8, 8), (64, 64, 1280, 4, 16),
               (64, 64, 512, 2, 32), (64, 160, 512, 13, 5)]
@@ -484,11 +484,16 @@ def test_routed_mode_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, T,
     """Bit for bit the grouped decode path (itself held against the oracle) on the grouping of the same ids: plain
     epilogue fp32 and bf16, SiLU*mul, the combine in fp32 and bf16 with rows per pair and per token."""
     fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
-    w = synth.normal_bf16((E, N, K), 0.02, seed=K + T).cuda()
+    _few_pairs_case(q, fmt, synth.normal_bf16((E, N, K), 0.02, seed=K + T).cuda(), T, topk, False)
+
+
+def _few_pairs_case(q, fmt, w, T, topk, fused):
+    E, N, K = w.shape
     x = synth.normal_bf16((T, K), 1.0, seed=K + T + 1).cuda()
     qw = q.qarl_quantize_weights(w, fmt)
     r = q.qarl_moe_route(synth.router_logits(T, E, K + T + 2).cuda(), topk)
     M, inv = T * topk, r.pairs.long()
+    ws = torch.full((M * (N + K),), -777.0, dtype=torch.float32, device="cuda")
 
     def grouped(rows, **kw):
         if fmt != q.QARL_W4A16_G128:
@@ -504,18 +509,34 @@ def test_routed_mode_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, T,
     kw = dict(epilogue=q.QARL_EPI_COMBINE, combine_w=r.w)
     for dt in (q.QARL_OUT_F32, q.QARL_OUT_BF16):
         for per_token, rows, ordered in ((False, xp, xp[inv]), (True, x, x[r.tokens.long()])):
-            got = q.qarl_qgemm_routed(qw, rows, r.ids, T, topk, per_token, out_dtype=dt, **kw)
+            got = q.qarl_qgemm_routed(qw, rows, r.ids, T, topk, per_token, out_dtype=dt, ws=ws, **kw)
             assert torch.equal(got, grouped(ordered.contiguous(), sorted_pairs=r.pairs, T=T, topk=topk, out_dtype=dt, **kw))
+    assert not fused or bool((ws == -777.0).all())   # no staging rows: the kernel for few pairs ran
 
 
-@pytest.mark.parametrize("fmt_name", ["fp8", "w4a8"])
-def test_routed_mode_rows_outside_the_fast_division_range(q, oracle, fmt_name):
+# Shapes whose combine runs on the kernels for few pairs (asserted), where these can go wrong.  int4: one pair, several units
+# of columns per workgroup with a remainder, the most pairs, a chunk of x beyond the registers and more than 64 KiB of LDS (16
+# slots).  FP8 / FP4: rows of more than four chunks per lane, a second pass over the slots and more than 64 KiB of LDS.
+_FUSED = ([(f,) + sh for f in ("w4a16", "w4a8") for sh in ((64, 32, 256, 1, 1), (64, 2080, 768, 16, 4), (64, 544, 768, 8, 8),
+                                                           (64, 4096, 2048, 1, 16))] +
+          [(f,) + sh for f in ("fp8", "fp4") for sh in ((64, 32, 256, 1, 1), (64, 1056, 1024, 3, 8), (64, 96, 3968, 3, 8),
+                                                        (128, 1056, 512, 15, 4), (64, 2048, 4096, 1, 16))])
+
+
+@pytest.mark.parametrize("fmt_name,E,N,K,T,topk", _FUSED)
+def test_fused_combine_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, T, topk):
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    _few_pairs_case(q, fmt, synth.normal_bf16((E, N, K), 0.02, seed=K + T, device="cuda"), T, topk, True)
+
+
+@pytest.mark.parametrize("fmt_name,T", [("fp8", 40), ("w4a8", 40), ("fp8", 8), ("w4a8", 8), ("fp4", 8)])   # 80 and 16 pairs
+def test_routed_mode_rows_outside_the_fast_division_range(q, oracle, fmt_name, T):
     """Rows whose scale leaves the range of the corrected-reciprocal division (absmax near 2^-100 and near 2^100),
     a zero row, negative zeros and a row of one repeated value: the kernel that quantizes its own rows must fall back
     to the IEEE division exactly where the row quantizer does, so routed and grouped results stay bit-identical, and
     the codes the grouped path consumed are the oracle's."""
-    fmt = q.QARL_FP8_E4M3_CH if fmt_name == "fp8" else q.QARL_W4A8_G128
-    E, N, K, T, topk = 4, 64, 512, 40, 2
+    fmt = {"fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    E, N, K, topk = 4, 64, 512, 2
     w = synth.normal_bf16((E, N, K), 0.02, seed=1901)
     x = synth.normal_bf16((T, K), 1.0, seed=1902).float()
     x[0] *= 2.0 ** -110
@@ -583,10 +604,12 @@ def test_layer_is_reproducible_run_to_run(q, path):
         assert torch.equal(first.view(torch.int16), again.view(torch.int16))
 
 
-def test_routed_mode_ids_outside_the_expert_range_leave_their_rows_alone(q, oracle):
+@pytest.mark.parametrize("fmt_name,T", [(f, T) for f in ("w4a16", "w4a8", "fp8", "fp4") for T in (20, 200)])   # few pairs and many
+def test_routed_mode_ids_outside_the_expert_range_leave_their_rows_alone(q, oracle, fmt_name, T):
     """Pairs whose id is not an expert (negative, >= E) select no weight matrix: their output rows keep what the
     buffer held, every other row is unaffected."""
-    E, N, K, T, topk = 4, 64, 256, 20, 2
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    E, N, K, topk = 4, 64, 256, 2
     w = synth.normal_bf16((E, N, K), 0.02, seed=31)
     x = synth.normal_bf16((T, K), 1.0, seed=32)
     rng = np.random.default_rng(33)
@@ -594,7 +617,7 @@ def test_routed_mode_ids_outside_the_expert_range_leave_their_rows_alone(q, orac
     ids[:, 1] = (ids[:, 0] + 1) % E                               # a token lists an expert at most once
     good = ids.copy()
     ids[2, 0], ids[7, 1], ids[19, 1] = -1, E, 1000
-    qw = q.qarl_quantize_weights(w.cuda())
+    qw = q.qarl_quantize_weights(w.cuda(), fmt)
     M = T * topk
     y = torch.full((M, N), -777.0, dtype=torch.float32, device="cuda")
     q.qarl_qgemm_routed(qw, x.cuda(), _i32(ids.reshape(-1)), T, topk, True, out=y, out_dtype=q.QARL_OUT_F32)
