@@ -314,7 +314,6 @@ __device__ __forceinline__ void wait_vmcnt_uniform(int n)
     case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
     case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
     case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
-    case 12: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
     default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
     }
 }
@@ -547,10 +546,9 @@ int launch_logprob_stream(LogprobStreamParams p, const int32_t *target, float *l
 {
     // one workgroup per CU, but no more partials per token than the workspace of the tiled kernel holds
     const int64_t units = ((int64_t)p.V + 7) / 8;
-    const int64_t max_units = 32;
-        const int tok = p.T <= 32 ? 32 : p.T <= 64 ? 64 : 128;
+    const int tok = p.T <= 32 ? 32 : p.T <= 64 ? 64 : 128;
     p.n_ranges = (int)min((int64_t)256, ((int64_t)p.V + kLTile - 1) / kLTile);
-    p.passes = (int)((units + (int64_t)p.n_ranges * max_units - 1) / ((int64_t)p.n_ranges * max_units));
+    p.passes = (int)((units + (int64_t)p.n_ranges * 32 - 1) / ((int64_t)p.n_ranges * 32));   // at most 32 units per tile
     p.rows8 = (int)((units + (int64_t)p.n_ranges * p.passes - 1) / ((int64_t)p.n_ranges * p.passes));
     p.pmax = (float *)ws;
     p.psum = p.pmax + (size_t)p.n_ranges * p.T;

@@ -13,9 +13,11 @@
 // In a slice of 8 k per lane the operand reads and the expansion of the next slice are spread between the four matrix
 // instructions of this one.  (Eight wavefronts of 64 x 32 with the codes in registers, operand reads twice as many per
 // matrix instruction, ran 2 % slower.)  A workgroup computes up to four neighbouring column blocks one after the other: the
-// expert lookup and the row gather are paid once, and the next block's first stage travels during the epilogue.  A
-// W4A16 layer of 16384 tokens with popular experts takes 1570 us with four blocks, 1585 with two, 1640 with one,
-// 1690 with all six / eight (fewer workgroups share a token tile in L2) and took 1670 with the wavefronts of 64 x 32.
+// expert lookup and the row gather are paid once, and the next block's first stage travels during the epilogue.  In
+// turn on one box a W4A16 layer of 16384 tokens with popular experts took 1570 us with four blocks, 1585 with two, 1640 with
+// one, 1690 with all six / eight (fewer workgroups share a token tile in L2), and 1670 with the wavefronts of 64 x 32; boxes
+// differ by several per cent (1570 to 1610 us).  Against those wavefronts a launch of one round or less is up to 1 us longer
+// (one wavefront per SIMD where there were two), and launches of two scale groups up to 15 %.
 //
 // What bounds it: 0.825 TFLOP of gate_up in 0.82-0.93 ms, about 0.95 PFLOP/s, where nothing but the matrix instructions of
 // this shape runs at 1.35; next to them a stage issues 6 VALU operations per matrix instruction (expansion 3.5, fold 2).

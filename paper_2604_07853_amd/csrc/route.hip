@@ -66,7 +66,7 @@ __device__ __forceinline__ float wave_sum_f32_dpp(float v)
 // PER: 64-expert groups, logits per lane (E = 192 takes the kernel of four).  Bound by issue: a round of the selection is
 // the arg-max reduction and little else.  The winning keys are kept, one per lane (a key holds both the logit and the id),
 // and the probabilities are formed behind the rounds, all at once.  128 experts, top-8: 16384 tokens 20.2 -> 11.0 us with
-// an exponential and a division in every round and four logits per lane before; a decode layer is 1 us shorter.
+// an exponential and a division in every round and four logits per lane before.
 template <int PER>
 __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(const uint16_t *__restrict__ logits, int T,
                                                                   int E, int topk, int renorm,
@@ -127,8 +127,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(const uint16_
 // them in ascending pair order, which keeps (t, slot) order: a pair's rank in a step comes from four ballots.  The bits of
 // the first four batches (131072 pairs of a workgroup) stay in registers, later ones are read again (cache hits).
 // Bound by the VALU work of the sweep, four operations per pair and expert (a comparison that adds its carry takes as
-// many and two wait states).  8192 and 16384 tokens, top-8 of 128: 11.4 us at the median, where a counting kernel
-// with one counter per expert and two sweeps with prefix sums by shuffles took 4.5 + 22.8.
+// many and two wait states).  Top-8 of 128: 11.5 us at 8192 tokens and 17.8 at 16384 (medians), where a counting kernel
+// with one counter per expert and two sweeps with prefix sums by shuffles took 4.5 + 22.8 at 16384.
 constexpr int kGroupThreads = 1024;
 constexpr int kGroupWaves = kGroupThreads / 64;
 constexpr int kGroupStep = 256;               // pairs per wavefront and step: four consecutive ones per lane
