@@ -419,11 +419,13 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
         set_error("qarl_qgemm_routed: COMBINE needs combine_w");
         return QARL_ERR_INVALID_ARG;
     }
-    // The kernels for few pairs write the combined rows while other workgroups still read x and the ids; the staged path
-    // writes them in a launch of its own, so a caller may put out on top of either.
-    const size_t comb_bytes = epilogue == QARL_EPI_COMBINE ? (size_t)T * W->N * (a.out_f32 ? 4 : 2) : 0;
-    const bool over_ids = comb_bytes && ranges_overlap(out, comb_bytes, topk_ids, (size_t)M * 4);
-    const bool in_place = over_ids || (comb_bytes && ranges_overlap(out, comb_bytes, x, (size_t)a.x_rows * W->K * 2));
+    // The kernels for few pairs write results while other workgroups still read x and the ids.  A combined row is written in a
+    // launch of its own on the staged path, so a caller may put out on top of either; and a row of the other epilogues is
+    // written there by the workgroup that has read it, where an expert has one slice (256 experts, or N <= 256).
+    const bool comb = epilogue == QARL_EPI_COMBINE;
+    const size_t out_bytes = (size_t)(comb ? T : M) * (epilogue == QARL_EPI_SILU_MUL ? W->N / 2 : W->N) * (a.out_f32 ? 4 : 2);
+    const bool over_ids = ranges_overlap(out, out_bytes, topk_ids, (size_t)M * 4);
+    const bool in_place = over_ids || ranges_overlap(out, out_bytes, x, (size_t)a.x_rows * W->K * 2);
     // They read the weights of every pair by themselves: with few experts, or many columns, the streaming kernels are faster
     // from a handful of pairs on.
     const bool int4 = int4_weights(W->fmt);
@@ -432,11 +434,11 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
         const double small_us = int4 ? qgemm_small_w4_us(W->fmt, W->N, W->K, T, topk, epilogue)
                                      : qgemm_small_fp8_us(W->fmt, W->N, W->K, T, topk, epilogue);
         if (small_us <= qgemm_stream_routed_us(W->fmt, W->N, W->K, W->E, T, topk, epilogue)) {
-            const float *cw = epilogue == QARL_EPI_COMBINE ? combine_w : nullptr;
+            const float *cw = comb ? combine_w : nullptr;
             return int4 ? launch_qgemm_small_w4(a, cw, st) : launch_qgemm_small_fp8(a, cw, st);
         }
     }
-    if (epilogue == QARL_EPI_COMBINE) {
+    if (comb) {
         a.epilogue = QARL_EPI_NONE;
         a.out = ws;
         a.out_f32 = 1;
@@ -447,7 +449,7 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
     }
     rc = launch_qgemm_stream(a, st);
     if (rc) return rc;
-    if (epilogue == QARL_EPI_COMBINE)
+    if (comb)
         return launch_combine((const float *)ws, combine_w, over_ids ? nullptr : topk_ids, W->E, T, topk, W->N, out,
                               out_dtype == QARL_OUT_F32, st);
     return QARL_OK;

@@ -651,6 +651,22 @@ def test_routed_combine_written_over_its_own_input(q, fmt_name):
     assert torch.equal(over_ids, want)
 
 
+@pytest.mark.parametrize("fmt_name,T", [(f, T) for f in ("w4a16", "w4a8", "fp8", "fp4") for T in (3, 200)])   # few pairs and many
+def test_routed_rows_written_over_their_own_input(q, fmt_name, T):
+    """256 experts: an expert's rows are read and written by one workgroup, so the rows of the plain and of the SiLU*mul epilogue
+    may replace the rows of x they come from (as wide as these in bf16)."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    E, K, topk = 256, 512, 8
+    ids = q.qarl_moe_route(synth.router_logits(T, E, 91).cuda(), topk).ids
+    x = synth.normal_bf16((T * topk, K), 1.0, seed=92).cuda()
+    for N, epi in ((K, q.QARL_EPI_NONE), (2 * K, q.QARL_EPI_SILU_MUL)):
+        qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=93).cuda(), fmt)
+        want = q.qarl_qgemm_routed(qw, x, ids, T, topk, False, epilogue=epi)
+        over = x.clone()
+        q.qarl_qgemm_routed(qw, over, ids, T, topk, False, epilogue=epi, out=over)
+        assert torch.equal(over, want)
+
+
 @pytest.mark.parametrize("fmt_name,T", [(f, T) for f in ("w4a16", "w4a8", "fp8", "fp4") for T in (8, 200)])
 def test_routed_combine_counts_ids_outside_the_expert_range_as_zeros(q, fmt_name, T):
     """Few and many pairs, whatever the workspace and the weights of such slots hold, also with out on top of the ids: the
