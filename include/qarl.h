@@ -196,7 +196,7 @@ int qarl_grouped_dw(const void *dy_bf16, const void *x_bf16, const int32_t *row_
  * quantizer of eq. (2) to the rows it gathers (s_x = absmax / 448 per row, e4m3 codes of x / s_x: the arithmetic
  * of qarl_quantize_rows_fp8), so a decode step has no separate quantizer launch for x or for the intermediate.
  * Results equal those of qarl_qgemm_grouped on the DECODE path with the grouping of the same ids (after
- * qarl_quantize_rows_fp8 for the e4m3-activation formats), bit for bit (same kernels, same order of operations per row).
+ * qarl_quantize_rows_fp8 for the e4m3-activation formats), bit for bit (same operations in the same order per row).
  * Supported: W4A16_G128 and W4A8_G128 (N % 32 == 0, K % 256 == 0, K <= 2048), FP8_E4M3_CH and FP4_E2M1_CH (N % 32 == 0,
  * K % 128 == 0, K <= 4096); T <= 512, T*topk <= 4096, a token listing an expert at most once (as the router's
  * output does; rows past 512 of one expert would be dropped); ids outside [0, E) select no expert and leave their
