@@ -45,11 +45,20 @@ __device__ __forceinline__ float silu_mul_f32(float g, float u)
     return g * __builtin_amdgcn_rcpf(1.f + t) * u;
 }
 
+// Largest value of the wavefront (all lanes active), the same in every lane: row shifts and two row broadcasts bring it to
+// lane 63 (six dependent VALU operations; six LDS permutes took the routed quantizers' start-up about 0.3 us).
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+#define QARL_MAX_STEP(CTRL, ROWS) \
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false)))
+    QARL_MAX_STEP(0x111, 0xf);   // row_shr:1
+    QARL_MAX_STEP(0x112, 0xf);   // row_shr:2
+    QARL_MAX_STEP(0x114, 0xf);   // row_shr:4
+    QARL_MAX_STEP(0x118, 0xf);   // row_shr:8
+    QARL_MAX_STEP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    QARL_MAX_STEP(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef QARL_MAX_STEP
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 __device__ __forceinline__ float wave_sum(float v)
@@ -67,18 +76,35 @@ __device__ __forceinline__ float wave_sum(float v)
 // way, hence the guard on s; below 2^-11 a quotient may differ from the IEEE one, where every value rounds
 // to an e4m3 zero; the sign is copied from x, as s > 0).  Checked against the IEEE divide for all 65536 bf16
 // values of x and 2^20 scales (the quantizer's own absmax / alpha and random ones): no difference at |x / s| >= 2^-11.
+// The scale is the same in all lanes (a wavefront reduction formed it) and is held as such, so that which of the two divisions a row
+// takes is one scalar branch per eight elements (a lane mask and a branch per element before: in the routed FP8 gate_up
+// launch of 256 tokens, 32 k elements per workgroup, 285 branches).
 struct RowScale {
     float s, y;
     bool fast;
-    __device__ __forceinline__ explicit RowScale(float s_) : s(s_), y(1.0f / s_)
+    __device__ __forceinline__ explicit RowScale(float s_) : s(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s_)))), y(1.0f / s)
     {
-        fast = s_ >= 0x1p-100f && s_ < 0x1p100f && (__float_as_uint(s_) & 0x7fffffu) != 0x7fffffu;
+        fast = s >= 0x1p-100f && s < 0x1p100f && (__float_as_uint(s) & 0x7fffffu) != 0x7fffffu;
     }
-    __device__ __forceinline__ float div(float x) const
+    // x / s of eight bf16 values held in four dwords
+    __device__ __forceinline__ void div8(u32x4 v, float (&t)[8]) const
     {
-        if (!fast) return x / s;
-        const float q0 = x * y;
-        return copysignf(fmaf(fmaf(-q0, s, x), y, q0), x);   // the sign of x also where the steps end in +0 (x = -0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = v[i];
+            t[2 * i] = __uint_as_float(w << 16);
+            t[2 * i + 1] = __uint_as_float(w & 0xffff0000u);
+        }
+        if (fast) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = t[i], q0 = x * y;
+                t[i] = copysignf(fmaf(fmaf(-q0, s, x), y, q0), x);   // the sign of x also where the steps end in +0 (x = -0)
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = t[i] / s;
+        }
     }
 };
 
@@ -111,11 +137,9 @@ __device__ __forceinline__ u32x2 e4m3_quantize_bf16x8(const RowScale &rs, u32x4 
     u32x2 o = {0, 0};
     if (rs.s != 0.f) {
         float t[8];
+        rs.div8(v, t);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            t[2 * i] = __builtin_amdgcn_fmed3f(rs.div(__uint_as_float(v[i] << 16)), -448.f, 448.f);
-            t[2 * i + 1] = __builtin_amdgcn_fmed3f(rs.div(__uint_as_float(v[i] & 0xffff0000u)), -448.f, 448.f);
-        }
+        for (int i = 0; i < 8; ++i) t[i] = __builtin_amdgcn_fmed3f(t[i], -448.f, 448.f);
         int w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[0], t[1], 0, false);
         w0 = __builtin_amdgcn_cvt_pk_fp8_f32(t[2], t[3], w0, true);
         int w1 = __builtin_amdgcn_cvt_pk_fp8_f32(t[4], t[5], 0, false);

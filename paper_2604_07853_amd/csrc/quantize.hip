@@ -139,11 +139,7 @@ __device__ __forceinline__ void store_codes_bf16x8(uint8_t *codes, int64_t row, 
             // boundaries) on every boundary, its two neighbours, zeros of both signs, tiny and huge values and 2^16
             // random ones on gfx950: identical.
             float t[8];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                t[2 * i] = rs.div(__uint_as_float(v[i] << 16));
-                t[2 * i + 1] = rs.div(__uint_as_float(v[i] & 0xffff0000u));
-            }
+            rs.div8(v, t);
             w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[0], t[4], 1.0f, 0);
             w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[1], t[5], 1.0f, 1);
             w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, t[2], t[6], 1.0f, 2);
