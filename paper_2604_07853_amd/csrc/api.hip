@@ -447,6 +447,7 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
             if (rc) return rc;
         }
     }
+    a.spread = comb || !in_place;   // the staging rows of COMBINE overlap nothing
     rc = launch_qgemm_stream(a, st);
     if (rc) return rc;
     if (comb)

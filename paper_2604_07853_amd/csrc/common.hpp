@@ -341,6 +341,7 @@ struct GemmArgs {
     const int32_t *ids = nullptr;
     int topk = 0;
     int x_per_token = 0;
+    int spread = 0;     // routed mode: a popular expert's rows may be worked on by any workgroup (out overlaps neither x nor ids)
 };
 int launch_qgemm_stream(const GemmArgs &a, hipStream_t s);
 bool qgemm_stream_supported(int fmt, int N, int K);

@@ -15,7 +15,9 @@
 //
 // Experts with more than 16*MT rows: the grid carries m_split row blocks per (expert,
 // slice), mapped to consecutive workgroups of the same XCD so that their identical weight
-// reads meet in that XCD's L2; rows beyond 16*MT*m_split take further passes.
+// reads meet in that XCD's L2; rows beyond 16*MT*m_split take further passes, or, in the
+// routed mode, are dealt to the workgroups without rows and those of the popular experts
+// (routed_rows.hpp).
 //
 // Routed mode (QX): the kernel is driven by the router's ids and by 16-bit activations.  Every
 // workgroup lists its expert's (token, slot) pairs itself and quantizes the token rows it
@@ -29,7 +31,7 @@
 
 #include <algorithm>
 
-#include "common.hpp"
+#include "routed_rows.hpp"
 
 namespace qarl {
 
@@ -56,10 +58,8 @@ struct StreamParams {
     // or the pair id, output row = pair id
     const int32_t *ids;
     int n_ids, topk, x_per_token;
+    int spread;      // row blocks beyond the grid's are dealt out (spread_item)
 };
-
-constexpr int kIdsMax = 4096;    // pairs a workgroup scans (8 per thread)
-constexpr int kIdsRows = 512;    // rows of one expert it can list: one per token, T <= 512
 
 // LDS bytes per activation row: the row plus 16 bytes, so consecutive rows skew by 4 banks.
 __host__ __device__ constexpr int x_stride(int K) { return K + 16; }
@@ -68,29 +68,32 @@ __host__ __device__ constexpr int x_stride(int K) { return K + 16; }
 size_t stream_lds_bytes(int K, int MT, bool routed = false)
 {
     const size_t rows = (size_t)MT * 16;
-    return rows * 12 + 16 + rows * x_stride(K) + (routed ? 8 * (size_t)kIdsRows + 4 * kSWaves : 0);
+    return rows * 12 + 16 + rows * x_stride(K) + (routed ? (size_t)kIdsBytes : 0);
 }
 
 // EPI: NONE or SILU_MUL; MT: 16-row token tiles per block; R: ring depth in 128-k steps (must divide K/128);
-// W4: the weights are packed e2m1 codes (half a byte per weight) instead of e4m3 bytes; QX: routed mode.
-template <int EPI, int MT, int R, bool W4, bool QX>
-__global__ __launch_bounds__(kSThreads, 1) void qgemm_stream_fp8_kernel(StreamParams p)
+// W4: the weights are packed e2m1 codes (half a byte per weight) instead of e4m3 bytes; QX: routed mode;
+// SPREAD (with QX): the row blocks beyond the grid's are dealt out (spread_item) instead of being further passes.
+// TAIL: the shares of popular experts, after the workgroup's own row block; returns whether to go on with them.
+template <int EPI, int MT, int R, bool W4, bool QX, bool SPREAD, bool TAIL>
+__device__ __forceinline__ bool stream_fp8_body(const StreamParams &p, int tid, unsigned bid)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int kRowsMax = MT * 16;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, q = lane >> 4;
     const int N = p.N, K = p.K, G = K / kGroup;
     const int stride = x_stride(K);
 
     // workgroup id -> (expert, slice, row block).  Ids go round-robin over the 8 XCDs; the row
     // blocks of one (expert, slice) take consecutive positions on the same XCD.
-    const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+    const int xcd = (int)(bid & 7), pos = (int)(bid >> 3);
     const int mh = pos % p.m_split;
     const int unit_id = (pos / p.m_split) * 8 + xcd;
-    if (unit_id >= p.E * p.n_slices) return;
-    const int e = unit_id / p.n_slices, slice = unit_id % p.n_slices;
+    if (unit_id >= p.E * p.n_slices) return false;
+    int e = unit_id / p.n_slices;
+    const int slice = unit_id % p.n_slices;
 
     int *s_row = (int *)smem;                              // [kRowsMax] activation row of each tile row
     int *s_orow = (int *)(smem + kRowsMax * 4);            // [kRowsMax] output row, -1 past the expert's last row
@@ -100,10 +103,9 @@ __global__ __launch_bounds__(kSThreads, 1) void qgemm_stream_fp8_kernel(StreamPa
 
     // this workgroup's pairs of weight tiles: units u_lo .. u_hi-1
     const int per_slice = (p.n_units + p.n_slices - 1) / p.n_slices;
-    const int u_lo = slice * per_slice, u_hi = min(p.n_units, u_lo + per_slice);
-    const int n_pairs = max(0, u_hi - u_lo);  // pairs of this workgroup; wavefronts draw them from an LDS counter
+    int u_lo = slice * per_slice, n_pairs = max(0, min(p.n_units, u_lo + per_slice) - u_lo);  // pairs of this workgroup; wavefronts draw them from an LDS counter
     const int words_per_row = W4 ? K / 8 : K / 4;
-    const int64_t ebase = (int64_t)e * N;
+    int64_t ebase = (int64_t)e * N;
 
     auto tile_row = [&](int pi, int nt) -> int {  // weight row of this lane in tile nt of the slice's pi-th pair
         const int u = u_lo + pi;
@@ -144,57 +146,14 @@ __global__ __launch_bounds__(kSThreads, 1) void qgemm_stream_fp8_kernel(StreamPa
     int row0, Me;
     int *tmp_map = (int *)(xs + kRowsMax * stride);   // routed mode: [kIdsRows] activation rows, [kIdsRows] pair ids, [kSWaves] counts
     if (QX) {
-        // Thread tid looks at pairs 8 tid .. 8 tid + 7.  Matches keep their order: the rows of an expert are its
-        // pairs by increasing pair id, the (token, slot) order a stable grouping gives.
-        const int base = tid * 8;
-        uint32_t hits = 0;
-#pragma unroll
-        for (int q4 = 0; q4 < 2; ++q4) {
-            const int b4 = base + 4 * q4;
-            i32x4 v4 = {-1, -1, -1, -1};
-            if (b4 + 3 < p.n_ids) {
-                v4 = *(const i32x4 *)(p.ids + b4);
-            } else {
-                for (int k = 0; b4 + k < p.n_ids; ++k) v4[k] = p.ids[b4 + k];
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) hits |= (v4[k] == e) ? (1u << (4 * q4 + k)) : 0u;
-        }
-        const int cnt = __popc(hits);
-        int incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int *s_wcnt = tmp_map + 2 * kIdsRows;
-        if (lane == 63) s_wcnt[wave] = incl;
-        lds_barrier();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kSWaves; ++w) {
-            const int cw = s_wcnt[w];
-            before += w < wave ? cw : 0;
-            total += cw;
-        }
-        int rank = before + incl - cnt;
-        for (uint32_t hm = hits; hm; hm &= hm - 1) {
-            const int pr = base + __builtin_ctz(hm);
-            if (rank < kIdsRows) {
-                tmp_map[rank] = p.x_per_token ? pr / p.topk : pr;
-                tmp_map[kIdsRows + rank] = pr;
-            }
-            ++rank;
-        }
-        row0 = 0;
-        Me = min(total, kIdsRows);
+        row0 = Me = 0;
+        if (!TAIL) Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
     } else {
         row0 = p.offsets[e];
         Me = p.offsets[e + 1] - row0;
     }
-    if (Me <= mh * kRowsMax) return;
-
-    for (int m0 = mh * kRowsMax; m0 < Me; m0 += kRowsMax * p.m_split) {
+    // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + n_pairs - 1
+    auto run_block = [&](int m0) __attribute__((always_inline)) {
         const int mrem = min(kRowsMax, Me - m0);
         lds_barrier();  // the pair list is complete / the previous pass is done with the LDS tile
         if (tid < kRowsMax) {
@@ -361,19 +320,57 @@ __global__ __launch_bounds__(kSThreads, 1) void qgemm_stream_fp8_kernel(StreamPa
             }
             pi = npi;
         }
+    };
+    if constexpr (!SPREAD) {
+        for (int m0 = mh * kRowsMax; m0 < Me; m0 += kRowsMax * p.m_split) run_block(m0);
+        return false;
+    } else if constexpr (!TAIL) {
+        if (mh * kRowsMax < Me) run_block(mh * kRowsMax);
+        return mh * kRowsMax >= Me || Me > p.m_split * kRowsMax;   // no row of its own, or a popular expert
+    } else {
+        // shares of the row blocks beyond the grid's, in halves of a slice
+        constexpr int kSubs = 2;
+        const int e_own = e, half = (per_slice + 1) / kSubs;
+        int *s_hist = tmp_map + 2 * kIdsRows + kListWaves;
+        count_rows(p.ids, p.n_ids, p.E, s_hist);
+        SpreadItem it;
+#pragma unroll 1
+        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 4 : 5, p.m_split, p.n_slices, kSubs, e_own, mh, slice, k, it); ++k) {
+            e = it.e;
+            ebase = (int64_t)e * N;
+            const int sl = it.sub / kSubs;
+            u_lo = sl * per_slice + (it.sub % kSubs) * half;
+            n_pairs = max(0, min(min(p.n_units, (sl + 1) * per_slice), u_lo + it.n_sub * half) - u_lo);
+            lds_barrier();   // the previous block is done with the list
+            Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
+            if (it.block * kRowsMax < Me) run_block(it.block * kRowsMax);
+        }
+        return false;
     }
 }
 
-template <int EPI, int MT, int R, bool W4, bool QX>
+template <int EPI, int MT, int R, bool W4, bool QX, bool SPREAD>
+__global__ __launch_bounds__(kSThreads, 1) void qgemm_stream_fp8_kernel(StreamParams p)
+{
+    if (!stream_fp8_body<EPI, MT, R, W4, QX, SPREAD, false>(p, threadIdx.x, blockIdx.x)) return;
+    if constexpr (SPREAD) {
+        const FreshArgs<StreamParams> f;
+        stream_fp8_body<EPI, MT, R, W4, QX, SPREAD, true>(f.p, f.tid, f.bid);
+    }
+}
+
+template <int EPI, int MT, int R, bool W4, bool QX, bool SPREAD = false>
 int launch_cfg_w(const StreamParams &p, hipStream_t s)
 {
+    if constexpr (QX && !SPREAD)
+        if (p.spread) return launch_cfg_w<EPI, MT, R, W4, QX, true>(p, s);
     const size_t lds = stream_lds_bytes(p.K, MT, QX);
     if (lds > 160 * 1024) {
         set_error("qgemm (decode path): K=%d needs %zu bytes of LDS per workgroup, more than the 160 KiB of a CU", p.K, lds);
         return QARL_ERR_UNSUPPORTED;
     }
     static LdsLimitOnce once;
-    auto kern = qgemm_stream_fp8_kernel<EPI, MT, R, W4, QX>;
+    auto kern = qgemm_stream_fp8_kernel<EPI, MT, R, W4, QX, SPREAD>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(stream fp8)")) return rc;
     const int64_t units = (int64_t)p.E * p.n_slices;
     const int64_t grid = ((units + 7) / 8) * 8 * p.m_split;
@@ -460,6 +457,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     }
     p.m_split = g.m_split;
     p.n_slices = g.n_slices;
+    p.spread = spread_blocks(a, 16 * g.MT * g.m_split);
     if (g.MT == 1) return launch_ring<EPI, 1>(p, s);
     return launch_ring<EPI, 2>(p, s);
 }

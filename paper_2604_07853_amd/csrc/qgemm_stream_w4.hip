@@ -32,10 +32,13 @@
 //
 // Experts with more than 32*MT rows: the grid carries row blocks per (expert, slice), mapped to
 // consecutive workgroups of the same XCD so that their identical weight reads meet in that
-// XCD's L2; rows beyond that take further passes.
+// XCD's L2; rows beyond that take further passes, or, in the routed mode, are dealt to the
+// workgroups without rows and those of the popular experts (routed_rows.hpp).
 #include <math.h>
 
-#include "common.hpp"
+#include <type_traits>
+
+#include "routed_rows.hpp"
 
 namespace qarl {
 
@@ -76,11 +79,9 @@ struct W4Params {
     // gathers (the row quantizer's arithmetic), keeps the e4m3 values as exact bf16 in the LDS tile and the row
     // scales in LDS for the epilogue.
     int qx;
+    int spread;        // row blocks beyond the grid's are dealt out (spread_item)
 };
 constexpr int kQxScaleBytes = 4 * 64;   // LDS for the row scales of a block (up to 64 rows), routed mode
-
-constexpr int kIdsMax = 4096;    // pairs a workgroup scans (8 per thread)
-constexpr int kIdsRows = 512;    // rows of one expert it can list: one per token, T <= 512
 
 // LDS bytes per activation row: the row plus 16 bytes, so consecutive rows skew by 4 banks.
 __host__ __device__ constexpr int x_stride(int K) { return K * 2 + 16; }
@@ -100,8 +101,10 @@ size_t lds_bytes(int K, int MT, bool half = false)
 // HALF (with MT = 1): the LDS tile holds 16 token rows instead of 32, which is what fits for K up to 4096 (the
 // hidden size of the dense models); the matrix instruction still takes 32 rows, its rows 16..31 re-read rows 0..15
 // and their results are dropped.
-template <int EPI, int MT, int R, bool NT, bool HALF = false>
-__global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p)
+// SPREAD: routed mode, the row blocks beyond the grid's are dealt out (spread_item); else they are further passes.
+// TAIL: the shares of popular experts, after the workgroup's own row block; returns whether to go on with them.
+template <int EPI, int MT, int R, bool NT, bool HALF, bool SPREAD, bool TAIL>
+__device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsigned bid)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     static_assert(!HALF || MT == 1, "the 16-row tile goes with one 32-row MFMA tile");
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
     constexpr int kScBufs = HALF ? 1 : 2;        // scale buffers per wavefront
     constexpr bool kSilu = (EPI == QARL_EPI_SILU_MUL);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     // lane -> column 16 t + c of the pair's 32 weight rows, half h of every 16-k MFMA step
     const int c = lane & 15, t = (lane >> 4) & 1, h = lane >> 5, m32 = lane & 31;
     const int N = p.N, K = p.K, G = K / kGroup;
@@ -118,12 +121,13 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
 
     // workgroup id -> (expert, slice, row block).  Ids go round-robin over the 8 XCDs; the row
     // blocks of one (expert, slice) take consecutive positions on the same XCD.
-    const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+    const int xcd = (int)(bid & 7), pos = (int)(bid >> 3);
     const int m_split = 1 << p.msplit_sh;
     const int mh = pos & (m_split - 1);
     const int unit_id = (pos >> p.msplit_sh) * 8 + xcd;
-    if (unit_id >= (p.E << p.slice_sh)) return;
-    const int e = unit_id >> p.slice_sh, slice = unit_id & ((1 << p.slice_sh) - 1);
+    if (unit_id >= (p.E << p.slice_sh)) return false;
+    int e = unit_id >> p.slice_sh;
+    const int slice = unit_id & ((1 << p.slice_sh) - 1);
 
     int *s_row = (int *)smem;                              // [kIdx] activation row of each tile row (rows past the end repeat the last one)
     int *s_orow = (int *)(smem + kIdx * 4);                // [kIdx] output row, -1 past the expert's last row
@@ -136,9 +140,8 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
     unsigned char *xs = smem + kIdx * 8 + 16 + G * kRows * 4 + kWaves * kScBufs * 32 * G * 2;  // [kRows][stride]
 
     // this workgroup's pairs of weight tiles: units u_lo .. u_hi-1
-    const int u_lo = slice * p.per_slice, u_hi = min(p.n_units, u_lo + p.per_slice);
-    const int n_pairs = max(0, u_hi - u_lo);
-    const int64_t ebase = (int64_t)e * N;
+    int u_lo = slice * p.per_slice, n_pairs = max(0, min(p.n_units, u_lo + p.per_slice) - u_lo);
+    int64_t ebase = (int64_t)e * N;
 
     // 16-row tile of this lane (its half t of the 32 MFMA columns) in the slice's pi-th pair
     auto pair_tile16 = [&](int pi) -> int {
@@ -205,56 +208,11 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
     // this expert's pairs, [kIdsRows] pair ids, then the pair count of every wavefront's share of the ids
     int *tmp_map = (int *)(p.map_mode == 2 ? xs + kRows * stride : xs);
     const int m4 = routed ? kIdsRows : (p.M + 3) & ~3;
-    float *s_rsc = (float *)(xs + kRows * stride + 8 * kIdsRows + 4 * kWaves);   // [kIdx] row scales (routed W4A8)
+    float *s_rsc = (float *)(xs + kRows * stride + kIdsBytes);   // [kIdx] row scales (routed W4A8)
     int row0, Me;
     if (routed) {
-        // Thread tid looks at pairs 8 tid .. 8 tid + 7.  Matches keep their order: the rows of an expert are its
-        // pairs by increasing pair id, the (token, slot) order a stable grouping gives.
-        const int base = tid * 8;
-        int idv[8];
-#pragma unroll
-        for (int q4 = 0; q4 < 2; ++q4) {
-            const int b4 = base + 4 * q4;
-            i32x4 v4 = {-1, -1, -1, -1};
-            if (b4 + 3 < p.n_ids) {
-                v4 = *(const i32x4 *)(p.ids + b4);
-            } else {
-                for (int k = 0; b4 + k < p.n_ids; ++k) v4[k] = p.ids[b4 + k];
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) idv[4 * q4 + k] = v4[k];
-        }
-        uint32_t hits = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) hits |= (idv[k] == e) ? (1u << k) : 0u;
-        const int cnt = __popc(hits);
-        int incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int *s_wcnt = tmp_map + 2 * kIdsRows;
-        if (lane == 63) s_wcnt[wave] = incl;
-        lds_barrier();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const int cw = s_wcnt[w];
-            before += w < wave ? cw : 0;
-            total += cw;
-        }
-        int rank = before + incl - cnt;
-        for (uint32_t hm = hits; hm; hm &= hm - 1) {
-            const int pr = base + __builtin_ctz(hm);
-            if (rank < kIdsRows) {
-                tmp_map[rank] = p.x_per_token ? pr / p.topk : pr;
-                tmp_map[m4 + rank] = pr;
-            }
-            ++rank;
-        }
-        row0 = 0;
-        Me = min(total, kIdsRows);
+        row0 = Me = 0;
+        if (!TAIL) Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
     } else {
     if (map_in_lds) {
         constexpr int kPer = kMapMax / (4 * kThreads);
@@ -280,10 +238,8 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
     row0 = p.offsets[e];
     Me = p.offsets[e + 1] - row0;
     }
-    if (Me <= mh * kRows) return;
-
-    bool first_pass = true;
-    for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) {
+    // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + n_pairs - 1
+    auto run_block = [&](int m0, bool first_pass) __attribute__((always_inline)) {
         const int mrem = min(kRows, Me - m0);
         lds_barrier();  // the row map copy is complete / the previous pass is done with the LDS tile
         const bool use_tmp = map_in_lds && (first_pass || routed);   // the routed list has its own LDS region
@@ -517,7 +473,46 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
             park_scales((it + 1) & 1);
             pi = npi;
         }
-        first_pass = false;
+    };
+    if constexpr (!SPREAD) {
+        bool first_pass = true;
+        for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) {
+            run_block(m0, first_pass);
+            first_pass = false;
+        }
+        return false;
+    } else if constexpr (!TAIL) {
+        if (mh * kRows < Me) run_block(mh * kRows, true);
+        return mh * kRows >= Me || Me > m_split * kRows;   // no row of its own, or a popular expert
+    } else {
+        // shares of the row blocks beyond the grid's, in halves of a slice
+        constexpr int kSubs = 2;
+        const int e_own = e, half = (p.per_slice + 1) / kSubs;
+        int *s_hist = tmp_map + 2 * kIdsRows + kListWaves;
+        count_rows(p.ids, p.n_ids, p.E, s_hist);
+        SpreadItem it;
+#pragma unroll 1
+        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 5 : 6, m_split, 1 << p.slice_sh, kSubs, e_own, mh, slice, k, it); ++k) {
+            e = it.e;
+            ebase = (int64_t)e * N;
+            const int sl = it.sub / kSubs;
+            u_lo = sl * p.per_slice + (it.sub % kSubs) * half;
+            n_pairs = max(0, min(min(p.n_units, (sl + 1) * p.per_slice), u_lo + it.n_sub * half) - u_lo);
+            lds_barrier();   // the previous block is done with the list
+            Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
+            if (it.block * kRows < Me) run_block(it.block * kRows, false);
+        }
+        return false;
+    }
+}
+
+template <int EPI, int MT, int R, bool NT, bool HALF, bool SPREAD>
+__global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p)
+{
+    if (!stream_w4_body<EPI, MT, R, NT, HALF, SPREAD, false>(p, threadIdx.x, blockIdx.x)) return;
+    if constexpr (SPREAD) {
+        const FreshArgs<W4Params> f;
+        stream_w4_body<EPI, MT, R, NT, HALF, SPREAD, true>(f.p, f.tid, f.bid);
     }
 }
 
@@ -529,23 +524,25 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
 // meet all 64 rows.  The weight ring runs through (chunk, pair, group) without a break; between two chunks the
 // workgroup meets at a barrier and gathers the next K-range of its token rows.  Scales go from global memory
 // straight to the lane that folds them (the 8 groups of a chunk are one 16-byte load).
-template <int EPI, int PW, int NC>
-__global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Params p)
+// SPREAD, TAIL: as above.
+template <int EPI, int PW, int NC, bool SPREAD, bool TAIL>
+__device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, unsigned bid)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int kRows = 64, R = 4, GC = 8;   // rows per block, ring depth, scale groups per chunk
     constexpr bool kSilu = (EPI == QARL_EPI_SILU_MUL);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, t = (lane >> 4) & 1, h = lane >> 5, m32 = lane & 31;
     const int N = p.N, K = p.K, G = K / kGroup, KC = K / NC;
     const int stride = x_stride(KC);
 
-    const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
+    const int xcd = (int)(bid & 7), pos = (int)(bid >> 3);
     const int m_split = 1 << p.msplit_sh;
     const int mh = pos & (m_split - 1);
     const int unit_id = (pos >> p.msplit_sh) * 8 + xcd;
-    if (unit_id >= (p.E << p.slice_sh)) return;
-    const int e = unit_id >> p.slice_sh, slice = unit_id & ((1 << p.slice_sh) - 1);
+    if (unit_id >= (p.E << p.slice_sh)) return false;
+    int e = unit_id >> p.slice_sh;
+    const int slice = unit_id & ((1 << p.slice_sh) - 1);
 
     int *s_row = (int *)smem;                              // [kRows]
     int *s_orow = (int *)(smem + kRows * 4);               // [kRows]
@@ -553,8 +550,8 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
     unsigned char *xs = smem + kRows * 8 + GC * kRows * 4;  // [kRows][stride]
     int *tmp_map = (int *)(xs + kRows * stride);           // routed mode: [kIdsRows] rows, [kIdsRows] pair ids, [kWaves] counts
 
-    const int u_lo = slice * p.per_slice;                  // this workgroup's pairs: u_lo .. u_lo + 8 PW - 1
-    const int64_t ebase = (int64_t)e * N;
+    int u_lo = slice * p.per_slice;                        // this workgroup's pairs: u_lo .. u_lo + 8 PW - 1
+    int64_t ebase = (int64_t)e * N;
     auto pair_tile16 = [&](int pi, int tt) -> int {
         const int u = u_lo + pi;
         if (kSilu) return (tt ? (N / 2) / 16 : 0) + u;
@@ -582,58 +579,15 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
     const bool routed = p.ids != nullptr;
     int row0, Me;
     if (routed) {
-        const int base = tid * 8;
-        int idv[8];
-#pragma unroll
-        for (int q4 = 0; q4 < 2; ++q4) {
-            const int b4 = base + 4 * q4;
-            i32x4 v4 = {-1, -1, -1, -1};
-            if (b4 + 3 < p.n_ids) {
-                v4 = *(const i32x4 *)(p.ids + b4);
-            } else {
-                for (int k = 0; b4 + k < p.n_ids; ++k) v4[k] = p.ids[b4 + k];
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) idv[4 * q4 + k] = v4[k];
-        }
-        uint32_t hits = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) hits |= (idv[k] == e) ? (1u << k) : 0u;
-        const int cnt = __popc(hits);
-        int incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        int *s_wcnt = tmp_map + 2 * kIdsRows;
-        if (lane == 63) s_wcnt[wave] = incl;
-        lds_barrier();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const int cw = s_wcnt[w];
-            before += w < wave ? cw : 0;
-            total += cw;
-        }
-        int rank = before + incl - cnt;
-        for (uint32_t hm = hits; hm; hm &= hm - 1) {
-            const int pr = base + __builtin_ctz(hm);
-            if (rank < kIdsRows) {
-                tmp_map[rank] = p.x_per_token ? pr / p.topk : pr;
-                tmp_map[kIdsRows + rank] = pr;
-            }
-            ++rank;
-        }
-        row0 = 0;
-        Me = min(total, kIdsRows);
+        row0 = Me = 0;
+        if (!TAIL) Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
     } else {
         row0 = p.offsets[e];
         Me = p.offsets[e + 1] - row0;
     }
-    if (Me <= mh * kRows) return;
-
-    for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) {
+    // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + 8 NJ - 1
+    auto run_block = [&](auto nj_c, int m0) __attribute__((always_inline)) {
+        constexpr int NJ = decltype(nj_c)::value;
         const int mrem = min(kRows, Me - m0);
         lds_barrier();  // the pair list is complete / the previous pass is done with the LDS tile
         if (tid < kRows) {
@@ -649,9 +603,9 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
             s_row[tid] = xr;
             s_orow[tid] = tid < mrem ? orow : -1;
         }
-        f32x16 acc[PW][2];
+        f32x16 acc[NJ][2];
 #pragma unroll
-        for (int j = 0; j < PW; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -704,11 +658,11 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
             }
             // ---- this wavefront's pairs over the chunk's groups
 #pragma unroll
-            for (int j = 0; j < PW; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 const int pi = wave + 8 * j;
                 // what follows (chunk, pair) in the stream: the next pair of the chunk, the first pair of the next chunk,
                 // or, at the very end, lines that are cached already
-                const bool last_pair = (j == PW - 1);
+                const bool last_pair = (j == NJ - 1);
                 const int npi = last_pair ? wave : pi + 8;
                 const int nch = last_pair ? (ch + 1 < NC ? ch + 1 : 0) : ch;
                 sc_nxt = load_scales(npi, nch);
@@ -758,7 +712,7 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
 
         // ---- epilogue of the wavefront's pairs
 #pragma unroll
-        for (int j = 0; j < PW; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             const int u = u_lo + wave + 8 * j;
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
@@ -798,21 +752,58 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Par
                 }
             }
         }
+    };
+    if constexpr (!SPREAD) {
+        for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) run_block(std::integral_constant<int, PW>(), m0);
+        return false;
+    } else if constexpr (!TAIL) {
+        if (mh * kRows < Me) run_block(std::integral_constant<int, PW>(), mh * kRows);
+        return mh * kRows >= Me || Me > m_split * kRows;
+    } else {
+        // shares of the row blocks beyond the grid's, eight pairs (one per wavefront) each
+        const int e_own = e;
+        int *s_hist = tmp_map + 2 * kIdsRows + kListWaves;
+        count_rows(p.ids, p.n_ids, p.E, s_hist);
+        SpreadItem it;
+#pragma unroll 1
+        for (int k = 0; spread_item(s_hist, p.E, 6, m_split, 1 << p.slice_sh, PW, e_own, mh, slice, k, it); ++k) {
+            e = it.e;
+            ebase = (int64_t)e * N;
+            u_lo = it.sub * kWaves;   // a slice is PW sub-items
+            lds_barrier();   // the previous block is done with the list
+            Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
+            if (it.block * kRows >= Me) continue;
+            if (it.n_sub == PW) run_block(std::integral_constant<int, PW>(), it.block * kRows);
+            else run_block(std::integral_constant<int, 1>(), it.block * kRows);
+        }
+        return false;
+    }
+}
+
+template <int EPI, int PW, int NC, bool SPREAD>
+__global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_wide_kernel(W4Params p)
+{
+    if (!stream_w4_wide_body<EPI, PW, NC, SPREAD, false>(p, threadIdx.x, blockIdx.x)) return;
+    if constexpr (SPREAD) {
+        const FreshArgs<W4Params> f;
+        stream_w4_wide_body<EPI, PW, NC, SPREAD, true>(f.p, f.tid, f.bid);
     }
 }
 
 size_t wide_lds_bytes(int K, int NC, bool routed)
 {
-    return (size_t)64 * 8 + 8 * 64 * 4 + (size_t)64 * x_stride(K / NC) + (routed ? 8 * (size_t)kIdsRows + 4 * kWaves : 0);
+    return (size_t)64 * 8 + 8 * 64 * 4 + (size_t)64 * x_stride(K / NC) + (routed ? (size_t)kIdsBytes : 0);
 }
 
-template <int EPI, int PW>
+template <int EPI, int PW, bool SPREAD = false>
 int launch_wide(const W4Params &p, hipStream_t s)
 {
+    if constexpr (!SPREAD)
+        if (p.spread) return launch_wide<EPI, PW, true>(p, s);
     constexpr int NC = 2;
     const size_t lds = wide_lds_bytes(p.K, NC, p.ids != nullptr);
     static LdsLimitOnce once;
-    auto kern = qgemm_stream_w4_wide_kernel<EPI, PW, NC>;
+    auto kern = qgemm_stream_w4_wide_kernel<EPI, PW, NC, SPREAD>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(stream w4 wide)")) return rc;
     const int64_t units = (int64_t)p.E << p.slice_sh;
     const int64_t grid = (((units + 7) / 8) * 8) << p.msplit_sh;
@@ -820,18 +811,20 @@ int launch_wide(const W4Params &p, hipStream_t s)
     return check_hip(hipGetLastError(), "qgemm_stream_w4_wide_kernel");
 }
 
-template <int EPI, int MT, int R, bool NT, bool HALF = false>
+template <int EPI, int MT, int R, bool NT, bool HALF = false, bool SPREAD = false>
 int launch_cfg_nt(const W4Params &p, hipStream_t s)
 {
+    if constexpr (!SPREAD && !HALF)
+        if (p.spread) return launch_cfg_nt<EPI, MT, R, NT, HALF, true>(p, s);
     size_t lds = lds_bytes(p.K, MT, HALF);
-    if (p.ids) lds += 8 * (size_t)kIdsRows + 4 * kWaves + kQxScaleBytes;
+    if (p.ids) lds += (size_t)kIdsBytes + kQxScaleBytes;
     else if (p.map_mode == 2) lds += 8 * (size_t)((p.M + 3) & ~3);
     if (lds > 160 * 1024) {
         set_error("qgemm (decode path): K=%d needs %zu bytes of LDS per workgroup, more than the 160 KiB of a CU", p.K, lds);
         return QARL_ERR_UNSUPPORTED;
     }
     static LdsLimitOnce once;
-    auto kern = qgemm_stream_w4_kernel<EPI, MT, R, NT, HALF>;
+    auto kern = qgemm_stream_w4_kernel<EPI, MT, R, NT, HALF, SPREAD>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(stream w4)")) return rc;
     const int64_t units = (int64_t)p.E << p.slice_sh;
     const int64_t grid = (((units + 7) / 8) * 8) << p.msplit_sh;
@@ -906,6 +899,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     p.x_per_token = a.x_per_token;
     p.qx = (a.ids && a.fmt == QARL_W4A8_G128) ? 1 : 0;
     p.n_units = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2) / 16 : a.N / 32;
+    p.spread = 0;
     const W4Grid g = w4_grid(a.N, a.K, a.E, a.M);
     const double need = g.need;
     const int MT = g.MT, max_slices = g.max_slices, ssh = g.slice_sh;
@@ -931,6 +925,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
             p.per_slice = per_w;
             p.map_mode = 0;
             if (a.ids) p.row_map = p.out_row_map = p.offsets = nullptr;
+            p.spread = spread_blocks(a, 64 << msh_w);
             switch (per_w / kWaves) {
             case 1: return launch_wide<EPI, 1>(p, s);
             case 2: return launch_wide<EPI, 2>(p, s);
@@ -961,6 +956,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
         }
         p.row_map = p.out_row_map = p.offsets = nullptr;
         p.map_mode = 2;
+        p.spread = spread_blocks(a, (32 * MT) << p.msplit_sh);   // (no 16-row tile here: K <= 2048)
         if (MT == 1) return launch_ring<EPI, 1>(p, s);
         return launch_ring<EPI, 2>(p, s);
     }
@@ -996,7 +992,7 @@ bool qgemm_stream_w4_routed_supported(int N, int K, int T, int topk)
 {
     if (!qgemm_stream_w4_supported(N, K) || K > 2048 || T <= 0 || topk <= 0) return false;
     if (T > kIdsRows || (int64_t)T * topk > kIdsMax) return false;
-    return lds_bytes(K, 1) + 8 * (size_t)kIdsRows + 4 * kWaves + kQxScaleBytes <= 160 * 1024;
+    return lds_bytes(K, 1) + (size_t)kIdsBytes + kQxScaleBytes <= 160 * 1024;
 }
 
 int launch_qgemm_stream_w4(const GemmArgs &a, hipStream_t s)

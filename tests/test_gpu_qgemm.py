@@ -722,3 +722,39 @@ def test_routed_combine_of_few_pairs_reads_shared_weights_once(q, fmt_name, E, N
         rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(rows)
     want = q.qarl_qgemm_grouped(qw, rows, off, M, sorted_pairs=pairs.int(), T=T, topk=topk, path=q.QARL_PATH_DECODE, **kw)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("fmt_name,E,N,K,T,topk,named", [
+    ("w4a16", 16, 64, 512, 512, 4, 4),         # every token names the same experts: the others' workgroups take their row blocks
+    ("w4a16", 3, 96, 256, 200, 2, 3),          # no workgroup without rows, a slice of three pairs of tiles
+    ("w4a16", 256, 32, 256, 512, 8, 9),        # as many experts as the counts hold, one pair of tiles per slice
+    ("w4a16", 257, 32, 256, 512, 8, 9),        # one more: further blocks are passes
+    ("w4a16", 70, 1536, 2048, 512, 4, 40),     # 64-row blocks over a K-chunked tile, three pairs per wavefront, shares of one
+    ("w4a8", 8, 288, 1024, 150, 3, 3), ("fp8", 8, 288, 2048, 100, 3, 4), ("fp8", 5, 64, 128, 17, 2, 2),
+    ("fp4", 64, 96, 512, 512, 8, 8), ("fp4", 64, 512, 256, 37, 8, 20)])
+@pytest.mark.parametrize("twice", [False, True])
+def test_routed_row_blocks_of_popular_experts_equal_grouped_decode(q, fmt_name, E, N, K, T, topk, named, twice):
+    """Bit for bit the grouped decode path where only the first `named` experts have rows; twice: every token names its first
+    expert in its last slot too, so that an expert may have more rows than there are tokens (up to the 512 the call lists)."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    g = torch.Generator().manual_seed(E + N + K + T)
+    ids = torch.stack([torch.randperm(named, generator=g)[:topk] for _ in range(T)])
+    if twice:
+        ids[:, -1] = ids[:, 0]
+        if int(torch.bincount(ids.flatten()).max()) > 512:
+            pytest.skip("an expert lists at most 512 rows")
+    M = T * topk
+    pairs = torch.argsort(ids.flatten(), stable=True)
+    off = torch.zeros(E + 1, dtype=torch.int32)
+    off[1:] = torch.cumsum(torch.bincount(ids.flatten(), minlength=E), 0)
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K + N, device="cuda"), fmt)
+    x = synth.normal_bf16((T, K), 1.0, seed=T, device="cuda")
+    rows, kw = x, {}
+    if fmt != q.QARL_W4A16_G128:
+        rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(x)
+    d_ids, d_tok, d_pairs = ids.int().flatten().cuda(), (pairs // topk).int().cuda(), pairs.cuda()
+    for epi, dt in ((q.QARL_EPI_NONE, q.QARL_OUT_F32), (q.QARL_EPI_SILU_MUL, q.QARL_OUT_BF16)):
+        want = q.qarl_qgemm_grouped(qw, rows, off.cuda(), M, row_map=d_tok, epilogue=epi, out_dtype=dt, path=q.QARL_PATH_DECODE, **kw)
+        got = torch.full_like(want, float("nan"))
+        q.qarl_qgemm_routed(qw, x, d_ids, T, topk, True, epilogue=epi, out=got, out_dtype=dt)
+        assert torch.equal(got[d_pairs], want)
