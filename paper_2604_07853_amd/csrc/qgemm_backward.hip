@@ -207,6 +207,278 @@ __global__ __launch_bounds__(kBwThreads, 4) void qgemm_dx_kernel(DxParams p)
     }
 }
 
+// ---- dX on 256 x 256 tiles, i.e. two scale groups.  A stage holds 64 contraction elements n: the gradient rows as they are
+// stored, Ds [256 rows][64 n] (asynchronous copies, 128-byte rows, chunk c of row r at position c ^ (r & 7)), and the
+// expanded codes Ws [64 n][256 k] (512-byte rows, swz_tr); two of each, and two of the raw codes Cs, each wavefront its own
+// 1 KiB block, copied two stages ahead and expanded one stage ahead.  Eight wavefronts of 64 rows x 128 columns, one scale group
+// each, so that a wavefront scales exactly the operand it multiplies, in registers: the gradient operand comes from LDS unscaled, and
+// the matrix core scales it.  v_mfma_f32_4x4x4 is sixteen products of 4 x 4 matrices, one per four neighbouring lanes; lane j of the
+// four holds column j of the second operand and of the result (four elements each) and row j of the first.  With diag(s[n .. n + 3])
+// as the first, a lane's four gradients of its row come back as four exact fp32 products: one instruction of 8 cycles for two
+// unpackings and a multiplication per element.  Rows that no wavefront has (a wavefront of 64 rows past the expert's end) are not
+// multiplied.  Gate_up, 16384 tokens, Zipf router: 1332 -> 1110 us (the 128 x 128 tiles
+// above move twice the LDS bytes per matrix instruction and scale through VALU); without copies, scaling and expansion it would take 747, without the
+// scaling 1029, without the copies 1018: what is left is matrix instructions, and the rest adds to them.
+constexpr int kDxWTile = 256, kDxWStage = 64;
+constexpr int kDxWDsB = kDxWTile * kDxWStage * 2, kDxWWs = 2 * kDxWDsB, kDxWWsB = kDxWStage * kDxWTile * 2, kDxWCs = kDxWWs + 2 * kDxWWsB;
+constexpr int kDxWCsB = kDxWStage * kDxWTile / 2, kDxWSc = kDxWCs + 2 * kDxWCsB;   // LDS offsets and sizes; then [2][N] scales
+__host__ __device__ constexpr size_t dx_wide_lds(int N) { return kDxWSc + (size_t)N * 4; }
+
+__device__ __forceinline__ TrBase tr_base_dx(int col0, int lane)
+{
+    const int r16 = lane & 15, g = lane >> 4;
+    const int row = 8 * (g >> 1) + (r16 >> 2);                // the row this lane ADDRESSES (second read: + 4)
+    const int colq = col0 + 16 * (g & 1) + 4 * (r16 & 3);     // first of the four columns it addresses
+    TrBase b;
+    b.lo = row * 512 + (((colq >> 3) ^ swz_tr(row)) << 4) + (colq & 4) * 2;
+    b.hi = (row + 4) * 512 + (((colq >> 3) ^ swz_tr(row + 4)) << 4) + (colq & 4) * 2;
+    return b;
+}
+
+__global__ __launch_bounds__(kBwThreads, 2) void qgemm_dx_wide_kernel(DxParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ __attribute__((aligned(16))) int s_orow[kDxWTile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wg = wave & 1, m32 = lane & 31, h = lane >> 5;   // rows 64 wr .., scale group wg of the two
+    const int N = p.N, K = p.K, G = K / kGroup;
+
+    GroupedTile tile;
+    if (!find_grouped_tile<kDxWTile>(p.offsets, p.E, K / kDxWTile, tile)) return;
+    const int e = tile.e, kb = tile.block;
+    const int row0 = p.offsets[e] + tile.mtile * kDxWTile;
+    const int mrem = min(kDxWTile, p.offsets[e + 1] - row0);
+
+    // ---- copies.  Instruction i (0..3) of the wavefront moves the gradient rows 32 w + 8 i .. + 7; lane L fills position L % 8 of
+    // row L / 8 of them.  Rows past the expert's end repeat its last one (their results are never stored).
+    const unsigned char *ybase = (const unsigned char *)(p.dy + (int64_t)row0 * N);
+    uint32_t yoff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        yoff[i] = (uint32_t)min(wave * 32 + 8 * i + (lane >> 3), mrem - 1) * (uint32_t)(N * 2) + (uint32_t)(((lane & 7) ^ (lane >> 3)) << 4);
+    const unsigned char *cbase = (const unsigned char *)(p.codes + (((int64_t)e * N / 16 + wr) * G + 2 * kb + wg) * 256) + lane * 16;
+    auto copy_rows = [&](int s, int i) {
+        copy16_to_lds(ybase + yoff[i] + (uint32_t)(s * kDxWStage * 2), smem + (s & 1) * kDxWDsB + (wave * 32 + 8 * i) * (kDxWStage * 2));
+    };
+    auto copy_codes = [&](int s) {
+        copy16_to_lds(cbase + (uint64_t)(uint32_t)s * (uint32_t)(4 * G * 1024), smem + kDxWCs + (s & 1) * kDxWCsB + wave * 1024);
+    };
+    const int stages = N / kDxWStage;   // at least two
+#pragma unroll
+    for (int i = 0; i < 4; ++i) copy_rows(0, i);
+    copy_codes(0);
+    copy_codes(1);
+    if (tid < kDxWTile) s_orow[tid] = tid < mrem ? (p.out_row_map ? p.out_row_map[row0 + tid] : row0 + tid) : -1;
+    {
+        uint16_t *sc = (uint16_t *)(smem + kDxWSc);
+        for (int n = tid; n < N; n += kBwThreads) {
+            const uint32_t v = *(const uint32_t *)(p.scales + ((int64_t)e * N + n) * G + 2 * kb);
+            sc[n] = (uint16_t)v;
+            sc[N + n] = (uint16_t)(v >> 16);
+        }
+    }
+
+    // ---- expansion: lane (k range q = lane / 16, row lane % 16) of this wavefront's block of stage s
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)smem;
+    const int nl = wr * 16 + (lane & 15);
+    const uint32_t wdst = kDxWWs + nl * 512 + (((wg * 16 + (lane >> 4) * 4) ^ swz_tr(nl)) << 4);
+    auto read_codes = [&](int s) { return *(const u32x4 *)(smem + kDxWCs + (s & 1) * kDxWCsB + wave * 1024 + lane * 16); };
+    // (as asm: in front of an LDS store the compiler can see it drains the copies in flight)
+    auto expand_word = [&](int s, uint32_t w, int j) {
+        const u32x4 v = __builtin_bit_cast(u32x4, unpack_int4_word(w));
+        asm volatile("ds_write_b128 %0, %1" ::"v"((wdst ^ (uint32_t)(j << 4)) + (lds0 + (uint32_t)((s & 1) * kDxWWsB))), "v"(v) : "memory");
+    };
+
+    // ---- operands of a slice (16 contraction elements): the gradient rows, the scales of the lane's row of the two diagonals, the codes
+    int aoff[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) aoff[st] = (wr * 64 + m32) * (kDxWStage * 2) + (((2 * st + h) ^ (m32 & 7)) << 4);
+    const int soff = kDxWSc + (wg * N + 8 * h + (lane & 3)) * 2;
+    TrBase tb[4];
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) tb[nt] = tr_base_dx(wg * 128 + nt * 32, lane);
+    struct Frags {
+        bf16x8 a[2], b[4];   // scaled gradients, codes
+    };
+    // (asm for the same reason; waited for by hand, with the wait tied to the registers)
+    auto read_tr = [&](uint32_t base, const TrBase &t, auto off_c) -> bf16x8 {
+        constexpr int off = decltype(off_c)::value;
+        struct {
+            s16x4 lo, hi;
+        } v;
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v.lo) : "v"(base + (uint32_t)t.lo), "n"(off));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v.hi) : "v"(base + (uint32_t)t.hi), "n"(off));
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto wait_frags = [&](Frags &f) {
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]));
+    };
+    const int dsh = (lane & 1) * 16;
+    const uint32_t dlo = (lane & 2) ? 0u : 0xffffffffu;
+    const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+    float rowsum[2] = {0.f, 0.f};
+    f32x16 acc[2][4];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[rt][nt][i] = 0.f;
+    // gradient rows of one row tile times the two diagonals (eight contraction elements per lane)
+    auto scaled = [&](int rt, u32x4 g, const u32x2 (&diag)[2]) -> bf16x8 {
+        u32x4 o;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const u32x2 gw = {g[2 * w], g[2 * w + 1]};
+            const f32x4 d = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, diag[w]), __builtin_bit_cast(s16x4, gw),
+                                                                   f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                bf16x2 pr;
+                pr[0] = (__bf16)d[2 * i];
+                pr[1] = (__bf16)d[2 * i + 1];
+                // row sum of the ROUNDED values: both halves times 1.0, added to the running sum in one operation
+                rowsum[rt] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, rowsum[rt], false);
+                o[2 * w + i] = __builtin_bit_cast(uint32_t, pr);
+            }
+        }
+        return __builtin_bit_cast(bf16x8, o);
+    };
+    // Under the eight MFMAs of `cur`, slice j of stage ks is read (behind the first three) and scaled (from the fifth on) into
+    // `nxt`; stage ks + 1 is copied in slice 0, its codes, copied a stage ago, are expanded in slices 1 and 2.
+    u32x4 cw = {0, 0, 0, 0};
+    auto slice = [&](const Frags &cur, Frags &nxt, int ks, auto j_c, auto more_t) {
+        constexpr int j = decltype(j_c)::value;
+        constexpr bool more = decltype(more_t)::value;
+        const int buf = ks & 1;
+        const uint32_t base = lds0 + kDxWWs + buf * kDxWWsB;
+        constexpr std::integral_constant<int, j * 16 * 512> off{};
+        u32x4 g[2];
+        uint32_t sv[2];
+        u32x2 diag[2];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int nt = i >> 1, rt = i & 1;
+            acc[rt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[rt], cur.b[nt], acc[rt][nt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == 0) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    g[r] = *(const u32x4 *)(smem + buf * kDxWDsB + aoff[j] + r * (32 * kDxWStage * 2));
+                    sv[r] = *(const uint16_t *)(smem + soff + ks * (kDxWStage * 2) + (16 * j + 4 * r) * 2);
+                }
+            } else if (i < 3) {
+                nxt.b[2 * i - 2] = read_tr(base, tb[2 * i - 2], off);
+                nxt.b[2 * i - 1] = read_tr(base, tb[2 * i - 1], off);
+            } else if (i == 4) {
+                wait_frags(nxt);
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const uint32_t v = sv[w] << dsh;
+                    diag[w] = u32x2{v & dlo, v & ~dlo};
+                }
+                nxt.a[0] = scaled(0, g[0], diag);
+            } else if (i == 5) {
+                nxt.a[1] = scaled(1, g[1], diag);
+            }
+            if (more) {
+                if (j == 0 && (i & 1)) copy_rows(ks + 1, i >> 1);
+                if (j == 1 && i == 0 && ks + 2 < stages) copy_codes(ks + 2);
+                if (j == 0 && i == 2) cw = read_codes(ks + 1);
+                if ((j == 1 || j == 2) && (i == 3 || i == 7)) expand_word(ks + 1, cw[(j - 1) * 2 + (i >> 2)], (j - 1) * 2 + (i >> 2));
+            }
+            if (i < 4) __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto stage_barrier = [&]() {   // own copies landed, own LDS operations done; then everybody's
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    Frags last, f0, f1, f2, f3;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) last.a[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) last.b[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    stage_barrier();
+    cw = read_codes(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) expand_word(0, cw[j], j);
+    stage_barrier();
+    auto stage = [&](int ks, auto more_t) {
+        slice(last, f0, ks, std::integral_constant<int, 0>{}, more_t);
+        slice(f0, f1, ks, std::integral_constant<int, 1>{}, more_t);
+        slice(f1, f2, ks, std::integral_constant<int, 2>{}, more_t);
+        slice(f2, f3, ks, std::integral_constant<int, 3>{}, more_t);
+        stage_barrier();
+        last = f3;
+    };
+    if (wr * 64 >= mrem) {   // no row of this wavefront's: its copies and its share of the codes only
+        for (int ks = 0; ks < stages; ++ks) {
+            if (ks + 1 < stages) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) copy_rows(ks + 1, i);
+                cw = read_codes(ks + 1);
+                if (ks + 2 < stages) copy_codes(ks + 2);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) expand_word(ks + 1, cw[j], j);
+            }
+            stage_barrier();
+        }
+        return;
+    }
+    for (int ks = 0; ks + 1 < stages; ++ks) stage(ks, std::true_type{});
+    stage(stages - 1, std::false_type{});
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) acc[rt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(last.a[rt], last.b[nt], acc[rt][nt], 0, 0, 0);
+
+    // ---- epilogue: lane (column m32 of tile nt, half h), register i -> row 32 rt + 8 (i / 4) + 4 h + i % 4.  32 rows x 128 columns
+    // turn through this wavefront's own LDS (rows that differ by 4 trade their 32-column halves: no bank conflicts) and
+    // leave as whole 512-byte (fp32) or 256-byte (bf16) row segments.
+    float *rs = (float *)(smem + kDxWCs) + wave * 64;
+    float *ot = (float *)smem + wave * (32 * 128);
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        const float r = rowsum[rt] + __shfl_xor(rowsum[rt], 32, 64);
+        if (h == 0) rs[rt * 32 + m32] = r;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            const f32x4 rs4 = *(const f32x4 *)(rs + rt * 32 + 8 * i4 + 4 * h);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 8 * i4 + 4 * h + i;
+                    ot[row * 128 + ((nt * 32 + m32) ^ ((row & 4) << 3))] = fmaf(16.f, acc[rt][nt][i4 * 4 + i], -24.f * rs4[i]);
+                }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 4
+        for (int pass = 0; pass < 16; ++pass) {
+            const int row = pass * 2 + h, col = m32 * 4;
+            const int64_t orow = s_orow[wr * 64 + rt * 32 + row];
+            const f32x4 v4 = *(const f32x4 *)(ot + row * 128 + (col ^ ((row & 4) << 3)));
+            if (orow < 0) continue;
+            const int64_t at = orow * K + kb * kDxWTile + wg * 128 + col;
+            if (p.out_f32) {
+                *(f32x4 *)((float *)p.out + at) = v4;
+            } else {
+                u32x2 ob;
+                ob[0] = (uint32_t)f32_to_bf16_hw(v4[0]) | ((uint32_t)f32_to_bf16_hw(v4[1]) << 16);
+                ob[1] = (uint32_t)f32_to_bf16_hw(v4[2]) | ((uint32_t)f32_to_bf16_hw(v4[3]) << 16);
+                *(u32x2 *)((uint16_t *)p.out + at) = ob;
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+}
+
 struct DwParams {
     const uint16_t *dy;   // bf16 [M][N], rows grouped by expert
     const uint16_t *x;    // bf16 [x_rows][K]
@@ -603,6 +875,18 @@ __global__ __launch_bounds__(kBwThreads, 2) void grouped_dw_wide_kernel(DwParams
 
 }  // namespace
 
+// The 256 x 256 tiles take 0.8-0.95 of the 128 x 128 ones' time on a full chip, but a tile is four times the work and there is one per CU:
+// from 512 rows per expert (a partial tile hurts less) and three rounds of workgroups on (half a tile more per expert than the rows
+// fill).  us, 128 x 128 against 256 x 256, 128 experts, even / Zipf router: gate_up (N 1536, K 2048) 2048 tokens
+// 204 / 229 against 194 / 255, 4096 343 / 364 against 304 / 373, 8192 640 / 660 against 542 / 565, 16384 (Zipf) 1332 against
+// 1110; down (N 2048, K 768) 4096 170 / 185 against 178 / 193, 8192 301 / 322 against 273 / 302; 64 experts (N 1024, K 512), two
+// rounds: 61 against 73.
+static bool dx_wide(const GemmArgs &a)
+{
+    return a.K % kDxWTile == 0 && dx_wide_lds(a.N) + 4 * kDxWTile <= (size_t)kMaxLdsBytes && a.M >= (int64_t)a.E * 512 &&
+           (a.M / kDxWTile + a.E / 2) * (a.K / kDxWTile) >= 3 * 256;
+}
+
 int launch_qgemm_dx(const GemmArgs &a, hipStream_t s)
 {
     if (a.E > 256 || a.N % kStageN != 0 || a.K % kTK != 0 || a.N > 8192) {
@@ -620,11 +904,19 @@ int launch_qgemm_dx(const GemmArgs &a, hipStream_t s)
     p.N = a.N;
     p.K = a.K;
     p.out_f32 = a.out_f32;
-    const int64_t slots = (a.M + kTM - 1) / kTM + a.E;
-    const int64_t total = ((slots * (a.K / kTK) + 7) / 8) * 8;
+    const bool wide = dx_wide(a);
+    const int tm = wide ? kDxWTile : kTM, tk = wide ? kDxWTile : kTK;
+    const int64_t slots = (a.M + tm - 1) / tm + a.E;
+    const int64_t total = ((slots * (a.K / tk) + 7) / 8) * 8;
     if (total > 0x7fffffffLL) {
         set_error("qgemm dx: grid too large");
         return QARL_ERR_UNSUPPORTED;
+    }
+    if (wide) {
+        static LdsLimitOnce once;
+        if (int rc = raise_lds_limit((const void *)qgemm_dx_wide_kernel, once, "hipFuncSetAttribute(qgemm dx wide)")) return rc;
+        qgemm_dx_wide_kernel<<<dim3((unsigned)total), dim3(kBwThreads), dx_wide_lds(a.N), s>>>(p);
+        return check_hip(hipGetLastError(), "qgemm_dx_wide_kernel");
     }
     const size_t lds = (size_t)(kTM + kTK) * kStageN * 2 + (size_t)a.N * 4;
     static LdsLimitOnce once;

@@ -180,3 +180,47 @@ def test_backward_errors(q):
     with pytest.raises(q.QarlError) as ei:
         q.qarl_grouped_dw(dy, torch.zeros((4, 128), dtype=torch.bfloat16, device="cuda"), _i32([0, 4]), 1)
     assert ei.value.status == q.QARL_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("E,N,K,rows", [(2, 128, 4096, (6401, 5888)),             # two stages, a tile of one row, a last tile that is full
+                                        (3, 1536, 4096, (0, 6100, 6144 - 192)),   # an expert without rows, last tiles of 212 and 64 rows
+                                        (1, 384, 12288, (4101,)),                 # a tile of five rows
+                                        (1, 3840, 4096, (12300,)), (1, 3968, 4096, (12300,))])    # the longest contraction whose scales fit LDS, and one more
+def test_dx_of_many_rows(q, oracle, E, N, K, rows):
+    """From 512 rows per expert and three rounds of workgroups on: 256 x 256 tiles where the scales fit LDS.  Against 64-bit sums
+    of the same operands (the scaled gradients rounded to bf16), so that only the order of the sums is left.  The sums of
+    a (q + 24) and of -24 a each have about 24 / 2.6 = 10 times the rms of their difference (q of normal weights has an rms of 2.6),
+    and a chain of N fp32 additions is off by up to about sqrt(N) half ulps of such a value: 10 * 2^-24 * sqrt(N)."""
+    seed = 8700 + N + K
+    M = sum(rows)
+    assert M >= 512 * E and (M // 256 + E // 2) * (K // 256) >= 768
+    rng = np.random.default_rng(seed)
+    w = synth.normal_bf16((E, N, K), 0.02, seed=seed, device="cuda")
+    dy = synth.normal_bf16((M, N), 1.0, seed=seed + 1, device="cuda")
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    scatter = _i32(rng.permutation(M).astype(np.int32))
+    qw = q.qarl_quantize_weights(w)
+    codes = oracle.dequant_int4(*oracle.quantize_int4(np_bits(w)))            # s*q
+    sc = qw.scales.float()                                                    # [E][N][K / 128]
+    dx = q.qarl_qgemm_grouped_dx(qw, dy, _i32(off), M, out_dtype=q.QARL_OUT_F32)
+    for e in range(E):
+        lo, hi = off[e], off[e + 1]
+        deq = torch.from_numpy(codes[e]).cuda()
+        for g in range(K // 128):
+            s = sc[e, :, g]
+            a = (dy[lo:hi].float() * s).to(torch.bfloat16).double()
+            ref = a @ torch.round(deq[:, g * 128:(g + 1) * 128].double() / s[:, None].double())
+            got = dx[lo:hi, g * 128:(g + 1) * 128].double()
+            if hi > lo:
+                err = float(((got - ref).abs() / (ref.abs() + ref.pow(2).mean().sqrt())).max())
+                assert err <= max(TOL_F32, 10 * 2.0 ** -24 * N ** 0.5), (e, g)
+    dxb = torch.full((M + 1, K), 7.0, dtype=torch.bfloat16, device="cuda")
+    q.qarl_qgemm_grouped_dx(qw, dy, _i32(off), M, out_row_map=scatter, out=dxb)
+    assert torch.equal(dxb[scatter.long()], dx.to(torch.bfloat16)) and bool((dxb[M] == 7).all())
+    # gradients with one element per row return rows of s*q bit for bit
+    n = torch.from_numpy(rng.integers(0, N, M)).cuda()
+    hot = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+    hot[torch.arange(M, device="cuda"), n] = 1.0
+    dx = q.qarl_qgemm_grouped_dx(qw, hot, _i32(off), M, out_dtype=q.QARL_OUT_F32)
+    for e in range(E):
+        assert torch.equal(dx[off[e]:off[e + 1]], torch.from_numpy(codes[e]).cuda().float()[n[off[e]:off[e + 1]]])
