@@ -758,3 +758,25 @@ def test_routed_row_blocks_of_popular_experts_equal_grouped_decode(q, fmt_name, 
         got = torch.full_like(want, float("nan"))
         q.qarl_qgemm_routed(qw, x, d_ids, T, topk, True, epilogue=epi, out=got, out_dtype=dt)
         assert torch.equal(got[d_pairs], want)
+
+
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
+@pytest.mark.parametrize("E,rows,tiled", [(64, 16, False), (64, 17, True), (64, 64, True), (48, 17, False), (48, 64, False), (257, 20, None)])
+def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows, tiled):
+    """Bit for bit the path the rule names; the streaming one where the workspace does not hold the tiled path's, or out is x."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    N = K = 256
+    M = E * rows
+    cut = np.sort(np.random.default_rng(E + rows).integers(0, M + 1, E - 1))
+    off = _i32(np.concatenate([[0], cut, [M]]))
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=E, device="cuda"), fmt)
+    x, kw = synth.normal_bf16((M, K), 1.0, seed=rows, device="cuda"), {}
+    if fmt != q.QARL_W4A16_G128:
+        x, kw["x_scales"] = q.qarl_quantize_rows_fp8(x)
+    by = {p: q.qarl_qgemm_grouped(qw, x, off, M, path=p, out_dtype=q.QARL_OUT_F32, **kw) for p in _paths(q)
+          if tiled is not None or p == q.QARL_PATH_DECODE}                    # (the tiled path takes at most 256 experts)
+    got = q.qarl_qgemm_grouped(qw, x, off, M, out_dtype=q.QARL_OUT_F32, **kw)
+    assert torch.equal(got, by[q.QARL_PATH_PREFILL if tiled else q.QARL_PATH_DECODE])
+    if fmt == q.QARL_W4A16_G128:
+        none = torch.empty((16,), dtype=torch.uint8, device="cuda")
+        assert torch.equal(q.qarl_qgemm_grouped(qw, x, off, M, out_dtype=q.QARL_OUT_F32, ws=none), by[q.QARL_PATH_DECODE])
