@@ -216,7 +216,10 @@ __device__ __forceinline__ bool stream_fp8_body(const StreamParams &p, int tid, 
                 }
             };
             if (n16 <= 4 * 64) {
-                gather_q(std::integral_constant<int, 2 * MT>(), std::integral_constant<int, 4>(), 0, true);
+                // (64 rows: two batches of four rows per wavefront, as many as its registers hold)
+#pragma unroll 1
+                for (int i = 0; i < (MT + 1) / 2; ++i)
+                    gather_q(std::integral_constant<int, MT == 1 ? 2 : 4>(), std::integral_constant<int, 4>(), i * 32, i == 0);
             } else {
 #pragma unroll 1
                 for (int i = 0; i < MT; ++i)
@@ -328,19 +331,18 @@ __device__ __forceinline__ bool stream_fp8_body(const StreamParams &p, int tid, 
         if (mh * kRowsMax < Me) run_block(mh * kRowsMax);
         return mh * kRowsMax >= Me || Me > p.m_split * kRowsMax;   // no row of its own, or a popular expert
     } else {
-        // shares of the row blocks beyond the grid's, in halves of a slice
-        constexpr int kSubs = 2;
-        const int e_own = e, half = (per_slice + 1) / kSubs;
+        // shares of the row blocks beyond the grid's: a pair per wavefront each, or a slice
+        const int e_own = e, subs = (per_slice + kSWaves - 1) / kSWaves;
         int *s_hist = tmp_map + 2 * kIdsRows + kListWaves;
         count_rows(p.ids, p.n_ids, p.E, s_hist);
         SpreadItem it;
 #pragma unroll 1
-        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 4 : 5, p.m_split, p.n_slices, kSubs, e_own, mh, slice, k, it); ++k) {
+        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 4 : MT == 2 ? 5 : 6, p.m_split, p.n_slices, subs, e_own, mh, slice, k, it); ++k) {
             e = it.e;
             ebase = (int64_t)e * N;
-            const int sl = it.sub / kSubs;
-            u_lo = sl * per_slice + (it.sub % kSubs) * half;
-            n_pairs = max(0, min(min(p.n_units, (sl + 1) * per_slice), u_lo + it.n_sub * half) - u_lo);
+            const int sl = it.sub / subs;
+            u_lo = sl * per_slice + (it.sub - sl * subs) * kSWaves;
+            n_pairs = max(0, min(min(p.n_units, (sl + 1) * per_slice), u_lo + it.n_sub * kSWaves) - u_lo);
             lds_barrier();   // the previous block is done with the list
             Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
             if (it.block * kRowsMax < Me) run_block(it.block * kRowsMax);
@@ -381,8 +383,12 @@ int launch_cfg_w(const StreamParams &p, hipStream_t s)
 template <int EPI, int MT, int R>
 int launch_cfg(const StreamParams &p, hipStream_t s)
 {
-    if (p.ids) return p.w4 ? launch_cfg_w<EPI, MT, R, true, true>(p, s) : launch_cfg_w<EPI, MT, R, false, true>(p, s);
-    return p.w4 ? launch_cfg_w<EPI, MT, R, true, false>(p, s) : launch_cfg_w<EPI, MT, R, false, false>(p, s);
+    if constexpr (R == 4) {   // e2m1 codes only (launch_ring)
+        return p.ids ? launch_cfg_w<EPI, MT, R, true, true>(p, s) : launch_cfg_w<EPI, MT, R, true, false>(p, s);
+    } else {
+        if (p.ids) return p.w4 ? launch_cfg_w<EPI, MT, R, true, true>(p, s) : launch_cfg_w<EPI, MT, R, false, true>(p, s);
+        return p.w4 ? launch_cfg_w<EPI, MT, R, true, false>(p, s) : launch_cfg_w<EPI, MT, R, false, false>(p, s);
+    }
 }
 
 template <int EPI, int MT>
@@ -409,15 +415,20 @@ StreamGrid stream_grid(int N, int K, int E, int64_t M, bool routed)
     // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
     const double mean = (double)M / (double)E;
     const double need = mean + 4.0 * sqrt(mean);
-    // token tiles per workgroup: limited by the LDS tile, which holds the whole K of every row
-    const int mt_fit = stream_lds_bytes(K, 2, routed) <= 160 * 1024 ? 2 : (stream_lds_bytes(K, 1, routed) <= 160 * 1024 ? 1 : 0);
-    g.MT = need <= 16.0 ? 1 : 2;  // more rows per expert go to further row blocks (m_split)
+    // token tiles per workgroup: limited by the LDS tile, which holds the whole K of every row, and by the gather (16 blocks of 16
+    // bytes per thread).  More rows per expert go to further row blocks (m_split), each a pass over the expert's weights.  Blocks of
+    // 64 rows where the slices alone fill the chip (routed layers, top-8 of 128, two blocks of 32 -> one of 64: 300 tokens FP8
+    // 196 -> 148 us, FP4 137 -> 107, 512 tokens 203 -> 160 and 144 -> 118); with few experts blocks of 32 run side by side
+    // (16 experts 1536 x 2048, 48 rows each: FP8 30 against 33 us, FP4 24 against 28).
+    const int mt_fit = stream_lds_bytes(K, 4, routed) <= 160 * 1024 && K <= 2048 ? 4 : stream_lds_bytes(K, 2, routed) <= 160 * 1024 ? 2
+                       : stream_lds_bytes(K, 1, routed) <= 160 * 1024 ? 1 : 0;
+    const int max_slices = (N / 32 + kSWaves - 1) / kSWaves;
+    g.MT = need <= 16.0 ? 1 : need <= 32.0 || mt_fit < 4 || E * max_slices < 256 ? 2 : 4;
     if (g.MT > mt_fit) g.MT = mt_fit < 1 ? 0 : 1;
     const int ms = g.MT ? (int)ceil(need / (16.0 * g.MT)) : 1;
     g.m_split = ms < 1 ? 1 : (ms > 8 ? 8 : ms);
     // slices per expert: aim at one workgroup per CU, at least one pair of tiles per wavefront
     g.n_slices = (256 + E * g.m_split - 1) / (E * g.m_split);
-    const int max_slices = (N / 32 + kSWaves - 1) / kSWaves;
     if (g.n_slices > max_slices) g.n_slices = max_slices;
     if (g.n_slices < 1) g.n_slices = 1;
     return g;
@@ -459,7 +470,8 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     p.n_slices = g.n_slices;
     p.spread = spread_blocks(a, 16 * g.MT * g.m_split);
     if (g.MT == 1) return launch_ring<EPI, 1>(p, s);
-    return launch_ring<EPI, 2>(p, s);
+    if (g.MT == 2) return launch_ring<EPI, 2>(p, s);
+    return launch_ring<EPI, 4>(p, s);
 }
 
 }  // namespace

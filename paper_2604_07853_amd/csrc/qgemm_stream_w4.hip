@@ -485,19 +485,18 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
         if (mh * kRows < Me) run_block(mh * kRows, true);
         return mh * kRows >= Me || Me > m_split * kRows;   // no row of its own, or a popular expert
     } else {
-        // shares of the row blocks beyond the grid's, in halves of a slice
-        constexpr int kSubs = 2;
-        const int e_own = e, half = (p.per_slice + 1) / kSubs;
+        // shares of the row blocks beyond the grid's: a pair per wavefront each, or a slice
+        const int e_own = e, subs = (p.per_slice + kWaves - 1) / kWaves;
         int *s_hist = tmp_map + 2 * kIdsRows + kListWaves;
         count_rows(p.ids, p.n_ids, p.E, s_hist);
         SpreadItem it;
 #pragma unroll 1
-        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 5 : 6, m_split, 1 << p.slice_sh, kSubs, e_own, mh, slice, k, it); ++k) {
+        for (int k = 0; spread_item(s_hist, p.E, MT == 1 ? 5 : 6, m_split, 1 << p.slice_sh, subs, e_own, mh, slice, k, it); ++k) {
             e = it.e;
             ebase = (int64_t)e * N;
-            const int sl = it.sub / kSubs;
-            u_lo = sl * p.per_slice + (it.sub % kSubs) * half;
-            n_pairs = max(0, min(min(p.n_units, (sl + 1) * p.per_slice), u_lo + it.n_sub * half) - u_lo);
+            const int sl = it.sub / subs;
+            u_lo = sl * p.per_slice + (it.sub - sl * subs) * kWaves;
+            n_pairs = max(0, min(min(p.n_units, (sl + 1) * p.per_slice), u_lo + it.n_sub * kWaves) - u_lo);
             lds_barrier();   // the previous block is done with the list
             Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
             if (it.block * kRows < Me) run_block(it.block * kRows, false);

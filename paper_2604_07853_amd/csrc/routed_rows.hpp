@@ -91,8 +91,8 @@ __device__ __forceinline__ void count_rows(const int32_t *ids, int n_ids, int E,
 // round all takers one sub-item each.  All compute the same assignment from the same counts, nothing is exchanged.  The
 // other workgroups, i.e. all of them under an even router, neither count nor ask (counting in all of them costs a layer
 // 1.2 us).  As passes of the popular expert's own workgroups, its CUs worked alone while the rest of the chip was idle.
-// Layers of 128 experts 2048 x 768, top-8, Zipf 1.1, 64 / 256 / 512 tokens, before -> after in us: W4A16 108 / 391 / 593 ->
-// 69 / 81 / 166, W4A8 130 / 482 / 784 -> 76 / 86 / 149, FP8 323 / 719 / 1290 -> 99 / 119 / 192, FP4 207 / 486 / 830 -> 69 / 87 / 136.
+// Layers of 128 experts 2048 x 768, top-8, Zipf 1.1, 64 / 256 / 512 tokens, before -> after in us: W4A16 108 / 392 / 593 ->
+// 69 / 82 / 166, W4A8 130 / 483 / 783 -> 76 / 88 / 152, FP8 323 / 720 / 1290 -> 99 / 119 / 213, FP4 207 / 486 / 830 -> 69 / 87 / 177.
 
 // A kernel's argument, thread and workgroup ids read anew: what is computed from them belongs to the shares alone and is not kept
 // in registers through the workgroup's own block (kept, it cost the launches of an even router 1-2 %).

@@ -730,6 +730,7 @@ def test_routed_combine_of_few_pairs_reads_shared_weights_once(q, fmt_name, E, N
     ("w4a16", 256, 32, 256, 512, 8, 9),        # as many experts as the counts hold, one pair of tiles per slice
     ("w4a16", 257, 32, 256, 512, 8, 9),        # one more: further blocks are passes
     ("w4a16", 70, 1536, 2048, 512, 4, 40),     # 64-row blocks over a K-chunked tile, three pairs per wavefront, shares of one
+    ("fp8", 96, 544, 2048, 512, 8, 60), ("fp4", 70, 512, 512, 512, 4, 70),   # blocks of 64 rows, slices that are no multiple of eight pairs
     ("w4a8", 8, 288, 1024, 150, 3, 3), ("fp8", 8, 288, 2048, 100, 3, 4), ("fp8", 5, 64, 128, 17, 2, 2),
     ("fp4", 64, 96, 512, 512, 8, 8), ("fp4", 64, 512, 256, 37, 8, 20)])
 @pytest.mark.parametrize("twice", [False, True])
