@@ -205,6 +205,14 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
                       int T, int topk, int epilogue, const float *combine_w, void *out, int out_dtype,
                       void *ws, size_t ws_bytes, void *stream);
 
+/* A decode step's MoE layer in one call: qarl_moe_route (ids and weights only, into topk_ids and topk_w [T][topk]), then
+ * qarl_qgemm_routed on gate_up (SILU_MUL, x bf16 [T][K], into a_bf16 [T*topk][N/2]) and on down (COMBINE, into out [T][down N]).
+ * Launches what the three calls launch; limits, workspace (that of the down call) and errors are theirs. */
+int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down, const void *x,
+                          const void *logits_bf16, int T, int topk, int renorm, int32_t *topk_ids,
+                          float *topk_w, void *a_bf16, void *out, int out_dtype, void *ws,
+                          size_t ws_bytes, void *stream);
+
 /* LM head fused with the per-token log-prob: z = inv_temperature * h W_lm^T (bf16 inputs,
  * fp32 accumulation, logits never stored), logprob[t] = z[t][target[t]] - logsumexp_v z[t][v].
  * If ref_logprob is given, also the mismatch comparison of eq. (3) in log space:

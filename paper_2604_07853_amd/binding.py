@@ -26,7 +26,7 @@ QARL_OUT_BF16, QARL_OUT_F32 = 0, 1
 # the first six return a string or a size, the rest a qarl_status
 EXPORTS = ["qarl_last_error", "qarl_qgemm_workspace_bytes", "qarl_logprob_workspace_bytes",
            "qarl_token_logprob_static_limit", "qarl_codes_bytes", "qarl_scales_bytes", "qarl_quantize_weights", "qarl_quantize_rows_fp8", "qarl_moe_route", "qarl_qgemm_grouped",
-           "qarl_qgemm_routed", "qarl_token_logprob", "qarl_logprob_mismatch", "qarl_tbpo_objective",
+           "qarl_qgemm_routed", "qarl_moe_layer_routed", "qarl_token_logprob", "qarl_logprob_mismatch", "qarl_tbpo_objective",
            "qarl_token_logprob_static", "qarl_codes_to_canonical", "qarl_qgemm_grouped_dx",
            "qarl_grouped_dw"]
 
@@ -66,6 +66,8 @@ def lib():
                                          C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
         L.qarl_qgemm_routed.argtypes = [C.POINTER(qarl_qweight), C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int,
                                         C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
+        L.qarl_moe_layer_routed.argtypes = [C.POINTER(qarl_qweight)] * 2 + [C.c_void_p] * 2 + [C.c_int] * 3 + [C.c_void_p] * 4 + \
+                                           [C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
         L.qarl_token_logprob.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_float,
                                          C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_float, C.c_void_p,
                                          C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
@@ -338,6 +340,14 @@ class MoELayer:
             self.sa = torch.empty((M,), dtype=torch.float32, device=device)
 
     def forward(self, x, logits):
+        if self.routed and logits.shape == (self.T, self.E):
+            # one call per layer: a step of a few tokens is bound by the host otherwise (three calls took 25 us of Python)
+            assert logits.dtype == torch.bfloat16 and logits.is_cuda and logits.is_contiguous()
+            r = self.routing
+            _check(lib().qarl_moe_layer_routed(C.byref(self.gu.desc), C.byref(self.dn.desc), x.data_ptr(), logits.data_ptr(), self.T,
+                                               self.topk, 1, r.ids.data_ptr(), r.w.data_ptr(), self.a.data_ptr(), self.out.data_ptr(),
+                                               QARL_OUT_BF16, self.ws.data_ptr(), self.ws.numel(), torch.cuda.current_stream().cuda_stream))
+            return self.out
         if self.routed:
             r = qarl_moe_route(logits, self.topk, True, out=self.routing, group=False)
             qarl_qgemm_routed(self.gu, x, r.ids, self.T, self.topk, True, epilogue=QARL_EPI_SILU_MUL, out=self.a,

@@ -479,6 +479,24 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
     return QARL_OK;
 }
 
+int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down, const void *x, const void *logits_bf16, int T,
+                          int topk, int renorm, int32_t *topk_ids, float *topk_w, void *a_bf16, void *out, int out_dtype, void *ws,
+                          size_t ws_bytes, void *stream)
+{
+    int rc = check_qweight(gate_up, "qarl_moe_layer_routed");
+    if (!rc) rc = check_qweight(down, "qarl_moe_layer_routed");
+    if (rc) return rc;
+    if (gate_up->E != down->E || gate_up->N != 2 * down->K) {
+        set_error("qarl_moe_layer_routed: down [E][N][K] must have gate_up's E and K = N / 2 of it (got E=%d N=%d and E=%d K=%d)",
+                  gate_up->E, gate_up->N, down->E, down->K);
+        return QARL_ERR_INVALID_ARG;
+    }
+    rc = qarl_moe_route(logits_bf16, T, gate_up->E, topk, renorm, topk_ids, topk_w, nullptr, nullptr, nullptr, nullptr, stream);
+    if (!rc) rc = qarl_qgemm_routed(gate_up, x, 1, topk_ids, T, topk, QARL_EPI_SILU_MUL, nullptr, a_bf16, QARL_OUT_BF16, ws, ws_bytes, stream);
+    if (!rc) rc = qarl_qgemm_routed(down, a_bf16, 0, topk_ids, T, topk, QARL_EPI_COMBINE, topk_w, out, out_dtype, ws, ws_bytes, stream);
+    return rc;
+}
+
 int qarl_qgemm_grouped_dx(const qarl_qweight *W, const void *dy_bf16, const int32_t *expert_offsets, int64_t M,
                           const int32_t *out_row_map, void *dx, int out_dtype, void *stream)
 {
