@@ -341,6 +341,11 @@ struct GemmArgs {
     const int32_t *ids = nullptr;
     int topk = 0;
     int x_per_token = 0;
+    // few-pair kernels, SILU_MUL: route the tokens themselves (logits bf16 [T][E]) and write ids and weights, which `ids` then is not read for
+    const void *logits = nullptr;
+    int renorm = 0;
+    int32_t *ids_out = nullptr;
+    float *w_out = nullptr;
     int spread = 0;     // routed mode: a popular expert's rows may be worked on by any workgroup (out overlaps neither x nor ids)
 };
 int launch_qgemm_stream(const GemmArgs &a, hipStream_t s);

@@ -8,7 +8,7 @@
 //
 // 128 experts, hidden 2048, intermediate 768, top-8, layer of router, gate_up, down + combine: 1 token FP8 81 -> 26 us
 // (gate_up 49 -> 10.5, down + combine 29 -> 10), FP4 52 -> 25 us.
-#include "common.hpp"
+#include "route_token.hpp"
 
 namespace qarl {
 
@@ -22,6 +22,11 @@ struct SmallFp8Params {
     const float *combine_w;  // [T][topk], combine epilogue
     void *out;
     int E, N, K, out_f32, topk, x_per_token;
+    // SILU_MUL: the workgroup routes its token itself and the token's first one writes ids and weights (ids is not read)
+    const uint16_t *logits;   // [T][E], or null
+    int32_t *ids_out;
+    float *w_out;
+    int renorm;
     int n_slices;            // workgroups along the weight tiles
 };
 
@@ -47,7 +52,15 @@ __global__ __launch_bounds__(EPI == QARL_EPI_COMBINE ? 512 : 256, 2) void qgemm_
     float *s_y = s_rsc + 16;                             // [nslot or kWaves][16] results
 
     int idv = -1;   // expert of every slot, lane i: slot i
-    if (lane < nslot) idv = p.ids[pair0 + lane];
+    TokenLogits<kMaxPerLane> routed;   // of the workgroup that writes its token's ids and weights
+    bool writes = false;
+    if (kSilu && p.logits) {
+        const int token = item / p.topk, slot = item - token * p.topk;
+        TokenLogits<kMaxPerLane> l(p.logits + (int64_t)token * p.E, p.E);
+        routed = l;
+        writes = slice == 0 && slot == 0 && wave == kWaves - 1;
+        idv = l.expert((uint32_t)__builtin_amdgcn_readlane((int)l.select(slot + 1), slot));
+    } else if (lane < nslot) idv = p.ids[pair0 + lane];
     // rows to quantize: wave, wave + kWaves, ...; lane L holds the chunks L, L + 64, ... of eight values
     const int n16 = K / 8;
     const bool same_row = kComb && p.x_per_token;
@@ -110,6 +123,10 @@ __global__ __launch_bounds__(EPI == QARL_EPI_COMBINE ? 512 : 256, 2) void qgemm_
         sw = p.scales[row];
     };
     if (busy && wave < (kComb ? nslot : kWaves)) start(kComb ? wave : 0);
+    if (kSilu && writes) {   // under the weights' way
+        const int64_t o = (int64_t)(item / p.topk) * p.topk;
+        route_token<kMaxPerLane>(routed, p.E, p.topk, p.renorm, p.ids_out + o, p.w_out + o);
+    }
 
     if (wave < n_rows) quantize_row(wave, v0);
     for (int r = wave + kWaves; r < n_rows; r += kWaves) {
@@ -217,6 +234,10 @@ int launch_qgemm_small_fp8(const GemmArgs &a, const float *combine_w, hipStream_
     p.out_f32 = a.out_f32;
     p.topk = a.topk;
     p.x_per_token = a.x_per_token;
+    p.logits = (const uint16_t *)a.logits;
+    p.ids_out = a.ids_out;
+    p.w_out = a.w_out;
+    p.renorm = a.renorm;
     const int slots = epi == QARL_EPI_COMBINE ? a.topk : 1;
     p.n_slices = epi == QARL_EPI_COMBINE ? a.N / 16 : (a.N / 16 + 3) / 4;
     const size_t lds = (size_t)slots * a.K + 64 + 16 * 16 * 4;

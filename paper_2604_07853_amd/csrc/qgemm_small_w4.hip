@@ -14,7 +14,7 @@
 //
 // Combine epilogue: the topk slots of a token meet in one workgroup, which weights and adds them in slot order (as
 // combine_kernel does) and writes the output row: no staging rows, no second launch.
-#include "common.hpp"
+#include "route_token.hpp"
 
 namespace qarl {
 
@@ -31,6 +31,11 @@ struct SmallParams {
     const float *combine_w;  // [T][topk], combine epilogue
     void *out;
     int E, N, K, out_f32, topk, x_per_token;
+    // SILU_MUL: the workgroup routes its token itself and the token's first one writes ids and weights (ids is not read)
+    const uint16_t *logits;   // [T][E], or null
+    int32_t *ids_out;
+    float *w_out;
+    int renorm;
     int qx;          // W4A8: the rows go through the activation quantizer
     int n_units;     // pairs of 16-row weight tiles per expert
     int units;       // of them per workgroup
@@ -69,7 +74,15 @@ __global__ __launch_bounds__(kThreads, 4) void qgemm_small_w4_kernel(SmallParams
 
     // expert of every slot: lane i holds slot i's; an id outside [0, E) selects no expert
     int idv = -1;
-    if (lane < nslot) idv = p.ids[pair0 + lane];
+    TokenLogits<kMaxPerLane> routed;   // of the workgroup that writes its token's ids and weights
+    bool writes = false;
+    if (kSilu && p.logits) {
+        const int token = item / p.topk, slot = item - token * p.topk;
+        TokenLogits<kMaxPerLane> l(p.logits + (int64_t)token * p.E, p.E);
+        routed = l;
+        writes = slice == 0 && slot == 0 && wave == kWaves - 1;
+        idv = l.expert((uint32_t)__builtin_amdgcn_readlane((int)l.select(slot + 1), slot));
+    } else if (lane < nslot) idv = p.ids[pair0 + lane];
     // token rows, 16-byte chunks: thread -> chunk tid, tid + 512, ... of the nslot rows
     const int n16 = K / 8, chunks = nslot * n16;
     const int64_t xrow0 = p.x_per_token ? item / (kComb ? 1 : p.topk) : pair0;
@@ -133,6 +146,11 @@ __global__ __launch_bounds__(kThreads, 4) void qgemm_small_w4_kernel(SmallParams
             sc[i] = 0;
             if (folds && i < G / 2) sc[i] = src[i];
         }
+    }
+
+    if (kSilu && writes) {   // under the weights' way
+        const int64_t o = (int64_t)(item / p.topk) * p.topk;
+        route_token<kMaxPerLane>(routed, p.E, p.topk, p.renorm, p.ids_out + o, p.w_out + o);
     }
 
     // ---- token rows to LDS
@@ -328,6 +346,10 @@ int launch_qgemm_small_w4(const GemmArgs &a, const float *combine_w, hipStream_t
     p.out_f32 = a.out_f32;
     p.topk = a.topk;
     p.x_per_token = a.x_per_token;
+    p.logits = (const uint16_t *)a.logits;
+    p.ids_out = a.ids_out;
+    p.w_out = a.w_out;
+    p.renorm = a.renorm;
     p.qx = a.fmt == QARL_W4A8_G128;
     p.n_units = a.N / 32;
     const int G = a.K / kGroup, slots = epi == QARL_EPI_COMBINE ? a.topk : 1;

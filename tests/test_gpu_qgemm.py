@@ -781,3 +781,57 @@ def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows, tiled):
     if fmt == q.QARL_W4A16_G128:
         none = torch.empty((16,), dtype=torch.uint8, device="cuda")
         assert torch.equal(q.qarl_qgemm_grouped(qw, x, off, M, out_dtype=q.QARL_OUT_F32, ws=none), by[q.QARL_PATH_DECODE])
+
+
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
+@pytest.mark.parametrize("E,T,topk", [(64, 1, 1), (128, 1, 8), (192, 3, 5), (256, 8, 8), (128, 5, 16), (128, 40, 8)])
+def test_layer_in_one_call_equals_its_three_calls(q, fmt_name, E, T, topk):
+    """Few tokens: gate_up routes its tokens itself; many: the router is launched in front.  Bit for bit, ids and weights too,
+    equal logits included; also where an output lies on an input, which keeps the router's launch."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    H = I = 256
+    gu, dn = synth.expert_weights(E, H, I, seed=E + T, device="cuda")
+    gu, dn = q.qarl_quantize_weights(gu, fmt), q.qarl_quantize_weights(dn, fmt)
+    x = synth.normal_bf16((T, H), 1.0, seed=T, device="cuda")
+    lg = synth.router_logits(T, E, seed=E, device="cuda")
+    lg[:, 1::2] = lg[:, ::2]                                       # every logit twice: the lower id wins
+    for renorm in (1, 0):
+        r = q.qarl_moe_route(lg, topk, bool(renorm))
+        a = q.qarl_qgemm_routed(gu, x, r.ids, T, topk, True, epilogue=q.QARL_EPI_SILU_MUL)
+        want = q.qarl_qgemm_routed(dn, a, r.ids, T, topk, False, epilogue=q.QARL_EPI_COMBINE, combine_w=r.w)
+        for shared in (False, True):
+            ids = torch.full((T * topk,), -7, dtype=torch.int32, device="cuda")
+            w = torch.full((T * topk,), float("nan"), device="cuda")
+            got_a, out = torch.full_like(a, float("nan")), torch.full_like(want, float("nan"))
+            logits = lg.clone()
+            if shared:                                             # the ids are written over the logits they come from
+                if T * topk * 4 > logits.numel() * 2:
+                    continue
+                ids = logits.view(torch.int32).flatten()[:T * topk]
+            ws = torch.empty((max(q.qarl_qgemm_workspace_bytes(dn, T * topk, T * topk, q.QARL_EPI_COMBINE), 16),), dtype=torch.uint8, device="cuda")
+            q._check(q.lib().qarl_moe_layer_routed(q.C.byref(gu.desc), q.C.byref(dn.desc), x.data_ptr(), logits.data_ptr(), T, topk, renorm,
+                                                   ids.data_ptr(), w.data_ptr(), got_a.data_ptr(), out.data_ptr(), q.QARL_OUT_BF16,
+                                                   ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream))
+            assert torch.equal(ids, r.ids.flatten()) and torch.equal(w, r.w.flatten())
+            assert torch.equal(got_a, a) and torch.equal(out, want)
+    layer = q.MoELayer(gu, dn, T, topk, q.QARL_PATH_DECODE)
+    r = q.qarl_moe_route(lg, topk)
+    assert torch.equal(layer.forward(x, lg), q.qarl_qgemm_routed(dn, q.qarl_qgemm_routed(gu, x, r.ids, T, topk, True, epilogue=q.QARL_EPI_SILU_MUL),
+                                                                 r.ids, T, topk, False, epilogue=q.QARL_EPI_COMBINE, combine_w=r.w))
+
+
+def test_layer_in_one_call_errors(q):
+    gu, dn = synth.expert_weights(64, 256, 256, seed=1, device="cuda")
+    gu, dn = q.qarl_quantize_weights(gu), q.qarl_quantize_weights(dn)
+    t = torch.zeros((1 << 16,), dtype=torch.uint8, device="cuda")
+
+    def call(g, d, T, topk, logits=True, ws=t.numel()):
+        p = t.data_ptr()
+        with pytest.raises(q.QarlError) as ei:
+            q._check(q.lib().qarl_moe_layer_routed(q.C.byref(g.desc), q.C.byref(d.desc), p, p if logits else None, T, topk, 1, p, p, p, p, 0, p, ws, None))
+        return ei.value.status
+    assert call(dn, dn, 1, 8) == q.QARL_ERR_INVALID_ARG            # the second matrices do not follow the first
+    assert call(gu, dn, 1, 65) == q.QARL_ERR_UNSUPPORTED           # the router's limits
+    assert call(gu, dn, -1, 8) == q.QARL_ERR_INVALID_ARG
+    assert call(gu, dn, 1, 8, logits=False) == q.QARL_ERR_INVALID_ARG
+    assert call(gu, dn, 513, 1) == q.QARL_ERR_UNSUPPORTED          # the routed GEMMs' limits
