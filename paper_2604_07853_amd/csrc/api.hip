@@ -697,7 +697,7 @@ int qarl_token_logprob(const void *h_bf16, const void *w_lm_bf16, const int32_t 
         set_error("qarl_token_logprob: h and w_lm must be 16-byte aligned");
         return QARL_ERR_ALIGNMENT;
     }
-    const size_t need = qarl_logprob_workspace_bytes(T, H, V);
+    const size_t need = logprob_ws_least(T, V);
     if (need && (!ws || ws_bytes < need || !aligned16(ws))) {
         set_error("qarl_token_logprob: needs %zu bytes of 16-byte aligned workspace (got %zu)", need, ws_bytes);
         return QARL_ERR_WORKSPACE;
@@ -706,7 +706,7 @@ int qarl_token_logprob(const void *h_bf16, const void *w_lm_bf16, const int32_t 
         set_error("qarl_token_logprob: comparison outputs need ref_logprob");
         return QARL_ERR_INVALID_ARG;
     }
-    int rc = launch_logprob(h_bf16, w_lm_bf16, target, T, H, V, inv_temperature, logprob, ws, (hipStream_t)stream);
+    int rc = launch_logprob(h_bf16, w_lm_bf16, target, T, H, V, inv_temperature, logprob, ws, ws_bytes, (hipStream_t)stream);
     if (rc) return rc;
     if (ref_logprob && (delta || seq_w || seq_w_clipped))
         return qarl_logprob_mismatch(logprob, ref_logprob, T, seq_offsets, S, tis_cap_c, delta, nullptr, seq_w,

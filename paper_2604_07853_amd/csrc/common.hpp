@@ -377,8 +377,9 @@ int launch_group_sums(const void *x_bf16, int64_t rows, int K, float *sums, hipS
 int launch_combine(const float *y_pair_order, const float *w, const int32_t *ids, int E, int T, int topk, int N, void *out,
                    int out_f32, hipStream_t s);
 int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T, int H, int V,
-                   float inv_temp, float *logprob, void *ws, hipStream_t s);
+                   float inv_temp, float *logprob, void *ws, size_t ws_bytes, hipStream_t s);
 size_t logprob_ws_bytes(int T, int H, int V);
+size_t logprob_ws_least(int T, int V);   // enough for every call; up to 128 tokens the size above lets more CUs take part
 // Device address, on the current device, of the library's own file-scope scratch array (kLogprobScratchBytes).
 constexpr size_t kLogprobScratchBytes = (size_t)4 << 20;
 int logprob_static_scratch(void **ptr);

@@ -542,12 +542,16 @@ int launch_lmhead_stream(const LogprobStreamParams &p, hipStream_t s)
     return check_hip(hipGetLastError(), "lmhead_stream_kernel");
 }
 
-int launch_logprob_stream(LogprobStreamParams p, const int32_t *target, float *logprob, void *ws, hipStream_t s)
+// Ranges of the streaming path: one per CU, none below 64 rows.
+static int stream_ranges(int V) { return (int)min((int64_t)256, ((int64_t)V + 63) / 64); }
+
+int launch_logprob_stream(LogprobStreamParams p, const int32_t *target, float *logprob, void *ws, size_t ws_bytes, hipStream_t s)
 {
-    // one workgroup per CU, but no more partials per token than the workspace of the tiled kernel holds
+    // a workspace of the least size holds a partial per token and tile column: 126 ranges for 32003 rows, which took
+    // 31 us for one token (H = 2048) and 27 on 251
     const int64_t units = ((int64_t)p.V + 7) / 8;
     const int tok = p.T <= 32 ? 32 : p.T <= 64 ? 64 : 128;
-    p.n_ranges = (int)min((int64_t)256, ((int64_t)p.V + kLTile - 1) / kLTile);
+    p.n_ranges = (int)min((int64_t)stream_ranges(p.V), (int64_t)(ws_bytes / (2 * sizeof(float) * (size_t)p.T)));
     p.passes = (int)((units + (int64_t)p.n_ranges * 32 - 1) / ((int64_t)p.n_ranges * 32));   // at most 32 units per tile
     p.rows8 = (int)((units + (int64_t)p.n_ranges * p.passes - 1) / ((int64_t)p.n_ranges * p.passes));
     p.pmax = (float *)ws;
@@ -562,15 +566,17 @@ int launch_logprob_stream(LogprobStreamParams p, const int32_t *target, float *l
     return check_hip(hipGetLastError(), "lse_stream_finalize_kernel");
 }
 
+size_t logprob_ws_least(int T, int V) { return (2 * ((size_t)(V + kLTile - 1) / kLTile) + 1) * (size_t)T * sizeof(float); }
+
 size_t logprob_ws_bytes(int T, int H, int V)
 {
     (void)H;
-    const size_t nb = (size_t)(V + kLTile - 1) / kLTile;
-    return (2 * nb + 1) * (size_t)T * sizeof(float);
+    const size_t least = logprob_ws_least(T, V);
+    return T <= kSMaxTok ? max(least, 2 * (size_t)stream_ranges(V) * T * sizeof(float)) : least;
 }
 
 int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T, int H, int V, float inv_temp,
-                   float *logprob, void *ws, hipStream_t s)
+                   float *logprob, void *ws, size_t ws_bytes, hipStream_t s)
 {
     LogprobParams p;
     p.h = (const uint16_t *)h;
@@ -603,7 +609,7 @@ int launch_logprob(const void *h, const void *wlm, const int32_t *target, int T,
         q.H = H;
         q.V = V;
         q.inv_temp = inv_temp;
-        return launch_logprob_stream(q, target, logprob, ws, s);
+        return launch_logprob_stream(q, target, logprob, ws, ws_bytes, s);
     }
     const int64_t tiles = (int64_t)p.m_tiles * p.n_blocks;
     if (tiles > 0x7ffffff0LL) {

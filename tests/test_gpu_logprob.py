@@ -123,3 +123,21 @@ def test_logprob_written_over_its_own_inputs(q):
     buf[1:] = tg
     got = q.qarl_token_logprob_static(h, w, buf[1:], buf.view(torch.float32)[:T])
     assert (got - want).abs().max().item() <= TOL_LP
+
+
+@pytest.mark.parametrize("T,H,V", [(1, 64, 63), (128, 128, 65), (33, 64, 4100), (61, 128, 16385), (64, 64, 32003), (128, 64, 65537)])
+def test_logprob_by_workspace(q, oracle, T, H, V):
+    """Up to 128 tokens the workspace decides how many ranges of the vocabulary are streamed side by side: the size the query
+    names, the least a call takes (a partial per token and 256 rows), and less, which is refused."""
+    h, w, tg = synth.normal_bf16((T, H), 1.0, seed=T), synth.normal_bf16((V, H), 0.3, seed=V), synth.targets(T, V, seed=3)
+    tg[0], tg[-1] = 0, V - 1
+    ref = oracle.token_logprob(np_bits(h), np_bits(w), tg.numpy(), 1.0)
+    least = (2 * ((V + 255) // 256) + 1) * T * 4
+    for n in (q.qarl_logprob_workspace_bytes(T, H, V), least):
+        ws = torch.full((n + 256,), 255, dtype=torch.uint8, device="cuda")
+        got = q.qarl_token_logprob(h.cuda(), w.cuda(), tg.cuda(), ws=ws[:n])["logprob"].cpu().numpy().astype(np.float64)
+        assert np.abs(got - ref).max() <= TOL_LP * max(1.0, np.abs(ref).max() / 10)
+        assert bool((ws[n:] == 255).all())
+    with pytest.raises(q.QarlError) as ei:
+        q.qarl_token_logprob(h.cuda(), w.cuda(), tg.cuda(), ws=ws[:least - 4])
+    assert ei.value.status == q.QARL_ERR_WORKSPACE
