@@ -413,9 +413,12 @@ static int launch_fp8_cfg(const GemmArgs &a, hipStream_t s)
     p.out_f32 = a.out_f32;
     p.n_blocks = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2 + kFTN / 2 - 1) / (kFTN / 2) : (a.N + kFTN - 1) / kFTN;
     const int64_t slots = (a.M + kFTM - 1) / kFTM + a.E;
-    // a workgroup computes bpw neighbouring column blocks of its token tile one after the other: the expert
-    // lookup and the row gather are paid once, and a block's stores hide the first copies of the next
-    p.bpw = p.n_blocks >= 6 ? 3 : (p.n_blocks >= 2 ? 2 : 1);
+    // A workgroup computes bpw neighbouring column blocks of its token tile one after the other: the expert
+    // lookup and the row gather are paid once, and a block's stores hide the first copies of the next.  Not for the wide plain
+    // epilogue (the down projection): its blocks are short (768: six stages) next to their stores, and chains of three make a coarse last
+    // round.  N = 2048, K = 768, 128 experts, three blocks -> one, us: FP8 600 / 1024 / 2048 / 8192 / 16384 tokens 71 / 73 / 95 / 248 / 437 ->
+    // 62 / 63 / 81 / 231 / 428, FP4 56 / 60 / 84 / 213 / 359 -> 46 / 49 / 67 / 201 / 366; four blocks (N = 1024) are as fast in pairs.
+    p.bpw = p.n_blocks >= 6 ? (EPI == QARL_EPI_SILU_MUL ? 3 : 1) : (p.n_blocks >= 2 ? 2 : 1);
     p.n_bgroups = (p.n_blocks + p.bpw - 1) / p.bpw;
     const int64_t total = ((slots * p.n_bgroups + 7) / 8) * 8;
     if (total > 0x7fffffffLL) {
