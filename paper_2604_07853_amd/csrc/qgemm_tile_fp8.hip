@@ -415,10 +415,13 @@ static int launch_fp8_cfg(const GemmArgs &a, hipStream_t s)
     const int64_t slots = (a.M + kFTM - 1) / kFTM + a.E;
     // A workgroup computes bpw neighbouring column blocks of its token tile one after the other: the expert
     // lookup and the row gather are paid once, and a block's stores hide the first copies of the next.  Not for the wide plain
-    // epilogue (the down projection): its blocks are short (768: six stages) next to their stores, and chains of three make a coarse last
-    // round.  N = 2048, K = 768, 128 experts, three blocks -> one, us: FP8 600 / 1024 / 2048 / 8192 / 16384 tokens 71 / 73 / 95 / 248 / 437 ->
-    // 62 / 63 / 81 / 231 / 428, FP4 56 / 60 / 84 / 213 / 359 -> 46 / 49 / 67 / 201 / 366; four blocks (N = 1024) are as fast in pairs.
-    p.bpw = p.n_blocks >= 6 ? (EPI == QARL_EPI_SILU_MUL ? 3 : 1) : (p.n_blocks >= 2 ? 2 : 1);
+    // epilogue (the down projection) of up to 640 rows per expert: its blocks are short (768: six stages) next to their stores, and
+    // chains of three make a coarse last round.  N = 2048, K = 768, 128 experts, even / Zipf router, three blocks -> one, us: FP8 1024 tokens
+    // 73 / 68 -> 63 / 64, 2048 95 / 95 -> 81 / 86, 8192 248 / 240 -> 231 / 229, 16384 437 / 420 -> 428 / 424 (a layer of 13905, Zipf,
+    // 1028 -> 1048), FP4 60 / 56 -> 49 / 50, 84 / 84 -> 67 / 73, 213 / 212 -> 201 / 208, 359 / 379 -> 366 / 371; four blocks (N = 1024) are as
+    // fast in pairs.
+    const bool single = EPI != QARL_EPI_SILU_MUL && p.n_blocks >= 6 && a.M <= (int64_t)a.E * 640;
+    p.bpw = single ? 1 : p.n_blocks >= 6 ? 3 : (p.n_blocks >= 2 ? 2 : 1);
     p.n_bgroups = (p.n_blocks + p.bpw - 1) / p.bpw;
     const int64_t total = ((slots * p.n_bgroups + 7) / 8) * 8;
     if (total > 0x7fffffffLL) {
