@@ -92,7 +92,8 @@ const char *qarl_last_error(void);
 /* Bytes of `ws` that qarl_qgemm_grouped may need for a call with these weights, x_rows activation
  * rows, M problem rows and this epilogue, whichever path runs: fp32 staging of Y [M][N] for COMBINE,
  * plus, for W4A16, one fp32 sum per activation row and 128-k scale group (the prefill path computes
- * them once per call).  qarl_token_logprob has its own query. */
+ * them once per call).  qarl_token_logprob has its own query; for few tokens and small vocabularies it asks for
+ * more than the call needs at least (a partial per token and 256 vocabulary rows), with which it is faster. */
 size_t qarl_qgemm_workspace_bytes(const qarl_qweight *W, int64_t x_rows, int64_t M, int epilogue);
 size_t qarl_logprob_workspace_bytes(int T, int H, int V);
 
