@@ -286,9 +286,12 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float *__restri
 // (kTok / rows of the W bytes).  Copies of rows past T are not issued: what the LDS holds there only reaches columns
 // that no one reads.  The running (max, sum) of the workgroup's rows stays in LDS over its tiles: one partial per
 // token and workgroup, so the merge is one wavefront per token, which computes the target logit as well.
-// 151936 x 2048, whole call: 1 token 456 -> 103 us (6.0 TB/s), 61 tokens 484 -> 104-123 us, 128 tokens 497 -> 140 us
-// (bound by the compute phase between two barriers, no longer by the stream; beyond that the 256 x 256 tiles, which
-// take 210 us for 129 to 256 tokens, are as good: two 128-token tiles here took 220-230).
+// Operand reads run one slice ahead of the matrix instructions, across the stage barrier: 128 tokens 137-140 -> 131 us,
+// 61 tokens of a 32003-row vocabulary 28.9 -> 27.0.
+// 151936 x 2048, whole call: 1 token 456 -> 99 us (6.3 TB/s), 61 tokens 484 -> 103 us, 128 tokens 497 -> 130 us (the rows of
+// h, once per tile, are two thirds of the W bytes there: 8.4 TB/s of copies).  Beyond that the 256 x 256 tiles, which take
+// 206-209 us for 129 to 256 tokens, are as good: two 128-token tiles here took 220-230, tiles of 120 rows x 256 tokens
+// 200-219 (32003 rows 49-50 -> 44-47, 65000 x 1024 42-46 -> 46-48).
 constexpr int kSWaves = 8, kSMaxTok = 128;
 
 struct LogprobStreamParams {
@@ -416,6 +419,26 @@ __global__ __launch_bounds__(64 * kSWaves, 2) void lmhead_stream_kernel(LogprobS
 #pragma unroll
     for (int b = 0; b < kSBufs - 1; ++b)
         if (b < total) copy_stage(b);
+    // Operands of a slice, and of the slice before: reads run one slice ahead of the matrix instructions, across the stage
+    // barrier as well (a stage's last slice is multiplied behind the next barrier, under the first reads of that stage).
+    struct Frags {
+        bf16x8 a[MS], b[NT];
+    };
+    Frags f[2];
+    auto clear_last = [&]() {
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms) f[1].a[ms] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) f[1].b[nt] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    };
+    auto multiply = [&](const Frags &g) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms)
+                acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g.a[ms], g.b[nt], acc[ms][nt], 0, 0, 0);
+    };
+    clear_last();
     int ks = 0, tile = 0, buf = 0;
     for (int s = 0; s < total; ++s) {
         // stage s has landed: at most the copies of the kSBufs - 2 stages behind it are still on their way
@@ -428,22 +451,20 @@ __global__ __launch_bounds__(64 * kSWaves, 2) void lmhead_stream_kernel(LogprobS
         const unsigned char *bbase = ring + buf * stage_b + (rows + wt * NT * 32) * kLRowB;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+            if (busy) {
+                Frags &g = f[j & 1];
+#pragma unroll
+                for (int ms = 0; ms < MS; ++ms) g.a[ms] = *(const bf16x8 *)(abase + ms * 32 * kLRowB + aoff[j]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) g.b[nt] = *(const bf16x8 *)(bbase + nt * 32 * kLRowB + aoff[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(f[(j & 1) ^ 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (more) {   // the copies go out between the matrix instructions (128 tokens: 2-3 % faster than all in front)
 #pragma unroll
                 for (int i = 2 * j; i < 2 * j + 2; ++i)
                     if (i < 4 + kHCopies) copy_one(nbuf, i);
-            }
-            if (busy) {
-                bf16x8 a[MS];
-#pragma unroll
-                for (int ms = 0; ms < MS; ++ms) a[ms] = *(const bf16x8 *)(abase + ms * 32 * kLRowB + aoff[j]);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const bf16x8 b = *(const bf16x8 *)(bbase + nt * 32 * kLRowB + aoff[j]);
-#pragma unroll
-                    for (int ms = 0; ms < MS; ++ms)
-                        acc[ms][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ms], b, acc[ms][nt], 0, 0, 0);
-                }
             }
         }
         if (more) advance();
@@ -451,6 +472,8 @@ __global__ __launch_bounds__(64 * kSWaves, 2) void lmhead_stream_kernel(LogprobS
         if (++ks == stages) {
             // end of a tile: lane (c, h), register i of acc[ms][nt] -> row 32 (MS wm + ms) + 8 (i / 4) + 4 h + i % 4,
             // token 32 (NT wt + nt) + c
+            if (busy) multiply(f[1]);
+            clear_last();
             const int valid = (int)min((int64_t)rows, (int64_t)V - (first + (int64_t)tile * rows));
             const int row_lane = wm * MS * 32 + 4 * h;
 #pragma unroll
