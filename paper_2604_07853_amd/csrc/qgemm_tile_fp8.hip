@@ -8,16 +8,23 @@
 // operand and the tokens its column operand, so a lane ends up with four consecutive output columns of ONE
 // token per register quad: results leave in 16-byte (fp32) or 8-byte (bf16) stores, and the gate and up value
 // of a column meet in the same lane.  Token rows (gathered through row_map) and weight rows reach LDS by
-// asynchronous global -> LDS copies, three 128-k stages deep; 16-byte chunks of a row are XOR-swizzled with
-// the row index so that the copies (8 rows x 128 bytes per wavefront instruction) and the operand reads
-// (32 rows, one chunk) are free of bank conflicts.  The operand reads of half a stage run under the MFMAs
-// of the half before, across the stage barrier as well; the six (four) copy instructions of a stage are
-// issued one by one between its MFMAs, so that a wavefront that waits for room in the memory pipeline
-// waits while its matrix instructions execute.
+// asynchronous global -> LDS copies; 16-byte chunks of a row are XOR-swizzled with the row index so that the copies
+// (16 rows x 64 bytes per wavefront instruction) and the operand reads (32 rows, one chunk) are free of bank conflicts.
+//
+// Two workgroups share a CU (76 KiB of LDS and at most 128 registers each): three 64-k stages, one set of operand registers, a plain loop.
+// Copies, operand reads and matrix instructions of ONE workgroup add up instead of overlapping, whatever the tile and the
+// depth of its pipeline, and a third of a launch was lookups, first stages and epilogues; another workgroup on the same SIMDs fills
+// all of these.  The matrix instructions run at raised wave priority (large calls 1-2 % faster) with the stage's copies
+// between them (large FP4 calls 2 %), and the first weight rows are requested before the token rows' ids are known (FP8 1-2 %).
+// Against one workgroup per CU with three 128-k stages, operand reads half a stage ahead, and chains of up to three column
+// blocks per workgroup (which are slower here, 8192 tokens 664 -> 687 us), layers of 128 experts 2048 x 768, top-8, even / Zipf router, us:
+// FP8 600 tokens 168 / 151 -> 162 / 149, 1024 183 / 210 -> 181 / 182, 4096 394 / 398 -> 378 / 388, 8192 677 / 662 -> 653 / 648, 16384
+// 1238 / 1190 -> 1198 / 1190; FP4 600 128 / 111 -> 120 / 104, 1024 142 / 167 -> 136 / 135, 4096 353 / 358 -> 312 / 324, 8192 625 / 616 -> 558 / 566,
+// 16384 1162 / 1153 -> 1086 / 1076; 64 experts 1024 x 512, top-4, 8192 tokens FP8 175 -> 155, FP4 171 -> 146.
 //
 // FP4 weights (W4 = true) take the same kernel: the instruction reads e2m1 codes natively in its first
 // operand (format select 4), 16 bytes per lane instead of 32.  A weight row then has 64 bytes per stage
-// (four chunks, swizzled with (row >> 2) & 3), a stage is 32 KiB instead of 48, and no e4m3 copy of the
+// (four chunks, swizzled with (row >> 2) & 3) of 128 k, two stages of 32 KiB fill the same space, and no e4m3 copy of the
 // weights is ever written.  The library packs the eight codes of a word as (element b, element 4 + b) in
 // byte b; the instruction pairs nibble n of its first operand with byte n of the second within a group of
 // 16 k, so the token bytes of every 8-byte group are put into the order 0 4 1 5 2 6 3 7 after their LDS
@@ -30,9 +37,10 @@ namespace qarl {
 
 constexpr int kFThreads = 512;
 constexpr int kFTM = 128, kFTN = 256;        // token rows, weight rows per workgroup
-constexpr int kFKS = 128;                    // k per stage (= bytes of an e4m3 row; an e2m1 row has 64)
-constexpr int kFStages = 3;
-__host__ __device__ constexpr int stage_bytes(bool w4) { return kFTM * kFKS + kFTN * (w4 ? kFKS / 2 : kFKS); }
+constexpr int kWRowB = 64;                   // bytes of a weight row per stage
+__host__ __device__ constexpr int stage_k(bool w4) { return w4 ? 128 : 64; }   // = bytes of a token row
+__host__ __device__ constexpr int stage_bytes(bool w4) { return kFTM * stage_k(w4) + kFTN * kWRowB; }
+__host__ __device__ constexpr int stage_count(bool w4) { return w4 ? 2 : 3; }
 
 struct Tile8Params {
     const unsigned char *codes;   // [E][N][K] e4m3, or [E][N][K/2] packed e2m1
@@ -45,47 +53,44 @@ struct Tile8Params {
     void *out;
     int E, N, K, out_f32;
     int n_blocks;   // column blocks per expert
-    int bpw;        // consecutive column blocks one workgroup computes
-    int n_bgroups;  // ceil(n_blocks / bpw)
 };
 
 template <int EPI, bool W4>
-__global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Params p)
+__global__ __launch_bounds__(kFThreads, 4) void qgemm_tile_fp8_kernel(Tile8Params p)
 {
     constexpr int kFStageB = stage_bytes(W4);
-    constexpr int kWRowB = W4 ? kFKS / 2 : kFKS;   // bytes of a weight row per stage
-    constexpr int kWCopies = W4 ? 2 : 4;           // copy instructions per wavefront and stage for the weight rows
+    constexpr int kFKS = stage_k(W4), kStages = stage_count(W4);
+    constexpr int kACopies = W4 ? 2 : 1, kWCopies = 2;   // copy instructions per wavefront and stage
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr bool kSilu = (EPI == QARL_EPI_SILU_MUL);
     __shared__ __attribute__((aligned(16))) int s_rows[kFTM];
     __shared__ __attribute__((aligned(16))) int s_orow[kFTM];
     __shared__ __attribute__((aligned(16))) float s_xs[kFTM];
-    __shared__ __attribute__((aligned(16))) float s_wn[2][kFTN];   // channel scale of every LDS weight row, per column block parity
+    __shared__ __attribute__((aligned(16))) float s_wn[kFTN];   // channel scale of every LDS weight row
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int c = lane & 31, h = lane >> 5;
 
     GroupedTile tile;
-    if (!find_grouped_tile<kFTM>(p.offsets, p.E, p.n_bgroups, tile)) return;
-    const int e = tile.e, nb0 = tile.block * p.bpw;
+    if (!find_grouped_tile<kFTM>(p.offsets, p.E, p.n_blocks, tile)) return;
+    const int e = tile.e, nb = tile.block;
     const int row0 = p.offsets[e] + tile.mtile * kFTM;
     const int mrem = min(kFTM, p.offsets[e + 1] - row0);
+    // row ids (their loads go out in front of the weight copies below)
+    int xrow = 0, orow_g = -1;
     if (tid < kFTM) {
         // rows past the expert's end read the tile's first row (valid data, results never stored)
         const int i = row0 + (tid < mrem ? tid : 0);
-        const int xrow = p.row_map ? p.row_map[i] : i;
-        s_rows[tid] = xrow;
-        s_orow[tid] = tid < mrem ? (p.out_row_map ? p.out_row_map[i] : i) : -1;
-        s_xs[tid] = p.x_scales[xrow];
+        xrow = p.row_map ? p.row_map[i] : i;
+        orow_g = tid < mrem ? (p.out_row_map ? p.out_row_map[i] : i) : -1;
     }
-    lds_barrier();
 
     const int N = p.N, K = p.K;
     // LDS weight row rho (0..255) of this workgroup -> weight row of the expert.  SILU_MUL: every 32-row
     // tile holds 16 gate rows then the 16 matching up rows, so gate j and up j sit 16 lanes apart in the
     // MFMA result.  Rows past N read row 0 (valid data, results never stored).
-    auto weight_row = [&](int nb, int rho) -> int {
+    auto weight_row = [&](int rho) -> int {
         int n;
         bool ok;
         if (kSilu) {
@@ -99,61 +104,69 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
         return ok ? n : 0;
     };
 
-    // ---- copies: a wavefront instruction moves 8 rows x 128 bytes.  Chunk q of row r sits at
-    // r * 128 + (q ^ ((r >> 1) & 7)) * 16.  This wavefront copies token rows [16 w, 16 w + 16) and weight
-    // rows [32 w, 32 w + 32) of the tile.
-    const unsigned char *aptr[2];
+    // ---- copies: a wavefront instruction moves 16 rows x 64 bytes (token rows of an FP4 stage: 8 x 128).  Chunk q of row r sits at
+    // r * 64 + (q ^ ((r >> 2) & 3)) * 16 (r * 128 + (q ^ ((r >> 1) & 7)) * 16).  This wavefront copies token rows
+    // [16 w, 16 w + 16) and weight rows [32 w, 32 w + 32) of the tile.
+    const unsigned char *aptr[kACopies];
     uint32_t boff[kWCopies];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = wave * 16 + i * 8 + (lane >> 3);
-        const int q = (lane & 7) ^ ((r >> 1) & 7);
-        aptr[i] = p.x + (int64_t)s_rows[r] * K + q * 16;
+    for (int i = 0; i < kWCopies; ++i) {
+        const int r = wave * 32 + i * 16 + (lane >> 2);
+        const int q = (lane & 3) ^ ((r >> 2) & 3);
+        boff[i] = (uint32_t)weight_row(r) * (uint32_t)(W4 ? K / 2 : K) + q * 16;
     }
-    uint32_t soff = 0;   // weight row whose scale this lane copies: LDS row 64 (wave % 4) + lane
-    auto set_block = [&](int nb) {
-#pragma unroll
-        for (int i = 0; i < kWCopies; ++i) {
-            if (W4) {   // 16 rows x 64 bytes per instruction
-                const int r = wave * 32 + i * 16 + (lane >> 2);
-                const int q = (lane & 3) ^ ((r >> 2) & 3);
-                boff[i] = (uint32_t)weight_row(nb, r) * (uint32_t)(K / 2) + q * 16;
-            } else {
-                const int r = wave * 32 + i * 8 + (lane >> 3);
-                const int q = (lane & 7) ^ ((r >> 1) & 7);
-                boff[i] = (uint32_t)weight_row(nb, r) * (uint32_t)K + q * 16;
-            }
-        }
-        soff = (uint32_t)weight_row(nb, (wave & 3) * 64 + lane);
-    };
-    set_block(nb0);
     const unsigned char *wbase = p.codes + (int64_t)e * N * (W4 ? K / 2 : K);
     const float *sbase = p.scales + (int64_t)e * N;
-    // copy number j (0 .. 1 + kWCopies) of stage ks into buffer buf: two token copies, then the weight copies
+    // copy j of the wavefront's kACopies + kWCopies of stage ks into buffer buf
     auto copy_one = [&](int ks, int buf, int j) {
         unsigned char *dst = smem + buf * kFStageB;
-        if (j < 2) copy16_to_lds(aptr[j] + ks * kFKS, dst + (wave * 16 + j * 8) * kFKS);
-        else copy16_to_lds(wbase + (int64_t)ks * kWRowB + boff[j - 2], dst + kFTM * kFKS + (wave * 32) * kWRowB + (j - 2) * 1024);
+        if (j < kACopies) copy16_to_lds(aptr[j] + ks * kFKS, dst + wave * 16 * kFKS + j * 1024);
+        else copy16_to_lds(wbase + (int64_t)ks * kWRowB + boff[j - kACopies], dst + kFTM * kFKS + wave * 32 * kWRowB + (j - kACopies) * 1024);
     };
-    auto copy_stage = [&](int ks, int buf) {
+    const int stages = K / kFKS;
+    // the block's 256 channel scales, 4 bytes per lane (wavefronts w and w + 4 copy the same 64), and the weight rows of the first
+    // stages: they wait for no row id
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(sbase + weight_row((wave & 3) * 64 + lane)),
+                                     (__attribute__((address_space(3))) void *)(&s_wn[(wave & 3) * 64]), 4, 0, 0);
 #pragma unroll
-        for (int j = 0; j < 2 + kWCopies; ++j) copy_one(ks, buf, j);
-    };
+    for (int ks = 0; ks < kStages - 1; ++ks)
+        if (ks < stages)
+#pragma unroll
+            for (int j = 0; j < kWCopies; ++j) copy_one(ks, ks, kACopies + j);
+    if (tid < kFTM) {
+        s_rows[tid] = xrow;
+        s_orow[tid] = orow_g;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p.x_scales + xrow),
+                                         (__attribute__((address_space(3))) void *)(&s_xs[wave * 64]), 4, 0, 0);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < kACopies; ++i) {
+        const int r = W4 ? wave * 16 + i * 8 + (lane >> 3) : wave * 16 + (lane >> 2);
+        const int q = W4 ? (lane & 7) ^ ((r >> 1) & 7) : (lane & 3) ^ ((r >> 2) & 3);
+        aptr[i] = p.x + (int64_t)s_rows[r] * K + q * 16;
+    }
+#pragma unroll
+    for (int ks = 0; ks < kStages - 1; ++ks)
+        if (ks < stages)
+#pragma unroll
+            for (int j = 0; j < kACopies; ++j) copy_one(ks, ks, j);
 
-    // ---- operand reads: v_mfma_f32_32x32x64_f8f6f4 takes 32 bytes per lane and operand: lane (c,h), half t of
-    // the stage -> row c, bytes [64 t + 32 h, +32) = chunks 4t + 2h and 4t + 2h + 1 (both operands split k alike)
-    // e2m1 weights: 16 bytes per lane, chunk 2 t + h of the row's four
-    int foff[4], woff[2];
+    // ---- operand reads: v_mfma_f32_32x32x64_f8f6f4 takes 32 bytes per lane and operand: lane (c,h) -> row c, bytes [32 h, +32) =
+    // chunks 2h and 2h + 1 (both operands split k alike).  e2m1 weights: 16 bytes per lane, chunk 2 t + h of the row's
+    // four in half t of the stage
+    constexpr int kHalves = kFKS / 64;
+    int foff[kHalves * 2], woff[kHalves];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < kHalves; ++t) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             // e2m1 first operand: the instruction pairs its lane h with bytes [16 h, 16 h + 16) of the second operand's
             // lanes 0 and 1 (measured), so the token lanes take the 16-byte chunks h and 2 + h of the half stage
-            const int chunk = W4 ? 4 * t + h + 2 * u : 4 * t + 2 * h + u;
-            foff[t * 2 + u] = c * kFKS + ((chunk ^ ((c >> 1) & 7)) * 16);
+            const int chunk = W4 ? 4 * t + h + 2 * u : 2 * h + u;
+            foff[t * 2 + u] = c * kFKS + ((chunk ^ (W4 ? (c >> 1) & 7 : (c >> 2) & 3)) * 16);
         }
-        woff[t] = c * (kFKS / 2) + (((2 * t + h) ^ ((c >> 2) & 3)) * 16);
+        woff[t] = c * kWRowB + (((2 * t + h) ^ ((c >> 2) & 3)) * 16);
     }
     const int a_wave = wm * 64 * kFKS, b_wave = kFTM * kFKS + wn * 64 * kWRowB;
     struct Frags {
@@ -173,8 +186,8 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
                 const u32x4 lo = *(const u32x4 *)(base + woff[t] + b_wave + nt * 32 * kWRowB);
                 f.b[nt] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], 0, 0, 0, 0};
             } else {
-                const u32x4 lo = *(const u32x4 *)(base + foff[t * 2] + b_wave + nt * 32 * kFKS);
-                const u32x4 hi = *(const u32x4 *)(base + foff[t * 2 + 1] + b_wave + nt * 32 * kFKS);
+                const u32x4 lo = *(const u32x4 *)(base + foff[t * 2] + b_wave + nt * 32 * kWRowB);
+                const u32x4 hi = *(const u32x4 *)(base + foff[t * 2 + 1] + b_wave + nt * 32 * kWRowB);
                 f.b[nt] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             }
         }
@@ -203,109 +216,34 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
     auto mfma1 = [&](const Frags &f, int ms, int nt) {
         acc[ms][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f.b[nt], f.a[ms], acc[ms][nt], W4 ? 4 : 0, 0, 0, 0, 0, 0);
     };
-    auto mfma4 = [&](const Frags &f) {
-#pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) mfma1(f, ms, nt);
-    };
-
-    // Rotated loop (see logprob.hip): the MFMAs of a stage's last group run in the next trip, behind the
-    // stage barrier and under the first operand reads of the next stage.  The copies of stage s + 2 are
-    // issued during stage s into the buffer stage s - 1 has just left; the wait before the barrier
-    // leaves exactly those six (e2m1 weights: four) copies in flight.
-    constexpr int kCopies = 2 + kWCopies;
-    auto wait_stage = [&]() {   // all but the newest stage's copies have landed, own LDS reads are done; then the barrier
-        if (W4) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    };
-    const int stages = K / kFKS;
-    Frags last, g0, g1;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        last.a[i] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
-        last.b[i] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
-    // First two stages of a column block into buffers 0 and 1; in front of them the block's 256 channel
-    // scales, 4 bytes per lane (wavefronts w and w + 4 copy the same 64), into the half of s_wn the block's
-    // parity selects.  They are older than every stage copy, so each counted wait below covers them.
-    auto start_block = [&](int par) {
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(sbase + soff),
-                                         (__attribute__((address_space(3))) void *)(&s_wn[par][(wave & 3) * 64]), 4, 0, 0);
-        copy_stage(0, 0);
-        if (stages > 1) copy_stage(1, 1);
-    };
-    start_block(0);
-  for (int bi = 0; bi < p.bpw && nb0 + bi < p.n_blocks; ++bi) {
-    const int nb = nb0 + bi;
-    if (stages > 1)
-        wait_stage();   // stage 0 has landed (stores of the block before too)
-    else
-        copy_barrier();
-#pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[ms][nt][i] = 0.f;
     int buf = 0;
     for (int ks = 0; ks < stages; ++ks) {
-        const bool more = ks + 2 < stages;
-        const int nbuf = buf == 0 ? 2 : buf - 1;
-        // one MFMA, the operand reads of the next half, then MFMA and copy in turns
-        read_frags(g0, buf, 0);
-        mfma1(last, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, W4 ? 6 : 8, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(last, 0, 1);
-        if (more) copy_one(ks + 2, nbuf, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(last, 1, 0);
-        if (more) copy_one(ks + 2, nbuf, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(last, 1, 1);
-        if (more) copy_one(ks + 2, nbuf, 2);
-        pair_tokens(g0);
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(g1, buf, 1);
-        mfma1(g0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, W4 ? 6 : 8, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(g0, 0, 1);
-        if (more) copy_one(ks + 2, nbuf, 3);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(g0, 1, 0);
-        if (more && kCopies > 4) copy_one(ks + 2, nbuf, 4);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma1(g0, 1, 1);
-        if (more && kCopies > 4) copy_one(ks + 2, nbuf, 5);
-        pair_tokens(g1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (more)
-            wait_stage();
-        else
-            copy_barrier();
-        last = g1;
-        buf = buf == 2 ? 0 : buf + 1;
-    }
-    mfma4(last);
+        // stage ks has landed (the one behind it may be on its way) and stage ks - 1 is no longer read
+        if (kStages == 2 || ks + 1 == stages) copy_barrier();
+        else if (ks == 0) asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // stage 1's token copy
+        else asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");               // the stage's three
+        const bool more = ks + kStages - 1 < stages;
+        const int nbuf = buf == 0 ? kStages - 1 : buf - 1;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        last.a[i] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
-        last.b[i] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int t = 0; t < kHalves; ++t) {
+            Frags f;
+            read_frags(f, buf, t);
+            pair_tokens(f);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (t == 0 && more && i < kACopies + kWCopies) copy_one(ks + kStages - 1, nbuf, i);
+                mfma1(f, i >> 1, i & 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_setprio(0);
+        }
+        buf = buf == kStages - 1 ? 0 : buf + 1;
     }
+    lds_barrier();   // no stage buffer is read any more
 
     // ---- epilogue: lane (c,h), register i of acc[ms][nt] -> token row 64 wm + 32 ms + c, LDS weight row
     // 64 wn + 32 nt + 8 (i/4) + 4 h + i%4: four consecutive rows, i.e. output columns, per register quad.
-    // The first copies of the next column block are issued first (every buffer is free after the last
-    // barrier), so they travel while this block's results are scaled and stored.
-    if (bi + 1 < p.bpw && nb + 1 < p.n_blocks) {
-        set_block(nb + 1);
-        start_block((bi + 1) & 1);
-    }
-    const float *wsc = s_wn[bi & 1];
     const int ncols = kSilu ? N / 2 : N;
     const int esz = (kSilu || !p.out_f32) ? 2 : 4;
     const uint32_t rstride = (uint32_t)ncols * (uint32_t)esz;
@@ -325,7 +263,7 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
 #pragma unroll
                 for (int a4 = 0; a4 < 2; ++a4) {
                     const int r = 8 * a4 + 4 * h;
-                    const f32x4 sg = *(const f32x4 *)(wsc + rho0 + r), su = *(const f32x4 *)(wsc + rho0 + 16 + r);
+                    const f32x4 sg = *(const f32x4 *)(s_wn + rho0 + r), su = *(const f32x4 *)(s_wn + rho0 + 16 + r);
                     u32x2 o;
 #pragma unroll
                     for (int b2 = 0; b2 < 2; ++b2) {
@@ -344,24 +282,19 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
             } else {
                 const int ocol0 = nb * kFTN + rho0;
                 const bool tile_ok = ocol0 + 32 <= N;
-                // The 32 x 32 tile (lane: one token, four consecutive columns per register quad) turns through
-                // this wavefront's 4 KiB of the third stage buffer, which the next block's first copies leave
-                // alone, and leaves as 16-byte pieces of whole 128-byte row segments.  Chunks are XOR-swizzled
-                // with the row; the stores are written so that the compiler does not see them (in front of a
-                // visible LDS store it would drain the copies in flight for the next block).
-                unsigned char *ot = smem + 2 * kFStageB + wave * 4096;   // 32 KiB: fits the third stage buffer of either format
-                const uint32_t ot_a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)ot;
+                // The 32 x 32 tile (lane: one token, four consecutive columns per register quad) turns through this wavefront's
+                // 4 KiB of the stage buffers and leaves as 16-byte pieces of whole 128-byte row segments.  Chunks are
+                // XOR-swizzled with the row.
+                unsigned char *ot = smem + wave * 4096;
 #pragma unroll
                 for (int a4 = 0; a4 < 4; ++a4) {
                     const int r = 8 * a4 + 4 * h;
-                    const f32x4 sw = *(const f32x4 *)(wsc + rho0 + r);
+                    const f32x4 sw = *(const f32x4 *)(s_wn + rho0 + r);
                     f32x4 vv;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) vv[i] = acc[ms][nt][4 * a4 + i] * (xs * sw[i]);
-                    const uint32_t dst = ot_a + (uint32_t)(c * 128 + (((2 * a4 + h) ^ (c & 7)) << 4));
-                    asm volatile("ds_write_b128 %0, %1" ::"v"(dst), "v"(vv) : "memory");
+                    *(f32x4 *)(ot + c * 128 + (((2 * a4 + h) ^ (c & 7)) << 4)) = vv;
                 }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
                 for (int pass = 0; pass < 4; ++pass) {
                     const int row = pass * 8 + (lane >> 3);
@@ -380,11 +313,9 @@ __global__ __launch_bounds__(kFThreads, 2) void qgemm_tile_fp8_kernel(Tile8Param
                         }
                     }
                 }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
         }
     }
-  }
 }
 
 template <int EPI, bool W4>
@@ -413,17 +344,7 @@ static int launch_fp8_cfg(const GemmArgs &a, hipStream_t s)
     p.out_f32 = a.out_f32;
     p.n_blocks = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2 + kFTN / 2 - 1) / (kFTN / 2) : (a.N + kFTN - 1) / kFTN;
     const int64_t slots = (a.M + kFTM - 1) / kFTM + a.E;
-    // A workgroup computes bpw neighbouring column blocks of its token tile one after the other: the expert
-    // lookup and the row gather are paid once, and a block's stores hide the first copies of the next.  Not for the wide plain
-    // epilogue (the down projection) of up to 640 rows per expert: its blocks are short (768: six stages) next to their stores, and
-    // chains of three make a coarse last round.  N = 2048, K = 768, 128 experts, even / Zipf router, three blocks -> one, us: FP8 1024 tokens
-    // 73 / 68 -> 63 / 64, 2048 95 / 95 -> 81 / 86, 8192 248 / 240 -> 231 / 229, 16384 437 / 420 -> 428 / 424 (a layer of 13905, Zipf,
-    // 1028 -> 1048), FP4 60 / 56 -> 49 / 50, 84 / 84 -> 67 / 73, 213 / 212 -> 201 / 208, 359 / 379 -> 366 / 371; four blocks (N = 1024) are as
-    // fast in pairs.
-    const bool single = EPI != QARL_EPI_SILU_MUL && p.n_blocks >= 6 && a.M <= (int64_t)a.E * 640;
-    p.bpw = single ? 1 : p.n_blocks >= 6 ? 3 : (p.n_blocks >= 2 ? 2 : 1);
-    p.n_bgroups = (p.n_blocks + p.bpw - 1) / p.bpw;
-    const int64_t total = ((slots * p.n_bgroups + 7) / 8) * 8;
+    const int64_t total = ((slots * p.n_blocks + 7) / 8) * 8;
     if (total > 0x7fffffffLL) {
         set_error("qgemm (prefill path): grid too large");
         return QARL_ERR_UNSUPPORTED;
@@ -431,7 +352,7 @@ static int launch_fp8_cfg(const GemmArgs &a, hipStream_t s)
     static LdsLimitOnce once;
     auto kern = qgemm_tile_fp8_kernel<EPI, W4>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(tile fp8)")) return rc;
-    kern<<<dim3((unsigned)total), dim3(kFThreads), kFStages * stage_bytes(W4), s>>>(p);
+    kern<<<dim3((unsigned)total), dim3(kFThreads), stage_count(W4) * stage_bytes(W4), s>>>(p);
     return check_hip(hipGetLastError(), "qgemm_tile_fp8_kernel");
 }
 
