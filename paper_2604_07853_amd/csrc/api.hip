@@ -237,18 +237,24 @@ int qarl_moe_route(const void *logits_bf16, int T, int E, int topk, int renorm, 
                         sorted_pairs, sorted_tokens, (hipStream_t)stream);
 }
 
-// QARL_PATH_AUTO between 16 and 64 rows per expert.  With 64 experts or more the tiled kernels fill the chip, and they do not mind
-// popular experts, whose row blocks the streaming kernels of the grouped call take one after the other.  Gate_up + down (2048 x 768,
-// 128 experts) in us, streaming against tiled, even router: 16 rows W4A16 72 against 93, W4A8 88 / 92, FP8 117 / 129, FP4
-// 67 / 92; 24 rows 95 / 92, 115 / 91, 175 / 132, 105 / 93; 32 rows 98 / 94, 119 / 93, 176 / 135, 107 / 94; 40 rows 172 / 94, 223 / 97,
-// 313 / 137, 186 / 96; under a Zipf router 2 to 13 times as long against at most 1.2 times.  Whole layers, even / Zipf: 520 tokens (33 rows)
-// W4A16 118 / 602 against 123 / 128, FP8 210 / 1229 against 173 / 161; 1024 tokens 202 / 897 against 170 / 166, 357 / 1683 against 192 / 210.  With few experts the streaming
-// kernels are ahead up to 64 rows (16 experts, 48 rows: FP8 40 against 63, FP4 29 / 61; W4A16 the same).  What the
-// tiled path would refuse, and a call whose workspace does not hold its group sums or whose results overlap its input, stays where it was.
+// QARL_PATH_AUTO up to 64 rows per expert.  The tiled kernels do not mind popular experts, whose row blocks the streaming kernels of the
+// grouped call take one after the other.  FP8: the tiled kernel (two workgroups per CU) is level with the streaming one at 8 rows per
+// expert and ahead of it beyond, whatever the number of experts: 2048 x 768 plain, 9 / 17 / 33 / 64 rows, streaming against tiled in us: 1 expert
+// 12 / 11 / 12 / 12 against 10 / 9 / 10 / 11, 32 experts 13 / 14 / 15 / 24 against 14 / 14 / 14 / 15, 128 37 / 40 / 44 / 73 against 36 / 37 / 38 / 41,
+// 256 87 / 94 / 104 / 161 against 88 / 89 / 96 / 106; 8 experts 4096 x 4096 35 / 36 / 39 / 53 against 32 / 32 / 33 / 34; gate_up + down of 128
+// experts, Zipf router, 8 / 16 rows 318 / 629 against 68 / 78.
+// Other formats: with 64 experts or more the tiled kernels fill the chip.  Gate_up + down (2048 x 768, 128 experts), even router: 16 rows
+// W4A16 72 against 93, W4A8 88 / 92, FP4 66 / 76; 24 rows 95 / 92, 115 / 91, 82 / 76; 32 rows 98 / 94, 119 / 93, 87 / 78; 40 rows
+// 172 / 94, 223 / 97, 148 / 81; under a Zipf router 2 to 13 times as long against at most 1.2 times.  Whole layers, even / Zipf: 520 tokens
+// (33 rows) W4A16 118 / 602 against 123 / 128; 1024 tokens 202 / 897 against 170 / 166.  With few experts the streaming kernels are
+// level or ahead up to 32 rows and more (16 experts, FP4 plain, 32 rows 9 against 10, one expert 4096 x 1024, 64 rows 22 / 23).
+// What the tiled path would refuse, and a call whose workspace does not hold its group sums or whose results overlap its input,
+// stays where it was.
 static bool auto_prefers_tiles(const qarl_qweight *W, const void *x, int64_t x_rows, int64_t M, int epilogue, const void *out, int out_f32,
                                const void *ws, size_t ws_bytes)
 {
-    if (W->E < 64 || W->E > 256 || M <= (int64_t)W->E * 16) return false;
+    const bool fp8 = W->fmt == QARL_FP8_E4M3_CH;
+    if (W->E > 256 || (!fp8 && W->E < 64) || M <= (int64_t)W->E * (fp8 ? 8 : 16)) return false;
     const bool int4 = int4_weights(W->fmt);
     if (int4 ? (int64_t)W->E * W->N * W->K / 2 >= (1LL << 32) : (int64_t)W->N * W->K >= (1LL << 32)) return false;
     const size_t need = ws_stage_bytes(W, M, epilogue) + ws_sums_bytes(W, x_rows) + ws_xwide_bytes(W, x_rows);

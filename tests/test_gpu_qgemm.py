@@ -762,10 +762,13 @@ def test_routed_row_blocks_of_popular_experts_equal_grouped_decode(q, fmt_name, 
 
 
 @pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
-@pytest.mark.parametrize("E,rows,tiled", [(64, 16, False), (64, 17, True), (64, 64, True), (48, 17, False), (48, 64, False), (257, 20, None)])
-def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows, tiled):
+@pytest.mark.parametrize("E,rows", [(64, 8), (64, 9), (64, 16), (64, 17), (64, 64), (48, 17), (48, 64), (3, 8), (3, 9), (257, 20)])
+def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows):
     """Bit for bit the path the rule names; the streaming one where the workspace does not hold the tiled path's, or out is x."""
     fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    tiled = rows > 8 if fmt_name == "fp8" else E >= 64 and rows > 16
+    if E > 256:
+        tiled = None
     N = K = 256
     M = E * rows
     cut = np.sort(np.random.default_rng(E + rows).integers(0, M + 1, E - 1))
