@@ -123,7 +123,15 @@ __global__ __launch_bounds__(kFThreads, 4) void qgemm_tile_fp8_kernel(Tile8Param
         if (j < kACopies) copy16_to_lds(aptr[j] + ks * kFKS, dst + wave * 16 * kFKS + j * 1024);
         else copy16_to_lds(wbase + (int64_t)ks * kWRowB + boff[j - kACopies], dst + kFTM * kFKS + wave * 32 * kWRowB + (j - kACopies) * 1024);
     };
+    auto copy_stage = [&](int ks, int buf) {
+#pragma unroll
+        for (int j = 0; j < kACopies + kWCopies; ++j) copy_one(ks, buf, j);
+    };
     const int stages = K / kFKS;
+    // FP4: a wavefront whose 64 rows lie past the expert's end only copies (layers of 128 experts, even / Zipf router: 520 tokens 116 / 98 ->
+    // 112 / 97 us, 1024 136 / 134 -> 134 / 129, 3000 245 / 253 -> 240 / 244; 64 experts the same).  FP8 is bound by its copies: 3000
+    // tokens 304 / 312 -> 297 / 311, but 520 tokens 158 -> 161 and 1024 181 -> 195.
+    const bool busy = !W4 || wm * 64 < mrem;
     // the block's 256 channel scales, 4 bytes per lane (wavefronts w and w + 4 copy the same 64), and the weight rows of the first
     // stages: they wait for no row id
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(sbase + weight_row((wave & 3) * 64 + lane)),
@@ -224,19 +232,23 @@ __global__ __launch_bounds__(kFThreads, 4) void qgemm_tile_fp8_kernel(Tile8Param
         else asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");               // the stage's three
         const bool more = ks + kStages - 1 < stages;
         const int nbuf = buf == 0 ? kStages - 1 : buf - 1;
+        if (busy) {
 #pragma unroll
-        for (int t = 0; t < kHalves; ++t) {
-            Frags f;
-            read_frags(f, buf, t);
-            pair_tokens(f);
-            __builtin_amdgcn_s_setprio(1);
+            for (int t = 0; t < kHalves; ++t) {
+                Frags f;
+                read_frags(f, buf, t);
+                pair_tokens(f);
+                __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (t == 0 && more && i < kACopies + kWCopies) copy_one(ks + kStages - 1, nbuf, i);
-                mfma1(f, i >> 1, i & 1);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < 4; ++i) {
+                    if (t == 0 && more && i < kACopies + kWCopies) copy_one(ks + kStages - 1, nbuf, i);
+                    mfma1(f, i >> 1, i & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __builtin_amdgcn_s_setprio(0);
             }
-            __builtin_amdgcn_s_setprio(0);
+        } else if (more) {
+            copy_stage(ks + kStages - 1, nbuf);
         }
         buf = buf == kStages - 1 ? 0 : buf + 1;
     }

@@ -129,9 +129,9 @@ def test_tiled_path_several_tiles_per_expert(q, oracle, fmt, E, N, K, rows):
 @pytest.mark.parametrize("fmt", ["fp8", "fp4"])
 @pytest.mark.parametrize("N,K", [(32, 128), (256, 256), (288, 640)])
 def test_tiled_path_at_the_edges_of_its_tiles(q, oracle, fmt, N, K):
-    """One row below, at and above a token tile, one and several column blocks, the fewest stages and more stages than buffers;
+    """One row below, at and above a token tile and half of one, one and several column blocks, the fewest stages and more stages than buffers;
     a row's result does not depend on the tile it lies in."""
-    rows = (127, 128, 129, 1, 0, 256)
+    rows = (127, 128, 129, 1, 0, 256, 64, 65)
     M, E = sum(rows), len(rows)
     w = synth.normal_bf16((E, N, K), 0.02, seed=N + K)
     x = synth.normal_bf16((M, K), 1.0, seed=N)
@@ -141,7 +141,7 @@ def test_tiled_path_at_the_edges_of_its_tiles(q, oracle, fmt, N, K):
     run = lambda o, n, xr, s: q.qarl_qgemm_grouped(qw, xr, _i32(o), n, x_scales=s, out_dtype=q.QARL_OUT_F32, path=q.QARL_PATH_PREFILL)
     y = run(off, M, xq, sx)
     assert norm_err(y.cpu().numpy(), gemm(*oracle.quantize_fp8_rows(np_bits(x)), wq, sw, off, np.arange(M, dtype=np.int32))) <= TOL_F32_FP8
-    for e, r in ((0, 126), (1, 127), (2, 128), (5, 255)):
+    for e, r in ((0, 126), (1, 127), (2, 128), (5, 255), (6, 63), (7, 64)):
         i = int(off[e]) + r
         one = run([0] * (e + 1) + [1] * (E - e), 1, xq[i:i + 1].contiguous(), sx[i:i + 1].contiguous())
         assert torch.equal(one[0], y[i])
