@@ -343,6 +343,7 @@ __device__ __forceinline__ bool stream_fp8_body(const StreamParams &p, int tid, 
             const int sl = it.sub / subs;
             u_lo = sl * per_slice + (it.sub - sl * subs) * kSWaves;
             n_pairs = max(0, min(min(p.n_units, (sl + 1) * per_slice), u_lo + it.n_sub * kSWaves) - u_lo);
+            if (n_pairs == 0) continue;   // the last slice may hold fewer pairs than it has shares for
             lds_barrier();   // the previous block is done with the list
             Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
             if (it.block * kRowsMax < Me) run_block(it.block * kRowsMax);

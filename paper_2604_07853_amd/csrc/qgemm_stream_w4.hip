@@ -181,7 +181,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
     uint32_t scr[kScRegs];
     const int sc_row = lane >> 1, sc_par = lane & 1, sc_half = G / 2;
     auto load_scales = [&](int pi) {
-        const int uu = u_lo + (pi < n_pairs ? pi : 0);
+        const int uu = pi < n_pairs ? u_lo + pi : min(u_lo, p.n_units - 1);   // (a slice past the last pair starts behind it)
         const int nt = sc_row >> 4;
         const int tile = kSilu ? (nt ? (N / 2) / 16 : 0) + uu : uu * 2 + nt;
         const uint32_t *src = (const uint32_t *)p.scales + ((ebase + tile * 16 + (sc_row & 15)) * G) / 2;
@@ -497,6 +497,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
             const int sl = it.sub / subs;
             u_lo = sl * p.per_slice + (it.sub - sl * subs) * kWaves;
             n_pairs = max(0, min(min(p.n_units, (sl + 1) * p.per_slice), u_lo + it.n_sub * kWaves) - u_lo);
+            if (n_pairs == 0) continue;   // the last slice may hold fewer pairs than it has shares for
             lds_barrier();   // the previous block is done with the list
             Me = list_pairs(p.ids, p.n_ids, e, p.x_per_token, p.topk, tmp_map);
             if (it.block * kRows < Me) run_block(it.block * kRows, false);

@@ -762,6 +762,35 @@ def test_routed_row_blocks_of_popular_experts_equal_grouped_decode(q, fmt_name, 
 
 
 @pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
+@pytest.mark.parametrize("E,N,K,T,topk,named", [(64, 544, 512, 256, 8, 12),    # slices of 9 and 8 pairs, two shares each: the last one has none
+                                                (2, 4128, 256, 100, 2, 2),     # 129 pairs in 16 slices of nine: the last slice has none
+                                                (4, 4128, 256, 100, 1, 1)])    # ... and takes a share of the popular expert's
+def test_shares_and_slices_without_columns(q, oracle, fmt_name, E, N, K, T, topk, named):
+    """The last `named` experts have all the rows, so a workgroup that counted past its last pair of weight tiles would look
+    behind the codes and scales.  Routed and grouped decode path bit for bit, W4A16 against the oracle too."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "fp8": q.QARL_FP8_E4M3_CH, "fp4": q.QARL_FP4_E2M1_CH, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    g = torch.Generator().manual_seed(E + N)
+    ids = torch.stack([E - 1 - torch.randperm(named, generator=g)[:topk] for _ in range(T)])
+    M = T * topk
+    pairs = torch.argsort(ids.flatten(), stable=True)
+    off = torch.zeros(E + 1, dtype=torch.int32)
+    off[1:] = torch.cumsum(torch.bincount(ids.flatten(), minlength=E), 0)
+    w, x = synth.normal_bf16((E, N, K), 0.02, seed=N), synth.normal_bf16((T, K), 1.0, seed=T)
+    qw, xd, kw = q.qarl_quantize_weights(w.cuda(), fmt), x.cuda(), {}
+    rows = xd
+    if fmt != q.QARL_W4A16_G128:
+        rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(xd)
+    y = q.qarl_qgemm_grouped(qw, rows, off.cuda(), M, row_map=(pairs // topk).int().cuda(), out_dtype=q.QARL_OUT_F32,
+                             path=q.QARL_PATH_DECODE, **kw)
+    got = torch.full_like(y, float("nan"))
+    q.qarl_qgemm_routed(qw, xd, ids.int().flatten().cuda(), T, topk, True, out=got, out_dtype=q.QARL_OUT_F32)
+    assert torch.equal(got[pairs.cuda()], y)
+    if fmt == q.QARL_W4A16_G128:
+        ref = oracle.qgemm_w4a16(np_bits(x), *oracle.quantize_int4(np_bits(w)), off.numpy(), (pairs // topk).numpy().astype(np.int32))
+        assert norm_err(y.cpu().numpy(), ref) <= TOL_F32
+
+
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
 @pytest.mark.parametrize("E,rows", [(64, 8), (64, 9), (64, 16), (64, 17), (64, 64), (48, 17), (48, 64), (3, 8), (3, 9), (257, 20)])
 def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows):
     """Bit for bit the path the rule names; the streaming one where the workspace does not hold the tiled path's, or out is x."""
