@@ -389,12 +389,11 @@ struct RouteJob {
     int renorm;
 };
 
-// route: launch the router in front, or let the kernel route its tokens itself.
-static int qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, const int32_t *topk_ids, int T,
-                        int topk, int epilogue, const float *combine_w, void *out, int out_dtype, void *ws,
-                        size_t ws_bytes, void *stream, const RouteJob *route)
+// Everything a routed call may be refused for, in front of its first launch (and, in a layer call, of the first launch of either).
+static int check_routed(const qarl_qweight *W, const void *x, const int32_t *topk_ids, int T, int topk, int epilogue,
+                        const float *combine_w, const void *out, int out_dtype, const void *ws, size_t ws_bytes)
 {
-    int rc = check_qweight(W, "qarl_qgemm_routed");
+    const int rc = check_qweight(W, "qarl_qgemm_routed");
     if (rc) return rc;
     if (T < 0 || topk <= 0) {
         set_error("qarl_qgemm_routed: T >= 0 and topk > 0 required");
@@ -431,6 +430,24 @@ static int qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, c
         set_error("qarl_qgemm_routed: x, topk_ids and out must be 16-byte aligned");
         return QARL_ERR_ALIGNMENT;
     }
+    const size_t stage = ws_stage_bytes(W, (int64_t)T * topk, epilogue);
+    if (stage > 0 && (!ws || ws_bytes < stage || !aligned16(ws))) {
+        set_error("qarl_qgemm_routed: this call needs %zu bytes of 16-byte aligned workspace (got %zu)", stage, ws_bytes);
+        return QARL_ERR_WORKSPACE;
+    }
+    if (epilogue == QARL_EPI_COMBINE && !combine_w) {
+        set_error("qarl_qgemm_routed: COMBINE needs combine_w");
+        return QARL_ERR_INVALID_ARG;
+    }
+    return QARL_OK;
+}
+
+// The launches of a call that check_routed has passed.  route: launch the router in front, or let the kernel route its tokens itself.
+static int launch_routed(const qarl_qweight *W, const void *x, int x_per_token, const int32_t *topk_ids, int T, int topk, int epilogue,
+                         const float *combine_w, void *out, int out_dtype, void *ws, void *stream, const RouteJob *route)
+{
+    if (T == 0) return QARL_OK;
+    int rc = QARL_OK;
     const int64_t M = (int64_t)T * topk;
     GemmArgs a;
     a.fmt = W->fmt;
@@ -453,16 +470,7 @@ static int qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, c
     a.ids = topk_ids;
     a.topk = topk;
     a.x_per_token = x_per_token ? 1 : 0;
-    const size_t stage = ws_stage_bytes(W, M, epilogue);
-    if (stage > 0 && (!ws || ws_bytes < stage || !aligned16(ws))) {
-        set_error("qarl_qgemm_routed: this call needs %zu bytes of 16-byte aligned workspace (got %zu)", stage, ws_bytes);
-        return QARL_ERR_WORKSPACE;
-    }
     hipStream_t st = (hipStream_t)stream;
-    if (epilogue == QARL_EPI_COMBINE && !combine_w) {
-        set_error("qarl_qgemm_routed: COMBINE needs combine_w");
-        return QARL_ERR_INVALID_ARG;
-    }
     // The kernels for few pairs write results while other workgroups still read x and the ids.  A combined row is written in a
     // launch of its own on the staged path, so a caller may put out on top of either; and a row of the other epilogues is
     // written there by the workgroup that has read it, where an expert has one slice (256 experts, or N <= 256).
@@ -518,7 +526,8 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
                       int topk, int epilogue, const float *combine_w, void *out, int out_dtype, void *ws,
                       size_t ws_bytes, void *stream)
 {
-    return qgemm_routed(W, x, x_per_token, topk_ids, T, topk, epilogue, combine_w, out, out_dtype, ws, ws_bytes, stream, nullptr);
+    const int rc = check_routed(W, x, topk_ids, T, topk, epilogue, combine_w, out, out_dtype, ws, ws_bytes);
+    return rc ? rc : launch_routed(W, x, x_per_token, topk_ids, T, topk, epilogue, combine_w, out, out_dtype, ws, stream, nullptr);
 }
 
 int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down, const void *x, const void *logits_bf16, int T,
@@ -539,11 +548,14 @@ int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down,
         set_error("qarl_moe_layer_routed: null pointer");
         return QARL_ERR_INVALID_ARG;
     }
+    rc = check_routed(gate_up, x, topk_ids, T, topk, QARL_EPI_SILU_MUL, nullptr, a_bf16, QARL_OUT_BF16, ws, ws_bytes);
+    if (!rc) rc = check_routed(down, a_bf16, topk_ids, T, topk, QARL_EPI_COMBINE, topk_w, out, out_dtype, ws, ws_bytes);
+    if (rc) return rc;
     // Few tokens: the workgroups of gate_up route their token themselves (a load and at most topk reductions more in front of the
     // weights, one launch less: one token, layer 18.5 -> 15.7 us W4A16).
     const RouteJob route = {logits_bf16, topk_ids, topk_w, renorm};
-    rc = qgemm_routed(gate_up, x, 1, topk_ids, T, topk, QARL_EPI_SILU_MUL, nullptr, a_bf16, QARL_OUT_BF16, ws, ws_bytes, stream, &route);
-    if (!rc) rc = qarl_qgemm_routed(down, a_bf16, 0, topk_ids, T, topk, QARL_EPI_COMBINE, topk_w, out, out_dtype, ws, ws_bytes, stream);
+    rc = launch_routed(gate_up, x, 1, topk_ids, T, topk, QARL_EPI_SILU_MUL, nullptr, a_bf16, QARL_OUT_BF16, ws, stream, &route);
+    if (!rc) rc = launch_routed(down, a_bf16, 0, topk_ids, T, topk, QARL_EPI_COMBINE, topk_w, out, out_dtype, ws, stream, nullptr);
     return rc;
 }
 

@@ -867,3 +867,27 @@ def test_layer_in_one_call_errors(q):
     assert call(gu, dn, -1, 8) == q.QARL_ERR_INVALID_ARG
     assert call(gu, dn, 1, 8, logits=False) == q.QARL_ERR_INVALID_ARG
     assert call(gu, dn, 513, 1) == q.QARL_ERR_UNSUPPORTED          # the routed GEMMs' limits
+
+
+def test_layer_in_one_call_is_refused_before_it_writes(q):
+    """What only the second GEMM is refused for leaves ids, weights and intermediate rows as they were."""
+    gu, dn = synth.expert_weights(64, 256, 256, seed=1, device="cuda")
+    w4 = q.qarl_quantize_weights(gu), q.qarl_quantize_weights(dn)
+    narrow = synth.expert_weights(64, 256, 128, seed=1, device="cuda")              # int4 down: K = 128 is no multiple of 256
+    narrow = [q.qarl_quantize_weights(w) for w in narrow]
+    for T in (1, 40):                                                               # the router inside gate_up, and in front of it
+        x, lg = synth.normal_bf16((T, 256), 1.0, seed=2, device="cuda"), synth.router_logits(T, 64, seed=3, device="cuda")
+        need = T * 8 * 256 * 4
+        ws = torch.empty((need + 256,), dtype=torch.uint8, device="cuda")
+        for (g, d), ws_at, ws_bytes, out_at, dt, status in ((w4, 0, need - 1, 0, 0, q.QARL_ERR_WORKSPACE), (w4, 8, need, 0, 0, q.QARL_ERR_WORKSPACE),
+                                                            (w4, 0, need, 2, 0, q.QARL_ERR_ALIGNMENT), (w4, 0, need, 0, 7, q.QARL_ERR_INVALID_ARG),
+                                                            (narrow, 0, need, 0, 0, q.QARL_ERR_UNSUPPORTED)):
+            ids = torch.full((T * 8,), -7, dtype=torch.int32, device="cuda")
+            w, a = torch.full((T * 8,), -7.0, device="cuda"), torch.full((T * 8, 256), -7.0, dtype=torch.bfloat16, device="cuda")
+            out = torch.full((T + 1, 256), -7.0, dtype=torch.bfloat16, device="cuda")
+            with pytest.raises(q.QarlError) as ei:
+                q._check(q.lib().qarl_moe_layer_routed(q.C.byref(g.desc), q.C.byref(d.desc), x.data_ptr(), lg.data_ptr(), T, 8, 1, ids.data_ptr(),
+                                                       w.data_ptr(), a.data_ptr(), out.data_ptr() + out_at, dt, ws.data_ptr() + ws_at, ws_bytes,
+                                                       torch.cuda.current_stream().cuda_stream))
+            assert ei.value.status == status
+            assert all(bool((t == -7).all()) for t in (ids, w, a, out)), (T, status)
