@@ -339,21 +339,28 @@ class MoELayer:
             self.aq = torch.empty((M, I), dtype=torch.uint8, device=device)
             self.sa = torch.empty((M,), dtype=torch.float32, device=device)
 
+    def _check_inputs(self, x, logits):
+        """The kernels see pointers and the layer's own sizes: logits are [T, E], x is bf16 rows of length H, row t for token t (rows
+        behind the T-th are not read; quantized ones have no room)."""
+        if logits.shape != (self.T, self.E):
+            raise ValueError("logits must be [%d, %d] (got %s)" % (self.T, self.E, list(logits.shape)))
+        assert logits.dtype == torch.bfloat16 and logits.is_cuda and logits.is_contiguous()
+        if x.shape != (self.T, self.H):
+            rows = x.numel() // self.H
+            if (x.shape[-1:] != (self.H,) or rows < self.T
+                    or not self.routed and (x.shape[0] != rows or self.fp8 and rows != self.T)):
+                raise ValueError("x must be [%d, %d] (got %s)" % (self.T, self.H, list(x.shape)))
+        if x.dtype != torch.bfloat16 or not x.is_cuda or not x.is_contiguous():
+            raise ValueError("x must be contiguous bf16 on the GPU")
+
     def forward(self, x, logits):
-        if self.routed and logits.shape == (self.T, self.E):
+        self._check_inputs(x, logits)
+        if self.routed:
             # one call per layer: a step of a few tokens is bound by the host otherwise (three calls took 25 us of Python)
-            assert logits.dtype == torch.bfloat16 and logits.is_cuda and logits.is_contiguous()
             r = self.routing
             _check(lib().qarl_moe_layer_routed(C.byref(self.gu.desc), C.byref(self.dn.desc), x.data_ptr(), logits.data_ptr(), self.T,
                                                self.topk, 1, r.ids.data_ptr(), r.w.data_ptr(), self.a.data_ptr(), self.out.data_ptr(),
                                                QARL_OUT_BF16, self.ws.data_ptr(), self.ws.numel(), torch.cuda.current_stream().cuda_stream))
-            return self.out
-        if self.routed:
-            r = qarl_moe_route(logits, self.topk, True, out=self.routing, group=False)
-            qarl_qgemm_routed(self.gu, x, r.ids, self.T, self.topk, True, epilogue=QARL_EPI_SILU_MUL, out=self.a,
-                              ws=self.ws)
-            qarl_qgemm_routed(self.dn, self.a, r.ids, self.T, self.topk, False, epilogue=QARL_EPI_COMBINE,
-                              combine_w=r.w, out=self.out, ws=self.ws)
             return self.out
         r = qarl_moe_route(logits, self.topk, True, out=self.routing)
         if self.fp8:
