@@ -224,3 +224,26 @@ def test_dx_of_many_rows(q, oracle, E, N, K, rows):
     dx = q.qarl_qgemm_grouped_dx(qw, hot, _i32(off), M, out_dtype=q.QARL_OUT_F32)
     for e in range(E):
         assert torch.equal(dx[off[e]:off[e + 1]], torch.from_numpy(codes[e]).cuda().float()[n[off[e]:off[e + 1]]])
+
+
+@pytest.mark.parametrize("N", [2048, 3840])
+def test_dx_is_as_exact_on_either_tile_size(q, N):
+    """The same rows on the 256 x 256 tiles (one call) and on the 128 x 128 ones (calls of fewer than 512 rows), each against 64-bit sums of
+    the rounded operands.  Both add the same products in the same matrix instructions and form a row sum in sixteen chains of N / 32
+    additions, so the 2-norms of their errors agree but for which rounding hits which row, about 1 / sqrt(M) = 1 %
+    of the row sums' share, itself a tenth: 0.2 % is asked for.  Chains of N / 4 are 0.7 % off."""
+    K, M = 4096, 12300
+    w, dy = synth.normal_bf16((1, N, K), 0.02, seed=N, device="cuda"), synth.normal_bf16((M, N), 1.0, seed=N + 1, device="cuda")
+    qw = q.qarl_quantize_weights(w)
+    wide = q.qarl_qgemm_grouped_dx(qw, dy, _i32([0, M]), M, out_dtype=q.QARL_OUT_F32)
+    small = torch.cat([q.qarl_qgemm_grouped_dx(qw, dy[r:r + 500].contiguous(), _i32([0, min(500, M - r)]), min(500, M - r), out_dtype=q.QARL_OUT_F32)
+                       for r in range(0, M, 500)])
+    shifts = 4 * torch.arange(8, device="cuda", dtype=torch.int32)
+    codes = (((q.qarl_codes_to_canonical(qw)[0, :, :, None] >> shifts) & 15) - 8).reshape(N, K).double()
+    err = {"wide": 0.0, "small": 0.0}
+    for g in range(K // 128):
+        c = slice(g * 128, (g + 1) * 128)
+        ref = (dy.float() * qw.scales[0, :, g].float()).to(torch.bfloat16).double() @ codes[:, c]
+        for name, got in (("wide", wide), ("small", small)):
+            err[name] += float((got[:, c].double() - ref).pow(2).sum())
+    assert (err["wide"] / err["small"]) ** 0.5 <= 1.002
