@@ -35,17 +35,6 @@ __device__ __forceinline__ uint32_t wave_max_u32_dpp(uint32_t v)
     QARL_DPP_STEP(uint32_t, umax2, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
-__device__ __forceinline__ float wave_max_f32_dpp(float v)
-{
-    const float ident = -INFINITY;
-    QARL_DPP_STEP(float, fmaxf, 0x111, 0xf);
-    QARL_DPP_STEP(float, fmaxf, 0x112, 0xf);
-    QARL_DPP_STEP(float, fmaxf, 0x114, 0xf);
-    QARL_DPP_STEP(float, fmaxf, 0x118, 0xf);
-    QARL_DPP_STEP(float, fmaxf, 0x142, 0xa);
-    QARL_DPP_STEP(float, fmaxf, 0x143, 0xc);
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
 // Sum in the fixed order the shifts imply; every lane gets the same value.
 __device__ __forceinline__ float wave_sum_f32_dpp(float v)
 {
@@ -109,7 +98,7 @@ __device__ __forceinline__ void route_token(TokenLogits<PER> l, int E, int topk,
     float m = -INFINITY;
 #pragma unroll
     for (int j = 0; j < PER; ++j) m = fmaxf(m, l.val[j]);
-    m = wave_max_f32_dpp(m);
+    m = wave_max(m);   // (a number or an infinity: a lane starts from -inf)
     float z = 0.f;
 #pragma unroll
     for (int j = 0; j < PER; ++j)
