@@ -127,6 +127,35 @@ def test_tiled_path_several_tiles_per_expert(q, oracle, fmt, E, N, K, rows):
 
 
 @pytest.mark.parametrize("fmt", ["fp8", "fp4"])
+@pytest.mark.parametrize("E,N,K,rows", [(64, 256, 128, 20), (64, 512, 768, 33), (64, 256, 2048, 17), (8, 256, 4096, 9)])
+def test_both_paths_are_equally_exact(q, oracle, fmt, E, N, K, rows):
+    """The streaming path adds 32 products per matrix instruction, the tiled one 64, and QARL_PATH_AUTO chooses by size.  Against 64-bit
+    sums of the same codes: a sum loses the bits below 2^-14 of the largest product of its instruction, which for Gaussian data is
+    the same power of two for 32 and 64 of them in nearly all instructions (measured: FP8 the same error, FP4 up to 0.8 % more; 5 %
+    are allowed).  A bf16 result then carries its own rounding, 1.66e-3 of its value, and this error beside it, at most 1.5e-5: the
+    paths' errors agree to (1.5e-5 / 1.66e-3)^2 / 2 = 4e-5, and 1e-4 is asked for."""
+    w = synth.normal_bf16((E, N, K), 0.02, seed=N + K)
+    x = synth.normal_bf16((E * rows, K), 1.0, seed=K, device="cuda")
+    off = _i32(np.arange(E + 1) * rows)
+    wq, sw, _, qw = _quantized(q, oracle, fmt, w)
+    xq, sx = q.qarl_quantize_rows_fp8(x)
+    if fmt == "fp8":
+        wd = torch.tensor(wq, device="cuda").view(torch.float8_e4m3fn).double()
+    else:
+        e2m1 = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6], dtype=torch.float64, device="cuda")
+        wd = torch.cat([e2m1, -e2m1])[torch.tensor(wq, device="cuda").long()]
+    xd = (xq.view(torch.float8_e4m3fn).double() * sx.double()[:, None]).reshape(E, rows, K)
+    ref = torch.cat([xd[e] @ (wd[e] * torch.tensor(sw[e], device="cuda").double()[:, None]).T for e in range(E)])
+    err = {}
+    for dt in (q.QARL_OUT_F32, q.QARL_OUT_BF16):
+        for path in (q.QARL_PATH_DECODE, q.QARL_PATH_PREFILL):
+            y = q.qarl_qgemm_grouped(qw, xq, off, E * rows, x_scales=sx, out_dtype=dt, path=path).double()
+            err[dt, path] = float(((y - ref).pow(2).sum() / ref.pow(2).sum()).sqrt())
+        assert err[dt, q.QARL_PATH_PREFILL] <= err[dt, q.QARL_PATH_DECODE] * (1.05 if dt == q.QARL_OUT_F32 else 1.0001), err
+    assert err[q.QARL_OUT_F32, q.QARL_PATH_PREFILL] <= 2e-5, err
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "fp4"])
 @pytest.mark.parametrize("N,K", [(32, 128), (256, 256), (288, 640)])
 def test_tiled_path_at_the_edges_of_its_tiles(q, oracle, fmt, N, K):
     """One row below, at and above a token tile and half of one, one and several column blocks, the fewest stages and more stages than buffers;
