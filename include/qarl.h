@@ -91,9 +91,10 @@ const char *qarl_last_error(void);
 
 /* Bytes of `ws` that qarl_qgemm_grouped may need for a call with these weights, x_rows activation
  * rows, M problem rows and this epilogue, whichever path runs: fp32 staging of Y [M][N] for COMBINE,
- * plus, for W4A16, one fp32 sum per activation row and 128-k scale group (the prefill path computes
- * them once per call).  qarl_token_logprob has its own query; for few tokens and small vocabularies it asks for
- * more than the call needs at least (a partial per token and 256 vocabulary rows), with which it is faster. */
+ * plus, for W4A16 and W4A8, one fp32 sum per activation row and 128-k scale group (the prefill path computes
+ * them once per call) and, for W4A8, the rows as bf16.  qarl_token_logprob has its own query; for few tokens and small
+ * vocabularies it asks for more than the call needs at least (a partial per token and 256 vocabulary rows), with which it is
+ * faster. */
 size_t qarl_qgemm_workspace_bytes(const qarl_qweight *W, int64_t x_rows, int64_t M, int epilogue);
 size_t qarl_logprob_workspace_bytes(int T, int H, int V);
 
@@ -156,9 +157,12 @@ int qarl_moe_route(const void *logits_bf16, int T, int E, int topk, int renorm, 
  *                        token in slot order with weights combine_w [T][topk]; sorted_pairs as
  *                        written by qarl_moe_route
  *   out_dtype  QARL_OUT_BF16 or QARL_OUT_F32 (SILU_MUL: bf16 only)
- *   path       AUTO picks DECODE when the mean rows per expert is small and the shape fits it
- *              (DECODE keeps whole rows of x in LDS: W4A16 needs K % 256 == 0 and K <= 4096, with 16-row
- *              instead of 32-row blocks beyond 2048)
+ *   path       AUTO picks DECODE up to 64 rows per expert (M <= 64 E) where the shape fits it (DECODE keeps whole rows of x
+ *              in LDS: W4A16 needs K % 256 == 0 and K <= 4096, with 16-row instead of 32-row blocks beyond
+ *              2048), else PREFILL; and PREFILL already from more than 16 rows per expert on with 64 to 256 experts, FP8 from
+ *              more than 8 with up to 256, where ws holds qarl_qgemm_workspace_bytes and out does not overlap x (COMBINE: wherever
+ *              out lies).  The paths add in different orders: with AUTO the last bits of a row may change with E, M,
+ *              ws_bytes and that overlap; name a path where they must not
  * Errors: INVALID_ARG, ALIGNMENT, UNSUPPORTED (shape outside the kernels' domain),
  * WORKSPACE (ws missing or smaller than the call needs).  M == 0 is a no-op. */
 int qarl_qgemm_grouped(const qarl_qweight *W, const void *x, const float *x_scales, int64_t x_rows,
@@ -208,7 +212,9 @@ int qarl_qgemm_routed(const qarl_qweight *W, const void *x, int x_per_token, con
 
 /* A decode step's MoE layer in one call: qarl_moe_route (ids and weights only, into topk_ids and topk_w [T][topk]), then
  * qarl_qgemm_routed on gate_up (SILU_MUL, x bf16 [T][K], into a_bf16 [T*topk][N/2]) and on down (COMBINE, into out [T][down N]).
- * Launches what the three calls launch; limits, workspace (that of the down call) and errors are theirs. */
+ * Results equal those of the three calls bit for bit; for few pairs the router is not launched, gate_up's workgroups route
+ * their tokens themselves and write topk_ids and topk_w.  Limits, workspace (that of the down call) and errors are theirs; a call
+ * that returns one has launched nothing. */
 int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down, const void *x,
                           const void *logits_bf16, int T, int topk, int renorm, int32_t *topk_ids,
                           float *topk_w, void *a_bf16, void *out, int out_dtype, void *ws,
@@ -223,7 +229,8 @@ int qarl_moe_layer_routed(const qarl_qweight *gate_up, const qarl_qweight *down,
  * exp(clip(mean delta, -log c, log c)), c = tis_cap_c > 1.
  *   h bf16 [T][H], w_lm bf16 [V][H], target int32 [T]; H % 64 == 0; inv_temperature > 0
  *   and finite.  A target outside [0, V) gives logprob NaN for that token.  logprob may lie on top
- *   of h, w_lm or target.
+ *   of h, w_lm or target.  Up to 128 tokens the partial sums of a token, and so the last bits of its log-prob, follow ws_bytes
+ *   between the least the call takes and what qarl_logprob_workspace_bytes names; they are the same from there on.
  *   delta, seq_w, seq_w_clipped may each be NULL; seq outputs need seq_offsets and S > 0. */
 int qarl_token_logprob(const void *h_bf16, const void *w_lm_bf16, const int32_t *target, int T,
                        int H, int V, float inv_temperature, float *logprob,

@@ -245,9 +245,12 @@ int qarl_moe_route(const void *logits_bf16, int T, int E, int topk, int renorm, 
 // experts, Zipf router, 8 / 16 rows 318 / 629 against 68 / 78.
 // Other formats: with 64 experts or more the tiled kernels fill the chip.  Gate_up + down (2048 x 768, 128 experts), even router: 16 rows
 // W4A16 72 against 93, W4A8 88 / 92, FP4 66 / 76; 24 rows 95 / 92, 115 / 91, 82 / 76; 32 rows 98 / 94, 119 / 93, 87 / 78; 40 rows
-// 172 / 94, 223 / 97, 148 / 81; under a Zipf router 2 to 13 times as long against at most 1.2 times.  Whole layers, even / Zipf: 520 tokens
-// (33 rows) W4A16 118 / 602 against 123 / 128; 1024 tokens 202 / 897 against 170 / 166.  With few experts the streaming kernels are
-// level or ahead up to 32 rows and more (16 experts, FP4 plain, 32 rows 9 against 10, one expert 4096 x 1024, 64 rows 22 / 23).
+// 172 / 94, 223 / 97, 148 / 81; under a Zipf router 2 to 13 times as long against at most 1.2 times.  Whole layers from 513 tokens on,
+// even / Zipf: W4A16 top-8 513 tokens (32 rows) 115 / 601 against 118 / 127, 640 185 / 598 against 122 / 135, 1000 194 / 916 against
+// 165 / 168; top-4 513 tokens (16 rows) 108 / 591 against 110 / 80, 1030 116 / 1100 against 118 / 108: up to 3 % given away to an
+// even router up to 33 rows, since the host does not know the router's counts; W4A8 and FP4 are faster under either (top-4 513 tokens 134 / 716
+// against 118 / 89, 112 / 563 against 106 / 78).  With few experts the streaming kernels are level or ahead up to 32 rows and
+// more (16 experts, FP4 plain, 32 rows 9 against 10, one expert 4096 x 1024, 64 rows 22 / 23).
 // What the tiled path would refuse, and a call whose workspace does not hold its group sums or whose results overlap its input,
 // stays where it was.
 static bool auto_prefers_tiles(const qarl_qweight *W, const void *x, int64_t x_rows, int64_t M, int epilogue, const void *out, int out_f32,
