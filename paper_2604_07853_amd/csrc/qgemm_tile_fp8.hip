@@ -11,7 +11,8 @@
 // asynchronous global -> LDS copies; 16-byte chunks of a row are XOR-swizzled with the row index so that the copies
 // (16 rows x 64 bytes per wavefront instruction) and the operand reads (32 rows, one chunk) are free of bank conflicts.
 //
-// Two workgroups share a CU (76 KiB of LDS and at most 128 registers each): three 64-k stages, one set of operand registers, a plain loop.
+// Two workgroups share a CU (74.5 KiB of LDS, FP4 66.5, and at most 128 registers each): three 64-k stages, one set of operand registers, a
+// plain loop.
 // Copies, operand reads and matrix instructions of ONE workgroup add up instead of overlapping, whatever the tile and the
 // depth of its pipeline, and a third of a launch was lookups, first stages and epilogues; another workgroup on the same SIMDs fills
 // all of these.  The matrix instructions run at raised wave priority (large calls 1-2 % faster) with the stage's copies
@@ -24,7 +25,7 @@
 //
 // FP4 weights (W4 = true) take the same kernel: the instruction reads e2m1 codes natively in its first
 // operand (format select 4), 16 bytes per lane instead of 32.  A weight row then has 64 bytes per stage
-// (four chunks, swizzled with (row >> 2) & 3) of 128 k, two stages of 32 KiB fill the same space, and no e4m3 copy of the
+// (four chunks, swizzled with (row >> 2) & 3) of 128 k, a workgroup two stages of 32 KiB, and no e4m3 copy of the
 // weights is ever written.  The library packs the eight codes of a word as (element b, element 4 + b) in
 // byte b; the instruction pairs nibble n of its first operand with byte n of the second within a group of
 // 16 k, so the token bytes of every 8-byte group are put into the order 0 4 1 5 2 6 3 7 after their LDS
