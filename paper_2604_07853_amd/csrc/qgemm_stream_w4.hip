@@ -181,7 +181,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
     uint32_t scr[kScRegs];
     const int sc_row = lane >> 1, sc_par = lane & 1, sc_half = G / 2;
     auto load_scales = [&](int pi) {
-        const int uu = pi < n_pairs ? u_lo + pi : min(u_lo, p.n_units - 1);   // (a slice past the last pair starts behind it)
+        const int uu = u_lo + (pi < n_pairs ? pi : 0);   // (no block is run without a pair)
         const int nt = sc_row >> 4;
         const int tile = kSilu ? (nt ? (N / 2) / 16 : 0) + uu : uu * 2 + nt;
         const uint32_t *src = (const uint32_t *)p.scales + ((ebase + tile * 16 + (sc_row & 15)) * G) / 2;
@@ -475,6 +475,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
         }
     };
     if constexpr (!SPREAD) {
+        if (n_pairs == 0) return false;   // the last slices may lie behind the last pair
         bool first_pass = true;
         for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) {
             run_block(m0, first_pass);
@@ -482,7 +483,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
         }
         return false;
     } else if constexpr (!TAIL) {
-        if (mh * kRows < Me) run_block(mh * kRows, true);
+        if (mh * kRows < Me && n_pairs > 0) run_block(mh * kRows, true);
         return mh * kRows >= Me || Me > m_split * kRows;   // no row of its own, or a popular expert
     } else {
         // shares of the row blocks beyond the grid's: a pair per wavefront each, or a slice
