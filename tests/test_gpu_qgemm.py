@@ -813,6 +813,9 @@ def test_auto_path_by_rows_per_expert(q, fmt_name, E, rows):
     if fmt == q.QARL_W4A16_G128:
         none = torch.empty((16,), dtype=torch.uint8, device="cuda")
         assert torch.equal(q.qarl_qgemm_grouped(qw, x, off, M, out_dtype=q.QARL_OUT_F32, ws=none), by[q.QARL_PATH_DECODE])
+        over = x.clone()                                                      # K = N: row i of the result on top of row i of x
+        q.qarl_qgemm_grouped(qw, over, off, M, out=over)
+        assert torch.equal(over, q.qarl_qgemm_grouped(qw, x, off, M, path=q.QARL_PATH_DECODE))
 
 
 @pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8", "fp8", "fp4"])
