@@ -248,18 +248,22 @@ __device__ __forceinline__ void copy_barrier()
 // contiguous eighth of the TRUE items (the blocks of one tile share its L2), the surplus workgroups of all XCDs leave.
 // (Eighths of the bound left the surplus on the last XCDs: 7 of 8 worked on 3001 tokens and 128 experts.  W4A8 layer of
 // 3001 tokens 415 -> 389 us, FP8 of 8192 723 -> 695, W4A16 of 16384 1697 -> 1682.)
+// The tile's rows come out of the scan as well: a second look at the offsets was one more dependent load in front of the row
+// ids (layers of 128 experts, W4A16 16384 tokens 1596 -> 1586 us, FP8 8192 651 -> 645, W4A8 3001 381 -> 374).
 struct GroupedTile {
-    int e, mtile, block;   // expert, tile within the expert, work item of the tile
+    int e, block;     // expert, work item of the tile
+    int row0, rows;   // first row, rows up to the expert's end (at most kTile)
 };
 template <int kTile>
 __device__ __forceinline__ bool find_grouped_tile(const int32_t *offsets, int E, int n_blocks, GroupedTile &t)
 {
     const int lane = threadIdx.x & 63;
-    int cnt[4], sum = 0;
+    int off[5], cnt[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) off[q] = offsets[min(lane * 4 + q, E)];   // (experts past E: no rows)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int ex = lane * 4 + q;
-        cnt[q] = ex < E ? (offsets[ex + 1] - offsets[ex] + kTile - 1) / kTile : 0;
+        cnt[q] = (off[q + 1] - off[q] + kTile - 1) / kTile;
         sum += cnt[q];
     }
     int incl = sum;
@@ -273,20 +277,22 @@ __device__ __forceinline__ bool find_grouped_tile(const int32_t *offsets, int E,
     if (idx >= per_xcd || v >= items) return false;
     const int slot = (int)(v / (unsigned)n_blocks);
     t.block = (int)(v - (unsigned)slot * (unsigned)n_blocks);
-    int base = incl - sum, found = -1, mt = 0;
+    int base = incl - sum, found = -1, row0 = 0, rows = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (slot >= base && slot < base + cnt[q]) {
             found = lane * 4 + q;
-            mt = slot - base;
+            row0 = off[q] + (slot - base) * kTile;
+            rows = min(kTile, off[q + 1] - row0);
         }
         base += cnt[q];
     }
     const unsigned long long hit = __ballot(found >= 0);
     if (hit == 0) return false;   // does not happen: slot < number of tiles
     const int src = __ffsll((long long)hit) - 1;
-    t.e = __builtin_amdgcn_readfirstlane(__shfl(found, src, 64));
-    t.mtile = __builtin_amdgcn_readfirstlane(__shfl(mt, src, 64));
+    t.e = __builtin_amdgcn_readlane(found, src);
+    t.row0 = __builtin_amdgcn_readlane(row0, src);
+    t.rows = __builtin_amdgcn_readlane(rows, src);
     return true;
 }
 

@@ -104,8 +104,7 @@ __global__ __launch_bounds__(kBwThreads, 4) void qgemm_dx_kernel(DxParams p)
     GroupedTile tile;
     if (!find_grouped_tile<kTM>(p.offsets, p.E, G, tile)) return;
     const int e = tile.e, g = tile.block;   // output column block = scale group
-    const int row0 = p.offsets[e] + tile.mtile * kTM;
-    const int mrem = min(kTM, p.offsets[e + 1] - row0);
+    const int row0 = tile.row0, mrem = tile.rows;
     if (tid < kTM) s_orow[tid] = tid < mrem ? (p.out_row_map ? p.out_row_map[row0 + tid] : row0 + tid) : -1;
     for (int n = tid; n < N; n += kBwThreads) sc[n] = bf16_bits_to_f32(p.scales[((int64_t)e * N + n) * G + g]);
 
@@ -246,8 +245,7 @@ __global__ __launch_bounds__(kBwThreads, 2) void qgemm_dx_wide_kernel(DxParams p
     GroupedTile tile;
     if (!find_grouped_tile<kDxWTile>(p.offsets, p.E, K / kDxWTile, tile)) return;
     const int e = tile.e, kb = tile.block;
-    const int row0 = p.offsets[e] + tile.mtile * kDxWTile;
-    const int mrem = min(kDxWTile, p.offsets[e + 1] - row0);
+    const int row0 = tile.row0, mrem = tile.rows;
 
     // ---- copies.  Instruction i (0..3) of the wavefront moves the gradient rows 32 w + 8 i .. + 7; lane L fills position L % 8 of
     // row L / 8 of them.  Rows past the expert's end repeat its last one (their results are never stored).

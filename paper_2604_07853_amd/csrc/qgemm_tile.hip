@@ -78,8 +78,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_tile_kernel(TileParams p)
     if (!find_grouped_tile<kRows>(p.offsets, p.E, p.n_bgroups, tile)) return;
     const int e = tile.e, nb_end = min(p.n_blocks, (tile.block + 1) * p.bpw);
     int nb = tile.block * p.bpw;   // column block
-    const int row0 = p.offsets[e] + tile.mtile * kRows;
-    const int mrem = min(kRows, p.offsets[e + 1] - row0);
+    const int row0 = tile.row0, mrem = tile.rows;
     if (tid < kRows) {
         // rows past the expert's end read the tile's first row (valid data, results never stored)
         const int i = row0 + (tid < mrem ? tid : 0);

@@ -76,8 +76,7 @@ __global__ __launch_bounds__(kFThreads, 4) void qgemm_tile_fp8_kernel(Tile8Param
     GroupedTile tile;
     if (!find_grouped_tile<kFTM>(p.offsets, p.E, p.n_blocks, tile)) return;
     const int e = tile.e, nb = tile.block;
-    const int row0 = p.offsets[e] + tile.mtile * kFTM;
-    const int mrem = min(kFTM, p.offsets[e + 1] - row0);
+    const int row0 = tile.row0, mrem = tile.rows;
     // row ids (their loads go out in front of the weight copies below)
     int xrow = 0, orow_g = -1;
     if (tid < kFTM) {
