@@ -177,6 +177,29 @@ def test_tiled_path_at_the_edges_of_its_tiles(q, oracle, fmt, N, K):
 
 
 @pytest.mark.parametrize("fmt", ["fp8", "fp4"])
+@pytest.mark.parametrize("N,K", [(32, 128), (352, 256), (256, 384), (544, 512), (96, 896)])
+def test_tiled_path_silu_pieces_and_stage_counts(q, oracle, fmt, N, K):
+    """Fewer, as many and more 128-k stages than a workgroup holds ahead, column blocks that end inside a 256-byte row piece of the gated
+    output, and rows scattered by an output order: every row is written whole, no other is touched."""
+    rows = (1, 130, 0, 64)
+    M, E = sum(rows), len(rows)
+    w = synth.normal_bf16((E, N, K), 0.02, seed=N + K)
+    x = synth.normal_bf16((M, K), 1.0, seed=N)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    rm = np.random.default_rng(N).permutation(M).astype(np.int32)
+    xq, sx = q.qarl_quantize_rows_fp8(x.cuda())
+    wq, sw, gemm, qw = _quantized(q, oracle, fmt, w)
+    y_ref = gemm(*oracle.quantize_fp8_rows(np_bits(x)), wq, sw, off, rm)
+    out = torch.full((M + 2, N // 2), 7.0, dtype=torch.bfloat16, device="cuda")   # a row in front and one behind
+    q.qarl_qgemm_grouped(qw, xq, _i32(off), M, row_map=_i32(rm), x_scales=sx, epilogue=q.QARL_EPI_SILU_MUL, path=q.QARL_PATH_PREFILL,
+                         out=out[1:1 + M])
+    a_bits, a_ref = oracle.silu_mul(y_ref)
+    assert norm_err_bf16(out[1:1 + M].float().cpu().numpy(), a_ref) <= TOL_BF16
+    assert flip_fraction(np_bits(out[1:1 + M].contiguous()), a_bits) <= MAX_FLIPS_FP8
+    assert bool((out[0] == 7).all()) and bool((out[M + 1] == 7).all())
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "fp4"])
 def test_one_hot_probe_four_token_tiles(q, oracle, fmt):
     """512 one-hot rows (448 e_k, scale 1) of one expert, 320 weight rows: the tiled kernel returns 448 times the
     dequantized weight bit for bit, i.e. every k of every stage meets its own weight element in every wavefront's tiles
