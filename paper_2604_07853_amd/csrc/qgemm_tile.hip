@@ -36,9 +36,10 @@ constexpr int kRows = 64, kCols = 256;        // tile of a workgroup
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kRowBytes = kGroup * 2;         // bytes of a token row per stage (bf16, no padding: chunks are swizzled)
 constexpr int kXBytes = kRows * kRowBytes;    // token rows of a stage
-constexpr int kWaveBytes = 4 * 1024 + 256 + 256;   // a wavefront's codes, group sums, scales
-constexpr int kStageBytes = kXBytes + kWaves * kWaveBytes;
-constexpr int kCopies = 10;                   // copies of a wavefront per stage
+constexpr int kWaveBytes = 4 * 1024;          // a wavefront's codes
+constexpr int kStageBytes = kXBytes + kWaves * kWaveBytes + 256;   // and the rows' group sums
+constexpr int kScaleBytes = 256;              // a wavefront's scales, a dword (two groups where they are even in number) per column
+constexpr int kTileLds = 2 * kStageBytes + 2 * kWaves * kScaleBytes;
 
 struct TileParams {
     const unsigned char *codes;   // 1 KiB blocks [E * N / 16][K / 128]
@@ -118,16 +119,15 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_tile_kernel(TileParams p)
         sidx_c[1] = (uint32_t)__shfl((int)sidx, 32 + c, 64);
     };
     set_block();
-    auto copy_one = [&](int g, int buf, int j) {
-        unsigned char *xs = smem + buf * kStageBytes, *ws = xs + kXBytes + wave * kWaveBytes;
-        if (j < 4) copy16_to_lds(xsrc[j] + g * kRowBytes, xs + (wave * 16 + j * 4) * kRowBytes);
-        else if (j < 8) copy16_to_lds(p.codes + (boff[j - 4] + (uint32_t)g * 1024u), ws + (j - 4) * 1024);
-        else if (j == 8) copy4_to_lds(sum_src + g, ws + 4096);
-        else copy4_to_lds(p.scales + (((sidx + (uint32_t)g) * 2u) & ~3u), ws + 4096 + 256);
-    };
+    const int sc_sh = 1 - (G & 1);   // the dword of a column's scale serves two groups where there is an even number of them
     auto copy_stage = [&](int g, int buf) {
+        unsigned char *xs = smem + buf * kStageBytes, *ws = xs + kXBytes + wave * kWaveBytes;
 #pragma unroll
-        for (int j = 0; j < kCopies; ++j) copy_one(g, buf, j);
+        for (int j = 0; j < 4; ++j) copy16_to_lds(xsrc[j] + g * kRowBytes, xs + (wave * 16 + j * 4) * kRowBytes);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) copy16_to_lds(p.codes + (boff[j] + (uint32_t)g * 1024u), ws + j * 1024);
+        if (wave == (g & 3)) copy4_to_lds(sum_src + g, xs + kXBytes + kWaves * kWaveBytes);
+        if (!(g & sc_sh)) copy4_to_lds(p.scales + (((sidx + (uint32_t)g) * 2u) & ~3u), smem + 2 * kStageBytes + (((g >> sc_sh) & 1) * kWaves + wave) * kScaleBytes);
     };
 
     // ---- operand reads.  Lane (row or column c of the tile, half h) takes k [64 h + 8 j, + 8) of the stage in slice j: chunk
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_tile_kernel(TileParams p)
 #pragma unroll
     for (int j = 0; j < 8; ++j) xoff[j] = c * kRowBytes + (((8 * h + j) ^ (c & 15)) << 4);
     const int woff = kXBytes + wave * kWaveBytes + (c >> 4) * 1024 + h * 512 + (c & 15) * 16;
-    const int soff = kXBytes + wave * kWaveBytes + 4096;
+    const int soff = kXBytes + kWaves * kWaveBytes;
 
     f32x16 acc[2][2];   // [row tile][column tile]
     auto stage = [&](int g, auto buf_c) {
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_tile_kernel(TileParams p)
         float s16[2];
 #pragma unroll
         for (int ns = 0; ns < 2; ++ns) {
-            const uint32_t d = *(const uint32_t *)(st + soff + 256 + (ns * 32 + c) * 4);
+            const uint32_t d = *(const uint32_t *)(smem + 2 * kStageBytes + (((g >> sc_sh) & 1) * kWaves + wave) * kScaleBytes + (ns * 32 + c) * 4);
             s16[ns] = 16.f * __uint_as_float(((sidx_c[ns] + (uint32_t)g) & 1) ? d & 0xffff0000u : d << 16);
         }
         f32x16 ag[2][2];
@@ -353,7 +353,7 @@ static int launch_cfg(const GemmArgs &a, hipStream_t s)
     static LdsLimitOnce once;
     auto kern = qgemm_tile_kernel<EPI>;
     if (int rc = raise_lds_limit((const void *)kern, once, "hipFuncSetAttribute(tile)")) return rc;
-    kern<<<dim3((unsigned)total), dim3(kThreads), 2 * kStageBytes, s>>>(p);
+    kern<<<dim3((unsigned)total), dim3(kThreads), kTileLds, s>>>(p);
     return check_hip(hipGetLastError(), "qgemm_tile_kernel");
 }
 
