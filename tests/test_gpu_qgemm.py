@@ -529,6 +529,35 @@ def test_fused_combine_of_few_pairs_equals_grouped_decode(q, fmt_name, E, N, K, 
     _few_pairs_case(q, fmt, synth.normal_bf16((E, N, K), 0.02, seed=K + T, device="cuda"), T, topk, True)
 
 
+@pytest.mark.parametrize("fmt_name", ["fp8", "fp4"])
+@pytest.mark.parametrize("E,N,K,T,topk", [(16, 96, 128, 100, 2),      # fewer stages than the ring in LDS has: registers
+                                          (16, 96, 256, 100, 2),      # as many (FP4: fewer)
+                                          (16, 64, 384, 60, 2),       # one more (FP4: half a stage, registers)
+                                          (16, 544, 768, 31, 1),      # 16-row blocks, slices of nine pairs
+                                          (128, 512, 768, 300, 8),    # 64-row blocks, one per slice
+                                          (16, 32, 1024, 500, 2),     # several row blocks of 32: temporal copies
+                                          (3, 64, 2048, 90, 2)])      # a token tile that fills most of the LDS
+def test_routed_ring_in_lds_equals_the_register_ring(q, fmt_name, E, N, K, T, topk):
+    """The grouped decode call keeps its weight ring in registers.  Every output kind, bit for bit, and no row in front of the
+    output or behind it: rows past an expert's end are stored out of the bounds of a buffer that ends with the output."""
+    fmt = q.QARL_FP8_E4M3_CH if fmt_name == "fp8" else q.QARL_FP4_E2M1_CH
+    M = T * topk
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K + N, device="cuda"), fmt)
+    x = synth.normal_bf16((T, K), 1.0, seed=K + T, device="cuda")
+    r = q.qarl_moe_route(synth.router_logits(T, 64 * ((E + 63) // 64), T, device="cuda"), topk)
+    ids = (r.ids % E).reshape(-1).contiguous()
+    pairs = torch.argsort(ids, stable=True)
+    off = _i32(np.concatenate([[0], np.cumsum(np.bincount(ids.cpu().numpy(), minlength=E))]))
+    xq, sx = q.qarl_quantize_rows_fp8(x)
+    for epi, dt in ((q.QARL_EPI_NONE, q.QARL_OUT_F32), (q.QARL_EPI_NONE, q.QARL_OUT_BF16), (q.QARL_EPI_SILU_MUL, q.QARL_OUT_BF16)):
+        want = q.qarl_qgemm_grouped(qw, xq, off, M, row_map=(pairs // topk).int(), x_scales=sx, epilogue=epi, out_dtype=dt,
+                                    path=q.QARL_PATH_DECODE)
+        buf = torch.full((M + 2, want.shape[1]), 7.0, dtype=want.dtype, device="cuda")
+        q.qarl_qgemm_routed(qw, x, ids, T, topk, True, epilogue=epi, out=buf[1:1 + M], out_dtype=dt)
+        assert torch.equal(buf[1:1 + M][pairs], want)
+        assert bool((buf[0] == 7).all()) and bool((buf[M + 1] == 7).all())
+
+
 @pytest.mark.parametrize("fmt_name,T", [("fp8", 40), ("w4a8", 40), ("fp8", 8), ("w4a8", 8), ("fp4", 8)])   # 80 and 16 pairs
 def test_routed_mode_rows_outside_the_fast_division_range(q, oracle, fmt_name, T):
     """Rows whose scale leaves the range of the corrected-reciprocal division (absmax near 2^-100 and near 2^100),
