@@ -190,8 +190,8 @@ __global__ __launch_bounds__(EPI == QARL_EPI_COMBINE ? 512 : 256, 2) void qgemm_
     }
 }
 
-// Where the line lies (the shapes of the int4 kernel's comment, layer): 8 tokens = 64 pairs FP8 80 us here against 91 on
-// the streaming kernel, FP4 50 against 62; 12 tokens 113 against 96, 70 against 65.  Below that the estimated times decide: the
+// Where the line lies (the shapes of the int4 kernel's comment, layer): 5 tokens = 40 pairs FP8 55 us here against 62 on
+// the streaming kernel, FP4 30 against 46; 8 tokens 75 against 66, 43 against 47.  Below that the estimated times decide: the
 // combine keeps a wavefront of eight busy per slot, so with few slots it loses early (128 experts, 2048 x 768, top-1 and 64
 // tokens: FP8 2.8 times the streaming kernel's time, FP4 4 times), and with few experts both epilogues do.
 constexpr int kSmallPairs = 64;
@@ -204,18 +204,20 @@ bool qgemm_small_fp8_supported(int N, int K, int T, int topk, int epilogue)
     return epilogue != QARL_EPI_COMBINE || topk <= 16;   // row scales and results of 16 slots
 }
 
-// See qgemm_small_w4_us.  Combine: a round of 256 workgroups takes its slots' rows and one tile (a second one beyond 8 slots).
+// See qgemm_small_w4_us; 19 500 calls, as many on the streaming kernel with its ring in LDS: off by 5 to 11 %.  By these estimates 5 % (FP4 2 %) of
+// the calls run on the kernel that is slower by more than 5 %, and the mean call takes 0.8 % (0.3 %) more than on the faster of the two; by
+// those for the register ring it was 16 % (8 %) and 4.4 % (1.7 %).  Combine: a round of 256 workgroups takes its slots' rows and one tile (a second one beyond 8 slots).
 double qgemm_small_fp8_us(int fmt, int N, int K, int T, int topk, int epilogue)
 {
     const bool w4 = fmt == QARL_FP4_E2M1_CH;
     const int G = K / kGroup, M = T * topk;
     if (epilogue == QARL_EPI_COMBINE) {
         const int rounds = (T * (N / 16) + 255) / 256, more = topk > 8;
-        return 1.7 + rounds * (w4 ? 1.86 + 0.13 * topk + 0.154 * G + 0.023 * topk * G + more * (1.3 + 0.09 * G)
-                                  : 1.48 + 0.36 * topk + 0.112 * G + 0.06 * topk * G + more * 1.8);
+        return w4 ? 2.34 + rounds * (0.49 + 0.183 * topk + 0.069 * G + 0.024 * topk * G + more * (0.82 + 0.122 * G))
+                  : 1.38 + rounds * (1.03 + 0.455 * topk + 0.073 * G + 0.052 * topk * G + more * (0.54 + 0.147 * G));
     }
     const double wgs = M * ((N / 16 + 3) / 4) / 512.;
-    return w4 ? 3.9 + 0.18 * G + wgs * (1.3 + 0.24 * G) : 4.6 + 0.26 * G + wgs * (3.0 + 0.4 * G);
+    return w4 ? 3.28 + 0.136 * G + wgs * (1.36 + 0.233 * G) : 3.72 + 0.205 * G + wgs * (3.5 + 0.41 * G);
 }
 
 int launch_qgemm_small_fp8(const GemmArgs &a, const float *combine_w, hipStream_t s)
