@@ -33,23 +33,21 @@ __device__ __forceinline__ void load_ids(const int32_t *ids, int n_ids, int (&id
 // The pairs of expert e among the router's ids by increasing pair id, the (token, slot) order a stable grouping gives:
 // activation rows to list[0 ..], pair ids to list[kIdsRows ..]; returns their number.  list[2 kIdsRows ..] is scratch of
 // kListWaves counts.  The caller puts a barrier in front of its reads of the list, and one between two calls.
-__device__ __forceinline__ int list_pairs(const int32_t *ids, int n_ids, int e, int x_per_token, int topk, int *list)
+__device__ __forceinline__ int list_pairs(const int (&idv)[8], int e, int x_per_token, int topk, int *list)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, base = tid * 8;
-    int idv[8];
-    load_ids(ids, n_ids, idv);
+    // hits of the lanes below, of the whole wavefront: eight ballots (a scan by shuffles is six dependent LDS operations)
     uint32_t hits = 0;
+    int below = 0, in_wave = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) hits |= (idv[k] == e) ? (1u << k) : 0u;
-    const int cnt = __popc(hits);
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
+    for (int k = 0; k < 8; ++k) {
+        const uint64_t b = __ballot(idv[k] == e);
+        hits |= (idv[k] == e) ? (1u << k) : 0u;
+        below = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, below));
+        in_wave += __popcll(b);
     }
     int *s_wcnt = list + 2 * kIdsRows;
-    if (lane == 63) s_wcnt[wave] = incl;
+    if (lane == 0) s_wcnt[wave] = in_wave;
     lds_barrier();
     int before = 0, total = 0;
 #pragma unroll
@@ -58,7 +56,7 @@ __device__ __forceinline__ int list_pairs(const int32_t *ids, int n_ids, int e, 
         before += w < wave ? cw : 0;
         total += cw;
     }
-    int rank = before + incl - cnt;
+    int rank = before + below;
     for (uint32_t hm = hits; hm; hm &= hm - 1) {
         const int pr = base + __builtin_ctz(hm);
         if (rank < kIdsRows) {
@@ -68,6 +66,12 @@ __device__ __forceinline__ int list_pairs(const int32_t *ids, int n_ids, int e, 
         ++rank;
     }
     return min(total, kIdsRows);
+}
+__device__ __forceinline__ int list_pairs(const int32_t *ids, int n_ids, int e, int x_per_token, int topk, int *list)
+{
+    int idv[8];
+    load_ids(ids, n_ids, idv);
+    return list_pairs(idv, e, x_per_token, topk, list);
 }
 
 // Rows of every expert, s_hist[0 .. kSpreadExperts - 1]; ends with a barrier.
