@@ -79,6 +79,7 @@ struct W4Params {
     // gathers (the row quantizer's arithmetic), keeps the e4m3 values as exact bf16 in the LDS tile and the row
     // scales in LDS for the epilogue.
     int qx;
+    int one_tile;      // 64-row blocks: one row tile for blocks of at most 32 rows
     int spread;        // row blocks beyond the grid's are dealt out (spread_item)
 };
 constexpr int kQxScaleBytes = 4 * 64;   // LDS for the row scales of a block (up to 64 rows), routed mode
@@ -238,8 +239,9 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
     row0 = p.offsets[e];
     Me = p.offsets[e + 1] - row0;
     }
-    // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + n_pairs - 1
-    auto run_block = [&](int m0, bool first_pass) __attribute__((always_inline)) {
+    // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + n_pairs - 1, on NM of the block's MT row tiles
+    auto run_rows = [&](auto nm_c, int m0, bool first_pass) __attribute__((always_inline)) {
+        constexpr int NM = decltype(nm_c)::value;
         const int mrem = min(kRows, Me - m0);
         lds_barrier();  // the row map copy is complete / the previous pass is done with the LDS tile
         const bool use_tmp = map_in_lds && (first_pass || routed);   // the routed list has its own LDS region
@@ -360,7 +362,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
             const int q = lane >> 4;
             for (int g = wave; g < G; g += kWaves) {
 #pragma unroll
-                for (int mt = 0; mt < kRows / 16; ++mt) {
+                for (int mt = 0; mt < (HALF ? 1 : 2 * NM); ++mt) {
                     f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -384,9 +386,9 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
             if (lane == 0) npi = atomicAdd(s_next, 1);
             npi = __builtin_amdgcn_readfirstlane(npi);
             load_scales(npi);
-            f32x16 acc[MT];
+            f32x16 acc[NM];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[mt][i] = 0.f;
             for (int g0 = 0; g0 < G; g0 += R) {
@@ -398,9 +400,9 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
                     const int g = g0 + r;
                     Slot &cur = ring[r];
                     // lane (m32, h), register i of a 32x32 result -> token row 8 (i / 4) + 4 h + i % 4
-                    f32x16 ag[MT];
+                    f32x16 ag[NM];
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
+                    for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                         for (int i4 = 0; i4 < 4; ++i4) {
                             const f32x4 init = *(const f32x4 *)(sx + g * kRows + (mt * 32 + 8 * i4 + 4 * h) % kRows);
@@ -413,7 +415,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
                         for (int j = 0; j < 4; ++j) {
                             const bf16x8 bw = unpack_int4_word(cur.w[L][j]);
 #pragma unroll
-                            for (int mt = 0; mt < MT; ++mt) {
+                            for (int mt = 0; mt < NM; ++mt) {
                                 const bf16x8 a = *(const bf16x8 *)(xs + ((mt * 32 + m32) % kRows) * stride +
                                                                    (g * 128 + L * 64 + h * 32 + j * 8) * 2);
                                 ag[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bw, ag[mt], 0, 0, 0);
@@ -421,7 +423,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
                         }
                     const float s16 = 16.f * bf16_bits_to_f32(ssc[((it & 1) % kScBufs) * 32 * G + m32 * G + g]);
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
+                    for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) acc[mt][i] = fmaf(s16, ag[mt][i], acc[mt][i]);
                     fill(cur, r, nsrc);   // refill this slot with the group R ahead
@@ -430,7 +432,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
             // ---- epilogue of this pair
             const int u = u_lo + pi;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
+            for (int mt = 0; mt < NM; ++mt) {
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
                     const i32x4 orow4 = *(const i32x4 *)(s_orow + mt * 32 + 8 * i4 + 4 * h);
@@ -473,6 +475,14 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
             park_scales((it + 1) & 1);
             pi = npi;
         }
+    };
+    // A block of at most 32 rows takes one row tile of a 64-row kernel's two: half the operand reads and matrix instructions.  p.one_tile:
+    // where few blocks of an even router have more (64 / 128 experts with K = 1024, 300 tokens, layer 34 -> 28 / 74 -> 65 us); beside more of
+    // them the light blocks only take their bandwidth away (360 tokens: 75 -> 78 us).  Shares keep both row tiles (with the choice there too
+    // the kernel spilled: layers of 64 experts 1024 x 512, Zipf 1.1, 20-32 % slower).
+    auto run_block = [&](int m0, bool first_pass) __attribute__((always_inline)) {
+        if (MT == 1 || TAIL || !p.one_tile || Me - m0 > 32) run_rows(std::integral_constant<int, MT>(), m0, first_pass);
+        else run_rows(std::integral_constant<int, TAIL ? MT : 1>(), m0, first_pass);
     };
     if constexpr (!SPREAD) {
         if (n_pairs == 0) return false;   // the last slices may lie behind the last pair
@@ -522,7 +532,9 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
 // (expansion and matrix instructions are per weight, whatever the number of token rows).  Here K is walked in NC
 // chunks: the LDS tile holds 64 rows x K / NC, every wavefront owns PW pairs of weight tiles for the whole kernel
 // and keeps their accumulators (2 x 16 registers per pair) across the chunks, so the codes are expanded once and
-// meet all 64 rows.  The weight ring runs through (chunk, pair, group) without a break; between two chunks the
+// meet all 64 rows.  A block of at most 32 rows, most of them up to 400 tokens of 128 experts top-8, runs one of its two row tiles: with
+// both in every block each workgroup took 55 us of gate_up whatever its rows, and what a tile of padding costs is LDS reads and matrix
+// instructions at 60 % each.  A W4A16 layer of 272 / 336 / 512 tokens: 102 / 105 / 111 us before, 80 / 95 / 103 us now.  The weight ring runs through (chunk, pair, group) without a break; between two chunks the
 // workgroup meets at a barrier and gathers the next K-range of its token rows.  Scales go from global memory
 // straight to the lane that folds them (the 8 groups of a chunk are one 16-byte load).
 // SPREAD, TAIL: as above.
@@ -587,8 +599,8 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
         Me = p.offsets[e + 1] - row0;
     }
     // one row block, rows m0 .. of the expert's, against the pairs u_lo .. u_lo + 8 NJ - 1
-    auto run_block = [&](auto nj_c, int m0) __attribute__((always_inline)) {
-        constexpr int NJ = decltype(nj_c)::value;
+    auto run_rows = [&](auto nj_c, auto nm_c, int m0) __attribute__((always_inline)) {
+        constexpr int NJ = decltype(nj_c)::value, NM = decltype(nm_c)::value;
         const int mrem = min(kRows, Me - m0);
         lds_barrier();  // the pair list is complete / the previous pass is done with the LDS tile
         if (tid < kRows) {
@@ -604,11 +616,11 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
             s_row[tid] = xr;
             s_orow[tid] = tid < mrem ? orow : -1;
         }
-        f32x16 acc[NJ][2];
+        f32x16 acc[NJ][NM];
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
+            for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[j][mt][i] = 0.f;
         u32x4 sc_cur = load_scales(wave, 0), sc_nxt = sc_cur;
@@ -621,10 +633,11 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
             // row's KC * 2 = 2 KiB; wavefront w copies rows 8 w .. 8 w + 7.  Rows past the expert's end repeat its
             // last row (their results are never stored).
             {
+                const int rows8 = s_row[wave * 8 + (lane & 7)];
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
                     const int r = wave * 8 + (u >> 1), hh = u & 1;
-                    const int xr = __builtin_amdgcn_readfirstlane(s_row[min(r, mrem - 1)]);
+                    const int xr = __builtin_amdgcn_readlane(rows8, u >> 1);
                     const unsigned char *src = (const unsigned char *)p.x + ((uint32_t)xr * (uint32_t)K * 2u +
                                                                               (uint32_t)(ch * KC * 2 + hh * 1024 + lane * 16));
                     copy16_to_lds(src, xs + r * stride + hh * 1024);
@@ -641,8 +654,8 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                 const u32x4 ones4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
                 const bf16x8 ones = __builtin_bit_cast(bf16x8, ones4);
                 const int q = lane >> 4;
-                for (int unit = wave; unit < GC * 4; unit += kWaves) {
-                    const int g = unit >> 2, mt = unit & 3;
+                for (int unit = wave; unit < GC * 2 * NM; unit += kWaves) {
+                    const int g = unit / (2 * NM), mt = unit % (2 * NM);
                     f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -675,9 +688,9 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                     for (int r = 0; r < R; ++r) {
                         const int g = g0 + r;   // group within the chunk
                         Slot &cur = ring[r];
-                        f32x16 ag[2];
+                        f32x16 ag[NM];
 #pragma unroll
-                        for (int mt = 0; mt < 2; ++mt)
+                        for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                             for (int i4 = 0; i4 < 4; ++i4) {
                                 const f32x4 init = *(const f32x4 *)(sx + g * kRows + mt * 32 + 8 * i4 + 4 * h);
@@ -690,7 +703,7 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                             for (int jj = 0; jj < 4; ++jj) {
                                 const bf16x8 bw = unpack_int4_word(cur.w[L][jj]);
 #pragma unroll
-                                for (int mt = 0; mt < 2; ++mt) {
+                                for (int mt = 0; mt < NM; ++mt) {
                                     const bf16x8 a = *(const bf16x8 *)(xs + (mt * 32 + m32) * stride +
                                                                        (g * 128 + L * 64 + h * 32 + jj * 8) * 2);
                                     ag[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bw, ag[mt], 0, 0, 0);
@@ -700,7 +713,7 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                         const uint32_t sw = g0 ? sc_cur[2 + (r >> 1)] : sc_cur[r >> 1];
                         const float s16 = 16.f * __uint_as_float((r & 1) ? (sw & 0xffff0000u) : (sw << 16));
 #pragma unroll
-                        for (int mt = 0; mt < 2; ++mt)
+                        for (int mt = 0; mt < NM; ++mt)
 #pragma unroll
                             for (int i = 0; i < 16; ++i) acc[j][mt][i] = fmaf(s16, ag[mt][i], acc[j][mt][i]);
                         fill(cur, r, nsrc);
@@ -716,7 +729,7 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
         for (int j = 0; j < NJ; ++j) {
             const int u = u_lo + wave + 8 * j;
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
+            for (int mt = 0; mt < NM; ++mt) {
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
                     const i32x4 orow4 = *(const i32x4 *)(s_orow + mt * 32 + 8 * i4 + 4 * h);
@@ -728,14 +741,13 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                     if (kSilu) {
 #pragma unroll
                         for (int ip = 0; ip < 2; ++ip) {
-                            // lanes of the gate tile (t = 0) finish row 2 ip, lanes of the up tile row 2 ip + 1: each
-                            // sends the value of the row it does not finish to its partner 16 lanes away
-                            const float v0 = acc[j][mt][i4 * 4 + 2 * ip], v1 = acc[j][mt][i4 * 4 + 2 * ip + 1];
-                            const float recv = __shfl_xor(t ? v0 : v1, 16, 64);
-                            const float gv = t ? recv : v0, uv = t ? v1 : recv;
+                            // (as in the kernel above: afterwards every lane holds a gate value and the up value of its column)
+                            const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[j][mt][i4 * 4 + 2 * ip]),
+                                                                              __float_as_uint(acc[j][mt][i4 * 4 + 2 * ip + 1]),
+                                                                              false, false);
                             const int64_t orow = t ? orow4[2 * ip + 1] : orow4[2 * ip];
                             if (orow >= 0) {
-                                const float a = silu_mul_f32(gv, uv);
+                                const float a = silu_mul_f32(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
                                 ((uint16_t *)p.out)[orow * (N / 2) + u * 16 + c] = f32_to_bf16_hw(a);
                             }
                         }
@@ -753,6 +765,11 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
                 }
             }
         }
+    };
+    // as above: one of the two row tiles for at most 32 rows, both in shares
+    auto run_block = [&](auto nj_c, int m0) __attribute__((always_inline)) {
+        if (TAIL || Me - m0 > 32) run_rows(nj_c, std::integral_constant<int, 2>(), m0);
+        else run_rows(nj_c, std::integral_constant<int, TAIL ? 2 : 1>(), m0);
     };
     if constexpr (!SPREAD) {
         for (int m0 = mh * kRows; m0 < Me; m0 += kRows * m_split) run_block(std::integral_constant<int, PW>(), m0);
@@ -904,6 +921,8 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     const W4Grid g = w4_grid(a.N, a.K, a.E, a.M);
     const double need = g.need;
     const int MT = g.MT, max_slices = g.max_slices, ssh = g.slice_sh;
+    const double mean = (double)a.M / (double)a.E;
+    p.one_tile = mean + 2.6 * sqrt(mean) <= 32.0;   // (about the largest of 128 experts under an even router)
     p.half_tile = g.half_tile;
     p.msplit_sh = g.msplit_sh;
     p.slice_sh = ssh;

@@ -7,9 +7,10 @@
 // v_mfma_f32_32x32x16_bf16): every operand read, every start value and every expanded word feeds two matrix
 // instructions, and no packed weight is read or expanded twice in a workgroup.  Everything a stage (one scale group)
 // needs reaches LDS by asynchronous copies one stage ahead: 16 KiB of gathered token rows (16-byte chunks XOR-swizzled
-// with the row, so that copies and operand reads are free of bank conflicts) and, for each wavefront alone, its four
-// 1 KiB blocks of codes, the group sums and the scales of its columns.  Two stages are 68 KiB, a wavefront takes at most 256
-// registers: two workgroups per CU that run out of step, one's lookup, first stage and stores under the other's loop.
+// with the row, so that copies and operand reads are free of bank conflicts), the rows' group sums, copied once for the
+// workgroup, and, for each wavefront alone, its four 1 KiB blocks of codes and its columns' scales, where the groups are even in
+// number a dword of two groups every second stage (sums and scales per wavefront and stage: 1 % slower at 16384 tokens; with
+// none of either in the loop 4 % faster).  Two stages are 66.5 KiB, a wavefront takes at most 256 registers: two workgroups per CU that run out of step, one's lookup, first stage and stores under the other's loop.
 // In a slice of 8 k per lane the operand reads and the expansion of the next slice are spread between the four matrix
 // instructions of this one.  (Eight wavefronts of 64 x 32 with the codes in registers, operand reads twice as many per
 // matrix instruction, ran 2 % slower.)  A workgroup computes up to four neighbouring column blocks one after the other: the

@@ -753,6 +753,39 @@ def test_routed_combine_of_few_pairs_reads_shared_weights_once(q, fmt_name, E, N
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8"])
+@pytest.mark.parametrize("N,K", [(512, 2048), (96, 768), (288, 1024)])   # 64-row blocks: K-chunked tile, rings of three and four
+def test_int4_row_blocks_at_the_edge_of_a_row_tile(q, fmt_name, N, K):
+    """64-row blocks run one or two row tiles, by the expert's rows: 64, 33, 32, 31, 1 and 0 rows give bit for bit what the
+    kernel of 32-row blocks gives on at most 16 rows at a time."""
+    fmt = {"w4a16": q.QARL_W4A16_G128, "w4a8": q.QARL_W4A8_G128}[fmt_name]
+    counts, E, T, topk = [64, 33, 32, 31, 1, 0], 6, 64, 3
+    ids = torch.full((T, topk), 5, dtype=torch.int32)
+    ids[:, 0] = 0
+    ids[:33, 1], ids[33:, 1] = 1, 3          # 33 and 31
+    ids[:32, 2], ids[32, 2] = 2, 4           # 32 and 1
+    M = sum(counts)                          # the slots left over name expert 5, whose rows are not looked at
+    assert torch.bincount(ids.flatten())[:5].tolist() == counts[:5]
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K + N, device="cuda"), fmt)
+    x = synth.normal_bf16((T, K), 1.0, seed=T, device="cuda")
+    pairs = torch.argsort(ids.flatten(), stable=True)[:M].cuda()
+    tok = (pairs // topk).int()
+    rows, kw = x, {}
+    if fmt != q.QARL_W4A16_G128:
+        rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(x)
+    off = torch.tensor([0] + np.cumsum(counts).tolist(), dtype=torch.int32, device="cuda")
+    for epi, dt in ((q.QARL_EPI_NONE, q.QARL_OUT_F32), (q.QARL_EPI_SILU_MUL, q.QARL_OUT_BF16)):
+        routed = q.qarl_qgemm_routed(qw, x, ids.flatten().cuda(), T, topk, True, epilogue=epi, out_dtype=dt)[pairs]
+        grouped = q.qarl_qgemm_grouped(qw, rows, off, M, row_map=tok, epilogue=epi, out_dtype=dt, path=q.QARL_PATH_DECODE, **kw)
+        for e, n in enumerate(counts):
+            for r0 in range(0, n, 16):
+                n16, at = min(16, n - r0), sum(counts[:e]) + r0
+                one = torch.tensor([0 if i <= e else n16 for i in range(E + 1)], dtype=torch.int32, device="cuda")
+                want = q.qarl_qgemm_grouped(qw, rows, one, n16, row_map=tok[at:at + n16].contiguous(), epilogue=epi, out_dtype=dt,
+                                            path=q.QARL_PATH_DECODE, **kw)
+                assert torch.equal(routed[at:at + n16], want) and torch.equal(grouped[at:at + n16], want)
+
+
 @pytest.mark.parametrize("fmt_name,E,N,K,T,topk,named", [
     ("w4a16", 16, 64, 512, 512, 4, 4),         # every token names the same experts: the others' workgroups take their row blocks
     ("w4a16", 3, 96, 256, 200, 2, 3),          # no workgroup without rows, a slice of three pairs of tiles
