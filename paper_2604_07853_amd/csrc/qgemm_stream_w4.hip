@@ -630,14 +630,19 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
             lds_barrier();  // row ids are written / every wavefront has left the previous chunk's tile
             // ---- gather the K-range of the token rows by asynchronous global -> LDS copies (no registers: the
             // accumulators of all pairs stay live across this point): a wavefront instruction moves 1 KiB, half of a
-            // row's KC * 2 = 2 KiB; wavefront w copies rows 8 w .. 8 w + 7.  Rows past the expert's end repeat its
-            // last row (their results are never stored).
+            // row's KC * 2 = 2 KiB; wavefront w copies rows w, 8 + w ...  Rows past the expert's end repeat its last row in a block
+            // of two row tiles; in a block of one they stay as they are: a row of the tile feeds its own results only, and theirs
+            // are never stored (three W4A16 layers of 257 / 272 / 300 tokens 262 / 265 / 283 -> 257 / 262 / 281 us; left out with two
+            // row tiles too, a Zipf router's 272 tokens took 325 -> 327).
             {
-                const int rows8 = s_row[wave * 8 + (lane & 7)];
+                constexpr int RW = 4 * NM;
+                const int sw = __builtin_amdgcn_readfirstlane(wave), n_rows = __builtin_amdgcn_readfirstlane(mrem);
+                const int rows = s_row[sw + 8 * (lane & (RW - 1))];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int r = wave * 8 + (u >> 1), hh = u & 1;
-                    const int xr = __builtin_amdgcn_readlane(rows8, u >> 1);
+                for (int u = 0; u < 2 * RW; ++u) {
+                    const int r = sw + 8 * (u >> 1), hh = u & 1;
+                    if (NM == 1 && r >= n_rows) break;
+                    const int xr = __builtin_amdgcn_readlane(rows, u >> 1);
                     const unsigned char *src = (const unsigned char *)p.x + ((uint32_t)xr * (uint32_t)K * 2u +
                                                                               (uint32_t)(ch * KC * 2 + hh * 1024 + lane * 16));
                     copy16_to_lds(src, xs + r * stride + hh * 1024);
