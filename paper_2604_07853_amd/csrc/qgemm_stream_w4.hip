@@ -876,14 +876,19 @@ int launch_ring(const W4Params &p, hipStream_t s)
 
 // Row blocks and slices of the weight tiles that a launch gives every expert (the wide kernel chooses its own).
 struct W4Grid {
-    double need;      // rows per expert the grid should cover in one pass: mean + 4 sigma of a uniform router
+    double need;      // rows per expert the grid should cover in one pass: mean + 4 (3.75, below) sigma of a uniform router
     int MT, half_tile, msplit_sh, slice_sh, max_slices;
 };
-W4Grid w4_grid(int N, int K, int E, int64_t M)
+W4Grid w4_grid(int N, int K, int E, int64_t M, bool dealt)   // dealt: row blocks beyond the grid's are dealt out, not further passes
 {
     W4Grid g;
     const double mean = (double)M / (double)E;
-    g.need = mean + 4.0 * sqrt(mean);
+    // One expert beyond the grid costs a second pass, or a share: 3.75 sigma (at 128 experts top-8 blocks of 32 rows up to 266 tokens instead
+    // of 256) where shares are dealt and there are 128 experts or more.  Three layers of 128 experts, 64-row -> 32-row blocks, even / Zipf
+    // router, us: W4A16 264 tokens 240 / 325 -> 231 / 245-262, W4A8 262 tokens 319 / 364 -> 249 / 265.  At 278 tokens (3.5 sigma) some expert of
+    // three layers had 33 rows for two of three even routers (260 -> 307).  64 experts 2048 x 512 have fewer workgroups without rows: 130
+    // tokens 133 / 176 -> 132 / 213.
+    g.need = mean + (dealt && E >= 128 ? 3.75 : 4.0) * sqrt(mean);
     // 64-row blocks where the whole K of 64 rows fits the LDS tile, 32-row blocks otherwise, 16-row blocks for K
     // beyond 2048
     g.MT = (g.need > 32.0 && lds_bytes(K, 2) <= 160 * 1024) ? 2 : 1;
@@ -923,7 +928,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     p.qx = (a.ids && a.fmt == QARL_W4A8_G128) ? 1 : 0;
     p.n_units = (EPI == QARL_EPI_SILU_MUL) ? (a.N / 2) / 16 : a.N / 32;
     p.spread = 0;
-    const W4Grid g = w4_grid(a.N, a.K, a.E, a.M);
+    const W4Grid g = w4_grid(a.N, a.K, a.E, a.M, spread_blocks(a, 32) != 0);
     const double need = g.need;
     const int MT = g.MT, max_slices = g.max_slices, ssh = g.slice_sh;
     const double mean = (double)a.M / (double)a.E;
@@ -1001,7 +1006,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
 
 int qgemm_stream_w4_units_per_wave(int N, int K, int E, int64_t M)
 {
-    const int n = kWaves << w4_grid(N, K, E, M).slice_sh;
+    const int n = kWaves << w4_grid(N, K, E, M, false).slice_sh;   // (the calls that ask have at most 64 pairs: far below the line)
     return (N / 32 + n - 1) / n;
 }
 

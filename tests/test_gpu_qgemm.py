@@ -786,6 +786,28 @@ def test_int4_row_blocks_at_the_edge_of_a_row_tile(q, fmt_name, N, K):
                 assert torch.equal(routed[at:at + n16], want) and torch.equal(grouped[at:at + n16], want)
 
 
+@pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8"])
+@pytest.mark.parametrize("T", [257, 266, 267])        # 128 experts top-8: 32-row blocks with dealt shares end at 266 tokens
+@pytest.mark.parametrize("N,K,zipf", [(512, 2048, 0.0), (512, 2048, 1.1), (96, 768, 1.1)])
+def test_int4_block_height_of_many_experts(q, fmt_name, T, N, K, zipf):
+    """Blocks of 32 or 64 rows, by the routed call's expected rows: bit for bit the grouped call's results."""
+    fmt, E, topk = {"w4a16": q.QARL_W4A16_G128, "w4a8": q.QARL_W4A8_G128}[fmt_name], 128, 8
+    M = T * topk
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K + N, device="cuda"), fmt)
+    x = synth.normal_bf16((T, K), 1.0, seed=T, device="cuda")
+    r = q.qarl_moe_route(synth.router_logits(T, E, T, device="cuda", zipf_s=zipf), topk)
+    ids = r.ids.reshape(-1).contiguous()
+    pairs = torch.argsort(ids, stable=True)
+    off = _i32(np.concatenate([[0], np.cumsum(np.bincount(ids.cpu().numpy(), minlength=E))]))
+    rows, kw = x, {}
+    if fmt != q.QARL_W4A16_G128:
+        rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(x)
+    for epi, dt in ((q.QARL_EPI_NONE, q.QARL_OUT_F32), (q.QARL_EPI_SILU_MUL, q.QARL_OUT_BF16)):
+        want = q.qarl_qgemm_grouped(qw, rows, off, M, row_map=(pairs // topk).int(), epilogue=epi, out_dtype=dt, path=q.QARL_PATH_DECODE, **kw)
+        got = q.qarl_qgemm_routed(qw, x, ids, T, topk, True, epilogue=epi, out_dtype=dt)[pairs]
+        assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("fmt_name,E,N,K,T,topk,named", [
     ("w4a16", 16, 64, 512, 512, 4, 4),         # every token names the same experts: the others' workgroups take their row blocks
     ("w4a16", 3, 96, 256, 200, 2, 3),          # no workgroup without rows, a slice of three pairs of tiles
