@@ -27,10 +27,13 @@ StreamGrid stream_grid(int N, int K, int E, int64_t M, bool routed, bool w4)
     // 64 rows where the slices alone fill the chip (routed layers, top-8 of 128, two blocks of 32 -> one of 64: 300 tokens FP8
     // 196 -> 148 us, FP4 137 -> 107, 512 tokens 203 -> 160 and 144 -> 118); with few experts blocks of 32 run side by side
     // (16 experts 1536 x 2048, 48 rows each: FP8 30 against 33 us, FP4 24 against 28).
-    // FP4, routed: 64 rows only where the ring in LDS fits beside them; else two blocks of 32, the second reading the weights out of L2 (300 / 400 /
+    // FP4, routed: where the ring in LDS fits beside 32 rows and not beside 64, two blocks of 32, the second reading the weights out of L2 (300 / 400 /
     // 512 tokens, even router, layer 102 / 108 / 113 -> 102 / 106 / 111 us, Zipf 114 / 116 / 163 -> 113 / 115 / 134; FP8, whose codes are twice as
-    // many: 141 / 147 / 153 -> 152 / 159 / 164).
-    const bool mt4 = stream_lds_bytes(K, 4, routed) <= 160 * 1024 && K <= 2048 && !(routed && w4 && lr_lds_bytes(K, 4, kLrStages, N / 32, 1) > 160 * 1024);
+    // many: 141 / 147 / 153 -> 152 / 159 / 164).  K an odd multiple of 128 has no ring in LDS at either height and keeps 64 rows (128 experts, top-8,
+    // 32 -> 64 rows, 270 / 400 / 512 tokens: 1408 x 768 111 / 117 / 119 -> 84 / 90 / 93 us, Zipf 119 / 120 / 136 -> 98 / 101 / 140; 1664 x 1408
+    // 247 / 253 / 256 -> 166 / 175 / 181, Zipf 243 / 244 / 246 -> 176 / 179 / 242; 1920 x 768, Zipf, 512 tokens 139 -> 155).
+    auto ring_in_lds = [&](int MT) { return lr_shape_fits(w4, K, MT, kLrStages, N / 32, 1); };
+    const bool mt4 = stream_lds_bytes(K, 4, routed) <= 160 * 1024 && K <= 2048 && !(routed && w4 && ring_in_lds(2) && !ring_in_lds(4));
     const int mt_fit = mt4 ? 4 : stream_lds_bytes(K, 2, routed) <= 160 * 1024 ? 2
                        : stream_lds_bytes(K, 1, routed) <= 160 * 1024 ? 1 : 0;
     const int max_slices = (N / 32 + kSWaves - 1) / kSWaves;

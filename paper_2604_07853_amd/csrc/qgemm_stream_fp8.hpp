@@ -543,11 +543,16 @@ inline size_t lr_lds_bytes(int K, int MT, int R, int n_units, int n_slices)
     return (size_t)lr_ring_at(K, MT) + (size_t)kSWaves * R * 4096 + (size_t)per_slice * 32 * 4;
 }
 
+// Whether a routed launch of this shape keeps its ring in LDS: whole lines of k in stages of 128 bytes, one per stage of the ring at least
+inline bool lr_shape_fits(bool w4, int K, int MT, int R, int n_units, int n_slices)
+{
+    const int k_stage = w4 ? 256 : 128;
+    return K % k_stage == 0 && K / k_stage >= R && lr_lds_bytes(K, MT, R, n_units, n_slices) <= 160 * 1024;
+}
+
 inline bool lr_fits(const StreamParams &p, int MT, int R)
 {
-    if (!p.ids || (p.w4 && p.K % 256 != 0)) return false;
-    const int n_steps = p.K / (p.w4 ? 256 : 128);
-    return n_steps >= R && lr_lds_bytes(p.K, MT, R, p.n_units, p.n_slices) <= 160 * 1024 && (int64_t)p.n_ids * p.N * 4 < 0xfffffff0LL;
+    return p.ids && lr_shape_fits(p.w4, p.K, MT, R, p.n_units, p.n_slices) && (int64_t)p.n_ids * p.N * 4 < 0xfffffff0LL;
 }
 
 template <int EPI, int MT, int R, bool W4, bool QX, int LR = 0, bool SPREAD = false>
@@ -582,13 +587,15 @@ int launch_ring(const StreamParams &p, hipStream_t s)
     if (lr_fits(p, MT, kLrStages)) return launch_lr<EPI, MT, kLrStages, W4>(p, s);
     auto go = [&](auto r_c) -> int {
         constexpr int R = decltype(r_c)::value;
-        return p.ids ? launch_cfg_w<EPI, MT, R, W4, true>(p, s) : launch_cfg_w<EPI, MT, R, W4, false>(p, s);
+        // (64 rows of e2m1 codes in the routed mode: only K = 256 and odd numbers of groups come here)
+        if constexpr (W4 && MT == 4 && R == 4) return launch_cfg_w<EPI, MT, R, W4, false>(p, s);
+        else return p.ids ? launch_cfg_w<EPI, MT, R, W4, true>(p, s) : launch_cfg_w<EPI, MT, R, W4, false>(p, s);
     };
     // ring depth (steps in flight per wavefront): 8 KiB per wavefront, i.e. two steps of e4m3 codes (4 KiB each: two
     // tiles, two 1 KiB loads per tile) or four steps of e2m1 codes, already saturate HBM with eight wavefronts per CU;
     // twice that measured 4 % slower on the gate_up launch, and a deeper ring would push the gather into spilling
     if constexpr (W4) {
-        if (G % 4 == 0) return go(std::integral_constant<int, 4>());
+        if (G % 4 == 0 && !(MT == 4 && p.ids)) return go(std::integral_constant<int, 4>());
         if (G % 3 == 0) return go(std::integral_constant<int, 3>());
     }
     if (G % 2 == 0) return go(std::integral_constant<int, 2>());

@@ -558,6 +558,26 @@ def test_routed_ring_in_lds_equals_the_register_ring(q, fmt_name, E, N, K, T, to
         assert bool((buf[0] == 7).all()) and bool((buf[M + 1] == 7).all())
 
 
+@pytest.mark.parametrize("K,tiles", [(2048, 2), (1920, 4), (1408, 4), (384, 4), (256, 4)])
+def test_fp4_block_height_follows_the_ring(q, K, tiles):
+    """More than 32 rows per expert to expect: two blocks of 32 rows only where that makes room for the ring in LDS (K = 2048).
+    An odd number of 128-k groups, or fewer stages than the ring has, never takes it and keeps one block of 64.  Same bits."""
+    E, N, T, topk = 128, 512, 300, 8
+    qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K, device="cuda"), q.QARL_FP4_E2M1_CH)
+    x = synth.normal_bf16((T, K), 1.0, seed=T, device="cuda")
+    r = q.qarl_moe_route(synth.router_logits(T, E, T, device="cuda"), topk)
+    xq, sx = q.qarl_quantize_rows_fp8(x)
+    want = q.qarl_qgemm_grouped(qw, xq, r.offsets, T * topk, row_map=r.tokens, x_scales=sx, out_dtype=q.QARL_OUT_F32, path=q.QARL_PATH_DECODE)
+    got = torch.empty_like(want)
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, out=got, out_dtype=q.QARL_OUT_F32)
+        torch.cuda.synchronize()
+    assert torch.equal(got[r.pairs.long()], want)
+    names = [e.name for e in prof.events() if "qgemm_stream_fp8_kernel<" in e.name]
+    assert [int(n.split("qgemm_stream_fp8_kernel<")[1].split(",")[1]) for n in names] == [tiles], names   # <epilogue, 16-row tiles of a block, ...>
+
+
 @pytest.mark.parametrize("fmt_name,T", [("fp8", 40), ("w4a8", 40), ("fp8", 8), ("w4a8", 8), ("fp4", 8)])   # 80 and 16 pairs
 def test_routed_mode_rows_outside_the_fast_division_range(q, oracle, fmt_name, T):
     """Rows whose scale leaves the range of the corrected-reciprocal division (absmax near 2^-100 and near 2^100),
