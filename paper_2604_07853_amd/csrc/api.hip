@@ -491,11 +491,7 @@ static int launch_routed(const qarl_qweight *W, const void *x, int x_per_token, 
         // in a layer call the streaming kernel needs the router's launch in front (FP8, 64 experts 1024 x 512, top-4, 6 tokens: 19.6 us per layer
         // with the few-pair gate_up that routes its tokens itself, 21.4 with router and streaming kernel)
         const double route_us = route ? 2.5 : 0.;
-        // An FP8 combine of short rows stays with the few-pair kernel up to 16 % above the streaming estimate: it needs no staging rows, and
-        // calls of this size have left the caller's workspace as it was (128 experts 1056 x 512, 15 tokens top-4: 17.3 us here, 13.3 us with
-        // staging rows and a combine launch; over 1783 shapes with K <= 512 the mean loss to the better kernel is 0.9 %, 0.05 % without).
-        const double margin = comb && W->fmt == QARL_FP8_E4M3_CH && W->K <= 512 ? 1.16 : 1.;
-        if (small_us <= margin * qgemm_stream_routed_us(W->fmt, W->N, W->K, W->E, T, topk, epilogue) + route_us) {
+        if (small_us <= qgemm_stream_routed_us(W->fmt, W->N, W->K, W->E, T, topk, epilogue) + route_us) {
             const float *cw = comb ? combine_w : nullptr;
             if (route) {
                 // (the workgroups read logits and x while the first ones write: nothing written may lie on what is read)
