@@ -536,15 +536,31 @@ def test_fp8_combine_past_the_few_pair_line_takes_the_staging_rows(q, E, N, K, T
     _few_pairs_case(q, q.QARL_FP8_E4M3_CH, synth.normal_bf16((E, N, K), 0.02, seed=K + T, device="cuda"), T, topk, False)
 
 
+def _stream_fp8_launches(call):
+    """call's result, and (16-row tiles of a block, weight ring in LDS) of its qgemm_stream_fp8_kernel launches."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        r = call()
+        torch.cuda.synchronize()
+    args = [e.name.split("qgemm_stream_fp8_kernel<")[1].split(">")[0].split(", ") for e in prof.events() if "qgemm_stream_fp8_kernel<" in e.name]
+    return r, [(int(a[1]), a[5] != "0") for a in args]   # <epilogue, tiles, ring depth, e2m1, routed, ring, shares>
+
+
 @pytest.mark.parametrize("fmt_name", ["fp8", "fp4"])
-@pytest.mark.parametrize("E,N,K,T,topk", [(16, 96, 128, 100, 2),      # fewer stages than the ring in LDS has: registers
-                                          (16, 96, 256, 100, 2),      # as many (FP4: fewer)
-                                          (16, 64, 384, 60, 2),       # one more (FP4: half a stage, registers)
-                                          (16, 544, 768, 31, 1),      # 16-row blocks, slices of nine pairs
-                                          (128, 512, 768, 300, 8),    # 64-row blocks, one per slice
-                                          (16, 32, 1024, 500, 2),     # several row blocks of 32: temporal copies
-                                          (3, 64, 2048, 90, 2)])      # a token tile that fills most of the LDS
-def test_routed_ring_in_lds_equals_the_register_ring(q, fmt_name, E, N, K, T, topk):
+@pytest.mark.parametrize("E,N,K,T,topk,tiles,ring", [   # ring: the formats that keep it in LDS
+    (16, 96, 128, 100, 2, 2, ()),                       # fewer stages than the ring in LDS has: registers
+    (16, 96, 256, 100, 2, 2, ("fp8",)),                 # as many (FP4: fewer)
+    (16, 64, 384, 60, 2, 2, ("fp8",)),                  # one more (FP4: half a stage, registers)
+    (16, 544, 768, 65, 1, 1, ("fp8", "fp4")),           # 16-row blocks, slices of six and five pairs
+    (128, 1056, 768, 20, 4, 1, ("fp8", "fp4")),         # slices of 17 and 16 pairs: a wavefront's second and third pair; six stages, FP4 three
+    (128, 1056, 640, 100, 4, 1, ("fp8",)),              # ... five stages
+    (128, 1056, 1280, 300, 4, 2, ("fp8", "fp4")),       # ... blocks of 32 rows, ten stages, FP4 five
+    (128, 1056, 640, 300, 8, 4, ("fp8",)),              # ... of 64 rows, five stages
+    (128, 1056, 1280, 300, 8, 4, ("fp8", "fp4")),       # ... ten, FP4 five
+    (128, 512, 768, 300, 8, 4, ("fp8", "fp4")),         # 64-row blocks, a pair per wavefront
+    (16, 32, 1024, 500, 2, 2, ("fp8", "fp4")),          # several row blocks of 32: temporal copies
+    (3, 64, 2048, 90, 2, 2, ("fp8", "fp4"))])           # a token tile that fills most of the LDS
+def test_routed_ring_in_lds_equals_the_register_ring(q, fmt_name, E, N, K, T, topk, tiles, ring):
     """The grouped decode call keeps its weight ring in registers.  Every output kind, bit for bit, and no row in front of the
     output or behind it: rows past an expert's end are stored out of the bounds of a buffer that ends with the output."""
     fmt = q.QARL_FP8_E4M3_CH if fmt_name == "fp8" else q.QARL_FP4_E2M1_CH
@@ -560,7 +576,8 @@ def test_routed_ring_in_lds_equals_the_register_ring(q, fmt_name, E, N, K, T, to
         want = q.qarl_qgemm_grouped(qw, xq, off, M, row_map=(pairs // topk).int(), x_scales=sx, epilogue=epi, out_dtype=dt,
                                     path=q.QARL_PATH_DECODE)
         buf = torch.full((M + 2, want.shape[1]), 7.0, dtype=want.dtype, device="cuda")
-        q.qarl_qgemm_routed(qw, x, ids, T, topk, True, epilogue=epi, out=buf[1:1 + M], out_dtype=dt)
+        _, ran = _stream_fp8_launches(lambda: q.qarl_qgemm_routed(qw, x, ids, T, topk, True, epilogue=epi, out=buf[1:1 + M], out_dtype=dt))
+        assert ran == [(tiles, fmt_name in ring)]
         assert torch.equal(buf[1:1 + M][pairs], want)
         assert bool((buf[0] == 7).all()) and bool((buf[M + 1] == 7).all())
 
@@ -575,14 +592,9 @@ def test_fp4_block_height_follows_the_ring(q, K, tiles):
     r = q.qarl_moe_route(synth.router_logits(T, E, T, device="cuda"), topk)
     xq, sx = q.qarl_quantize_rows_fp8(x)
     want = q.qarl_qgemm_grouped(qw, xq, r.offsets, T * topk, row_map=r.tokens, x_scales=sx, out_dtype=q.QARL_OUT_F32, path=q.QARL_PATH_DECODE)
-    got = torch.empty_like(want)
-    torch.cuda.synchronize()
-    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
-        q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, out=got, out_dtype=q.QARL_OUT_F32)
-        torch.cuda.synchronize()
+    got, ran = _stream_fp8_launches(lambda: q.qarl_qgemm_routed(qw, x, r.ids, T, topk, True, out_dtype=q.QARL_OUT_F32))
     assert torch.equal(got[r.pairs.long()], want)
-    names = [e.name for e in prof.events() if "qgemm_stream_fp8_kernel<" in e.name]
-    assert [int(n.split("qgemm_stream_fp8_kernel<")[1].split(",")[1]) for n in names] == [tiles], names   # <epilogue, 16-row tiles of a block, ...>
+    assert [t for t, _ in ran] == [tiles]
 
 
 @pytest.mark.parametrize("fmt_name,T", [("fp8", 40), ("w4a8", 40), ("fp8", 8), ("w4a8", 8), ("fp4", 8)])   # 80 and 16 pairs
@@ -781,28 +793,33 @@ def test_routed_combine_of_few_pairs_reads_shared_weights_once(q, fmt_name, E, N
 
 
 @pytest.mark.parametrize("fmt_name", ["w4a16", "w4a8"])
+@pytest.mark.parametrize("T,topk", [(64, 5), (80, 4)])   # no expert can pass the grid's 64 rows; one could (the kernels with shares)
 @pytest.mark.parametrize("N,K", [(512, 2048), (96, 768), (288, 1024)])   # 64-row blocks: K-chunked tile, rings of three and four
-def test_int4_row_blocks_at_the_edge_of_a_row_tile(q, fmt_name, N, K):
-    """64-row blocks run one or two row tiles, by the expert's rows: 64, 33, 32, 31, 1 and 0 rows give bit for bit what the
+def test_int4_row_blocks_at_the_edge_of_a_row_tile(q, fmt_name, N, K, T, topk):
+    """64-row blocks run one or two row tiles, by the expert's rows: 64, 33, 32, 31, 1 and 0 rows, and some between, give bit for bit what the
     kernel of 32-row blocks gives on at most 16 rows at a time."""
     fmt = {"w4a16": q.QARL_W4A16_G128, "w4a8": q.QARL_W4A8_G128}[fmt_name]
-    counts, E, T, topk = [64, 33, 32, 31, 1, 0], 6, 64, 3
-    ids = torch.full((T, topk), 5, dtype=torch.int32)
-    ids[:, 0] = 0
-    ids[:33, 1], ids[33:, 1] = 1, 3          # 33 and 31
+    E, M = 16, T * topk
+    mean = M / E
+    assert mean + 3.75 * mean ** 0.5 > 32 >= mean + 2.6 * mean ** 0.5    # blocks of 64 rows, one row tile allowed
+    t = torch.arange(T)
+    fill = [[6], [7], [8, 9, 10], [11, 12, 13], [14, 15]]                # the experts of a slot that none of the six takes
+    ids = torch.stack([torch.tensor(fill[s])[t % len(fill[s])] for s in range(topk)], 1)
+    ids[:64, 0] = 0
+    ids[:33, 1], ids[33:64, 1] = 1, 3        # 33 and 31
     ids[:32, 2], ids[32, 2] = 2, 4           # 32 and 1
-    M = sum(counts)                          # the slots left over name expert 5, whose rows are not looked at
-    assert torch.bincount(ids.flatten())[:5].tolist() == counts[:5]
+    counts = torch.bincount(ids.flatten(), minlength=E).tolist()
+    assert counts[:6] == [64, 33, 32, 31, 1, 0] and max(counts) == 64
     qw = q.qarl_quantize_weights(synth.normal_bf16((E, N, K), 0.02, seed=K + N, device="cuda"), fmt)
     x = synth.normal_bf16((T, K), 1.0, seed=T, device="cuda")
-    pairs = torch.argsort(ids.flatten(), stable=True)[:M].cuda()
-    tok = (pairs // topk).int()
+    pairs = torch.argsort(ids.flatten(), stable=True).cuda()
+    tok, d_ids = (pairs // topk).int(), ids.int().flatten().cuda()
     rows, kw = x, {}
     if fmt != q.QARL_W4A16_G128:
         rows, kw["x_scales"] = q.qarl_quantize_rows_fp8(x)
     off = torch.tensor([0] + np.cumsum(counts).tolist(), dtype=torch.int32, device="cuda")
     for epi, dt in ((q.QARL_EPI_NONE, q.QARL_OUT_F32), (q.QARL_EPI_SILU_MUL, q.QARL_OUT_BF16)):
-        routed = q.qarl_qgemm_routed(qw, x, ids.flatten().cuda(), T, topk, True, epilogue=epi, out_dtype=dt)[pairs]
+        routed = q.qarl_qgemm_routed(qw, x, d_ids, T, topk, True, epilogue=epi, out_dtype=dt)[pairs]
         grouped = q.qarl_qgemm_grouped(qw, rows, off, M, row_map=tok, epilogue=epi, out_dtype=dt, path=q.QARL_PATH_DECODE, **kw)
         for e, n in enumerate(counts):
             for r0 in range(0, n, 16):
