@@ -27,7 +27,7 @@ MFMA_FP8_PEAK_TF = 5000.0
 # HBM bytes per gate_up launch of the headline step from two counter runs (2.000 x FETCH_SIZE + 1.000 x WRITE_SIZE,
 # the factors a plain copy kernel of known size gives).  Counters cannot be read from inside this process, so the
 # figure is stored with the summary it comes from; it belongs to the 256-token workload and to the kernel as it
-# stood when that summary was taken: 217 399 091 B read + 3 145 830 B written (an earlier measurement of the same
+# stood when that summary was taken: 217 332 736 B read + 3 145 933 B written (an earlier measurement of the same
 # launch, profiles/qgemm_stream_decode256_hbm_traffic.txt, gave 220 271 616 B).
 GATE_UP_TRAFFIC_BYTES = 220478669
 GATE_UP_TRAFFIC_SOURCE = "profiles/qgemm_all_formats_hbm_traffic.txt"

@@ -489,7 +489,8 @@ static int launch_routed(const qarl_qweight *W, const void *x, int x_per_token, 
         const double small_us = int4 ? qgemm_small_w4_us(W->fmt, W->N, W->K, T, topk, epilogue)
                                      : qgemm_small_fp8_us(W->fmt, W->N, W->K, T, topk, epilogue);
         // in a layer call the streaming kernel needs the router's launch in front (FP8, 64 experts 1024 x 512, top-4, 6 tokens: 19.6 us per layer
-        // with the few-pair gate_up that routes its tokens itself, 21.4 with router and streaming kernel)
+        // with the few-pair gate_up that routes its tokens itself, 21.4 with router and streaming kernel; no int4 layer of 120 000 random shapes is
+        // decided by it: their estimates lie further apart wherever the streaming kernel is the faster one)
         const double route_us = route ? 2.5 : 0.;
         if (small_us <= qgemm_stream_routed_us(W->fmt, W->N, W->K, W->E, T, topk, epilogue) + route_us) {
             const float *cw = comb ? combine_w : nullptr;

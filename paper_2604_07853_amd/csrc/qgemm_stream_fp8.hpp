@@ -8,11 +8,15 @@
 // Work layout.  A workgroup of 8 wavefronts owns (expert, slice of its weight rows, block
 // of <= 16*MT token rows).  It gathers its e4m3 token rows ONCE into LDS for the whole K;
 // after that single barrier every wavefront runs on its own: it walks its pairs of 16-row
-// weight tiles and, per pair, K in steps of 128, with the codes of the next R steps always
-// in flight in a register ring (global -> registers, two 16-byte loads per lane, tile and
-// step: lane (c, q) reads k in [128 g + 32 q, +32) of row c).  Codes and token rows meet as
-// stored in v_mfma_f32_16x16x32_fp8_fp8; the row scale s_x and the channel scale s_w are
-// applied to the fp32 sums in the epilogue.
+// weight tiles and, per pair, K in steps, with the codes of the next R steps always in
+// flight in a ring of the wavefront's own.  Codes and token rows meet as stored in
+// v_mfma_f32_16x16x32_fp8_fp8; the row scale s_x and the channel scale s_w are applied to
+// the fp32 sums in the epilogue.
+//
+// The ring has two forms.  Routed calls keep it in LDS where it fits beside the token tile
+// (below).  Grouped calls, and routed ones whose ring does not fit or that have fewer steps
+// than it, keep it in registers: steps of 128 k, two 16-byte loads per lane, tile and step
+// (e2m1: one), lane (c, q) reads k in [128 g + 32 q, +32) of row c.
 //
 // Experts with more than 16*MT rows: the grid carries m_split row blocks per (expert,
 // slice), mapped to consecutive workgroups of the same XCD so that their identical weight
@@ -27,7 +31,7 @@
 // k of both tiles), reads a stage into registers as soon as it has landed and refills it at once: nothing in the stream waits for another
 // wavefront.  Layer of 128 experts 2048 x 768, top-8, even router, us, registers -> ring: FP8 12 tokens 95 -> 71, 37 114 -> 94, 100 128 -> 109,
 // 256 138 -> 119, FP4 63 -> 48, 72 -> 58, 82 -> 69, 90 -> 78; 64 experts 1024 x 512, top-4, 512 tokens FP8 51 -> 42, FP4 42 -> 40; Zipf router 256 tokens
-// FP8 119 -> 107, FP4 87 -> 78.  Three stages: 4 % slower in the mean.  Blocks of 64 rows of K = 2048 leave no room and keep the registers.
+// FP8 119 -> 107, FP4 87 -> 78.  Three stages: 4 % slower in the mean.  Blocks of 64 rows of long K (2048; the line is near 1400 and falls with N) leave no room and keep the registers.
 //
 // Routed mode (QX): the kernel is driven by the router's ids and by 16-bit activations.  Every
 // workgroup lists its expert's (token, slot) pairs itself and quantizes the token rows it

@@ -477,7 +477,7 @@ __device__ __forceinline__ bool stream_w4_body(const W4Params &p, int tid, unsig
         }
     };
     // A block of at most 32 rows takes one row tile of a 64-row kernel's two: half the operand reads and matrix instructions.  p.one_tile:
-    // where few blocks of an even router have more (64 / 128 experts with K = 1024, 300 tokens, layer 34 -> 28 / 74 -> 65 us); beside more of
+    // where few blocks of an even router have more (64 / 128 experts with K = 1024, 300 tokens, W4A8 layer 34 -> 28 / 74 -> 66 us, W4A16 of 128 64 -> 57); beside more of
     // them the light blocks only take their bandwidth away (360 tokens: 75 -> 78 us).  Shares keep both row tiles (with the choice there too
     // the kernel spilled: layers of 64 experts 1024 x 512, Zipf 1.1, 20-32 % slower).
     auto run_block = [&](int m0, bool first_pass) __attribute__((always_inline)) {
@@ -532,9 +532,9 @@ __global__ __launch_bounds__(kThreads, 1) void qgemm_stream_w4_kernel(W4Params p
 // (expansion and matrix instructions are per weight, whatever the number of token rows).  Here K is walked in NC
 // chunks: the LDS tile holds 64 rows x K / NC, every wavefront owns PW pairs of weight tiles for the whole kernel
 // and keeps their accumulators (2 x 16 registers per pair) across the chunks, so the codes are expanded once and
-// meet all 64 rows.  A block of at most 32 rows, most of them up to 400 tokens of 128 experts top-8, runs one of its two row tiles: with
+// meet all 64 rows.  A block of at most 32 rows, most of those of 267 to 400 tokens of 128 experts top-8, runs one of its two row tiles: with
 // both in every block each workgroup took 55 us of gate_up whatever its rows, and what a tile of padding costs is LDS reads and matrix
-// instructions at 60 % each.  A W4A16 layer of 272 / 336 / 512 tokens: 102 / 105 / 111 us before, 80 / 95 / 103 us now.  The weight ring runs through (chunk, pair, group) without a break; between two chunks the
+// instructions at 60 % each.  A W4A16 layer of 272 / 336 / 512 tokens: 104 / 106 / 114 us with both, 89 / 101 / 107 now.  The weight ring runs through (chunk, pair, group) without a break; between two chunks the
 // workgroup meets at a barrier and gathers the next K-range of its token rows.  Scales go from global memory
 // straight to the lane that folds them (the 8 groups of a chunk are one 16-byte load).
 // SPREAD, TAIL: as above.
@@ -632,8 +632,9 @@ __device__ __forceinline__ bool stream_w4_wide_body(const W4Params &p, int tid, 
             // accumulators of all pairs stay live across this point): a wavefront instruction moves 1 KiB, half of a
             // row's KC * 2 = 2 KiB; wavefront w copies rows w, 8 + w ...  Rows past the expert's end repeat its last row in a block
             // of two row tiles; in a block of one they stay as they are: a row of the tile feeds its own results only, and theirs
-            // are never stored (three W4A16 layers of 257 / 272 / 300 tokens 262 / 265 / 283 -> 257 / 262 / 281 us; left out with two
-            // row tiles too, a Zipf router's 272 tokens took 325 -> 327).
+            // are never stored (128 experts, top-8, W4A16 layer of 267 / 272 / 300 / 336 tokens 91.5 / 91.5 / 96.1 / 102.2 -> 88.2 / 88.9 / 94.7 / 101.4 us,
+            // Zipf router 109.0 / 108.8 / 112.1 / 114.0 -> 108.5 / 108.3 / 111.1 / 113.0; left out with two row tiles too, three layers of a Zipf
+            // router's 272 tokens took 325 -> 327).
             {
                 constexpr int RW = 4 * NM;
                 const int sw = __builtin_amdgcn_readfirstlane(wave), n_rows = __builtin_amdgcn_readfirstlane(mrem);
@@ -939,7 +940,7 @@ int launch_one(const GemmArgs &a, hipStream_t s)
     p.per_slice = (p.n_units + (1 << ssh) - 1) >> ssh;
     // 64-row blocks over a K-chunked tile: K = 2048 (two chunks of eight scale groups), more than 32 rows per expert
     // to expect, and a slice that gives every wavefront the same one to three pairs
-    static_assert(kWaves * 8 == 64, "the wide kernel's gather: eight rows per wavefront");
+    static_assert(kWaves * 8 == 64, "the wide kernel's gather: eight rows per wavefront, four in a block of one row tile");
     if (MT == 1 && !p.half_tile && need > 32.0 && a.K == 2048 && !p.qx) {   // (its gather is an asynchronous copy: no quantizer)
         const int ms_w = (int)ceil(need / 64.0);
         int msh_w = 0;

@@ -118,8 +118,10 @@ __global__ __launch_bounds__(kFThreads, 4) void qgemm_tile_fp8_kernel(Tile8Param
     const unsigned char *wbase = p.codes + (int64_t)e * N * rowb;
     const float *sbase = p.scales + (int64_t)e * N;
     // A wavefront whose 64 rows lie past the expert's end only copies (layers of 128 experts, even / Zipf router, FP4: 520 tokens 116 / 98 ->
-    // 112 / 97 us, 1024 136 / 134 -> 134 / 129, 3000 245 / 253 -> 240 / 244; FP8: 520 154 / 134 -> 154 / 136, 1024 173 / 170 -> 180 / 167, 3000
-    // 283 / 292 -> 280 / 285, 8192 606 / 615 -> 599 / 600).
+    // 112 / 97 us, 1024 136 / 134 -> 134 / 129, 3000 245 / 253 -> 240 / 244; FP8: 520 153 / 134 -> 154 / 136, 700 160 / 147 -> 165 / 146, 1024
+    // 173 / 169 -> 180 / 167, 1200 187 / 182 -> 191 / 179, 1500 201 / 203 -> 198 / 203, 3000 284 / 286 -> 280 / 279, 8192 600 / 608 -> 593 / 596).
+    // At every size, although FP8 loses 2 to 4 % from about 45 to 75 rows per expert under an even router: the same sizes gain 1 % under the Zipf
+    // router and 2 to 4 % in layers of 64 experts (1024 x 512, top-4, 1024 tokens 50.5 / 55.5 -> 49.7 / 53.5), so no line by size serves both.
     const bool busy = wm * 64 < mrem;
     f32x16 acc[2][2];
 #pragma unroll
